@@ -26,21 +26,85 @@ constexpr int kBlocks = 1024;
 static_assert(sizeof(scratch) == sizeof(double) * 3 * kBlocks, "scratch holds one triple per workgroup");
 constexpr int kThreads = 256;
 
+// What one lane has seen of a comparison.  `seen` is the largest scaled error of the whole wave as of its last batch
+// (a hair below it, so that rounding in the test cannot hide a larger one).
+struct CompareAcc { double mx, se, sr, seen; };
+
+// Nv elements of c and ref.  |d| / (|ref| + 1) only matters where it beats the largest one seen: the test for that is a
+// product, and the divisions run only in waves where a lane passes it (for values in random order once in k batches at
+// the k-th batch).  Equal elements never do; a NaN or an infinite reference always does and makes the maximum infinite.
+template <int NV>
+__device__ __forceinline__ void compare_batch(const float (&c)[NV], const float (&ref)[NV], CompareAcc &a)
+{
+    bool beats = false;
+#pragma unroll
+    for (int e = 0; e < NV; ++e) {
+        const double r = ref[e], d = (double)c[e] - r;
+        beats |= d != 0.0 && !(fabs(d) < a.seen * (fabs(r) + 1.0));
+        a.se += d * d;
+        a.sr += r * r;
+    }
+    if (__any(beats)) {
+#pragma unroll
+        for (int e = 0; e < NV; ++e) {
+            const double r = ref[e], s = fabs((double)c[e] - r) / (fabs(r) + 1.0);
+            a.mx = (s <= a.mx) ? a.mx : (s == s ? s : INFINITY);   // NaN -> inf
+        }
+        double w = a.mx;
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) w = fmax(w, __shfl_xor(w, o));
+        a.seen = w * (1.0 - 1e-15);
+    }
+}
+
+__device__ __forceinline__ void load_vec(float (&v)[4], const float *p) { const f32x4_t t = *(const f32x4_t *)p; v[0] = t.x; v[1] = t.y; v[2] = t.z; v[3] = t.w; }
+__device__ __forceinline__ void load_vec(float (&v)[1], const float *p) { v[0] = *p; }
+
 // rows == NULL: c and ref are both n elements.  rows != NULL: ref holds n = n_rows * row_len
 // elements, the rows rows[0..n_rows) of c viewed as a matrix with row_len columns.
+// V = 4: 16-byte loads (both arrays 16-byte aligned; with rows also row_len % 4 == 0), else single elements.
+// The kernel is bound by memory: what counts is bytes in flight, so a lane has U pieces of both arrays under way before
+// it uses the first (4 x 2 x 16 bytes with V = 4: 33 MB over the chip's 262144 lanes).  On 71.7 M elements (573 MB)
+// 111 us, launch and wait for the result included (5.1 TB/s; a large copy moves 4.8); with one 4-byte pair per lane, a 64-bit division
+// per element, a copy back and a fold on the host it was 201 us, and 24 KB took 25 us instead of 19.  Where the rows are sampled, a lane's place moves by the
+// same number of rows and columns every step: no division by row_len per element.
+template <int V, bool ROWS>
 __global__ __launch_bounds__(kThreads)
-void compare_partial(const float *__restrict__ c, const float *__restrict__ ref, long n,
-                     const int *__restrict__ rows, long row_len, double *__restrict__ part)
+void compare_partial(const float *__restrict__ c, const float *__restrict__ ref, long n, const int *__restrict__ rows,
+                     long row_len, long drow, long dcol /* rows and columns a lane moves by per step */, double *__restrict__ part)
 {
-    double mx = 0.0, se = 0.0, sr = 0.0;
-    for (long i = (long)blockIdx.x * kThreads + threadIdx.x; i < n; i += (long)gridDim.x * kThreads) {
-        const long ci = rows ? (long)rows[i / row_len] * row_len + i % row_len : i;
-        const double r = ref[i], d = (double)c[ci] - r;
-        const double s = fabs(d) / (fabs(r) + 1.0);
-        mx = (s <= mx) ? mx : (s == s ? s : INFINITY);   // NaN -> inf
-        se += d * d;
-        sr += r * r;
+    constexpr int U = 4;
+    CompareAcc a = {0.0, 0.0, 0.0, 0.0};
+    const long step = (long)gridDim.x * kThreads, first = (long)blockIdx.x * kThreads + threadIdx.x, pieces = n / V;
+    long row = 0, col = 0;
+    if (ROWS) { row = first * V / row_len; col = first * V % row_len; }
+    // The loop runs for whole workgroups (compare_batch looks across the lanes of a wave): a lane past the end takes
+    // zeros for both values, which count for nothing.
+    for (long base = (long)blockIdx.x * kThreads; base < pieces; base += U * step) {
+        float cv[U][V], rv[U][V];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const long i = base + u * step + threadIdx.x;
+#pragma unroll
+            for (int e = 0; e < V; ++e) cv[u][e] = rv[u][e] = 0.f;
+            if (i < pieces) {
+                load_vec(cv[u], c + (ROWS ? (long)rows[row] * row_len + col : i * V));
+                load_vec(rv[u], ref + i * V);
+            }
+            if (ROWS) {
+                row += drow; col += dcol;
+                if (col >= row_len) { col -= row_len; ++row; }
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) compare_batch<V>(cv[u], rv[u], a);
     }
+    if (V > 1 && !ROWS && blockIdx.x == 0) {   // the last n % V elements (rows: row_len is a multiple of V, so n is)
+        const long i = pieces * V + threadIdx.x;
+        const float cv[1] = {i < n ? c[i] : 0.f}, rv[1] = {i < n ? ref[i] : 0.f};
+        compare_batch<1>(cv, rv, a);
+    }
+    double mx = a.mx, se = a.se, sr = a.sr;
     __shared__ double smx[kThreads], sse[kThreads], ssr[kThreads];
     smx[threadIdx.x] = mx; sse[threadIdx.x] = se; ssr[threadIdx.x] = sr;
     __syncthreads();
@@ -59,19 +123,32 @@ void compare_partial(const float *__restrict__ c, const float *__restrict__ ref,
     }
 }
 
-// Finishes a comparison on the device: folds the per-workgroup partials in workgroup order (the
-// order the host-side fold of compare_f32 uses, so both give the same bits) and writes
-// result[0] = max_scaled, result[1] = rel_fro.
-__global__ void compare_finish(const double *__restrict__ part, int blocks, double *__restrict__ result)
+// Finishes a comparison on the device: one workgroup folds the per-workgroup partials (always in the same order) and
+// writes result[0] = max_scaled, result[1] = rel_fro.
+__global__ __launch_bounds__(kThreads)
+void compare_finish(const double *__restrict__ part, int blocks, double *__restrict__ result)
 {
     double mx = 0.0, se = 0.0, sr = 0.0;
-    for (int b = 0; b < blocks; ++b) {
+    for (int b = threadIdx.x; b < blocks; b += kThreads) {
         mx = fmax(mx, part[b * 3 + 0]);
         se += part[b * 3 + 1];
         sr += part[b * 3 + 2];
     }
-    result[0] = mx;
-    result[1] = sr > 0.0 ? sqrt(se / sr) : (se > 0.0 ? INFINITY : 0.0);
+    __shared__ double smx[kThreads], sse[kThreads], ssr[kThreads];
+    smx[threadIdx.x] = mx; sse[threadIdx.x] = se; ssr[threadIdx.x] = sr;
+    __syncthreads();
+    for (int s = kThreads / 2; s > 0; s >>= 1) {
+        if (threadIdx.x < s) {
+            smx[threadIdx.x] = fmax(smx[threadIdx.x], smx[threadIdx.x + s]);
+            sse[threadIdx.x] += sse[threadIdx.x + s];
+            ssr[threadIdx.x] += ssr[threadIdx.x + s];
+        }
+        __syncthreads();
+    }
+    if (threadIdx.x == 0) {
+        result[0] = smx[0];
+        result[1] = ssr[0] > 0.0 ? sqrt(sse[0] / ssr[0]) : (sse[0] > 0.0 ? INFINITY : 0.0);
+    }
 }
 
 // Deadline control block of the scalar template: {start tick, allowed ticks, expired flag}.
@@ -205,7 +282,6 @@ __global__ __launch_bounds__(256) void transpose_tiles_16(TransposeJob j0, Trans
 }
 
 std::mutex g_ws_mutex;
-double *g_ws[64] = {nullptr};   // one workspace per device, kept until the process ends
 double *g_static_ws[64] = {nullptr};   // device address of `scratch` on each device
 unsigned long long *g_ctl[64] = {nullptr};
 double g_ticks_per_ms[64] = {0.0};
@@ -214,6 +290,40 @@ double g_ticks_per_ms[64] = {0.0};
 
 namespace opevo {
 
+// Both kernels of a comparison on `stream`: part holds 3 doubles for each of kBlocks workgroups, result 2 doubles (device
+// memory, or host memory the device can write).
+static int enqueue_compare(const float *c, const float *ref, int64_t n, const int *rows, int64_t row_len,
+                           hipStream_t stream, double *part, double *result)
+{
+    const bool vec = reinterpret_cast<uintptr_t>(c) % 16 == 0 && reinterpret_cast<uintptr_t>(ref) % 16 == 0 &&
+                     (!rows || row_len % 4 == 0);
+    const int64_t per_block = int64_t(kThreads) * (vec ? 4 : 1);
+    const int blocks = int(std::max<int64_t>(1, std::min<int64_t>(kBlocks, (n + per_block - 1) / per_block)));
+    auto *k = vec ? (rows ? compare_partial<4, true> : compare_partial<4, false>)
+                  : (rows ? compare_partial<1, true> : compare_partial<1, false>);
+    const int64_t step = int64_t(blocks) * per_block;
+    hipLaunchKernelGGL(k, dim3(blocks), dim3(kThreads), 0, stream, c, ref, (long)n, rows, (long)row_len,
+                       (long)(step / row_len), (long)(step % row_len), part);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return hip_fail(e, "compare_partial launch");
+    hipLaunchKernelGGL(compare_finish, dim3(1), dim3(kThreads), 0, stream, (const double *)part, blocks, result);
+    e = hipGetLastError();
+    return e == hipSuccess ? OPEVO_OK : hip_fail(e, "compare_finish launch");
+}
+
+// What a comparison that returns to the host needs: partials on the device and two doubles of pinned host memory that
+// the device writes (no copy back).  One per comparison under way on a device; kept for the next one, at most kSpare of them.
+struct CompareWorkspace { double *part = nullptr, *result = nullptr; };
+static constexpr size_t kSpare = 8;
+static std::vector<CompareWorkspace> g_spare[64];
+
+static void release(CompareWorkspace &w)
+{
+    if (w.part) (void)hipFree(w.part);
+    if (w.result) (void)hipHostFree(w.result);
+    w = CompareWorkspace();
+}
+
 int compare_f32(const float *c, const float *ref, int64_t n, const int *rows, int64_t row_len,
                 hipStream_t stream, double *max_scaled, double *rel_fro)
 {
@@ -221,34 +331,29 @@ int compare_f32(const float *c, const float *ref, int64_t n, const int *rows, in
     hipError_t e = hipGetDevice(&dev);
     if (e != hipSuccess) return hip_fail(e, "hipGetDevice");
     if (dev < 0 || dev >= 64) return fail(OPEVO_E_HIP, "device index %d out of range", dev);
-    double *ws;
+    CompareWorkspace w;
     {
         std::lock_guard<std::mutex> lock(g_ws_mutex);
-        if (!g_ws[dev]) {
-            e = hipMalloc(&g_ws[dev], sizeof(double) * 3 * kBlocks);
-            if (e != hipSuccess) return hip_fail(e, "hipMalloc(compare workspace)");
-        }
-        ws = g_ws[dev];
+        if (!g_spare[dev].empty()) { w = g_spare[dev].back(); g_spare[dev].pop_back(); }
     }
-    int blocks = int(std::min<int64_t>(kBlocks, (n + kThreads - 1) / kThreads));
-    if (blocks < 1) blocks = 1;
-    hipLaunchKernelGGL(compare_partial, dim3(blocks), dim3(kThreads), 0, stream, c, ref, (long)n, rows,
-                       (long)row_len, ws);
-    e = hipGetLastError();
-    if (e != hipSuccess) return hip_fail(e, "compare_partial launch");
-    std::vector<double> host(size_t(3) * blocks);
-    e = hipMemcpyAsync(host.data(), ws, sizeof(double) * 3 * blocks, hipMemcpyDeviceToHost, stream);
-    if (e != hipSuccess) return hip_fail(e, "hipMemcpyAsync");
-    e = hipStreamSynchronize(stream);
-    if (e != hipSuccess) return hip_fail(e, "hipStreamSynchronize");
-    double mx = 0.0, se = 0.0, sr = 0.0;
-    for (int b = 0; b < blocks; ++b) {
-        mx = std::fmax(mx, host[b * 3 + 0]);
-        se += host[b * 3 + 1];
-        sr += host[b * 3 + 2];
+    if (!w.part) {
+        e = hipMalloc(&w.part, sizeof(double) * 3 * kBlocks);
+        if (e == hipSuccess) e = hipHostMalloc(&w.result, sizeof(double) * 2, hipHostMallocDefault);
+        if (e != hipSuccess) { release(w); return hip_fail(e, "compare workspace"); }
     }
-    if (max_scaled) *max_scaled = mx;
-    if (rel_fro) *rel_fro = sr > 0.0 ? std::sqrt(se / sr) : (se > 0.0 ? INFINITY : 0.0);
+    int rc = enqueue_compare(c, ref, n, rows, row_len, stream, w.part, w.result);
+    if (rc == OPEVO_OK) {
+        e = hipStreamSynchronize(stream);
+        if (e != hipSuccess) rc = hip_fail(e, "hipStreamSynchronize");
+    }
+    if (rc != OPEVO_OK) return rc;   // the kernels may still be under way (or recorded): the workspace is not used again
+    if (max_scaled) *max_scaled = w.result[0];
+    if (rel_fro) *rel_fro = w.result[1];
+    {
+        std::lock_guard<std::mutex> lock(g_ws_mutex);
+        if (g_spare[dev].size() < kSpare) { g_spare[dev].push_back(w); w = CompareWorkspace(); }
+    }
+    release(w);
     return OPEVO_OK;
 }
 
@@ -274,17 +379,9 @@ int compare_f32_static(const float *c, const float *ref, int64_t n, hipStream_t 
 {
     double *ws = nullptr;
     if (int rc = static_scratch(&ws)) return rc;
-    int blocks = int(std::min<int64_t>(kBlocks, (n + kThreads - 1) / kThreads));
-    if (blocks < 1) blocks = 1;
-    // every workgroup overwrites its own three partials and the fold reads only those `blocks`
-    // triples, so nothing left in the array by an earlier call is ever read: no clearing needed
-    hipLaunchKernelGGL(compare_partial, dim3(blocks), dim3(kThreads), 0, stream, c, ref, (long)n,
-                       (const int *)nullptr, 1L, ws);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return hip_fail(e, "compare_partial launch");
-    hipLaunchKernelGGL(compare_finish, dim3(1), dim3(1), 0, stream, (const double *)ws, blocks, result_dev);
-    e = hipGetLastError();
-    return e == hipSuccess ? OPEVO_OK : hip_fail(e, "compare_finish launch");
+    // every workgroup overwrites its own three partials and the fold reads only those of the workgroups launched,
+    // so nothing left in the array by an earlier call is ever read: no clearing needed
+    return enqueue_compare(c, ref, n, nullptr, 1, stream, ws, result_dev);
 }
 
 int deadline_ctl(unsigned long long **ctl)
