@@ -178,6 +178,9 @@ typedef enum { OPEVO_F32 = 0, OPEVO_BF16 = 1, OPEVO_F16 = 2 } opevo_dtype;
  *         Conv2d  B(2) Cout(4) H(4) W(4) R(2) unroll{0,1},  R = Cin*Hk*Wk
  *         MFMA kernels (bf16/fp16 inputs) where the per-wave tile is made of 32x32 or 16x16
  *         atoms and the LDS tile of whole MFMA K-steps; a scalar-FMA kernel otherwise.
+ *         MatMul / BMM with 16-bit inputs and an extent that is no multiple of 16 (rows and columns of at least 8
+ *         elements): the workgroup tile, whatever its extents, is rounded up to whole 16x16x32 atoms (at most eight times the
+ *         work, the overhang is not stored) and dealt to waves by the library; opevo_plan reports that division.
  *         fp32 inputs: 32x32x2 fp32 MFMA atoms; MatMul / BMM where the per-wave tile is made of
  *         32x32 atoms and the LDS tile is a multiple of 8 (and the contiguous axes multiples of 4),
  *         Conv2d with the same widening as above (slabs padded to 8, wave tiles rounded up to 32);
@@ -302,7 +305,8 @@ typedef struct {
     int32_t status;        /* OPEVO_OK or OPEVO_E_INVALID                                      */
     int32_t path;          /* 0 scalar FMA, 1 MFMA 32x32x16, 2 MFMA 16x16x32, 3 MFMA 32x32x16 with
                               operands streamed global -> LDS directly, 4 fp32 MFMA 32x32x2,
-                              5 Conv2d with an LDS-resident image patch (either atom)          */
+                              5 Conv2d with an LDS-resident image patch (either atom), 6 MatMul / BMM
+                              whose extents are no multiples of 16, tiles of any extent on MFMA 16x16x32 */
     int32_t grid[3];
     int32_t block;         /* threads per workgroup                                            */
     int32_t lds_bytes;

@@ -165,6 +165,48 @@ static void patch_pitches(const opevo_op &op, int64_t bh, int64_t bw, bool padde
     image = ph * row + ((bh * bw - ph * row) % 16 + 16) % 16;
 }
 
+// How the ragged MFMA template runs a tile of bm x bn with slabs of about bk: wave grid, atoms per wave, slab width.
+struct Ragged { int wm = 0, wn = 0, mi = 0, ni = 0, ks = 0, slabs = 0, stages = 1; int64_t lds = 0; };
+
+static bool plan_ragged(const opevo_op &op, int64_t bm, int64_t bn, int64_t bk, int64_t kpart, bool pipelined, Ragged &out)
+{
+    // every operand is loaded in pieces of 8 consecutive elements of a row, with 32-bit element offsets inside a batch
+    if (kpart < 8 || op.N < 8 || (op.trans_a && op.M < 8) || op.M * op.K >= (int64_t(1) << 31) || op.K * op.N >= (int64_t(1) << 31)) return false;
+    const int64_t ma = (bm + 15) / 16, na = (bn + 15) / 16;
+    if (ma * na * 256 > 8 * bm * bn || ma * na > 16 * 32) return false;
+    // waves: the division with the fewest padded atoms, then the one closest to four waves (one per SIMD; eight where the
+    // tile has 64 atoms and more), then the one with the fewest fragment reads
+    const int64_t want = ma * na >= 64 ? 8 : 4;
+    int64_t best = INT64_MAX;
+    for (int64_t wm = 1; wm <= std::min<int64_t>(ma, 16); ++wm)
+        for (int64_t wn = 1; wn <= std::min<int64_t>(na, 16 / wm); ++wn) {
+            const int64_t mi = (ma + wm - 1) / wm, ni = (na + wn - 1) / wn, nw = wm * wn;
+            if (mi * ni > 32) continue;
+            const int64_t off = nw > want ? nw - want : (want - nw) * 4;      // too few waves are worse than too many
+            const int64_t score = (wm * mi * wn * ni * 8 + off * std::min<int64_t>(ma * na, 32)) * 64 + nw * (mi + ni);
+            if (score < best) { best = score; out.wm = int(wm); out.wn = int(wn); out.mi = int(mi); out.ni = int(ni); }
+        }
+    if (best == INT64_MAX) return false;
+    // slab: the member's, rounded up to whole MFMA steps of 32 and at most 128; among the shorter ones the one that pads
+    // the reduction least (a slab costs about as much as 8 steps of padding), as far as LDS and staging registers go
+    const int64_t top = std::max<int64_t>(32, std::min<int64_t>(128, (std::min(bk, kpart) + 31) / 32 * 32)), nt = 64 * out.wm * out.wn;
+    best = INT64_MAX;
+    for (int64_t ks = 32; ks <= top; ks += 32) {
+        auto odd16 = [](int64_t n) { return ((n + 15) / 16 | 1) * 16; };
+        const int64_t slabs = (kpart + ks - 1) / ks;
+        const int64_t a_stage = op.trans_a ? ks * odd16(out.wm * out.mi * 16) + ks / 8 * 64 : out.wm * out.mi * 16 * (ks + 8);
+        const int64_t b_stage = ks * odd16(out.wn * out.ni * 16) + ks / 8 * 64;
+        const int64_t a_pieces = op.trans_a ? ks * ((bm + 7) / 8) : bm * (ks / 8), b_pieces = ks * ((bn + 7) / 8);
+        const int64_t regs = 4 * ((a_pieces + nt - 1) / nt + (b_pieces + nt - 1) / nt);
+        const int stages = pipelined && slabs > 1 ? 2 : 1;
+        const int64_t lds = stages * (a_stage + b_stage) * 2;
+        if (lds > kMaxLds || regs + 4 * out.mi * out.ni > 256) continue;
+        const int64_t score = slabs * (ks + 8) + (lds > kMaxLds / 2 ? slabs * 16 : 0);   // two workgroups per compute unit where it can be
+        if (score <= best) { best = score; out.ks = int(ks); out.slabs = int(slabs); out.stages = stages; out.lds = lds; }
+    }
+    return best != INT64_MAX;
+}
+
 static void invalid(opevo_plan &p, const char *fmt, long a = 0, long b = 0)
 {
     p.status = OPEVO_E_INVALID;
@@ -516,6 +558,20 @@ int decode(const opevo_op &op, int variant, const int32_t *cfg, Decoded &out)
             dlds_stages(BM, 0, false, true) == nstage_dlds && (BK % 64 == 0 || nstage_dlds % 2 == 0))   // one K step per slab: an even ring
             dlds_atom16 = true;
     }
+    // MatMul / BMM operators with an extent that is no multiple of 16 have no member on the templates above (or only the few
+    // whose tiles skip that axis): their members run on the ragged MFMA template instead of the scalar one.  It takes the
+    // workgroup tile as it is, rounds it up to whole 16x16 atoms and deals those to waves by itself.  Measured on 1000^3
+    // against the scalar template: tiles of 20 x 100 (rounded up 1.8 times) 15.6 against 1124 us, 10 x 20 (2.6) 39 against 519, 8 x 8
+    // (4) 79 against 310, 4 x 8 and 8 x 4 (8 times) 144 and 171 against 356 and 381: by about 16 times nothing is left, so
+    // the line lies at 8.
+    Ragged rg;
+    if (four_level && path == 0 && op.dtype != OPEVO_F32 && op.kind != OPEVO_CONV2D && subm * subn == 1 &&
+        (op.M % 16 != 0 || op.N % 16 != 0 || op.K % 16 != 0) &&
+        plan_ragged(op, BM, BN, BK, op.K / ksplit, flagv != 0 || op.kind == OPEVO_BMM, rg)) {
+        path = 6;
+        WM = rg.wm; WN = rg.wn; TM = rg.mi * 16; TN = rg.ni * 16;
+        TMacc = TM; TNacc = TN; BK = rg.ks; ksteps = rg.slabs;
+    }
     const bool b_kmajor = path == 3 && (b_packed || op.kind == OPEVO_CONV2D);
     const bool nhwc = nhwc_ok && (path == 1 || path == 2 || path == 3);
     // a transposed first operand is staged by the MFMA templates like B (rows of 8 along M), so it
@@ -525,7 +581,7 @@ int decode(const opevo_op &op, int variant, const int32_t *cfg, Decoded &out)
     int64_t NT, nwr = WM * WN * patch_kw;   // nwr: waves the workgroup really runs
     if (four_level) {
         if (path == 0) nwr = std::min<int64_t>(nwr, kMaxThreads / 64);   // the scalar template deals outputs round-robin to any number of threads
-        else while (path != 5 && nwr > kMaxThreads / 64) {      // largest divisor of WM * WN that fits
+        else while (path != 5 && path != 6 && nwr > kMaxThreads / 64) {      // largest divisor of WM * WN that fits
             int64_t best = 1;
             for (int64_t dv = kMaxThreads / 64; dv >= 1; --dv) if ((WM * WN) % dv == 0) { best = dv; break; }
             nwr = best;
@@ -537,7 +593,7 @@ int decode(const opevo_op &op, int variant, const int32_t *cfg, Decoded &out)
         if (NT > 256) NT = 256;
     }
     int64_t acc = (path == 0) ? (BM * BN + NT - 1) / NT : (TMacc * TNacc) / 64;
-    const int nstage = path == 5 ? patch_stages : path == 3 ? nstage_dlds : (path != 0 && flagv && ksteps > 1) ? 2 : 1;
+    const int nstage = path == 6 ? rg.stages : path == 5 ? patch_stages : path == 3 ? nstage_dlds : (path != 0 && flagv && ksteps > 1) ? 2 : 1;
     int64_t lds = 0;
     if (path == 0) lds = (BM * BK + BK * BN) * 4;
     else if (path == 4 && op.kind == OPEVO_CONV2D) {
@@ -549,6 +605,7 @@ int decode(const opevo_op &op, int variant, const int32_t *cfg, Decoded &out)
     else if (path == 5)   // the stages, or (more than one wave per tile) one atom of every wave if that is more
         lds = std::max<int64_t>(nstage * (nb2 * patch_image * (patch_cs + 8) + op.hk * op.wk * BM * patch_cs + 64) * 2,
                                 patch_kw > 1 ? nwr * (patch_atom == 32 ? 4 : 1) * 1024 : 0);
+    else if (path == 6) lds = rg.lds;
     else if (stage_lds) lds = nstage * (BM + BN) * (BKP + kPad) * 2 + (ragged ? 16 * (BKP + kPad) * 2 : 0);   // overhang rows stay inside the allocation
 
     p.path = path;
@@ -561,7 +618,7 @@ int decode(const opevo_op &op, int variant, const int32_t *cfg, Decoded &out)
     p.tile[0] = int32_t(BM); p.tile[1] = int32_t(BN); p.tile[2] = int32_t(BK);
     p.wave_tile[0] = int32_t(four_level ? TM : BM); p.wave_tile[1] = int32_t(four_level ? TN : BN);
     p.sub_tiles[0] = int32_t(subm); p.sub_tiles[1] = int32_t(subn);
-    p.wave_passes = int32_t(four_level && nwr > 0 && path != 5 ? (WM * WN) / nwr : 1);
+    p.wave_passes = int32_t(four_level && nwr > 0 && path != 5 && path != 6 ? (WM * WN) / nwr : 1);
 
     // ---- black-box constraints made explicit: such members get fitness 0 (Sec. 4.2)
     if (NT > kMaxThreads) invalid(p, "%ld threads per workgroup > %ld", long(NT), long(kMaxThreads));
@@ -575,7 +632,7 @@ int decode(const opevo_op &op, int variant, const int32_t *cfg, Decoded &out)
                                                        : (BM * (BK / 4) + NT - 1) / NT + (BK * (BN / 4) + NT - 1) / NT;
         if (chunks * 4 > 256) invalid(p, "%ld staging registers per lane > 256", long(chunks * 4));
     }
-    else if (path != 0 && path != 3 && path != 5 && stage_lds) {
+    else if (path != 0 && path != 3 && path != 5 && path != 6 && stage_lds) {
         // register budget of the slab in flight: 16-byte pieces per thread
         const int64_t a_chunks = op.trans_a ? 8 * (((BK / 8) * (BM / 8) + NT - 1) / NT) : (BM * (BKP / 8) + NT - 1) / NT;
         const int64_t b_chunks = (op.kind == OPEVO_CONV2D) ? (BN * (BKP / 8) + NT - 1) / NT
@@ -584,7 +641,7 @@ int decode(const opevo_op &op, int variant, const int32_t *cfg, Decoded &out)
             invalid(p, "%ld staging registers per lane > 256", long((a_chunks + b_chunks) * 4));
     }
 
-    out.tmpl = path == 0 ? "gemm_scalar" : path == 3 ? "gemm_mfma_dlds" : path == 4 ? "gemm_mfma_f32" : path == 5 ? "conv_patch" : "gemm_mfma";
+    out.tmpl = path == 0 ? "gemm_scalar" : path == 3 ? "gemm_mfma_dlds" : path == 4 ? "gemm_mfma_f32" : path == 5 ? "conv_patch" : path == 6 ? "gemm_ragged" : "gemm_mfma";
     // one symbol per configuration, so profiles list each instantiated kernel on its own line
     {
         std::ostringstream nm;
@@ -600,11 +657,12 @@ int decode(const opevo_op &op, int variant, const int32_t *cfg, Decoded &out)
       << " -DK=" << op.K << " -DBM=" << BM << " -DBN=" << BN << " -DBK=" << BK << " -DKSTEPS=" << ksteps
       << " -DNT=" << NT << " -DBATCH_INNER=" << binner << " -DFLAG=" << flagv << " -DA_TRANS=" << (op.trans_a ? 1 : 0);
     if (path != 0) {
-        D << " -DATOM=" << (path == 5 ? patch_atom : (path == 2 || dlds_atom16) ? 16 : 32) << " -DWM=" << WM << " -DWN=" << WN << " -DTM=" << TM
+        D << " -DATOM=" << (path == 5 ? patch_atom : (path == 2 || path == 6 || dlds_atom16) ? 16 : 32) << " -DWM=" << WM << " -DWN=" << WN << " -DTM=" << TM
           << " -DTN=" << TN << " -DFM=" << FM << " -DFN=" << FN << " -DPAD=" << kPad
           << " -DNSTAGE=" << nstage << " -DNSTG=" << nstage << " -DSTAGE_LDS=" << (stage_lds ? 1 : 0);
         if (nwr != WM * WN && path != 5) D << " -DNWR=" << nwr;
     }
+    if (path == 6) D << " -DKS=" << rg.ks << " -DNSL=" << rg.slabs << " -DMI=" << rg.mi << " -DNI=" << rg.ni << " -DLDS_BYTES=" << lds;
     if (subm * subn > 1) {
         D << " -DSUBM=" << subm << " -DSUBN=" << subn;
     }
