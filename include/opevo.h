@@ -188,6 +188,11 @@ typedef enum { OPEVO_F32 = 0, OPEVO_BF16 = 1, OPEVO_F16 = 2 } opevo_dtype;
  *         Conv2d widens this: an LDS tile of any length is zero-padded to whole K-steps, and a
  *         per-wave tile that is no multiple of 16 is rounded up to whole 16x16 atoms as long as
  *         that at most doubles the work (the overhang is computed and not stored).
+ *         Conv2d with 16-bit inputs, fewer than 16 input channels, kernels at most 16 wide, tiles of whole 16 output
+ *         channels and boxes at least 4 pixels wide (in every Conv2d space; not with a split reduction or channels-last
+ *         copies): the image rows under the box are staged in LDS for the whole reduction, whatever its split, the tile is
+ *         dealt to waves by the library, and a workgroup may take several boxes in turn (opevo_plan's grid then has fewer
+ *         workgroups than boxes).
  *         Folding: a member that asks for more than a workgroup has is not scored 0 but run as serial
  *         work, so that the search sees a slow member with its own place in the landscape: a per-wave
  *         tile of more than 256 accumulators per lane is cut (a prime at a time along its longer side)
@@ -306,7 +311,8 @@ typedef struct {
     int32_t path;          /* 0 scalar FMA, 1 MFMA 32x32x16, 2 MFMA 16x16x32, 3 MFMA 32x32x16 with
                               operands streamed global -> LDS directly, 4 fp32 MFMA 32x32x2,
                               5 Conv2d with an LDS-resident image patch (either atom), 6 MatMul / BMM
-                              whose extents are no multiples of 16, tiles of any extent on MFMA 16x16x32 */
+                              whose extents are no multiples of 16, tiles of any extent on MFMA 16x16x32,
+                              7 Conv2d with fewer than 16 input channels, image rows in LDS (either atom) */
     int32_t grid[3];
     int32_t block;         /* threads per workgroup                                            */
     int32_t lds_bytes;

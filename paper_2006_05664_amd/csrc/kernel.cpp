@@ -9,6 +9,8 @@
 #include <new>
 #include <sstream>
 
+#include <elf.h>
+
 #include "code_cache.hpp"
 #include "pool.hpp"
 
@@ -25,16 +27,61 @@ int hip_fail(hipError_t e, const char *what)
         if (e_ != hipSuccess) return hip_fail(e_, #call);         \
     } while (0)
 
+// Private scratch bytes per lane that a code object declares for a kernel (register spills), from its kernel
+// descriptor: the symbol <name>.kd, 64 bytes whose second word is the private segment's size.  -1: no such symbol.
+static int code_scratch_bytes(const std::vector<char> &code, const std::string &name)
+{
+    Elf64_Ehdr eh;
+    if (code.size() < sizeof eh) return -1;
+    std::memcpy(&eh, code.data(), sizeof eh);
+    if (std::memcmp(eh.e_ident, ELFMAG, SELFMAG) != 0 || eh.e_shentsize != sizeof(Elf64_Shdr)) return -1;
+    auto section = [&](unsigned i, Elf64_Shdr &sh) {
+        const uint64_t at = eh.e_shoff + uint64_t(i) * sizeof sh;
+        if (i >= eh.e_shnum || at + sizeof sh > code.size()) return false;
+        std::memcpy(&sh, code.data() + at, sizeof sh);
+        return sh.sh_type != SHT_NOBITS && sh.sh_offset <= code.size() && sh.sh_size <= code.size() - sh.sh_offset;
+    };
+    const std::string want = name + ".kd";
+    for (unsigned i = 0; i < eh.e_shnum; ++i) {
+        Elf64_Shdr sym, str, in;
+        if (!section(i, sym) || (sym.sh_type != SHT_DYNSYM && sym.sh_type != SHT_SYMTAB) || !section(sym.sh_link, str)) continue;
+        for (uint64_t at = 0; at + sizeof(Elf64_Sym) <= sym.sh_size; at += sizeof(Elf64_Sym)) {
+            Elf64_Sym s;
+            std::memcpy(&s, code.data() + sym.sh_offset + at, sizeof s);
+            if (s.st_name >= str.sh_size || str.sh_size - s.st_name <= want.size() ||
+                std::memcmp(code.data() + str.sh_offset + s.st_name, want.c_str(), want.size() + 1) != 0)
+                continue;
+            if (!section(s.st_shndx, in) || s.st_value < in.sh_addr || s.st_value - in.sh_addr > in.sh_size || in.sh_size - (s.st_value - in.sh_addr) < 8) return -1;
+            uint32_t words[2];
+            std::memcpy(words, code.data() + in.sh_offset + (s.st_value - in.sh_addr), sizeof words);
+            return int(words[1]);
+        }
+    }
+    return -1;
+}
+
 int build_kernel(const opevo_op &op, int variant, const int32_t *cfg, opevo_kernel **out, double *compile_ms)
 {
     Decoded d;
     if (int rc = decode(op, variant, cfg, d)) return rc;
     if (d.plan.status != OPEVO_OK) return fail(OPEVO_E_INVALID, "invalid configuration: %s", d.plan.reason);
     const auto t0 = std::chrono::steady_clock::now();
-    const std::string key = code_cache_key(d.tmpl, d.defines);
+    std::string key = code_cache_key(d.tmpl, d.defines);
     CompileResult r;
-    const bool cached = code_cache_get(key, r.code);
+    bool cached = code_cache_get(key, r.code);
     if (!cached) r = pool_compile(d.tmpl, d.defines);
+    if (d.plan.path == 7 && r.status == OPEVO_OK && code_scratch_bytes(r.code, d.kernel_name) != 0) {
+        // the few-channels template keeps the kernel tensor in registers: a member whose estimate was too low and that
+        // spills runs where it would without that template (the spilling object stays cached, so that this is found at once next time)
+        if (!cached) code_cache_put(key, r.code);
+        d = Decoded();
+        if (int rc = decode(op, variant, cfg, d, false)) return rc;
+        if (d.plan.status != OPEVO_OK) return fail(OPEVO_E_INVALID, "invalid configuration: %s", d.plan.reason);
+        key = code_cache_key(d.tmpl, d.defines);
+        r = CompileResult();
+        cached = code_cache_get(key, r.code);
+        if (!cached) r = pool_compile(d.tmpl, d.defines);
+    }
     if (r.status == OPEVO_E_INVALID)
         return fail(r.status, "invalid configuration: %s [%s]", r.log.c_str(), d.kernel_name.c_str());
     if (r.status != OPEVO_OK)
@@ -144,8 +191,8 @@ int time_kernel(opevo_kernel *k, const void *a, const void *b, void *c, hipStrea
     if (int rc = load_kernel(k)) return rc;
     unsigned long long *ctl = nullptr;
     // the scalar template and folded members of the register-staged templates honour a deadline (the direct-to-LDS,
-    // LDS-resident-patch and ragged MFMA templates have no folded members)
-    if (timeout_ms > 0.0 && k->plan.path != 3 && k->plan.path != 5 && k->plan.path != 6)
+    // LDS-resident-patch, ragged MFMA and few-channels templates have no folded members)
+    if (timeout_ms > 0.0 && k->plan.path != 3 && k->plan.path != 5 && k->plan.path != 6 && k->plan.path != 7)
         if (int rc = deadline_ctl(&ctl)) return rc;
     // samples + 1 events: the samples run back to back, without a host round trip (and an idle
     // GPU) between them; only the first, estimating launch is followed by a synchronisation

@@ -207,13 +207,61 @@ static bool plan_ragged(const opevo_op &op, int64_t bm, int64_t bn, int64_t bk, 
     return best != INT64_MAX;
 }
 
+// How the few-channels convolution template runs a box: atom, wave grid, atoms per wave, padded kernel row, LDS bytes.
+struct Rows { int atom = 0, wm = 0, wn = 0, mi = 0, ni = 0, wkp = 0, persist = 0; int64_t lds = 0; };
+
+static bool plan_rows(const opevo_op &op, int64_t bm, int64_t nb2, int64_t bh, int64_t bw, int64_t boxes, int64_t m1, bool linear, Rows &out)
+{
+    // Boxes of fewer than 4 pixels across re-use too little of a staged row.  Elements are addressed with 31 bits inside the
+    // kernel tensor and inside the images of a box.
+    if (op.cin >= 16 || op.wk > 16 || op.win < 8 || bw < 4 || bm % 16 != 0 || op.a_elems() >= (int64_t(1) << 31) || op.a_elems() < 8 ||
+        nb2 * op.cin * op.hin * op.win >= (int64_t(1) << 31))
+        return false;
+    const int64_t atom = bm % 32 == 0 ? 32 : 16, q = op.wk <= 8 ? 1 : 2, rps = (atom == 32 ? 2 : 4) / q;   // rps: kernel rows per MFMA step
+    const int64_t spc = (op.hk + rps - 1) / rps, steps = op.cin * spc, bn = nb2 * bh * bw;
+    const int64_t ph = (bh - 1) * op.stride + op.hk, pitch = ((bw - 1) * op.stride + op.wk + 7) / 8 * 8;
+    const int64_t copy = (nb2 * op.cin * ph + spc * rps - op.hk) * pitch + q * 8;
+    const int64_t lds = op.stride % 2 ? 2 * ((copy + 127) / 128 * 128 + 64) * 2 : (copy + 7) / 8 * 8 * 2;
+    if (lds > kMaxLds) return false;
+    const int64_t ma = bm / atom, na = (bn + atom - 1) / atom;
+    int64_t best = INT64_MAX;
+    for (int64_t wm = 1; wm <= std::min<int64_t>(ma, 8); ++wm)
+        for (int64_t wn = 1; ma % wm == 0 && wn <= std::min<int64_t>(na, 8 / wm); ++wn) {
+            const int64_t mi = ma / wm, ni = (na + wn - 1) / wn, nw = wm * wn;
+            // registers of a lane (256: two waves on every SIMD): the kernel tensor's fragments, and the accumulators beside two sets of
+            // the image's fragments or the 16 pieces of the fill
+            const int64_t regs = 4 * steps * mi + std::max<int64_t>(mi * ni * (atom == 32 ? 16 : 4) + 8 * ni, 64) + 28;
+            if (regs > 256 || steps * mi * ni > 1024) continue;
+            // cycles of a box: the MFMAs of the SIMD with the most waves, or the fragment reads of all waves at 128 bytes a
+            // cycle; more than four waves leave no room for a second workgroup to load while this one multiplies
+            const int64_t mfma = steps * mi * ni * (atom == 32 ? 32 : 16) * ((nw + 3) / 4), reads = nw * steps * ni * 8;
+            const int64_t score = std::max(mfma, reads) * (nw > 4 ? 3 : 2) + std::min(mfma, reads);
+            if (score < best) { best = score; out.wm = int(wm); out.wn = int(wn); out.mi = int(mi); out.ni = int(ni); }
+        }
+    if (best == INT64_MAX) return false;
+    out.atom = int(atom); out.wkp = int(q * 8); out.lds = lds;
+    // with four and more boxes for every workgroup the chip holds, that many workgroups take them in turn and fetch the kernel
+    // tensor once
+    const int64_t resident = 256 * std::max<int64_t>(1, std::min<int64_t>(8 / (out.wm * out.wn), kMaxLds / lds));
+    if (!linear && boxes * m1 >= 4 * resident) out.persist = int(std::max<int64_t>(1, resident / m1 / 8) * 8);
+    return true;
+}
+
+// Members that cannot run without the few-channels template (a slab with too many staging registers, say) stay invalid:
+// which members of a space are valid does not depend on it.
+static bool valid_without_rows(const opevo_op &op, int variant, const int32_t *cfg)
+{
+    Decoded d;
+    return decode(op, variant, cfg, d, false) == OPEVO_OK && d.plan.status == OPEVO_OK;
+}
+
 static void invalid(opevo_plan &p, const char *fmt, long a = 0, long b = 0)
 {
     p.status = OPEVO_E_INVALID;
     snprintf(p.reason, sizeof p.reason, fmt, a, b);
 }
 
-int decode(const opevo_op &op, int variant, const int32_t *cfg, Decoded &out)
+int decode(const opevo_op &op, int variant, const int32_t *cfg, Decoded &out, bool rows_ok)
 {
     std::vector<opevo_param_desc> descs;
     if (int rc = op_param_descs(op, variant, descs)) return rc;
@@ -572,6 +620,15 @@ int decode(const opevo_op &op, int variant, const int32_t *cfg, Decoded &out)
         WM = rg.wm; WN = rg.wn; TM = rg.mi * 16; TN = rg.ni * 16;
         TMacc = TM; TNacc = TN; BK = rg.ks; ksteps = rg.slabs;
     }
+    // Conv2d with fewer than 16 input channels (no slab of whole channels for the patch template): image rows in LDS, taps of a
+    // kernel row as the reduction's groups of 8
+    Rows rows;
+    if (rows_ok && four_level && op.dtype != OPEVO_F32 && op.kind == OPEVO_CONV2D && (path == 0 || path == 1 || path == 2) && !nhwc_ok && subm * subn == 1 &&
+        ksplit == 1 && plan_rows(op, BM, nb2, BH, BW, n1, m1, linear, rows) && valid_without_rows(op, variant, cfg)) {
+        path = 7;
+        WM = rows.wm; WN = rows.wn; TM = rows.mi * rows.atom; TN = rows.ni * rows.atom;
+        TMacc = TM; TNacc = TN; BK = op.K; BKP = op.K; ksteps = 1; ragged = false; tap_box = false;
+    }
     const bool b_kmajor = path == 3 && (b_packed || op.kind == OPEVO_CONV2D);
     const bool nhwc = nhwc_ok && (path == 1 || path == 2 || path == 3);
     // a transposed first operand is staged by the MFMA templates like B (rows of 8 along M), so it
@@ -581,7 +638,7 @@ int decode(const opevo_op &op, int variant, const int32_t *cfg, Decoded &out)
     int64_t NT, nwr = WM * WN * patch_kw;   // nwr: waves the workgroup really runs
     if (four_level) {
         if (path == 0) nwr = std::min<int64_t>(nwr, kMaxThreads / 64);   // the scalar template deals outputs round-robin to any number of threads
-        else while (path != 5 && path != 6 && nwr > kMaxThreads / 64) {      // largest divisor of WM * WN that fits
+        else while (path != 5 && path != 6 && path != 7 && nwr > kMaxThreads / 64) {      // largest divisor of WM * WN that fits
             int64_t best = 1;
             for (int64_t dv = kMaxThreads / 64; dv >= 1; --dv) if ((WM * WN) % dv == 0) { best = dv; break; }
             nwr = best;
@@ -593,7 +650,7 @@ int decode(const opevo_op &op, int variant, const int32_t *cfg, Decoded &out)
         if (NT > 256) NT = 256;
     }
     int64_t acc = (path == 0) ? (BM * BN + NT - 1) / NT : (TMacc * TNacc) / 64;
-    const int nstage = path == 6 ? rg.stages : path == 5 ? patch_stages : path == 3 ? nstage_dlds : (path != 0 && flagv && ksteps > 1) ? 2 : 1;
+    const int nstage = path == 7 ? 1 : path == 6 ? rg.stages : path == 5 ? patch_stages : path == 3 ? nstage_dlds : (path != 0 && flagv && ksteps > 1) ? 2 : 1;
     int64_t lds = 0;
     if (path == 0) lds = (BM * BK + BK * BN) * 4;
     else if (path == 4 && op.kind == OPEVO_CONV2D) {
@@ -606,19 +663,21 @@ int decode(const opevo_op &op, int variant, const int32_t *cfg, Decoded &out)
         lds = std::max<int64_t>(nstage * (nb2 * patch_image * (patch_cs + 8) + op.hk * op.wk * BM * patch_cs + 64) * 2,
                                 patch_kw > 1 ? nwr * (patch_atom == 32 ? 4 : 1) * 1024 : 0);
     else if (path == 6) lds = rg.lds;
+    else if (path == 7) lds = rows.lds;
     else if (stage_lds) lds = nstage * (BM + BN) * (BKP + kPad) * 2 + (ragged ? 16 * (BKP + kPad) * 2 : 0);   // overhang rows stay inside the allocation
 
     p.path = path;
     const int64_t n_blocks = n1 * m1 * b1;
     if (linear) { p.grid[0] = int32_t(n_blocks > INT32_MAX ? INT32_MAX : n_blocks); p.grid[1] = 1; p.grid[2] = 1; }
     else { p.grid[0] = int32_t(n1); p.grid[1] = int32_t(m1); p.grid[2] = int32_t(b1); }
+    if (rows.persist > 0) p.grid[0] = rows.persist;   // workgroups that take several boxes each
     p.block = int32_t(NT > INT32_MAX ? INT32_MAX : NT);
     p.lds_bytes = int32_t(lds > INT32_MAX ? INT32_MAX : lds);
     p.acc_per_lane = int32_t(acc > INT32_MAX ? INT32_MAX : acc);
     p.tile[0] = int32_t(BM); p.tile[1] = int32_t(BN); p.tile[2] = int32_t(BK);
     p.wave_tile[0] = int32_t(four_level ? TM : BM); p.wave_tile[1] = int32_t(four_level ? TN : BN);
     p.sub_tiles[0] = int32_t(subm); p.sub_tiles[1] = int32_t(subn);
-    p.wave_passes = int32_t(four_level && nwr > 0 && path != 5 && path != 6 ? (WM * WN) / nwr : 1);
+    p.wave_passes = int32_t(four_level && nwr > 0 && path != 5 && path != 6 && path != 7 ? (WM * WN) / nwr : 1);
 
     // ---- black-box constraints made explicit: such members get fitness 0 (Sec. 4.2)
     if (NT > kMaxThreads) invalid(p, "%ld threads per workgroup > %ld", long(NT), long(kMaxThreads));
@@ -632,7 +691,7 @@ int decode(const opevo_op &op, int variant, const int32_t *cfg, Decoded &out)
                                                        : (BM * (BK / 4) + NT - 1) / NT + (BK * (BN / 4) + NT - 1) / NT;
         if (chunks * 4 > 256) invalid(p, "%ld staging registers per lane > 256", long(chunks * 4));
     }
-    else if (path != 0 && path != 3 && path != 5 && path != 6 && stage_lds) {
+    else if (path != 0 && path != 3 && path != 5 && path != 6 && path != 7 && stage_lds) {
         // register budget of the slab in flight: 16-byte pieces per thread
         const int64_t a_chunks = op.trans_a ? 8 * (((BK / 8) * (BM / 8) + NT - 1) / NT) : (BM * (BKP / 8) + NT - 1) / NT;
         const int64_t b_chunks = (op.kind == OPEVO_CONV2D) ? (BN * (BKP / 8) + NT - 1) / NT
@@ -641,7 +700,7 @@ int decode(const opevo_op &op, int variant, const int32_t *cfg, Decoded &out)
             invalid(p, "%ld staging registers per lane > 256", long((a_chunks + b_chunks) * 4));
     }
 
-    out.tmpl = path == 0 ? "gemm_scalar" : path == 3 ? "gemm_mfma_dlds" : path == 4 ? "gemm_mfma_f32" : path == 5 ? "conv_patch" : path == 6 ? "gemm_ragged" : "gemm_mfma";
+    out.tmpl = path == 0 ? "gemm_scalar" : path == 3 ? "gemm_mfma_dlds" : path == 4 ? "gemm_mfma_f32" : path == 5 ? "conv_patch" : path == 6 ? "gemm_ragged" : path == 7 ? "conv_rows" : "gemm_mfma";
     // one symbol per configuration, so profiles list each instantiated kernel on its own line
     {
         std::ostringstream nm;
@@ -657,11 +716,12 @@ int decode(const opevo_op &op, int variant, const int32_t *cfg, Decoded &out)
       << " -DK=" << op.K << " -DBM=" << BM << " -DBN=" << BN << " -DBK=" << BK << " -DKSTEPS=" << ksteps
       << " -DNT=" << NT << " -DBATCH_INNER=" << binner << " -DFLAG=" << flagv << " -DA_TRANS=" << (op.trans_a ? 1 : 0);
     if (path != 0) {
-        D << " -DATOM=" << (path == 5 ? patch_atom : (path == 2 || path == 6 || dlds_atom16) ? 16 : 32) << " -DWM=" << WM << " -DWN=" << WN << " -DTM=" << TM
+        D << " -DATOM=" << (path == 7 ? rows.atom : path == 5 ? patch_atom : (path == 2 || path == 6 || dlds_atom16) ? 16 : 32) << " -DWM=" << WM << " -DWN=" << WN << " -DTM=" << TM
           << " -DTN=" << TN << " -DFM=" << FM << " -DFN=" << FN << " -DPAD=" << kPad
           << " -DNSTAGE=" << nstage << " -DNSTG=" << nstage << " -DSTAGE_LDS=" << (stage_lds ? 1 : 0);
         if (nwr != WM * WN && path != 5) D << " -DNWR=" << nwr;
     }
+    if (path == 7) D << " -DWKP=" << rows.wkp << " -DMI=" << rows.mi << " -DNI=" << rows.ni << " -DLDS_BYTES=" << lds << " -DPERSIST=" << rows.persist << " -DNBOX=" << n1;
     if (path == 6) D << " -DKS=" << rg.ks << " -DNSL=" << rg.slabs << " -DMI=" << rg.mi << " -DNI=" << rg.ni << " -DLDS_BYTES=" << lds;
     if (subm * subn > 1) {
         D << " -DSUBM=" << subm << " -DSUBN=" << subn;
@@ -675,7 +735,7 @@ int decode(const opevo_op &op, int variant, const int32_t *cfg, Decoded &out)
         // fields are wide enough (byte offsets into the image tensor in 32 bits, padded image
         // coordinates in 15) and the table stays small (8 bytes per position of the reduction walk)
         const bool table = path != 0 && op.b_elems() < (int64_t(1) << 31) && op.hin + 2 * op.pad < 32768 &&
-                           op.win + 2 * op.pad < 32768 && op.hk < 32768 && op.wk < 32768 && ksplit * ksteps * BKP <= 8192 && !nhwc;
+                           op.win + 2 * op.pad < 32768 && op.hk < 32768 && op.wk < 32768 && ksplit * ksteps * BKP <= 8192 && !nhwc && path != 7;
         if (path != 0) D << " -DCONV_TABLE=" << (table ? 1 : 0);
         if (nhwc) D << " -DCONV_NHWC=1";
     }

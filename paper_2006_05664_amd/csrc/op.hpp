@@ -39,7 +39,8 @@ struct Decoded {
 };
 
 // OPEVO_OK (plan.status says valid/invalid) or OPEVO_E_ILLEGAL / OPEVO_E_ARG.
-int decode(const opevo_op &op, int variant, const int32_t *cfg, Decoded &out);
+// rows_ok = false: without the few-channels convolution template (a member that turned out to spill there).
+int decode(const opevo_op &op, int variant, const int32_t *cfg, Decoded &out, bool rows_ok = true);
 int op_param_descs(const opevo_op &op, int variant, std::vector<opevo_param_desc> &descs);
 
 }  // namespace opevo
