@@ -20,6 +20,62 @@
 #define PRAGMA_(x) _Pragma(#x)
 #define PRAGMA_UNROLL(n) PRAGMA_(unroll n)
 
+// MatMul / BatchMatMul tiles of at most 8 x 8 outputs that leave three quarters of the threads without one: 4 to 64 lanes share an
+// output, each taking every SPLIT-th step of the reduction straight from global memory, and add their partial sums across
+// the wave.  With one thread per output a 2 x 2 tile used 4 of its 64 lanes for a chain of K dependent steps, after a
+// round trip through LDS and its barrier; what is left is the launch and one load latency.  Measured on 64^3 fp32 in 2 x 2 tiles (1024
+// workgroups): 5.26 -> 2.62 us.  Larger tiles re-use operands enough to be better off in LDS: with two lanes per output (4 x 8
+// tiles) 512^3 took 103 us against 65, with four (4 x 4, 2 x 8) 1000^3 takes 736 and 730 us against 825 and 949.  A transposed first operand
+// would be read along its rows' stride by every lane (4 x 4 tiles of a batch of 64 x 64^3: 59 us against 49).
+constexpr int tiny_split()
+{
+    int s = 1;
+    while (2 * s <= 64 && 2 * s * BM * BN <= NT && 2 * s <= KSTEPS * BK) s *= 2;
+    return s;
+}
+#if OP != OP_CONV
+constexpr bool TINY = BM <= 8 && BN <= 8 && SUBM * SUBN == 1 && !A_TRANS && tiny_split() >= 4;
+#else
+constexpr bool TINY = false;
+#endif
+
+#if OP != OP_CONV
+// (the deadline is checked by every lane by itself, every 32 steps of its own: there is no barrier to leave together at)
+__device__ __forceinline__ void tiny_tile(const in_t *__restrict__ A, const in_t *__restrict__ B, float *__restrict__ C,
+                                          unsigned long long *ctl, const BlockId &bid, int tid)
+{
+    constexpr int S = tiny_split(), KT = KSTEPS * BK, FULL = KT / S;
+    const int o = tid / S, p = tid % S;
+    if (o >= BM * BN) return;                                    // whole groups of S lanes
+    const long gm = (long)bid.m * BM + o / BN, gn = (long)bid.n * BN + o % BN;
+    for (int bi = 0; bi < BATCH_INNER; ++bi) {
+#if KSPLIT > 1
+        const long batch = 0, kb = (long)bid.b * KT + p;
+#else
+        const long batch = (long)bid.b * BATCH_INNER + bi, kb = p;
+#endif
+        const in_t *a = A + batch * M * K + gm * K + kb;
+        const in_t *b = B + batch * K * N + kb * N + gn;
+        float acc = 0.f;
+        int j = 0;
+        for (; j + 8 <= FULL; j += 8) {
+            if (ctl && j % 32 == 0 && ctl[1] != 0 && wall_clock64() - ctl[0] > ctl[1]) { ctl[2] = 1; return; }
+#pragma unroll
+            for (int u = 0; u < 8; ++u)
+                acc = __builtin_fmaf(to_f32(a[(j + u) * S]), to_f32(b[(long)((j + u) * S) * N]), acc);
+        }
+#pragma unroll
+        for (int u = 0; u < FULL % 8; ++u)
+            acc = __builtin_fmaf(to_f32(a[(FULL / 8 * 8 + u) * S]), to_f32(b[(long)((FULL / 8 * 8 + u) * S) * N]), acc);
+        if (KT % S != 0 && p < KT % S)
+            acc = __builtin_fmaf(to_f32(a[FULL * S]), to_f32(b[(long)(FULL * S) * N]), acc);
+#pragma unroll
+        for (int d = S / 2; d > 0; d >>= 1) acc += __shfl_xor(acc, d);
+        if (p == 0) c_out(&C[batch * M * N + gm * N + gn], acc);
+    }
+}
+#endif
+
 extern "C" __global__ __launch_bounds__(NT)
 void KERNEL_NAME(const in_t *__restrict__ A, const in_t *__restrict__ B, float *__restrict__ C,
                   unsigned long long *ctl)
@@ -29,8 +85,11 @@ void KERNEL_NAME(const in_t *__restrict__ A, const in_t *__restrict__ B, float *
     float *Bs = smem_f + BM * BK;   // [BK][BN]
     __shared__ int expired;
     const int tid = threadIdx.x;
-    if (tid == 0) expired = 0;
     const BlockId bid = block_id();
+#if OP != OP_CONV
+    if constexpr (TINY) { tiny_tile(A, B, C, ctl, bid, tid); return; }
+#endif
+    if (tid == 0) expired = 0;
     constexpr int E = (BM * BN + NT - 1) / NT;
 
 #if OP == OP_CONV
