@@ -629,6 +629,23 @@ int decode(const opevo_op &op, int variant, const int32_t *cfg, Decoded &out, bo
         WM = rows.wm; WN = rows.wn; TM = rows.mi * rows.atom; TN = rows.ni * rows.atom;
         TMacc = TM; TNacc = TN; BK = op.K; BKP = op.K; ksteps = 1; ragged = false; tap_box = false;
     }
+    // Direct-to-LDS MatMul / BMM members of one or two waves (or four on short slabs) whose grid leaves every compute unit
+    // at most one workgroup: two groups of waves share the reduction.  A slab of one wave is a chain of latencies of some
+    // 0.15 us (64 x 64 x 8192 in 32 x 32 tiles: 22.2 -> 11.2 us; 96 x 160 x 512, 8 steps of 64: 3.40 -> 2.84; 480 x 480 x 1024: 4.81 -> 3.94); with more
+    // bytes per slab it is what a compute unit can load (12 KB, 2 waves: 80 workgroups x 32 steps 6.69 -> 5.50 us, x 8 steps 3.35 ->
+    // 3.61, 225 workgroups x 32 steps 8.65 -> 9.14; 8 KB, 4 waves: 64 workgroups x 32 steps 4.78 -> 4.48, 256 workgroups 5.56 -> 5.58; 16 KB, 4
+    // waves: always slower).  Four groups were nowhere better than two by more than the noise, and slower on most shapes.
+    int kgrp = 1;
+    if (path == 3 && op.kind != OPEVO_CONV2D && ksteps % 2 == 0) {
+        const int64_t nw = WM * WN, stage = (BM + BN) * BK * 2, per = stage / (1024 * nw), wgs = n1 * m1 * b1;
+        const bool pays = (nw == 1 && wgs <= 256 && ksteps >= 8) ||
+                          (nw == 2 && wgs <= (stage <= 8192 ? 256 : 128) && stage <= 12288 && ksteps >= 16) ||
+                          (nw == 4 && wgs <= 128 && stage <= 8192 && ksteps >= 32);
+        // (the ring of both groups within the LDS, the sum of one of them within the ring, the loads in flight countable)
+        for (int st = std::min(4, nstage_dlds); pays && st >= 2 && kgrp == 1; --st)
+            if (2 * st * stage <= kMaxLds && nw * TM * TN * 4 <= 2 * st * stage && (2 * st - 2) * per <= 63 &&
+                !(dlds_atom16 && BK % 64 != 0 && st % 2 != 0)) { kgrp = 2; nstage_dlds = 2 * st; }
+    }
     const bool b_kmajor = path == 3 && (b_packed || op.kind == OPEVO_CONV2D);
     const bool nhwc = nhwc_ok && (path == 1 || path == 2 || path == 3);
     // a transposed first operand is staged by the MFMA templates like B (rows of 8 along M), so it
@@ -671,7 +688,7 @@ int decode(const opevo_op &op, int variant, const int32_t *cfg, Decoded &out, bo
     if (linear) { p.grid[0] = int32_t(n_blocks > INT32_MAX ? INT32_MAX : n_blocks); p.grid[1] = 1; p.grid[2] = 1; }
     else { p.grid[0] = int32_t(n1); p.grid[1] = int32_t(m1); p.grid[2] = int32_t(b1); }
     if (rows.persist > 0) p.grid[0] = rows.persist;   // workgroups that take several boxes each
-    p.block = int32_t(NT > INT32_MAX ? INT32_MAX : NT);
+    p.block = int32_t(NT > INT32_MAX ? INT32_MAX : NT * kgrp);
     p.lds_bytes = int32_t(lds > INT32_MAX ? INT32_MAX : lds);
     p.acc_per_lane = int32_t(acc > INT32_MAX ? INT32_MAX : acc);
     p.tile[0] = int32_t(BM); p.tile[1] = int32_t(BN); p.tile[2] = int32_t(BK);
@@ -745,6 +762,7 @@ int decode(const opevo_op &op, int variant, const int32_t *cfg, Decoded &out, bo
     if (path == 5) D << " -DCS=" << patch_cs << " -DPWP=" << patch_row << " -DIPIX=" << patch_image << " -DKW=" << patch_kw << " -DLDS_BYTES=" << lds;
     if (b_kmajor) D << " -DB_KMAJOR=1 -DBNR=" << bnr;
     if (path == 3 && anr != BM) D << " -DANR=" << anr;
+    if (kgrp > 1) D << " -DKGRP=" << kgrp;
     if (kunroll) D << " -DKUNROLL=" << kunroll;
     if (ksplit > 1) D << " -DKSPLIT=" << ksplit;
     out.zero_bytes = ksplit > 1 ? op.c_elems() * 4 : 0;

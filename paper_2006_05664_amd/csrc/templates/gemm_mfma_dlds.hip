@@ -81,7 +81,16 @@ constexpr int KA = ATOM == 16 ? 32 : 16;        // reduction values one MFMA con
 #if OP == OP_CONV && !(B_KMAJOR && CONV_NHWC)
 #error "Conv2d runs on this template with channels-last operands only"
 #endif
-constexpr int NW = NT / 64;
+// KGRP groups of NT / 64 waves share a workgroup's tile, each walking its own KGRP-th of the reduction with NSTG / KGRP
+// stages of the ring to itself; their sums meet in LDS at the end.  For grids that leave compute units with a single
+// workgroup: the slabs of one workgroup are a chain of latencies (load, barrier, fragment reads, a few MFMAs), and KGRP chains
+// side by side take that much less time.
+#ifndef KGRP
+#define KGRP 1
+#endif
+constexpr int STAGES = NSTG / KGRP, GSTEPS = KSTEPS / KGRP;   // of one group
+static_assert(STAGES * KGRP == NSTG && GSTEPS * KGRP == KSTEPS && STAGES >= 2, "decoder and template disagree");
+constexpr int NW = NT / 64;                                   // waves of one group
 constexpr int MI = TM / ATOM, NI = (TN + ATOM - 1) / ATOM;
 constexpr int KK = BK / KA;                                   // MFMA K steps per slab
 #if ATOM == 16 && (A_TRANS || OP == OP_CONV || B_KMAJOR)
@@ -324,15 +333,22 @@ __device__ __forceinline__ v4s read_b_half(const u16 *stage, int wn, int lane, i
 #define WAIT_LGKM_VMCNT(n) __builtin_amdgcn_s_waitcnt((VMC(n) & 0xf) | ((VMC(n) >> 4) << 14) | (0x7 << 4) | (0x0 << 8))
 #define WAIT_LGKM() __builtin_amdgcn_s_waitcnt(0xf | (0x3 << 14) | (0x7 << 4) | (0x0 << 8))
 #define BARRIER() do { asm volatile("" ::: "memory"); __builtin_amdgcn_s_barrier(); asm volatile("" ::: "memory"); } while (0)
-#define KCLAMP(k) ((k) < KSTEPS ? (k) : KSTEPS - 1)
+#define KCLAMP(k) ((k) < GSTEPS ? (k) : GSTEPS - 1)
 
-extern "C" __global__ __launch_bounds__(NT)
+extern "C" __global__ __launch_bounds__(NT * KGRP)
 void KERNEL_NAME(const u16 *__restrict__ A, const u16 *__restrict__ B, float *__restrict__ C,
                  unsigned long long *ctl /* deadline control, used by the scalar template only */)
 {
-    __shared__ __attribute__((aligned(1024))) u16 ring[NSTG * STAGE];
+    __shared__ __attribute__((aligned(1024))) u16 whole_ring[NSTG * STAGE];
+    const int tid = threadIdx.x, lane = tid & 63;
+#if KGRP > 1
+    const int grp = __builtin_amdgcn_readfirstlane((tid >> 6) / NW), wave = (tid >> 6) % NW;
+#else
+    constexpr int grp = 0;
+    const int wave = tid >> 6;
+#endif
+    u16 *const ring = whole_ring + grp * (STAGES * STAGE);
     const unsigned ring_addr = __builtin_amdgcn_readfirstlane((unsigned)(unsigned long)(__attribute__((address_space(3))) u16 *)ring);   // LDS byte address
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int wm = wave / WN, wn = wave % WN;
     const BlockId bid = block_id();
     const int m0 = bid.m * BM, n0 = bid.n * BN;
@@ -371,6 +387,18 @@ void KERNEL_NAME(const u16 *__restrict__ A, const u16 *__restrict__ B, float *__
         const u16 *Bb = B + batch * K * N;
         float *Cb = C + batch * M * N;
 #endif
+#if KGRP > 1   // this group's part of the reduction
+#if A_TRANS
+        Ab += (long)grp * (GSTEPS * BK) * M;
+#else
+        Ab += grp * (GSTEPS * BK);
+#endif
+#if B_KMAJOR
+        Bb += grp * (GSTEPS * BK);
+#else
+        Bb += (long)grp * (GSTEPS * BK) * N;
+#endif
+#endif
 
         acc_t acc[MI][NI];
 #pragma unroll
@@ -384,13 +412,13 @@ void KERNEL_NAME(const u16 *__restrict__ A, const u16 *__restrict__ B, float *__
             WAIT_VMCNT(0);
             BARRIER();
         }
-        // prologue: slabs 0 .. NSTG-1 in flight (one per stage), slab 0 landed, its first fragments read
+        // prologue: slabs 0 .. STAGES-1 in flight (one per stage), slab 0 landed, its first fragments read
 #pragma unroll
-        for (int s = 0; s < NSTG; ++s)
+        for (int s = 0; s < STAGES; ++s)
 #pragma unroll
             for (int t = 0; t < PER; ++t)
                 issue_piece(t, Ab, Bb, ring_addr + s * STAGE * 2, m0, n0, kbase + KCLAMP(s) * BK, slot, aoff, boff);
-        WAIT_VMCNT((NSTG - 1) * PER);
+        WAIT_VMCNT((STAGES - 1) * PER);
         BARRIER();
         // Wave tiles of one or two atoms have too few MFMAs per 16-wide K step to cover the latency of the
         // next step's fragment reads (the steps of a slab then form a chain of LDS latencies).  Such
@@ -457,8 +485,8 @@ void KERNEL_NAME(const u16 *__restrict__ A, const u16 *__restrict__ B, float *__
             for (int kg = 0; kg < KG; ++kg) {
                 const bool last = kg + 1 == KG;
                 const int nact = NRG + (last ? PER : 0);
-                const u16 *nstage = ring + (last ? (s + 1) % NSTG : s) * STAGE;
-                static_assert(KG % 2 == 0 || NSTG % 2 == 0, "buffer halves must alternate at compile time");
+                const u16 *nstage = ring + (last ? (s + 1) % STAGES : s) * STAGE;
+                static_assert(KG % 2 == 0 || STAGES % 2 == 0, "buffer halves must alternate at compile time");
                 const int cur = (((s & 1) * (KG & 1)) + kg) & 1;
                 const int nkg = last ? 0 : kg + 1, nh = cur ^ 1;
 #pragma unroll
@@ -466,7 +494,7 @@ void KERNEL_NAME(const u16 *__restrict__ A, const u16 *__restrict__ B, float *__
                     const int g = m / (MI * NI), i = (m % (MI * NI)) / NI, j = m % NI;
                     acc[i][j] = MFMA(A_FRAG(cur * G + g, i), B_FRAG(cur * G + g, j), acc[i][j]);
                     if (m == 0 && last) {
-                        WAIT_LGKM_VMCNT((NSTG - 2) * PER);
+                        WAIT_LGKM_VMCNT((STAGES - 2) * PER);
                         BARRIER();
                     }
                     constexpr int UMAX = (NRG + PER + SLOTS - 1) / SLOTS + 1;    // most actions behind one MFMA
@@ -479,7 +507,7 @@ void KERNEL_NAME(const u16 *__restrict__ A, const u16 *__restrict__ B, float *__
                         else {
                             // the last group's actions: the NRG reads with the PER loads spread evenly among them
                             const int nl = a * PER / nact, nl1 = (a + 1) * PER / nact;
-                            if (nl1 > nl) issue_piece(nl, Ab, Bb, ring_addr + s * STAGE * 2, m0, n0, kbase + KCLAMP(q + NSTG) * BK, slot, aoff, boff);
+                            if (nl1 > nl) issue_piece(nl, Ab, Bb, ring_addr + s * STAGE * 2, m0, n0, kbase + KCLAMP(q + STAGES) * BK, slot, aoff, boff);
                             else group_read(nh, nstage, nkg, a - nl);
                         }
                     }
@@ -487,19 +515,51 @@ void KERNEL_NAME(const u16 *__restrict__ A, const u16 *__restrict__ B, float *__
                 }
             }
         };
-        constexpr int KMAIN = KSTEPS / NSTG * NSTG;
-        for (int kt = 0; kt < KMAIN; kt += NSTG) {
+        constexpr int KMAIN = GSTEPS / STAGES * STAGES;
+        for (int kt = 0; kt < KMAIN; kt += STAGES) {
 #pragma unroll
-            for (int s = 0; s < NSTG; ++s) slab_step(kt + s, s);
+            for (int s = 0; s < STAGES; ++s) slab_step(kt + s, s);
         }
 #pragma unroll
-        for (int s = 0; s < KSTEPS - KMAIN; ++s) slab_step(KMAIN + s, s);
+        for (int s = 0; s < GSTEPS - KMAIN; ++s) slab_step(KMAIN + s, s);
 
-        // The last NSTG slab steps issued loads past the end of K (redundant copies of the last
+        // The last STAGES slab steps issued loads past the end of K (redundant copies of the last
         // slab, so that the wait counts stay uniform).  They must have landed before this wave ends:
         // a load that arrives after the workgroup's LDS has been handed to another workgroup would
         // write into memory this kernel no longer owns.
         WAIT_VMCNT(0);
+#if KGRP > 1
+        // The groups' sums: all but the first put theirs in the ring, which nobody reads or fills any longer once every
+        // wave is here, R[group][wave][4 registers][lane]; the first adds them in the order of the groups.
+        static_assert((KGRP - 1) * NW * MI * NI * ACC_N * 256 <= NSTG * STAGE * 2, "the ring cannot hold the groups' sums");
+        f32x4 *R = (f32x4 *)whole_ring;
+        __syncthreads();
+        if (grp > 0) {
+#pragma unroll
+            for (int i = 0; i < MI; ++i)
+#pragma unroll
+                for (int j = 0; j < NI; ++j)
+#pragma unroll
+                    for (int r = 0; r < ACC_N / 4; ++r) {
+                        const f32x4 v = {acc[i][j][4 * r], acc[i][j][4 * r + 1], acc[i][j][4 * r + 2], acc[i][j][4 * r + 3]};
+                        R[((((grp - 1) * NW + wave) * MI + i) * NI + j) * (ACC_N / 4 * 64) + r * 64 + lane] = v;
+                    }
+        }
+        __syncthreads();
+        if (grp > 0) continue;
+#pragma unroll
+        for (int g = 0; g < KGRP - 1; ++g)
+#pragma unroll
+            for (int i = 0; i < MI; ++i)
+#pragma unroll
+                for (int j = 0; j < NI; ++j)
+#pragma unroll
+                    for (int r = 0; r < ACC_N / 4; ++r) {
+                        const f32x4 v = R[(((g * NW + wave) * MI + i) * NI + j) * (ACC_N / 4 * 64) + r * 64 + lane];
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) acc[i][j][4 * r + e] += v[e];
+                    }
+#endif
         // Epilogue: an atom's result sits with column (l % ATOM) in lane l; 32x32 atoms: register r is
         // row 8*(r/4) + 4*(l/32) + r%4; 16x16 atoms: row 4*(l/16) + r.
 #pragma unroll
