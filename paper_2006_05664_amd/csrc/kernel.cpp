@@ -66,21 +66,32 @@ int build_kernel(const opevo_op &op, int variant, const int32_t *cfg, opevo_kern
     if (int rc = decode(op, variant, cfg, d)) return rc;
     if (d.plan.status != OPEVO_OK) return fail(OPEVO_E_INVALID, "invalid configuration: %s", d.plan.reason);
     const auto t0 = std::chrono::steady_clock::now();
-    std::string key = code_cache_key(d.tmpl, d.defines);
+    std::string key;
     CompileResult r;
-    bool cached = code_cache_get(key, r.code);
-    if (!cached) r = pool_compile(d.tmpl, d.defines);
-    if (d.plan.path == 7 && r.status == OPEVO_OK && code_scratch_bytes(r.code, d.kernel_name) != 0) {
-        // the few-channels template keeps the kernel tensor in registers: a member whose estimate was too low and that
-        // spills runs where it would without that template (the spilling object stays cached, so that this is found at once next time)
+    bool cached = false;
+    auto compile = [&](const std::string &defines) {
+        key = code_cache_key(d.tmpl, defines);
+        r = CompileResult();
+        cached = code_cache_get(key, r.code);
+        if (!cached) r = pool_compile(d.tmpl, defines);
+        d.defines = defines;
+    };
+    // (an object that spills and is not used stays cached, so that a later build finds out at once)
+    auto spills = [&]() {
+        if (r.status != OPEVO_OK || code_scratch_bytes(r.code, d.kernel_name) <= 0) return false;
         if (!cached) code_cache_put(key, r.code);
+        return true;
+    };
+    const std::string plain = d.defines;
+    compile(plain + d.try_defines);
+    if (!d.try_defines.empty() && spills()) compile(plain);
+    if (d.plan.path == 7 && spills()) {
+        // the few-channels template keeps the kernel tensor in registers: a member whose estimate was too low
+        // runs where it would without that template
         d = Decoded();
         if (int rc = decode(op, variant, cfg, d, false)) return rc;
         if (d.plan.status != OPEVO_OK) return fail(OPEVO_E_INVALID, "invalid configuration: %s", d.plan.reason);
-        key = code_cache_key(d.tmpl, d.defines);
-        r = CompileResult();
-        cached = code_cache_get(key, r.code);
-        if (!cached) r = pool_compile(d.tmpl, d.defines);
+        compile(std::string(d.defines));
     }
     if (r.status == OPEVO_E_INVALID)
         return fail(r.status, "invalid configuration: %s [%s]", r.log.c_str(), d.kernel_name.c_str());

@@ -762,6 +762,10 @@ int decode(const opevo_op &op, int variant, const int32_t *cfg, Decoded &out, bo
     if (path == 5) D << " -DCS=" << patch_cs << " -DPWP=" << patch_row << " -DIPIX=" << patch_image << " -DKW=" << patch_kw << " -DLDS_BYTES=" << lds;
     if (b_kmajor) D << " -DB_KMAJOR=1 -DBNR=" << bnr;
     if (path == 3 && anr != BM) D << " -DANR=" << anr;
+    // fp32, two stages: the pipelined slab loop, but for short reductions on a full chip, where the other workgroups cover a
+    // slab's latency and the registers are better spent on them (a batch of 960 of 128 x 64 x 128 with the first operand transposed:
+    // 960 x 4 waves, 4 slabs, 27.0 us without and 29.9 with; 132 x 64 x 224 x 128, 924 x 2 waves, 2 slabs, 16.2 and 13.9)
+    if (path == 4 && nstage == 2 && !(ksteps < 8 && n_blocks * nwr >= 2048)) out.try_defines = " -DPIPELINED=1";
     if (kgrp > 1) D << " -DKGRP=" << kgrp;
     if (kunroll) D << " -DKUNROLL=" << kunroll;
     if (ksplit > 1) D << " -DKSPLIT=" << ksplit;

@@ -31,6 +31,9 @@ struct Decoded {
     opevo_plan plan;
     std::string tmpl;      // template name: "gemm_scalar" or "gemm_mfma"
     std::string defines;   // space separated -D options
+    // Options the kernel is better with where its registers hold them: a build whose kernel spills with them is done again
+    // without (empty: none).
+    std::string try_defines;
     std::string kernel_name;   // symbol of the instantiated kernel
     int64_t zero_bytes = 0;    // bytes of the output the host clears before every launch (split reduction), else 0
     // pre-pass before every launch: 0 none; 1 Conv2d: the kernel reads channels-last copies of both operands;

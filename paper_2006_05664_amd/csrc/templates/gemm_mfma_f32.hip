@@ -25,6 +25,9 @@
 // FLAG = 0: one stage, load -> barrier -> store -> barrier -> compute.
 
 typedef f32x16 acc_t;
+#ifndef PIPELINED
+#define PIPELINED 0
+#endif
 #ifndef BKP
 #define BKP BK
 #endif
@@ -93,15 +96,18 @@ __device__ __forceinline__ void load_slab(Slab &s, const float *__restrict__ Ab,
     }
 }
 
-__device__ __forceinline__ void store_slab(const Slab &s, float *As, float *Bs, int tid)
+// the thread's pieces n0 .. n1-1 of a slab (A's first)
+__device__ __forceinline__ void store_pieces(const Slab &s, float *As, float *Bs, int tid, int n0, int n1)
 {
 #pragma unroll
     for (int i = 0; i < NA; ++i) {
+        if (i < n0 || i >= n1) continue;
         const int q = tid + i * NT;
         if (A_CHUNKS % NT == 0 || q < A_CHUNKS) *(f32x4 *)(As + (q / (BKP / 4)) * LDA + (q % (BKP / 4)) * 4) = s.a[i];
     }
 #pragma unroll
     for (int i = 0; i < NB; ++i) {
+        if (NA + i < n0 || NA + i >= n1) continue;
         const int q = tid + i * NT;
         if (B_CHUNKS % NT == 0 || q < B_CHUNKS) *(f32x4 *)(Bs + (q / BN4) * LDB + (q % BN4) * 4) = s.b[i];
     }
@@ -128,10 +134,12 @@ __device__ __forceinline__ void load_slab(Slab &s, const float *__restrict__ Ab,
     }
 }
 
-__device__ __forceinline__ void store_slab(const Slab &s, float *As, float *Bs, int tid)
+// the thread's pieces n0 .. n1-1 of a slab (A's first)
+__device__ __forceinline__ void store_pieces(const Slab &s, float *As, float *Bs, int tid, int n0, int n1)
 {
 #pragma unroll
     for (int i = 0; i < NA; ++i) {
+        if (i < n0 || i >= n1) continue;
         const int q = tid + i * NT;
 #if A_TRANS
         if (A_CHUNKS % NT == 0 || q < A_CHUNKS) *(f32x4 *)(As + (q / (BM / 4)) * LDA + (q % (BM / 4)) * 4) = s.a[i];
@@ -141,44 +149,81 @@ __device__ __forceinline__ void store_slab(const Slab &s, float *As, float *Bs, 
     }
 #pragma unroll
     for (int i = 0; i < NB; ++i) {
+        if (NA + i < n0 || NA + i >= n1) continue;
         const int q = tid + i * NT;
         if (B_CHUNKS % NT == 0 || q < B_CHUNKS) *(f32x4 *)(Bs + (q / (BN / 4)) * LDB + (q % (BN / 4)) * 4) = s.b[i];
     }
 }
 #endif
+__device__ __forceinline__ void store_slab(const Slab &s, float *As, float *Bs, int tid) { store_pieces(s, As, Bs, tid, 0, NA + NB); }
+
+// The fragments of one group of 8 reduction steps: 4 values per lane and atom row, and per MFMA one per atom column.
+struct Frags { f32x4 a[MI]; float b[4][NI]; };
+__device__ __forceinline__ void load_frags(Frags &f, const float *As, const float *Bs, int wm, int wn, int lane, int g)
+{
+    const int l32 = lane & 31, half = lane >> 5;
+#if A_TRANS
+#pragma unroll
+    for (int i = 0; i < MI; ++i)
+#pragma unroll
+        for (int j4 = 0; j4 < 4; ++j4) f.a[i][j4] = As[(g * 8 + 4 * half + j4) * LDA + wm * TM + i * 32 + l32];
+#else
+#pragma unroll
+    for (int i = 0; i < MI; ++i) f.a[i] = *(const f32x4 *)(As + (wm * TM + i * 32 + l32) * LDA + g * 8 + 4 * half);
+#endif
+#pragma unroll
+    for (int j4 = 0; j4 < 4; ++j4)
+#pragma unroll
+        for (int j = 0; j < NI; ++j) f.b[j4][j] = Bs[(g * 8 + 4 * half + j4) * LDB + wn * TN + j * 32 + l32];
+}
+__device__ __forceinline__ void multiply(acc_t (&acc)[MI][NI], const Frags &f)
+{
+#pragma unroll
+    for (int j4 = 0; j4 < 4; ++j4)
+#pragma unroll
+        for (int i = 0; i < MI; ++i)
+#pragma unroll
+            for (int j = 0; j < NI; ++j)
+                acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(f.a[i][j4], f.b[j4][j], acc[i][j], 0, 0, 0);
+}
 
 __device__ __forceinline__ void compute_slab(acc_t (&acc)[MI][NI], const float *As, const float *Bs, int wm, int wn, int lane)
 {
-    const int l32 = lane & 31, half = lane >> 5;
 #if FLAG
 #pragma unroll
 #else
 #pragma unroll 1
 #endif
     for (int g = 0; g < BKP / 8; ++g) {
-        f32x4 af[MI];
-#if A_TRANS
-#pragma unroll
-        for (int i = 0; i < MI; ++i)
-#pragma unroll
-            for (int j4 = 0; j4 < 4; ++j4) af[i][j4] = As[(g * 8 + 4 * half + j4) * LDA + wm * TM + i * 32 + l32];
-#else
-#pragma unroll
-        for (int i = 0; i < MI; ++i) af[i] = *(const f32x4 *)(As + (wm * TM + i * 32 + l32) * LDA + g * 8 + 4 * half);
-#endif
-#pragma unroll
-        for (int j4 = 0; j4 < 4; ++j4) {
-            float bf[NI];
-#pragma unroll
-            for (int j = 0; j < NI; ++j) bf[j] = Bs[(g * 8 + 4 * half + j4) * LDB + wn * TN + j * 32 + l32];
-#pragma unroll
-            for (int i = 0; i < MI; ++i)
-#pragma unroll
-                for (int j = 0; j < NI; ++j)
-                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(af[i][j4], bf[j], acc[i][j], 0, 0, 0);
-        }
+        Frags f;
+        load_frags(f, As, Bs, wm, wn, lane, g);
+        multiply(acc, f);
     }
 }
+
+// PIPELINED (two stages, where the registers hold it): the loads of the next slab stay in front of this slab's MFMAs (left
+// to itself the compiler moves them behind the last one, next to the stores that use them, and every slab waits for
+// memory once), the fragments of a group are read before the MFMAs of the group before it, and the next slab goes to the
+// other stage between the MFMAs of the second half.  What is left between two slabs is the barrier and one fragment read;
+// workgroups that share a compute unit run in step and do not cover it for each other.
+// 512 x 4096 x 1024 in 64 x 64 tiles 47.0 -> 45.2 us (every compute unit has two workgroups); with one or none 512 x 1024 x 4096 in 32 x 64
+// tiles 230 -> 146 us, in 32 x 32 tiles 196 -> 86, 608 x 160 x 1536 in 32 x 32 tiles 90 -> 33.
+#if PIPELINED
+__device__ __forceinline__ void multiply_and_store(acc_t (&acc)[MI][NI], const float *As, const float *Bs, int wm, int wn, int lane,
+                                                   const Slab &next, float *An, float *Bn, int tid)
+{
+    constexpr int GROUPS = BKP / 8, HALF = GROUPS / 2, REST = GROUPS - HALF;
+    Frags f[2];
+    load_frags(f[0], As, Bs, wm, wn, lane, 0);
+#pragma unroll
+    for (int g = 0; g < GROUPS; ++g) {
+        if (g + 1 < GROUPS) load_frags(f[(g + 1) & 1], As, Bs, wm, wn, lane, g + 1);
+        multiply(acc, f[g & 1]);
+        if (g >= HALF) store_pieces(next, An, Bn, tid, (NA + NB) * (g - HALF) / REST, (NA + NB) * (g - HALF + 1) / REST);
+        __builtin_amdgcn_sched_barrier(0);
+    }
+}
+#endif
 
 extern "C" __global__ __launch_bounds__(NT)
 void KERNEL_NAME(const float *__restrict__ A, const float *__restrict__ B, float *__restrict__ C,
@@ -250,10 +295,16 @@ void KERNEL_NAME(const float *__restrict__ A, const float *__restrict__ B, float
         __syncthreads();
         for (int kt = 0; kt < KSTEPS; ++kt) {
             const int cur = kt & 1, nxt = cur ^ 1;
-            // slab index clamped past the end: one redundant load instead of a branch around the accumulators
+            // slab index clamped past the end: one redundant load instead of a branch around the accumulators (a last
+            // slab of its own was measured: up to a tenth slower with slabs of 16)
             LOAD_SLAB(slab, (kt + 1 < KSTEPS ? kt + 1 : KSTEPS - 1));
+#if PIPELINED
+            __builtin_amdgcn_sched_barrier(0);
+            multiply_and_store(acc, As + cur * A_STAGE, Bs + cur * B_STAGE, wm, wn, lane, slab, As + nxt * A_STAGE, Bs + nxt * B_STAGE, tid);
+#else
             compute_slab(acc, As + cur * A_STAGE, Bs + cur * B_STAGE, wm, wn, lane);
             store_slab(slab, As + nxt * A_STAGE, Bs + nxt * B_STAGE, tid);
+#endif
             __syncthreads();
         }
 #else
