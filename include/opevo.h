@@ -284,7 +284,8 @@ typedef enum { OPEVO_F32 = 0, OPEVO_BF16 = 1, OPEVO_F16 = 2 } opevo_dtype;
  *         slab's MFMA steps (taps x groups of channels) round-robin among themselves; their partial sums are added
  *         through LDS after the last slab, in the order of the waves (deterministic).  The workgroup then has
  *         (waves along Cout) x (waves along the pixels) x kwaves waves; where it cannot hold them (16 waves, registers,
- *         LDS for the final sum) the member runs with kwaves = 1. */
+ *         LDS for the final sum) the member runs with kwaves = 1.  With kwaves = 1, workgroups of one or two waves that
+ *         do not fill the chip run with two or four waves per tile. */
 typedef enum { OPEVO_TILE2 = 0, OPEVO_TILE4 = 1, OPEVO_TILE4X = 2, OPEVO_TILE4P = 3, OPEVO_TILE4K = 4, OPEVO_TILE4C = 5, OPEVO_TILE4T = 6,
                OPEVO_TILE4A = 7, OPEVO_TILE4L = 8 } opevo_variant;
 

@@ -261,7 +261,7 @@ static void invalid(opevo_plan &p, const char *fmt, long a = 0, long b = 0)
     snprintf(p.reason, sizeof p.reason, fmt, a, b);
 }
 
-int decode(const opevo_op &op, int variant, const int32_t *cfg, Decoded &out, bool rows_ok)
+int decode(const opevo_op &op, int variant, const int32_t *cfg, Decoded &out, bool extras)
 {
     std::vector<opevo_param_desc> descs;
     if (int rc = op_param_descs(op, variant, descs)) return rc;
@@ -401,31 +401,49 @@ int decode(const opevo_op &op, int variant, const int32_t *cfg, Decoded &out, bo
                     for (int64_t kw = int64_t(kReductionWaves[c[18]]); kw >= 1 && !patch_cs && tm % 16 == 0; kw /= 2) {
                         int64_t wn = WN, tn = TN;
                         while (wm * wn * kw > kMaxThreads / 64 && wn > 1) { const int64_t q = prime(wn); wn /= q; tn *= q; }
-                        const int64_t nw = wm * wn * kw, nt = 64 * nw;
-                        if (nt > kMaxThreads) continue;
+                        if (64 * wm * wn * kw > kMaxThreads) continue;
                         auto fits = [&](int64_t at) {
                             return tm % at == 0 && cs % (at == 32 ? 16 : 32) == 0 && up(tn, at) <= 2 * tn && tm * up(tn, at) <= 64 * kMaxAcc;
                         };
                         const int at = fits(32) && (!fits(16) || up(tn, 32) == up(tn, 16)) ? 32 : fits(16) ? 16 : 0;
-                        if (!at || kw > taps * (cs / (at == 32 ? 16 : 32))) continue;   // no atom fits; more waves than steps
+                        if (!at) continue;
                         // the fill: per thread, tasks of two channels x two pixels (images one pixel wide, which the template would fill pixel by pixel, stay with layout 0) and of two channels x all taps (kernel tensor)
-                        const int64_t fill_p = (cs / 2 * (op.win >= 2 ? pw / 2 + 1 : pw) * ph * nb2 + nt - 1) / nt, fill_a = (wm * tm * cs / 2 + nt - 1) / nt;
-                        // Registers: a lane has 512 / (waves per SIMD).  Counted: the accumulators, two sets of fragments (4 per
-                        // atom row and column; three sets for small wave tiles), the fill (3 + 2 per image task, 2 + taps per
-                        // kernel-tensor task: plan + data in flight), 24 for addresses, and where waves share a tile 40 + three
-                        // quarters of the accumulators again (the final sum moves them through ordinary registers).  An eighth
-                        // over is let through: the compiler fits such members.  Calibrated on compiled members: of 150 random
-                        // eligible ones the rule lets no spilling member through and turns away 3 that would have fitted; a
-                        // member that spills all the same is refused when its kernel is loaded.
-                        const int64_t fill = 5 * fill_p + (2 + taps) * fill_a;
-                        const int64_t accs = tm * up(tn, at) / 64;
-                        const int64_t frags = tm / at + up(tn, at) / at;
-                        const int64_t need = accs + (frags <= 3 ? 12 : 8) * frags + 24 + fill + (kw > 1 ? 40 + accs * 3 / 4 : 0);
-                        const int64_t have = 512 / ((nw + 3) / 4);
-                        // adding the partial sums of kw waves needs room for one atom of every wave
-                        const int64_t lds_r = kw > 1 ? nw * (at == 32 ? 4 : 1) * 1024 : 0;
-                        if (lds_p <= kMaxLds && lds_r <= kMaxLds && need <= have + have / 8) {
+                        // (w: the waves that share a tile)
+                        auto room = [&](int64_t w) {
+                            const int64_t nw = wm * wn * w, nt = 64 * nw;
+                            if (w > taps * (cs / (at == 32 ? 16 : 32))) return false;   // more waves than steps
+                            const int64_t fill_p = (cs / 2 * (op.win >= 2 ? pw / 2 + 1 : pw) * ph * nb2 + nt - 1) / nt, fill_a = (wm * tm * cs / 2 + nt - 1) / nt;
+                            // Registers: a lane has 512 / (waves per SIMD).  Counted: the accumulators, two sets of fragments (4 per
+                            // atom row and column; three sets for small wave tiles), the fill (3 + 2 per image task, 2 + taps per
+                            // kernel-tensor task: plan + data in flight), 24 for addresses, and where waves share a tile 40 + three
+                            // quarters of the accumulators again (the final sum moves them through ordinary registers).  An eighth
+                            // over is let through: the compiler fits such members.  Calibrated on compiled members: of 150 random
+                            // eligible ones the rule lets no spilling member through and turns away 3 that would have fitted; a
+                            // member that spills all the same is refused when its kernel is loaded.
+                            const int64_t fill = 5 * fill_p + (2 + taps) * fill_a;
+                            const int64_t accs = tm * up(tn, at) / 64;
+                            const int64_t frags = tm / at + up(tn, at) / at;
+                            const int64_t need = accs + (frags <= 3 ? 12 : 8) * frags + 24 + fill + (w > 1 ? 40 + accs * 3 / 4 : 0);
+                            const int64_t have = 512 / ((nw + 3) / 4);
+                            // adding the partial sums of kw waves needs room for one atom of every wave
+                            const int64_t lds_r = w > 1 ? nw * (at == 32 ? 4 : 1) * 1024 : 0;
+                            return lds_p <= kMaxLds && lds_r <= kMaxLds && need <= have + have / 8;
+                        };
+                        if (room(kw)) {
                             patch_cs = cs; patch_atom = at; patch_stages = st; patch_row = prow; patch_image = pimage; patch_kw = int(kw);
+                            // Workgroups of one or two waves that do not fill the chip get waves that share a tile although the member
+                            // asks for none: nothing else hides a fragment read there, and the fill is shared as well.  Measured, bf16,
+                            // 80 members of up to 512 workgroups, 1.00 to 2.1 times as fast: 12 x 256 x 13 x 13 * 96 x 256 x 5 x 5 as 36
+                            // workgroups of one wave 68.2 -> 31.9 us, 6 x 96 x 13 x 13 * 128 x 96 x 5 x 5 as 12 of two waves 28.1 -> 20.1.
+                            // Past one workgroup per compute unit: one wave as 475: 11.4 -> 10.7 with two, 10.6 with four; as 550: 20.5 ->
+                            // 20.5 and 26.2; two waves as 453 (32 accumulators a lane) 24.2 -> 22.8, but as 472 (96: a second workgroup no
+                            // longer finds registers) 18.4 -> 22.2.  Workgroups of three and more waves gain nothing or lose.
+                            if (extras && c[18] == 0 && wm * wn <= 2) {
+                                const int64_t wgs = n1 * m1;
+                                const bool fits_twice = wm * wn == 1 || tm * up(tn, at) <= 64 * 64;
+                                for (int64_t more = wgs > 512 || (wgs > 256 && !fits_twice) ? 1 : wm * wn == 1 && wgs <= 256 ? 4 : 2; more > 1 && patch_kw == 1; more /= 2)
+                                    if (room(more)) { patch_kw = int(more); out.extra_waves = true; }
+                            }
                             // the member as the template runs it
                             WM = wm; TM = tm; WN = wn; TN = tn; FM = std::gcd(FM, TM); FN = std::gcd(FN, TN);
                             ksteps = slabs; BK = cs * taps;
@@ -623,7 +641,7 @@ int decode(const opevo_op &op, int variant, const int32_t *cfg, Decoded &out, bo
     // Conv2d with fewer than 16 input channels (no slab of whole channels for the patch template): image rows in LDS, taps of a
     // kernel row as the reduction's groups of 8
     Rows rows;
-    if (rows_ok && four_level && op.dtype != OPEVO_F32 && op.kind == OPEVO_CONV2D && (path == 0 || path == 1 || path == 2) && !nhwc_ok && subm * subn == 1 &&
+    if (extras && four_level && op.dtype != OPEVO_F32 && op.kind == OPEVO_CONV2D && (path == 0 || path == 1 || path == 2) && !nhwc_ok && subm * subn == 1 &&
         ksplit == 1 && plan_rows(op, BM, nb2, BH, BW, n1, m1, linear, rows) && valid_without_rows(op, variant, cfg)) {
         path = 7;
         WM = rows.wm; WN = rows.wn; TM = rows.mi * rows.atom; TN = rows.ni * rows.atom;
