@@ -7,8 +7,11 @@
 // with every kernel row padded to WKP = 8 or 16 taps (363 -> 528 for 3 channels of 11 x 11; the slabs of 11 taps padded
 // to the MFMA step that the register-staged template takes are 1056, and gathered value by value).
 //   * The patch: the image rows under the box as the NCHW image has them, all channels and all kernel rows at once,
-//     P[image][ci][py][PITCH]; filled with 16-byte pieces at any alignment, without a transposition.  A piece that would
-//     cross an end of its image row is loaded from inside the row and shifted.  Positions outside the image are zeros.
+//     P[image][ci][py][PITCH]; filled with 16-byte pieces at any alignment, without a transposition.  With padding, a piece
+//     that would cross an end of its image row is loaded from inside the row and shifted, and positions outside the image are
+//     zeros; without, only the tensor's end is kept (no stored pixel uses what then stands past a row).
+//     A thread keeps its place in the row from pass to pass: with the piece's number taken apart by every extent, and each crossing
+//     piece shifted, 512 x 3 x 227 x 227 below took 233 us; now 205.
 //     A fragment is 16 bytes at x*STRIDE elements.  With an odd stride every second pixel starts at an odd element; those read a second copy
 //     of the patch that lies one element further left (NCOPY = 2), so that every fragment is at least 4-byte aligned.
 //   * The kernel tensor never enters the LDS: every wave keeps the fragments of its own output channels for the whole reduction in
@@ -16,7 +19,7 @@
 //   * Taps past the kernel's width (and kernel rows past its height, where a step takes several) are zeros in the kernel tensor's
 //     fragments AND are cleared in the image's: what the patch holds there are other pixels, which may be infinite.
 // Measured: 512 x 3 x 227 x 227 * 64 x 3 x 11 x 11, stride 4, bf16 (boxes of 4 images x 55 pixels): 980 us on the register-staged template (73
-// TFLOP/s: some ten instructions per gathered value), 233 us here (309 TFLOP/s, 2.4 TB/s).  Its matrix work alone is about
+// TFLOP/s: some ten instructions per gathered value), 205 us here (350 TFLOP/s, 2.7 TB/s).  Its matrix work alone is about
 // 60 us and its bytes 115; the boxes' loads, multiplications and stores follow one another and overlap only through the
 // second workgroup of a compute unit.
 // PERSIST > 0: that many workgroups along the boxes, each taking several; the kernel tensor is then fetched once per workgroup.
@@ -63,8 +66,22 @@ constexpr int COPY_MIN = ROWS * PITCH + (SPC * RPS - HK) * PITCH + WKP;
 constexpr int COPY = NCOPY == 2 ? (COPY_MIN + 127) / 128 * 128 + 64 : (COPY_MIN + 7) / 8 * 8;
 static_assert(NCOPY * COPY * 2 == LDS_BYTES, "decoder and template disagree");
 static_assert(WK <= WKP && (WKP == 8 || WKP == 16) && WIN >= 8 && BM == WM * MI * ATOM && WN * NI * ATOM >= BN && NT == 64 * WM * WN, "decoder and template disagree");
-constexpr int PIECES = NCOPY * ROWS * CPR;
-constexpr int BATCH = 16;                          // pieces a thread has in flight at a time
+// The fill's split: TPR threads along a patch row, RPP rows at a time, so that a thread keeps its place in the row (XP places if
+// the row is longer than the workgroup) and a pass costs it one small division instead of one of every extent.
+constexpr int TPR = CPR < NT ? CPR : NT, RPP = NT / TPR, XP = (CPR + NT - 1) / NT;
+constexpr int ROW_PASSES = (ROWS + RPP - 1) / RPP, PASSES = NCOPY * XP * ROW_PASSES;
+constexpr int BATCH = (PASSES + (PASSES + 17) / 18 - 1) / ((PASSES + 17) / 18);   // pieces a thread has in flight at a time: at most 18, evenly
+
+struct Pass {                                      // pass p: which copy, the rows from which on, the place's offset
+    int copy, row, place;
+    __device__ __forceinline__ constexpr Pass(int p) : copy(p / (ROW_PASSES * XP)), row(p / XP % ROW_PASSES * RPP), place(p % XP * NT) {}
+};
+// row / PH for 0 <= row < ROWS + RPP (a 24-bit multiplication where the product stays exact)
+__device__ __forceinline__ int div_rows(int row)
+{
+    if constexpr ((ROWS + RPP) * PH < (1 << 20) && ROWS + RPP <= 4095 && PH > 1) return (int)(((u32)row & 4095u) * ((1u << 20) / PH + 1) >> 20);
+    return row / PH;
+}
 
 // v shifted by sh elements towards element 0 (sh > 0) or away from it (sh < 0), zeros shifted in; 8 and more: all zeros
 __device__ __forceinline__ u32x4 shift_elements(u32x4 v, int sh)
@@ -163,32 +180,49 @@ void KERNEL_NAME(const u16 *__restrict__ A, const u16 *__restrict__ B, float *__
         const ColBlock cb = col_block(box);
         const int yin0 = cb.y0 * STRIDE - PAD_CONV, xin0 = cb.x0 * STRIDE - PAD_CONV;
         const u16 *img = B + (long)cb.nb0 * CIN * HIN * WIN;
+        // the last element a piece may start at (this box's images start at 0)
+        const int end = (int)min(((long)(N / (HOUT * WOUT)) - cb.nb0) * CIN * HIN * WIN - 8, 0x7fffffffL);
         // (the thread number is opaque to the compiler: the places of a thread's pieces would otherwise be kept in registers
         // from box to box and from the loads to the stores, next to the kernel tensor, and spill)
-        for (int q0 = 0; q0 < PIECES; q0 += BATCH * NT) {
+        for (int p0 = 0; p0 < PASSES; p0 += BATCH) {
             u32x4 v[BATCH];
             int ptid = tid;
             asm volatile("" : "+v"(ptid));
+            ptid &= 1023;
+            const int first = ptid / TPR, place = ptid % TPR;
 #pragma unroll
             for (int i = 0; i < BATCH; ++i) {
-                if (q0 + i * NT >= PIECES) break;
-                const int q = q0 + i * NT + ptid;
-                const int row = q / CPR % ROWS, copy = q / (CPR * ROWS), x = xin0 + q % CPR * 8 + copy, y = yin0 + row % PH;
+                if (p0 + i >= PASSES) break;
+                const Pass ps(p0 + i);
+                const int row = first + ps.row, c = place + ps.place, x = xin0 + c * 8 + ps.copy;
+                const int plane = div_rows(row), r = row - plane * PH, y = yin0 + r;
                 const u32x4 zero = {0u, 0u, 0u, 0u};
                 v[i] = zero;
-                if (q < PIECES && (unsigned)y < (unsigned)HIN)
-                    v[i] = *(const u32x4_a2 *)((const char *)img + 2u * (u32)((row / PH * HIN + y) * WIN + min(max(x, 0), WIN - 8)));
+                const bool mine = (RPP * TPR == NT || first < RPP) && (ps.row + RPP <= ROWS || row < ROWS) && (XP == 1 || c < CPR);
+                if (PAD_CONV == 0) {
+                    // nothing a stored pixel uses lies past the image row: what follows it in memory may stand there
+                    const int at = (plane * HIN + y) * WIN + x;
+                    if (mine) v[i] = *(const u32x4_a2 *)((const char *)img + 2u * (u32)min(at, end));
+                } else if (mine && (unsigned)y < (unsigned)HIN)
+                    v[i] = *(const u32x4_a2 *)((const char *)img + 2u * (u32)((plane * HIN + y) * WIN + min(max(x, 0), WIN - 8)));
             }
-            if (q0 == 0) __syncthreads();                      // the previous box has been multiplied
+            if (p0 == 0) __syncthreads();                      // the previous box has been multiplied
             asm volatile("" : "+v"(ptid));
+            ptid &= 1023;
+            const int first2 = ptid / TPR, place2 = ptid % TPR;
 #pragma unroll
             for (int i = 0; i < BATCH; ++i) {
-                if (q0 + i * NT >= PIECES) break;
-                const int q = q0 + i * NT + ptid;
-                const int row = q / CPR % ROWS, copy = q / (CPR * ROWS), x = xin0 + q % CPR * 8 + copy;
-                const int sh = x - min(max(x, 0), WIN - 8);
+                if (p0 + i >= PASSES) break;
+                const Pass ps(p0 + i);
+                const int row = first2 + ps.row, c = place2 + ps.place, x = xin0 + c * 8 + ps.copy;
+                int sh = x - min(max(x, 0), WIN - 8);
+                if (PAD_CONV == 0) {
+                    const int plane = div_rows(row), at = (plane * HIN + yin0 + row - plane * PH) * WIN + x;
+                    sh = max(at - end, 0);
+                }
                 if (sh != 0) v[i] = shift_elements(v[i], sh);
-                if (q < PIECES) *(u32x4 *)(smem + copy * COPY + row * PITCH + q % CPR * 8) = v[i];
+                if ((RPP * TPR == NT || first2 < RPP) && (ps.row + RPP <= ROWS || row < ROWS) && (XP == 1 || c < CPR))
+                    *(u32x4 *)(smem + ps.copy * COPY + row * PITCH + c * 8) = v[i];
             }
         }
         __syncthreads();

@@ -92,6 +92,19 @@ def test_every_address_and_the_sums(label, dims, variant, cfg):
         for box in range(plan.grid[0] * (plan.grid[1] if variant == V4X else 1) // (M // BM if variant == V4X else 1)):
             nb0, y0, x0 = box // (W1 * H1) * NB2, box // W1 % H1 * BH, box % W1 * BW
             patch = np.full(ncopy * COPY, np.nan)
+            # the fill's split: threads along a row, several rows at a time -- every piece once, row / PH by a 24-bit multiplication
+            NT = plan.block
+            TPR, XP = min(CPR, NT), -(-CPR // NT)
+            RPP = NT // TPR
+            RP = -(-ROWS // RPP)
+            seen = np.zeros((ncopy, ROWS, CPR), int)
+            for p in range(ncopy * XP * RP):
+                for tid in range(TPR * RPP):
+                    row, c = tid // TPR + p // XP % RP * RPP, tid % TPR + p % XP * NT
+                    assert row * (2 ** 20 // PH + 1) < 2 ** 32 and (PH == 1 or (ROWS + RPP) * PH >= 2 ** 20 or row * (2 ** 20 // PH + 1) >> 20 == row // PH)
+                    if row < ROWS and c < CPR:
+                        seen[p // (RP * XP), row, c] += 1
+            assert (seen == 1).all()
             for q in range(ncopy * ROWS * CPR):
                 row, copy, c = q // CPR % ROWS, q // (CPR * ROWS), q % CPR
                 x, y = x0 * S - PAD + c * 8 + copy, y0 * S - PAD + row % PH
@@ -99,6 +112,8 @@ def test_every_address_and_the_sums(label, dims, variant, cfg):
                 v = np.zeros(8)
                 if 0 <= y < HIN:
                     at = nb0 * CIN * HIN * WIN + (row // PH * HIN + y) * WIN + xs
+                    if PAD == 0:            # what follows the row in memory may stand past its end; the tensor's end is kept
+                        at, xs = min(at - xs + x, fi.size - 8), x + min(fi.size - 8 - (at - xs + x), 0)
                     assert 0 <= at and at + 8 <= fi.size
                     v = _shift(fi[at:at + 8], x - xs)
                 dst = copy * COPY + row * PITCH + c * 8
