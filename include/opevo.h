@@ -315,7 +315,8 @@ typedef struct {
                               whose extents are no multiples of 16, tiles of any extent on MFMA 16x16x32,
                               7 Conv2d with fewer than 16 input channels, image rows in LDS (either atom) */
     int32_t grid[3];
-    int32_t block;         /* threads per workgroup                                            */
+    int32_t block;         /* threads per workgroup (path 3: with the second group of waves, where two
+                              share the reduction; path 5: with the waves that share a tile)  */
     int32_t lds_bytes;
     int32_t acc_per_lane;  /* fp32 accumulators each lane holds                                */
     int32_t tile[3];       /* workgroup tile BM, BN, BK                                        */
@@ -366,7 +367,9 @@ int opevo_compile_pool_deadline(double seconds);
  * that the compiler gave private scratch memory (register spills) makes its first launch /
  * timing return OPEVO_E_INVALID: it would be slow, it would break the load counting of path 3,
  * and one spilling member of the register-staged template once gave wrong rows.  opevo_tune
- * scores both as invalid trials. */
+ * scores both as invalid trials.  What a template does of its own accord (path 4's pipelined
+ * loop, path 7, path 5's extra waves per tile) never makes a member spill: this call compiles
+ * it a second time without, if the first code object does. */
 int opevo_kernel_build(const opevo_op *op, int variant, const int32_t *cfg,
                        opevo_kernel **out, double *compile_ms);
 /* Compiling is by far the longest part of a trial (Sec. 6 gives it 8 CPU threads), and runs of
