@@ -85,7 +85,10 @@ template <int LEN, int C, int LD, int TILE>
 __device__ __forceinline__ void store_kr(u16 *S, u32x4 v, int q, int k0, int x0, bool last)
 {
     const int kr = q / C, x = q % C * 8;
-    if (TILE % 8 != 0 && x0 + TILE == LEN) v = shift_down(v, max(x0 + x - (LEN - 8), 0));
+    // A last piece can reach past the row's end in the last tile, and with tiles of 2 and 3 also in the ones before it (8 past the
+    // start of a tile is then more than two tiles on); whole multiples of 8 never do.
+    constexpr bool EARLIER_TOO = (TILE + 7) / 8 * 8 > 2 * TILE;
+    if (TILE % 8 != 0 && (EARLIER_TOO || x0 + TILE == LEN)) v = shift_down(v, max(x0 + x - (LEN - 8), 0));
     if (K_TAIL && last && k0 + kr >= KPART) { const u32x4 z = {0u, 0u, 0u, 0u}; v = z; }
     *(u32x4 *)(S + kr_off(LD, kr) + x) = v;
 }

@@ -1,7 +1,8 @@
 """CPU re-computation of the ragged MFMA template (MatMul / BatchMatMul whose extents are no multiples of 16): every global
 load lies inside its operand's matrix, every LDS store and fragment read inside the stage and aligned for its width, and the
 fragments hold the operand's values (zeros past the reduction's end) for every row and column of the tile -- for every
-workgroup, thread, piece and slab of small operators, with index arithmetic of its own for what is expected."""
+tile, thread, piece and slab of small operators (of more than 20 tiles along an axis the first two and the last six: a piece
+of 8 reaches past the row's end from no tile further left), with index arithmetic of its own for what is expected."""
 import re
 
 import numpy as np
@@ -20,6 +21,14 @@ CASES = [   # label, kind, dims, space, configuration
     ("batches, two per workgroup", P.OPEVO_BMM, (6, 20, 27, 50), P.OPEVO_TILE4, [3, 2, 1, 1, 1, 20, 3, 1, 1, 9, 2, 25, 1]),
     ("batches without the lds flag", P.OPEVO_BMM, (3, 33, 40, 48), P.OPEVO_TILE4, [3, 1, 3, 1, 1, 11, 2, 2, 1, 10, 1, 48, 0]),
     ("first operand transposed, odd rows", P.OPEVO_BMM_TA, (4, 27, 33, 70), P.OPEVO_TILE4, [4, 1, 1, 3, 1, 9, 3, 1, 1, 11, 2, 35, 1]),
+    ("3 columns: three tiles reach past the row's end", P.OPEVO_MATMUL, (16, 33, 64), P.OPEVO_TILE4, [1, 1, 1, 16, 11, 1, 1, 3, 1, 64, 1]),
+    ("3 columns, rows of 9", P.OPEVO_MATMUL, (48, 9, 40), P.OPEVO_TILE4, [1, 1, 1, 48, 3, 1, 1, 3, 2, 20, 1]),
+    ("2 columns", P.OPEVO_MATMUL, (16, 34, 64), P.OPEVO_TILE4, [1, 1, 1, 16, 17, 1, 1, 2, 1, 64, 1]),
+    ("4 columns", P.OPEVO_MATMUL, (20, 28, 48), P.OPEVO_TILE4, [1, 1, 1, 20, 7, 1, 1, 4, 2, 24, 1]),
+    ("5 columns", P.OPEVO_MATMUL, (20, 35, 48), P.OPEVO_TILE4, [1, 1, 1, 20, 7, 1, 1, 5, 2, 24, 1]),
+    ("9 columns", P.OPEVO_MATMUL, (20, 27, 48), P.OPEVO_TILE4, [1, 1, 1, 20, 3, 1, 1, 9, 2, 24, 1]),
+    ("first operand transposed, 3 rows", P.OPEVO_BMM_TA, (2, 33, 48, 64), P.OPEVO_TILE4, [2, 1, 11, 1, 1, 3, 1, 1, 1, 48, 1, 64, 1]),
+    ("first operand transposed, 2 rows", P.OPEVO_BMM_TA, (2, 18, 16, 40), P.OPEVO_TILE4, [1, 2, 9, 1, 1, 2, 1, 1, 1, 16, 2, 20, 1]),
     ("first operand transposed, columns of 8", P.OPEVO_BMM_TA, (2, 8, 24, 100), P.OPEVO_TILE4, [2, 1, 1, 1, 1, 8, 1, 1, 1, 24, 4, 25, 1]),
 ]
 
@@ -32,6 +41,10 @@ def _defs(op, variant, cfg):
 
 def _odd16(n):
     return ((n + 15) // 16 | 1) * 16
+
+
+def _tiles(n):
+    return range(n) if n <= 20 else [0, 1] + list(range(n - 6, n))
 
 
 class Operand:
@@ -70,7 +83,7 @@ class Operand:
                 start = (kb + min(k, kpart - 1)) * length + x
                 assert 0 <= x and x + 8 <= length
                 v = flat[start:start + 8]
-                sh = max(x0 + c * 8 - (length - 8), 0) if self.tile % 8 and x0 + self.tile == length else 0
+                sh = max(x0 + c * 8 - (length - 8), 0)
                 dst = self.off(kr, c * 8)
                 if last and k >= kpart:
                     v = np.zeros(8)
@@ -117,9 +130,9 @@ def test_every_address_and_every_fragment_value(label, kind, dims, variant, cfg)
     assert D["NSTG"] * (a.stage + b.stage) * 2 == plan.lds_bytes <= 160 * 1024
     for z in range(D.get("KSPLIT", 1)):
         for s in range(D["NSL"]):
-            for m in sorted({0, M // BM - 1}):
+            for m in _tiles(M // BM):
                 a.check(m * BM, z * kpart, kpart, s * D["KS"])
-            for n in sorted({0, N // BN - 1}):
+            for n in _tiles(N // BN):
                 b.check(n * BN, z * kpart, kpart, s * D["KS"])
     kernel, _ = P.opevo_kernel_build(op, variant, cfg)
     assert 1000 < P.opevo_kernel_code_size(kernel) < (128 << 10)
