@@ -152,9 +152,16 @@ __device__ __forceinline__ int b_swz(int krow) { return ((krow / B_RPW) % B_SWM)
 // fills, it guards later LDS reads with a wait for ALL outstanding loads, which would cut the
 // ring down to a single slab in flight.  The kernel places every wait these loads need itself
 // (WAIT_VMCNT below).
+// The compiler does not see a memory instruction here either, so it leaves out the five wait states that gfx9 asks for between
+// a vector instruction that writes a scalar register and a memory instruction that reads it as its address.  A base that
+// it has put aside in a lane of a vector register comes back by v_readlane right in front of this block (256^3 as 2 waves of
+// 128 x 32 on slabs of 128: three states before the load), and the load may take the register's old value, an address that
+// is not the kernel's.  A scalar instruction does wait for a vector instruction's result, and its own result may be read at
+// once: the load takes its base from a scalar copy, made where M0 needs a wait state anyway.
 __device__ __forceinline__ void dma16(const u16 *base, unsigned off, unsigned lds_base)
 {
-    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(off), "s"(base), "s"(lds_base) : "memory", "m0");
+    const u16 *copy;
+    asm volatile("s_mov_b32 m0, %3\n\ts_mov_b64 %0, %2\n\tglobal_load_lds_dwordx4 %1, %0" : "=&s"(copy) : "v"(off), "s"(base), "s"(lds_base) : "memory", "m0");
 }
 
 // The 1 KiB piece number `instr` of a stage's A part covers the 16-byte positions
