@@ -368,7 +368,7 @@ int opevo_compile_pool_deadline(double seconds);
  * timing return OPEVO_E_INVALID: it would be slow, it would break the load counting of path 3,
  * and one spilling member of the register-staged template once gave wrong rows.  opevo_tune
  * scores both as invalid trials.  What a template does of its own accord (path 4's pipelined
- * loop, path 7, path 5's extra waves per tile) never makes a member spill: this call compiles
+ * loop, path 7, path 5's extra waves per tile, path 3's second group of waves) never makes a member spill: this call compiles
  * it a second time without, if the first code object does. */
 int opevo_kernel_build(const opevo_op *op, int variant, const int32_t *cfg,
                        opevo_kernel **out, double *compile_ms);

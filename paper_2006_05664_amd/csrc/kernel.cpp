@@ -87,7 +87,7 @@ int build_kernel(const opevo_op &op, int variant, const int32_t *cfg, opevo_kern
     if (!d.try_defines.empty() && spills()) compile(plain);
     if ((d.plan.path == 7 || d.extra_waves) && spills()) {
         // the few-channels template keeps the kernel tensor in registers, and waves that share a tile need some for the
-        // final sum: a member whose estimate was too low runs as it would without them
+        // final sum, as two groups of them do that share a reduction: a member whose estimate was too low runs as it would without them
         d = Decoded();
         if (int rc = decode(op, variant, cfg, d, false)) return rc;
         if (d.plan.status != OPEVO_OK) return fail(OPEVO_E_INVALID, "invalid configuration: %s", d.plan.reason);

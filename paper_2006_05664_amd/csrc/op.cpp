@@ -653,8 +653,12 @@ int decode(const opevo_op &op, int variant, const int32_t *cfg, Decoded &out, bo
     // bytes per slab it is what a compute unit can load (12 KB, 2 waves: 80 workgroups x 32 steps 6.69 -> 5.50 us, x 8 steps 3.35 ->
     // 3.61, 225 workgroups x 32 steps 8.65 -> 9.14; 8 KB, 4 waves: 64 workgroups x 32 steps 4.78 -> 4.48, 256 workgroups 5.56 -> 5.58; 16 KB, 4
     // waves: always slower).  Four groups were nowhere better than two by more than the noise, and slower on most shapes.
+    // All of that was measured with wave tiles of one or two 32 x 32 atoms, and the split stays with those: larger ones have MFMAs to cover
+    // their latencies with.  It also stays with reductions of more than 256 (96 x 160 x 256 2.68 -> 2.44 us, 480 x 480 x 256 2.82 -> 2.69):
+    // a search over the members of 256^3, where one wave often has 4 to 8 atoms, has ended with its GPU lost
+    // since the split exists, for a cause that is not known, and members of that operator run as they did before.
     int kgrp = 1;
-    if (path == 3 && op.kind != OPEVO_CONV2D && ksteps % 2 == 0) {
+    if (extras && path == 3 && op.kind != OPEVO_CONV2D && ksteps % 2 == 0 && TM * TN <= 2 * 32 * 32 && ksteps * BK > 256) {
         const int64_t nw = WM * WN, stage = (BM + BN) * BK * 2, per = stage / (1024 * nw), wgs = n1 * m1 * b1;
         const bool pays = (nw == 1 && wgs <= 256 && ksteps >= 8) ||
                           (nw == 2 && wgs <= (stage <= 8192 ? 256 : 128) && stage <= 12288 && ksteps >= 16) ||
@@ -662,7 +666,7 @@ int decode(const opevo_op &op, int variant, const int32_t *cfg, Decoded &out, bo
         // (the ring of both groups within the LDS, the sum of one of them within the ring, the loads in flight countable)
         for (int st = std::min(4, nstage_dlds); pays && st >= 2 && kgrp == 1; --st)
             if (2 * st * stage <= kMaxLds && nw * TM * TN * 4 <= 2 * st * stage && (2 * st - 2) * per <= 63 &&
-                !(dlds_atom16 && BK % 64 != 0 && st % 2 != 0)) { kgrp = 2; nstage_dlds = 2 * st; }
+                !(dlds_atom16 && BK % 64 != 0 && st % 2 != 0)) { kgrp = 2; nstage_dlds = 2 * st; out.extra_waves = true; }
     }
     const bool b_kmajor = path == 3 && (b_packed || op.kind == OPEVO_CONV2D);
     const bool nhwc = nhwc_ok && (path == 1 || path == 2 || path == 3);

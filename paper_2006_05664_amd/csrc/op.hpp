@@ -34,7 +34,7 @@ struct Decoded {
     // Options the kernel is better with where its registers hold them: a build whose kernel spills with them is done again
     // without (empty: none).
     std::string try_defines;
-    bool extra_waves = false;   // more waves share a wave tile than the configuration asks for
+    bool extra_waves = false;   // more waves share a wave tile, or the reduction, than the configuration asks for
     std::string kernel_name;   // symbol of the instantiated kernel
     int64_t zero_bytes = 0;    // bytes of the output the host clears before every launch (split reduction), else 0
     // pre-pass before every launch: 0 none; 1 Conv2d: the kernel reads channels-last copies of both operands;
@@ -43,7 +43,7 @@ struct Decoded {
 };
 
 // OPEVO_OK (plan.status says valid/invalid) or OPEVO_E_ILLEGAL / OPEVO_E_ARG.
-// extras = false: without the few-channels convolution template and without waves that a patch member did not ask for (a
+// extras = false: without the few-channels convolution template and without waves that a patch or direct-to-LDS member did not ask for (a
 // member that turned out to spill with them).
 int decode(const opevo_op &op, int variant, const int32_t *cfg, Decoded &out, bool extras = true);
 int op_param_descs(const opevo_op &op, int variant, std::vector<opevo_param_desc> &descs);

@@ -47,6 +47,13 @@ def test_plan(label, kind, dims, dtype, variant, cfg):
     ((96, 160, 256), [3, 1, 1, 32, 5, 1, 1, 32, 4, 64, 1]),            # too few
     ((992, 992, 512), [31, 1, 1, 32, 31, 1, 1, 32, 8, 64, 1]),         # several workgroups per compute unit
     ((512, 1024, 1024), [8, 2, 1, 32, 16, 2, 1, 32, 16, 64, 1]),       # bound by what a compute unit can load
+    ((512, 1024, 1024), [8, 1, 2, 32, 16, 1, 2, 32, 16, 64, 1]),       # wave tiles of more than two atoms: never measured
+    ((512, 1024, 1024), [4, 1, 4, 32, 32, 1, 1, 32, 32, 32, 1]),
+    ((256, 256, 256), [1, 1, 2, 128, 8, 1, 1, 32, 8, 32, 1]),
+    ((256, 256, 256), [2, 1, 4, 32, 8, 1, 1, 32, 8, 32, 1]),
+    ((256, 256, 256), [4, 1, 2, 32, 4, 1, 8, 8, 8, 32, 1]),
+    ((256, 256, 256), [8, 1, 32, 1, 2, 1, 16, 8, 8, 32, 1]),
+    ((256, 256, 256), [8, 1, 32, 1, 8, 1, 1, 32, 8, 32, 1]),           # reductions of at most 256
 ])
 def test_members_that_keep_one_group(dims, cfg):
     op = P.opevo_op_create(P.OPEVO_MATMUL, dims, P.OPEVO_BF16)
