@@ -174,6 +174,19 @@ static bool plan_ragged(const opevo_op &op, int64_t bm, int64_t bn, int64_t bk, 
     if (kpart < 8 || op.N < 8 || (op.trans_a && op.M < 8) || op.M * op.K >= (int64_t(1) << 31) || op.K * op.N >= (int64_t(1) << 31)) return false;
     const int64_t ma = (bm + 15) / 16, na = (bn + 15) / 16;
     if (ma * na * 256 > 8 * bm * bn || ma * na > 16 * 32) return false;
+    const int64_t top = std::max<int64_t>(32, std::min<int64_t>(128, (std::min(bk, kpart) + 31) / 32 * 32));
+    // staging registers of a lane with slabs of ks and nt threads
+    auto staging = [&](int64_t ks, int64_t nt) {
+        const int64_t a_pieces = op.trans_a ? ks * ((bm + 7) / 8) : bm * (ks / 8), b_pieces = ks * ((bn + 7) / 8);
+        return 4 * ((a_pieces + nt - 1) / nt + (b_pieces + nt - 1) / nt);
+    };
+    // Registers: staging and accumulators within 256 with up to eight waves (one or two a SIMD: of 300 compiled members none spilled).
+    // With more a lane has 170 (9 - 12 waves) or 128, and what the kernel needs beside staging, accumulators and fragments
+    // counts: members with as little as 62 to spare spilled, so 66 are kept free.
+    auto room = [&](int64_t ks, int64_t nw, int64_t mi, int64_t ni) {
+        const int64_t held = staging(ks, 64 * nw) + 4 * mi * ni;
+        return nw <= 8 ? held <= 256 : held + 4 * (mi + ni) + 66 <= 512 / ((nw + 3) / 4);
+    };
     // waves: the division with the fewest padded atoms, then the one closest to four waves (one per SIMD; eight where the
     // tile has 64 atoms and more), then the one with the fewest fragment reads
     const int64_t want = ma * na >= 64 ? 8 : 4;
@@ -181,7 +194,7 @@ static bool plan_ragged(const opevo_op &op, int64_t bm, int64_t bn, int64_t bk, 
     for (int64_t wm = 1; wm <= std::min<int64_t>(ma, 16); ++wm)
         for (int64_t wn = 1; wn <= std::min<int64_t>(na, 16 / wm); ++wn) {
             const int64_t mi = (ma + wm - 1) / wm, ni = (na + wn - 1) / wn, nw = wm * wn;
-            if (mi * ni > 32) continue;
+            if (mi * ni > 32 || (nw > 8 && !room(32, nw, mi, ni))) continue;
             const int64_t off = nw > want ? nw - want : (want - nw) * 4;      // too few waves are worse than too many
             const int64_t score = (wm * mi * wn * ni * 8 + off * std::min<int64_t>(ma * na, 32)) * 64 + nw * (mi + ni);
             if (score < best) { best = score; out.wm = int(wm); out.wn = int(wn); out.mi = int(mi); out.ni = int(ni); }
@@ -189,18 +202,15 @@ static bool plan_ragged(const opevo_op &op, int64_t bm, int64_t bn, int64_t bk, 
     if (best == INT64_MAX) return false;
     // slab: the member's, rounded up to whole MFMA steps of 32 and at most 128; among the shorter ones the one that pads
     // the reduction least (a slab costs about as much as 8 steps of padding), as far as LDS and staging registers go
-    const int64_t top = std::max<int64_t>(32, std::min<int64_t>(128, (std::min(bk, kpart) + 31) / 32 * 32)), nt = 64 * out.wm * out.wn;
     best = INT64_MAX;
     for (int64_t ks = 32; ks <= top; ks += 32) {
         auto odd16 = [](int64_t n) { return ((n + 15) / 16 | 1) * 16; };
         const int64_t slabs = (kpart + ks - 1) / ks;
         const int64_t a_stage = op.trans_a ? ks * odd16(out.wm * out.mi * 16) + ks / 8 * 64 : out.wm * out.mi * 16 * (ks + 8);
         const int64_t b_stage = ks * odd16(out.wn * out.ni * 16) + ks / 8 * 64;
-        const int64_t a_pieces = op.trans_a ? ks * ((bm + 7) / 8) : bm * (ks / 8), b_pieces = ks * ((bn + 7) / 8);
-        const int64_t regs = 4 * ((a_pieces + nt - 1) / nt + (b_pieces + nt - 1) / nt);
         const int stages = pipelined && slabs > 1 ? 2 : 1;
         const int64_t lds = stages * (a_stage + b_stage) * 2;
-        if (lds > kMaxLds || regs + 4 * out.mi * out.ni > 256) continue;
+        if (lds > kMaxLds || !room(ks, out.wm * out.wn, out.mi, out.ni)) continue;
         const int64_t score = slabs * (ks + 8) + (lds > kMaxLds / 2 ? slabs * 16 : 0);   // two workgroups per compute unit where it can be
         if (score <= best) { best = score; out.ks = int(ks); out.slabs = int(slabs); out.stages = stages; out.lds = lds; }
     }

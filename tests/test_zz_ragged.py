@@ -4,6 +4,7 @@ fragments hold the operand's values (zeros past the reduction's end) for every r
 tile, thread, piece and slab of small operators (of more than 20 tiles along an axis the first two and the last six: a piece
 of 8 reaches past the row's end from no tile further left), with index arithmetic of its own for what is expected."""
 import re
+import subprocess
 
 import numpy as np
 import pytest
@@ -139,6 +140,32 @@ def test_every_address_and_every_fragment_value(label, kind, dims, variant, cfg)
     P.opevo_kernel_destroy(kernel)
 
 
+MANY_ATOMS = [   # members whose tile fits nine waves better than eight, where a lane has 170 registers instead of 256
+    ("20 atom columns", P.OPEVO_MATMUL, (231, 945, 330), P.OPEVO_TILE4, [7, 1, 11, 3, 1, 9, 21, 5, 330, 1, 1]),
+    ("9 x 14 atoms", P.OPEVO_MATMUL, (360, 840, 600), P.OPEVO_TILE4, [9, 10, 2, 2, 1, 60, 14, 1, 20, 30, 1]),
+    ("first operand transposed, 23 x 7 atoms", P.OPEVO_BMM_TA, (8, 360, 420, 250), P.OPEVO_TILE4, [4, 2, 1, 120, 3, 1, 3, 5, 7, 4, 250, 1, 1]),
+    ("first operand transposed, one stage", P.OPEVO_BMM_TA, (8, 360, 420, 250), P.OPEVO_TILE4, [1, 8, 4, 5, 9, 2, 1, 35, 3, 4, 125, 2, 0]),
+]
+
+
+@pytest.mark.parametrize("label,kind,dims,variant,cfg", MANY_ATOMS, ids=[c[0] for c in MANY_ATOMS])
+def test_the_division_among_waves_leaves_registers_enough(label, kind, dims, variant, cfg, tmp_path):
+    """A kernel with scratch memory (spilled registers) is refused at its first launch."""
+    op = P.opevo_op_create(kind, dims, P.OPEVO_BF16)
+    assert P.opevo_kernel_plan(op, variant, cfg).path == 6
+    P.opevo_code_cache_configure(str(tmp_path), 0)          # the cache's directory: where the code object can be read
+    try:
+        kernel, _ = P.opevo_kernel_build(op, variant, cfg)
+        P.opevo_kernel_destroy(kernel)
+    finally:
+        P.opevo_code_cache_configure(None, 256 << 20)
+    entry = next(tmp_path.iterdir()).read_bytes()
+    code = tmp_path / "kernel.co"
+    code.write_bytes(entry[entry.index(b"\x7fELF"):])
+    notes = subprocess.run(["/opt/rocm/llvm/bin/llvm-readelf", "--notes", str(code)], capture_output=True, text=True, check=True).stdout
+    assert re.search(r"private_segment_fixed_size:\s+0\b", notes), re.findall(r"private_segment_fixed_size:\s+\d+", notes)
+
+
 def test_which_members_take_the_ragged_template():
     def path(kind, dims, variant, cfg, dtype=P.OPEVO_BF16):
         plan = P.opevo_kernel_plan(P.opevo_op_create(kind, dims, dtype), variant, cfg)
@@ -151,6 +178,7 @@ def test_which_members_take_the_ragged_template():
     assert path(P.OPEVO_MATMUL, (36, 55, 64), V, [36, 1, 1, 1, 5, 1, 1, 11, 2, 32, 1]) == 0     # a single row: 23 times the work
     assert path(P.OPEVO_MATMUL, (36, 7, 64), V, [2, 1, 1, 18, 1, 1, 1, 7, 2, 32, 1]) == 0       # rows shorter than a piece
     assert path(P.OPEVO_MATMUL, (36, 55, 7), V, [2, 1, 1, 18, 5, 1, 1, 11, 1, 7, 1]) == 0
+    assert path(P.OPEVO_MATMUL, (1000, 1000, 1000), V, [1, 25, 5, 8, 10, 100, 1, 1, 200, 5, 0]) == 0     # 441 atoms: too many for eight waves
     assert path(P.OPEVO_MATMUL, (36, 55, 64), P.OPEVO_TILE2, [2, 18, 5, 11, 2, 32]) == 0
 
 
@@ -173,9 +201,9 @@ def test_random_members_of_ragged_operators_reach_the_template():
 
 @pytest.mark.gpu
 @pytest.mark.parametrize("dtype", ["bf16", "f16"])
-@pytest.mark.parametrize("label,kind,dims,variant,cfg", CASES, ids=[c[0] for c in CASES])
+@pytest.mark.parametrize("label,kind,dims,variant,cfg", CASES + MANY_ATOMS, ids=[c[0] for c in CASES + MANY_ATOMS])
 def test_results_match_the_oracle(label, kind, dims, variant, cfg, dtype):
-    """Inputs are exact in both precisions; what is left is an fp32 sum of at most 200 products: 1e-5 is 80 roundings."""
+    """Inputs are exact in both precisions; what is left is an fp32 sum of at most 600 products: 1e-5 is 80 roundings."""
     import torch
     from oracle import tensor as T
     from paper_2006_05664_amd import synth
