@@ -40,7 +40,8 @@ constexpr bool TINY = false;
 #endif
 
 #if OP != OP_CONV
-// (the deadline is checked by every lane by itself, every 32 steps of its own: there is no barrier to leave together at)
+// (the deadline is checked by every lane by itself, at the start of every batch and every 32 steps of its own: there is no
+// barrier to leave together at)
 __device__ __forceinline__ void tiny_tile(const in_t *__restrict__ A, const in_t *__restrict__ B, float *__restrict__ C,
                                           unsigned long long *ctl, const BlockId &bid, int tid)
 {
@@ -48,6 +49,11 @@ __device__ __forceinline__ void tiny_tile(const in_t *__restrict__ A, const in_t
     const int o = tid / S, p = tid % S;
     if (o >= BM * BN) return;                                    // whole groups of S lanes
     const long gm = (long)bid.m * BM + o / BN, gn = (long)bid.n * BN + o % BN;
+    auto expired = [&]() {
+        if (!ctl || ctl[1] == 0 || wall_clock64() - ctl[0] <= ctl[1]) return false;
+        ctl[2] = 1;
+        return true;
+    };
     for (int bi = 0; bi < BATCH_INNER; ++bi) {
 #if KSPLIT > 1
         const long batch = 0, kb = (long)bid.b * KT + p;
@@ -57,9 +63,10 @@ __device__ __forceinline__ void tiny_tile(const in_t *__restrict__ A, const in_t
         const in_t *a = A + batch * M * K + gm * K + kb;
         const in_t *b = B + batch * K * N + kb * N + gn;
         float acc = 0.f;
+        if (FULL < 8 && expired()) return;
         int j = 0;
         for (; j + 8 <= FULL; j += 8) {
-            if (ctl && j % 32 == 0 && ctl[1] != 0 && wall_clock64() - ctl[0] > ctl[1]) { ctl[2] = 1; return; }
+            if (j % 32 == 0 && expired()) return;
 #pragma unroll
             for (int u = 0; u < 8; ++u)
                 acc = __builtin_fmaf(to_f32(a[(j + u) * S]), to_f32(b[(long)((j + u) * S) * N]), acc);

@@ -60,3 +60,19 @@ def test_a_tiny_tile_honours_the_deadline():
     torch.cuda.synchronize()
     assert torch.all(c == float(1 << 22))
     P.opevo_kernel_destroy(kernel)
+
+
+def test_a_deadline_holds_where_a_lane_has_fewer_than_eight_steps():
+    import torch
+    op = P.opevo_op_create(P.OPEVO_MATMUL, (4096, 4096, 16), P.OPEVO_F32)     # 2^24 workgroups of one output, one step per lane: some ten ms
+    a, b = torch.ones(4096 * 16, device="cuda"), torch.ones(4096 * 16, device="cuda")
+    c = torch.empty(4096 * 4096, device="cuda")
+    kernel, _ = P.opevo_kernel_build(op, P.OPEVO_TILE2, [4096, 1, 4096, 1, 1, 16])
+    stream = torch.cuda.current_stream().cuda_stream
+    with pytest.raises(P.OpevoError) as e:
+        P.opevo_kernel_time(kernel, a.data_ptr(), b.data_ptr(), c.data_ptr(), stream, timeout_ms=0.5)
+    assert e.value.status == P.OPEVO_E_INVALID and "deadline" in e.value.message
+    P.opevo_kernel_launch(kernel, a.data_ptr(), b.data_ptr(), c.data_ptr(), stream)      # a launch has none
+    torch.cuda.synchronize()
+    assert torch.all(c == 16.0)
+    P.opevo_kernel_destroy(kernel)
