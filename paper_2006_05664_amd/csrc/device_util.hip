@@ -331,6 +331,10 @@ int compare_f32(const float *c, const float *ref, int64_t n, const int *rows, in
     hipError_t e = hipGetDevice(&dev);
     if (e != hipSuccess) return hip_fail(e, "hipGetDevice");
     if (dev < 0 || dev >= 64) return fail(OPEVO_E_HIP, "device index %d out of range", dev);
+    // A stream under capture cannot be waited for: refused before anything is recorded that would hold on to a workspace.
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(stream, &capture) != hipSuccess) (void)hipGetLastError();   // the default stream while another one captures
+    else if (capture != hipStreamCaptureStatusNone) return fail(OPEVO_E_HIP, "compare: the stream is being captured (opevo_compare_f32_static can be)");
     CompareWorkspace w;
     {
         std::lock_guard<std::mutex> lock(g_ws_mutex);
@@ -346,7 +350,7 @@ int compare_f32(const float *c, const float *ref, int64_t n, const int *rows, in
         e = hipStreamSynchronize(stream);
         if (e != hipSuccess) rc = hip_fail(e, "hipStreamSynchronize");
     }
-    if (rc != OPEVO_OK) return rc;   // the kernels may still be under way (or recorded): the workspace is not used again
+    if (rc != OPEVO_OK) return rc;   // the kernels may still be under way: the workspace is not used again
     if (max_scaled) *max_scaled = w.result[0];
     if (rel_fro) *rel_fro = w.result[1];
     {

@@ -70,3 +70,22 @@ def test_equal_arrays_and_a_reference_of_zeros(data):
     assert P.opevo_compare_f32(ones.data_ptr(), ones.data_ptr(), 1000, stream) == (0.0, 0.0)
     mx, fro = P.opevo_compare_f32(ones.data_ptr(), zeros.data_ptr(), 1000, stream)
     assert mx == 1.0 and np.isinf(fro)
+
+
+def test_a_stream_under_capture_is_refused_and_keeps_its_capture(data):
+    import torch
+    c, ref = data[0][:4099], data[1][:4099]
+    want = P.opevo_compare_f32(c.data_ptr(), ref.data_ptr(), 4099, data[2])      # a workspace is there
+    out, graph = torch.zeros(2, dtype=torch.float64, device="cuda"), torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        stream = torch.cuda.current_stream().cuda_stream
+        for _ in range(3):
+            with pytest.raises(P.OpevoError) as e:
+                P.opevo_compare_f32(c.data_ptr(), ref.data_ptr(), 4099, stream)
+            assert e.value.status == P.OPEVO_E_HIP and "captured" in e.value.message
+        P.opevo_compare_f32_static(c.data_ptr(), ref.data_ptr(), 4099, stream, out.data_ptr())
+    for _ in range(3):                                                            # what was recorded beside the refused calls runs
+        out.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert tuple(out.tolist()) == want == P.opevo_compare_f32(c.data_ptr(), ref.data_ptr(), 4099, data[2])
