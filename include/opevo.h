@@ -329,7 +329,9 @@ typedef struct {
 } opevo_plan;
 
 /* Decode + validate (host only, no GPU): OPEVO_E_ILLEGAL if cfg is not in the space;
- * otherwise OPEVO_OK with plan->status telling valid / invalid. */
+ * otherwise OPEVO_OK with plan->status telling valid / invalid.  The plan, and the options below, are those of the first
+ * code object opevo_kernel_build compiles; the few members that build compiles again (see there) run with fewer waves, or on
+ * another path, than the plan says. */
 int opevo_kernel_plan(const opevo_op *op, int variant, const int32_t *cfg, opevo_plan *plan);
 /* The hipRTC option string ("-DBM=.. ...") and template name the configuration renders to. */
 int opevo_kernel_defines(const opevo_op *op, int variant, const int32_t *cfg,

@@ -894,7 +894,7 @@ int opevo_kernel_defines(const opevo_op *op, int variant, const int32_t *cfg, ch
     if (!op || !cfg || !buf) return fail(OPEVO_E_ARG, "kernel_defines: NULL argument");
     Decoded d;
     if (int rc = decode(*op, variant, cfg, d)) return rc;
-    const std::string s = d.tmpl + ": " + d.defines;
+    const std::string s = d.tmpl + ": " + d.defines + d.try_defines;
     if (s.size() + 1 > cap) return fail(OPEVO_E_ARG, "kernel_defines: buffer too small (%zu needed)", s.size() + 1);
     std::memcpy(buf, s.c_str(), s.size() + 1);
     return OPEVO_OK;
