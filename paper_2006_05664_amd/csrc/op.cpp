@@ -794,10 +794,17 @@ int decode(const opevo_op &op, int variant, const int32_t *cfg, Decoded &out, bo
     if (path == 5) D << " -DCS=" << patch_cs << " -DPWP=" << patch_row << " -DIPIX=" << patch_image << " -DKW=" << patch_kw << " -DLDS_BYTES=" << lds;
     if (b_kmajor) D << " -DB_KMAJOR=1 -DBNR=" << bnr;
     if (path == 3 && anr != BM) D << " -DANR=" << anr;
-    // fp32, two stages: the pipelined slab loop, but for short reductions on a full chip, where the other workgroups cover a
-    // slab's latency and the registers are better spent on them (a batch of 960 of 128 x 64 x 128 with the first operand transposed:
-    // 960 x 4 waves, 4 slabs, 27.0 us without and 29.9 with; 132 x 64 x 224 x 128, 924 x 2 waves, 2 slabs, 16.2 and 13.9)
-    if (path == 4 && nstage == 2 && !(ksteps < 8 && n_blocks * nwr >= 2048)) out.try_defines = " -DPIPELINED=1";
+    // fp32, two stages: the pipelined slab loop, but not for
+    //  * short reductions on a full chip, where the other workgroups cover a slab's latency and the registers are better spent on
+    //    them (a batch of 960 of 128 x 64 x 128 with the first operand transposed: 960 x 4 waves, 4 slabs, 27.0 us without and 29.9
+    //    with; 2048 x 2048 x 128: 1024 x 2 waves, 16 slabs of 8, 15.7 and 17.5; but 132 x 64 x 224 x 128, 924 x 2 waves, 2 slabs, 16.2 and 13.9);
+    //  * convolutions on slabs of one group of 8: their values are gathered one by one, and with the gather pinned in front of so few
+    //    MFMAs nothing is gained (8 x 64 x 28 x 28 * 64 x 64 x 3 x 3 as 112 x 1 waves 77.6 us without and 82.1 with, as 112 x 7 waves 54.8 and 61.6; four others 0.7 %
+    //    faster to 2 % slower).
+    // Elsewhere, against the plain loop: 13 MatMul / BMM members on slabs of 8 1.00 - 1.46 times as fast, 70 members on longer slabs 0.97 - 1.56 and one
+    // (4 slabs of 24, 42 x 2 waves) 0.94.
+    const bool full_chip = n_blocks * nwr >= 2048, short_k = ksteps < 8 || ksteps * BKP <= 128;
+    if (path == 4 && nstage == 2 && !(short_k && full_chip) && !(op.kind == OPEVO_CONV2D && BKP == 8)) out.try_defines = " -DPIPELINED=1";
     if (kgrp > 1) D << " -DKGRP=" << kgrp;
     if (kunroll) D << " -DKUNROLL=" << kunroll;
     if (ksplit > 1) D << " -DKSPLIT=" << ksplit;
