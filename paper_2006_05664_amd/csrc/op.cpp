@@ -637,9 +637,9 @@ int decode(const opevo_op &op, int variant, const int32_t *cfg, Decoded &out, bo
     // MatMul / BMM operators with an extent that is no multiple of 16 have no member on the templates above (or only the few
     // whose tiles skip that axis): their members run on the ragged MFMA template instead of the scalar one.  It takes the
     // workgroup tile as it is, rounds it up to whole 16x16 atoms and deals those to waves by itself.  Measured on 1000^3
-    // against the scalar template: tiles of 20 x 100 (rounded up 1.8 times) 15.6 against 1124 us, 10 x 20 (2.6) 39 against 519, 8 x 8
-    // (4) 79 against 310, 4 x 8 and 8 x 4 (8 times) 144 and 171 against 356 and 381: by about 16 times nothing is left, so
-    // the line lies at 8.
+    // against the scalar template, one-wave members: tiles of 20 x 100 (atoms of 1.8 times the tile, dealt to four waves 2.05) 15.6 against 1124 us
+    // (that tile's best scalar member, 20 waves, 168), 10 x 20 (2.6) 39 against 519, 8 x 8 (4) 79 against 310, 4 x 8 and 8 x 4 (8 times)
+    // 144 and 171 against 356 and 381: by about 16 times nothing is left, so the line lies at 8.
     Ragged rg;
     if (four_level && path == 0 && op.dtype != OPEVO_F32 && op.kind != OPEVO_CONV2D && subm * subn == 1 &&
         (op.M % 16 != 0 || op.N % 16 != 0 || op.K % 16 != 0) &&

@@ -7,10 +7,11 @@
 // be rounded up by themselves).  What the atoms compute past the tile is not stored.  The reduction is walked in NSL slabs
 // of KS (the member's slab rounded up to whole MFMA steps), the last one filled up with zeros in both operands.
 //
-// Measured (bf16): 1000^3 in tiles of 20 x 100 168 us on the scalar template (its best member), 15.6 us here (128 TFLOP/s); 105 x 972 x 160 in
+// Measured (bf16): 1000^3 in tiles of 20 x 100 168 us on the scalar template (20 waves, the best there), 15.6 us here (128 TFLOP/s); 105 x 972 x 160 in
 // tiles of 15 x 54 60 -> 3.6 us; a batch of 11 x (35 x 36 x 35) 6.2 -> 3.5 us.
-// What bounds it: at these tiles the operand stream (1000^3 in tiles of 20 x 100: 0.12 GB through L2), so the point is
-// to move it in wide pieces whatever the alignment: every operand travels in 16-byte pieces of 8 consecutive elements,
+// What bounds it: at these tiles the operand stream (1000^3 in tiles of 20 x 100: 0.12 GB through L2) and, with two workgroups per
+// compute unit, the chain of 11 slabs (counters: matrix pipes 13 %, LDS 40 % of the busy time, a third of that bank conflicts), so the point
+// is to move it in wide pieces whatever the alignment: every operand travels in 16-byte pieces of 8 consecutive elements,
 // loaded at the 2-byte alignment an odd row length leaves.  A piece that would reach past its row is loaded from as far left as
 // it must be to end with the row, and shifted down when it is stored: no load leaves its operand's rows.
 //   * A [M][K]: pieces along k.  LDS As[row][KS + 8]: a fragment is one 16-byte read; the odd number of pieces per row spreads 16 rows
