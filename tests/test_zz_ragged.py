@@ -115,8 +115,7 @@ class Operand:
                     assert np.array_equal(got, want), (x, k, got, want)
 
 
-@pytest.mark.parametrize("label,kind,dims,variant,cfg", CASES, ids=[c[0] for c in CASES])
-def test_every_address_and_every_fragment_value(label, kind, dims, variant, cfg):
+def _check_member(kind, dims, variant, cfg):
     op = P.opevo_op_create(kind, dims, P.OPEVO_BF16)
     plan = P.opevo_kernel_plan(op, variant, cfg)
     tmpl, D = _defs(op, variant, cfg)
@@ -135,9 +134,29 @@ def test_every_address_and_every_fragment_value(label, kind, dims, variant, cfg)
                 a.check(m * BM, z * kpart, kpart, s * D["KS"])
             for n in _tiles(N // BN):
                 b.check(n * BN, z * kpart, kpart, s * D["KS"])
+
+
+@pytest.mark.parametrize("label,kind,dims,variant,cfg", CASES, ids=[c[0] for c in CASES])
+def test_every_address_and_every_fragment_value(label, kind, dims, variant, cfg):
+    _check_member(kind, dims, variant, cfg)
+    op = P.opevo_op_create(kind, dims, P.OPEVO_BF16)
     kernel, _ = P.opevo_kernel_build(op, variant, cfg)
     assert 1000 < P.opevo_kernel_code_size(kernel) < (128 << 10)
     P.opevo_kernel_destroy(kernel)
+
+
+@pytest.mark.parametrize("kind,dims", [(P.OPEVO_MATMUL, (20, 33, 45)), (P.OPEVO_MATMUL, (48, 18, 30)), (P.OPEVO_BMM, (2, 30, 50, 20)),
+                                       (P.OPEVO_BMM_TA, (2, 18, 27, 40))])
+def test_every_address_and_every_fragment_value_of_random_members(kind, dims):
+    op = P.opevo_op_create(kind, dims, P.OPEVO_BF16)
+    sp, rng, found = P.opevo_op_space(op, P.OPEVO_TILE4), P.opevo_rng_create(3), []
+    while len(found) < 15:
+        cfg = P.opevo_space_random(sp, rng)
+        if P.opevo_kernel_plan(op, P.OPEVO_TILE4, cfg).path == 6:
+            found.append([int(x) for x in cfg])
+    for cfg in found:
+        _check_member(kind, dims, P.OPEVO_TILE4, cfg)
+    P.opevo_rng_destroy(rng); P.opevo_space_destroy(sp)
 
 
 MANY_ATOMS = [   # members whose tile fits nine waves better than eight, where a lane has 170 registers instead of 256
