@@ -83,8 +83,10 @@ int build_kernel(const opevo_op &op, int variant, const int32_t *cfg, opevo_kern
         return true;
     };
     const std::string plain = d.defines;
-    compile(plain + d.try_defines);
-    if (!d.try_defines.empty() && spills()) compile(plain);
+    for (size_t i = 0; i < d.tries.size(); ++i) {
+        if (i > 0 && !spills()) break;
+        compile(plain + d.tries[i]);
+    }
     if ((d.plan.path == 7 || d.extra_waves) && spills()) {
         // the few-channels template keeps the kernel tensor in registers, and waves that share a tile need some for the
         // final sum, as two groups of them do that share a reduction: a member whose estimate was too low runs as it would without them

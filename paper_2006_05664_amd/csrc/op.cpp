@@ -794,17 +794,20 @@ int decode(const opevo_op &op, int variant, const int32_t *cfg, Decoded &out, bo
     if (path == 5) D << " -DCS=" << patch_cs << " -DPWP=" << patch_row << " -DIPIX=" << patch_image << " -DKW=" << patch_kw << " -DLDS_BYTES=" << lds;
     if (b_kmajor) D << " -DB_KMAJOR=1 -DBNR=" << bnr;
     if (path == 3 && anr != BM) D << " -DANR=" << anr;
-    // fp32, two stages: the pipelined slab loop, but not for
-    //  * short reductions on a full chip, where the other workgroups cover a slab's latency and the registers are better spent on
-    //    them (a batch of 960 of 128 x 64 x 128 with the first operand transposed: 960 x 4 waves, 4 slabs, 27.0 us without and 29.9
-    //    with; 2048 x 2048 x 128: 1024 x 2 waves, 16 slabs of 8, 15.7 and 17.5; but 132 x 64 x 224 x 128, 924 x 2 waves, 2 slabs, 16.2 and 13.9);
-    //  * convolutions on slabs of one group of 8: their values are gathered one by one, and with the gather pinned in front of so few
-    //    MFMAs nothing is gained (8 x 64 x 28 x 28 * 64 x 64 x 3 x 3 as 112 x 1 waves 77.6 us without and 82.1 with, as 112 x 7 waves 54.8 and 61.6; four others 0.7 %
-    //    faster to 2 % slower).
-    // Elsewhere, against the plain loop: 13 MatMul / BMM members on slabs of 8 1.00 - 1.46 times as fast, 70 members on longer slabs 0.97 - 1.56 and one
-    // (4 slabs of 24, 42 x 2 waves) 0.94.
-    const bool full_chip = n_blocks * nwr >= 2048, short_k = ksteps < 8 || ksteps * BKP <= 128;
-    if (path == 4 && nstage == 2 && !(short_k && full_chip) && !(op.kind == OPEVO_CONV2D && BKP == 8)) out.try_defines = " -DPIPELINED=1";
+    // fp32, two stages: the pipelined slab loop, but for short reductions on a full chip, where the other workgroups cover a
+    // slab's latency and the registers are better spent on them (a batch of 960 of 128 x 64 x 128 with the first operand transposed:
+    // 960 x 4 waves, 4 slabs, 27.0 us without and 29.9 with; 132 x 64 x 224 x 128, 924 x 2 waves, 2 slabs, 16.2 and 13.9).  Against the
+    // plain loop 13 MatMul / BMM members on slabs of 8 are 1.00 - 1.46 times as fast, 70 members on longer slabs 0.97 - 1.56 and one (4 slabs of
+    // 24, 42 x 2 waves) 0.94.
+    // Slabs of a single group of 8 have nothing to read ahead.  Convolutions on them, which gather value by value, and short
+    // reductions on a full chip have the plain loop with the second operand read step by step (8 x 64 x 28 x 28 * 64 x 64 x 3 x 3 as 112 x 1 waves 77.5 us so and
+    // 82.0 pipelined, as 112 x 7 waves 54.8 and 61.1, on slabs of 2 as 32 x 1 waves 1020 and 1139; 2048 x 2048 x 128, 1024 x 2 waves, 15.7 and 17.5; four other
+    // convolutions between 0.7 % slower and 2 % faster).
+    if (path == 4 && nstage == 2) {
+        const bool full_chip = n_blocks * nwr >= 2048;
+        if (BKP == 8 && (op.kind == OPEVO_CONV2D || (full_chip && ksteps * BKP <= 128))) out.tries = {" -DSTEP_READS=1", " -DPIPELINED=1", ""};
+        else if (!(full_chip && ksteps < 8)) out.tries = {" -DPIPELINED=1", ""};
+    }
     if (kgrp > 1) D << " -DKGRP=" << kgrp;
     if (kunroll) D << " -DKUNROLL=" << kunroll;
     if (ksplit > 1) D << " -DKSPLIT=" << ksplit;
@@ -901,7 +904,7 @@ int opevo_kernel_defines(const opevo_op *op, int variant, const int32_t *cfg, ch
     if (!op || !cfg || !buf) return fail(OPEVO_E_ARG, "kernel_defines: NULL argument");
     Decoded d;
     if (int rc = decode(*op, variant, cfg, d)) return rc;
-    const std::string s = d.tmpl + ": " + d.defines + d.try_defines;
+    const std::string s = d.tmpl + ": " + d.defines + d.tries.front();
     if (s.size() + 1 > cap) return fail(OPEVO_E_ARG, "kernel_defines: buffer too small (%zu needed)", s.size() + 1);
     std::memcpy(buf, s.c_str(), s.size() + 1);
     return OPEVO_OK;

@@ -31,9 +31,8 @@ struct Decoded {
     opevo_plan plan;
     std::string tmpl;      // template name: "gemm_scalar" or "gemm_mfma"
     std::string defines;   // space separated -D options
-    // Options the kernel is better with where its registers hold them: a build whose kernel spills with them is done again
-    // without (empty: none).
-    std::string try_defines;
+    // Options to compile with beside `defines`, the best first: a build whose kernel spills with one goes on to the next.
+    std::vector<std::string> tries = {""};
     bool extra_waves = false;   // more waves share a wave tile, or the reduction, than the configuration asks for
     std::string kernel_name;   // symbol of the instantiated kernel
     int64_t zero_bytes = 0;    // bytes of the output the host clears before every launch (split reduction), else 0

@@ -28,6 +28,9 @@ typedef f32x16 acc_t;
 #ifndef PIPELINED
 #define PIPELINED 0
 #endif
+#ifndef STEP_READS
+#define STEP_READS 0
+#endif
 #ifndef BKP
 #define BKP BK
 #endif
@@ -157,49 +160,6 @@ __device__ __forceinline__ void store_pieces(const Slab &s, float *As, float *Bs
 #endif
 __device__ __forceinline__ void store_slab(const Slab &s, float *As, float *Bs, int tid) { store_pieces(s, As, Bs, tid, 0, NA + NB); }
 
-// (B's values are read step by step: with those of a whole group read first, as the pipelined loop has them, 8 x 64 x 28 x 28 * 64 x 64 x 3 x 3
-// in wave tiles of 64 x 56 takes 82.0 us instead of 77.4, in 32 x 392 1117 instead of 1020)
-__device__ __forceinline__ void compute_slab(acc_t (&acc)[MI][NI], const float *As, const float *Bs, int wm, int wn, int lane)
-{
-    const int l32 = lane & 31, half = lane >> 5;
-#if FLAG
-#pragma unroll
-#else
-#pragma unroll 1
-#endif
-    for (int g = 0; g < BKP / 8; ++g) {
-        f32x4 af[MI];
-#if A_TRANS
-#pragma unroll
-        for (int i = 0; i < MI; ++i)
-#pragma unroll
-            for (int j4 = 0; j4 < 4; ++j4) af[i][j4] = As[(g * 8 + 4 * half + j4) * LDA + wm * TM + i * 32 + l32];
-#else
-#pragma unroll
-        for (int i = 0; i < MI; ++i) af[i] = *(const f32x4 *)(As + (wm * TM + i * 32 + l32) * LDA + g * 8 + 4 * half);
-#endif
-#pragma unroll
-        for (int j4 = 0; j4 < 4; ++j4) {
-            float bf[NI];
-#pragma unroll
-            for (int j = 0; j < NI; ++j) bf[j] = Bs[(g * 8 + 4 * half + j4) * LDB + wn * TN + j * 32 + l32];
-#pragma unroll
-            for (int i = 0; i < MI; ++i)
-#pragma unroll
-                for (int j = 0; j < NI; ++j)
-                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(af[i][j4], bf[j], acc[i][j], 0, 0, 0);
-        }
-    }
-}
-
-// PIPELINED (two stages, where the registers hold it): the loads of the next slab stay in front of this slab's MFMAs (left
-// to itself the compiler moves them behind the last one, next to the stores that use them, and every slab waits for
-// memory once), the fragments of a group are read before the MFMAs of the group before it, and the next slab goes to the
-// other stage between the MFMAs of the second half.  What is left between two slabs is the barrier and one fragment read;
-// workgroups that share a compute unit run in step and do not cover it for each other.
-// 512 x 4096 x 1024 in 64 x 64 tiles on slabs of 64 41.7 -> 38.4 us (every compute unit has two workgroups); with one or none 512 x 1024 x 4096
-// in 32 x 64 tiles 230 -> 146 us, in 32 x 32 tiles 196 -> 86, 608 x 160 x 1536 in 32 x 32 tiles 90 -> 33.
-#if PIPELINED
 // The fragments of one group of 8 reduction steps: 4 values per lane and atom row, and per MFMA one per atom column.
 struct Frags { f32x4 a[MI]; float b[4][NI]; };
 __device__ __forceinline__ void load_frags(Frags &f, const float *As, const float *Bs, int wm, int wn, int lane, int g)
@@ -230,15 +190,56 @@ __device__ __forceinline__ void multiply(acc_t (&acc)[MI][NI], const Frags &f)
                 acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(f.a[i][j4], f.b[j4][j], acc[i][j], 0, 0, 0);
 }
 
+__device__ __forceinline__ void compute_slab(acc_t (&acc)[MI][NI], const float *As, const float *Bs, int wm, int wn, int lane)
+{
+#if FLAG
+#pragma unroll
+#else
+#pragma unroll 1
+#endif
+    for (int g = 0; g < BKP / 8; ++g) {
+#if STEP_READS   // B's values read step by step: where a slab is a single group there is nothing between a group's reads and its MFMAs but themselves
+        const int l32 = lane & 31, half = lane >> 5;
+        Frags f;
+#if A_TRANS
+#pragma unroll
+        for (int i = 0; i < MI; ++i)
+#pragma unroll
+            for (int j4 = 0; j4 < 4; ++j4) f.a[i][j4] = As[(g * 8 + 4 * half + j4) * LDA + wm * TM + i * 32 + l32];
+#else
+#pragma unroll
+        for (int i = 0; i < MI; ++i) f.a[i] = *(const f32x4 *)(As + (wm * TM + i * 32 + l32) * LDA + g * 8 + 4 * half);
+#endif
+#pragma unroll
+        for (int j4 = 0; j4 < 4; ++j4) {
+#pragma unroll
+            for (int j = 0; j < NI; ++j) f.b[j4][j] = Bs[(g * 8 + 4 * half + j4) * LDB + wn * TN + j * 32 + l32];
+#pragma unroll
+            for (int i = 0; i < MI; ++i)
+#pragma unroll
+                for (int j = 0; j < NI; ++j)
+                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(f.a[i][j4], f.b[j4][j], acc[i][j], 0, 0, 0);
+        }
+#else
+        Frags f;
+        load_frags(f, As, Bs, wm, wn, lane, g);
+        multiply(acc, f);
+#endif
+    }
+}
+
+// PIPELINED (two stages, where the registers hold it): the loads of the next slab stay in front of this slab's MFMAs (left
+// to itself the compiler moves them behind the last one, next to the stores that use them, and every slab waits for
+// memory once), the fragments of a group are read before the MFMAs of the group before it, and the next slab goes to the
+// other stage between the MFMAs of the second half.  What is left between two slabs is the barrier and one fragment read;
+// workgroups that share a compute unit run in step and do not cover it for each other.
+// 512 x 4096 x 1024 in 64 x 64 tiles on slabs of 64 41.7 -> 38.4 us (every compute unit has two workgroups); with one or none 512 x 1024 x 4096
+// in 32 x 64 tiles 230 -> 146 us, in 32 x 32 tiles 196 -> 86, 608 x 160 x 1536 in 32 x 32 tiles 90 -> 33.
+#if PIPELINED
 __device__ __forceinline__ void multiply_and_store(acc_t (&acc)[MI][NI], const float *As, const float *Bs, int wm, int wn, int lane,
                                                    const Slab &next, float *An, float *Bn, int tid)
 {
     constexpr int GROUPS = BKP / 8, HALF = GROUPS / 2, REST = GROUPS - HALF;
-    if constexpr (GROUPS == 1) {     // nothing to read ahead: what is left of the pipeline are the loads in front
-        compute_slab(acc, As, Bs, wm, wn, lane);
-        store_slab(next, An, Bn, tid);
-        return;
-    }
     Frags f[2];
     load_frags(f[0], As, Bs, wm, wn, lane, 0);
 #pragma unroll
