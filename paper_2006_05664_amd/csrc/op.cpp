@@ -257,6 +257,66 @@ static bool plan_rows(const opevo_op &op, int64_t bm, int64_t nb2, int64_t bh, i
     return true;
 }
 
+// How the row-strip template runs a box of bm output channels x nb2 images x bh x bw pixels: atom, channels per slab, waves along the
+// channels, rows per wave, waves that share a wave tile.
+// kw_min: the patch template's division has that many partial sums per output, and so has this one, or more: with fewer the rounding errors of
+// the longer chains would be larger (2304 products: 1.8e-7 of the norm in two partial sums, 2.7e-7 in one, 1.6e-7 in three).
+struct Strip { int atom = 0, cs = 0, wm = 0, mi = 0, rows = 0, wn = 0, kw = 0, pitch = 0, min_waves = 0; int64_t lds = 0; };
+
+static bool plan_strip(const opevo_op &op, int64_t bm, int64_t nb2, int64_t bh, int64_t bw, int64_t wgs, int64_t kw_min, Strip &out)
+{
+    // Left to the patch template, by what was measured there: 1 x 1 kernels, which have no rows to re-use, with boxes of part of a row (96 -> 32
+    // channels at 56 x 56 9.2 -> 10.0 us) or slabs of 32 channels (96 -> 128 at 27 x 27 6.7 -> 7.1); fewer than two waves on every SIMD (32 -> 64 channels,
+    // 5 x 5, boxes of 3 rows of 27 17.2 -> 18.6) or four waves in a workgroup (48 -> 192, 5 x 5, 36 workgroups 10.6 -> 14.8); sharing of
+    // a tile with slabs of 16 channels or a single slab (48 -> 192, 3 x 3 5.2 -> 6.6); wave tiles of 32 x 32 atoms that read more than 9
+    // fragments for 8 MFMAs (48 -> 128, 3 x 3, two rows a wave 15.4 -> 16.2); more than half the LDS where the grid has a second
+    // workgroup for the compute unit (32 -> 192, 5 x 5, 810 workgroups 21.4 -> 23.7).
+    if (op.stride != 1 || (op.hk * op.wk == 1 && bw != op.wout)) return false;
+    const int64_t taps = op.hk * op.wk, ph = bh + op.hk - 1, pw = bw + op.wk - 1, pitch = (pw + 15) / 16 * 16;
+    double best = 1e300;
+    for (int64_t atom = 16; atom <= 32; atom += 16)
+        for (int64_t cs = atom == 16 ? 32 : 16; cs <= 128; cs *= 2) {
+            const int64_t ka = atom == 16 ? 32 : 16, strips = (bw + atom - 1) / atom, units = cs / ka * op.wk, nacc = atom == 16 ? 4 : 16;
+            if (bm % atom != 0 || op.cin % cs != 0 || 4 * strips * atom > 5 * bw) continue;   // at least four lanes of five have a pixel
+            for (int64_t wm = 1; wm <= 8; ++wm)
+                for (int64_t rows = 2; rows <= bh; ++rows)
+                    for (int64_t kw = kw_min; kw <= 8; ++kw) {
+                        if (bm / atom % wm != 0 || bh % rows != 0 || units % kw != 0) continue;
+                        const int64_t wn = nb2 * strips * (bh / rows), nw = wm * wn * kw, nt = 64 * nw, mi = bm / atom / wm;
+                        if (nw > kMaxThreads / 64 || (nw < 4 && wgs <= 512) || (kw > 1 && (atom == 32 || op.cin == cs))) continue;
+                        const int64_t stage = nb2 * ph * pitch * cs + taps * bm * cs, slabs = op.cin / cs;
+                        const int64_t lds = std::max<int64_t>((stage + 512) * 2, kw > 1 ? nw * (nacc / 4) * 1024 : 0);
+                        // registers of a lane: accumulators, the fill's plan, and two sets of a unit's fragments or the larger part's data
+                        const int64_t fill_p = (cs / 8 * (pw / 2 + 1) * ph * nb2 + nt - 1) / nt, fill_a = (bm * cs / 2 + nt - 1) / nt;
+                        const int64_t acc = mi * rows * nacc;
+                        const int64_t regs = acc + 3 * fill_p + 2 * fill_a + std::max(4 * (2 * op.hk * mi + 6), std::max(8 * fill_p, taps * fill_a)) + 30;
+                        const int64_t mfmas = units / kw * op.hk * rows * mi;       // of a wave and slab
+                        const int64_t frags = op.hk * mi + rows + op.hk - 1;        // fragments a unit reads
+                        if (lds > kMaxLds || acc > kMaxAcc || regs > 512 / ((nw + 3) / 4) || mfmas > 768) continue;
+                        if ((atom == 32 && 8 * frags > 9 * op.hk * rows * mi) || (wgs > 256 && 2 * lds > kMaxLds) || (taps == 1 && cs < 64)) continue;
+                        int64_t k = 1;                                              // workgroups a compute unit holds
+                        while (k < 8 && (k + 1) * lds <= kMaxLds && nw * (k + 1) <= 32 && regs <= 512 / ((nw * (k + 1) + 3) / 4)) ++k;
+                        k = std::max<int64_t>(1, std::min(k, (wgs + 255) / 256));
+                        if (nw * k < 8) continue;
+                        // Cycles of the k workgroups of a compute unit: what they keep busy together (matrix pipes, LDS), or one of them with
+                        // its exposed fill; a SIMD with few waves waits for its own latencies.  Of the forms of this sum tried on 133 compiled divisions of
+                        // 16 operators, this one's choice was on average 3 % slower than the fastest of each operator.
+                        const double mfma = double((nw + 3) / 4) * mfmas * (atom == 16 ? 16 : 32) * slabs;
+                        const double reads = double(nw) * (units / kw) * frags * 8 * slabs;
+                        const double stores = double(stage) * 2 / 128 * 2 * slabs, final_sum = kw > 1 ? double(acc) * nw * 8 : 0.0;
+                        const double own = slabs * (8.0 * fill_p + double(taps) * fill_a) * 6 + acc * 6.0;   // a wave's own loads, packing and stores
+                        const double together = std::max(mfma, reads + stores) * k * (1.0 + 1.0 / std::min(nw * k / 4.0, 8.0));
+                        const double alone = (mfma + stores + 4.0 * stores / slabs + 1000.0 * slabs + own + final_sum) * (1.0 + 1.0 / std::max(nw / 4.0, 1.0));
+                        const double cost = std::max(1.0, wgs / (256.0 * k)) * std::max(together, alone);
+                        if (cost >= best) continue;
+                        best = cost;
+                        out.atom = int(atom); out.cs = int(cs); out.wm = int(wm); out.mi = int(mi); out.rows = int(rows); out.wn = int(wn); out.kw = int(kw);
+                        out.pitch = int(pitch); out.min_waves = int(std::min<int64_t>(8, (nw * k + 3) / 4)); out.lds = lds;
+                    }
+        }
+    return best < 1e300;
+}
+
 // Members that cannot run without the few-channels template (a slab with too many staging registers, say) stay invalid:
 // which members of a space are valid does not depend on it.
 static bool valid_without_rows(const opevo_op &op, int variant, const int32_t *cfg)
@@ -328,6 +388,7 @@ int decode(const opevo_op &op, int variant, const int32_t *cfg, Decoded &out, bo
     int64_t patch_cs = 0;                  // Conv2d, TILE4L, layout 2: channels per slab of the LDS-resident patch (0: not on that template)
     int patch_atom = 0, patch_stages = 1, patch_kw = 1;
     int64_t patch_row = 0, patch_image = 0;   // its row pitch and image pitch in pixels
+    Strip strip;                              // strip.rows > 0: such a member on the row-strip template instead
     int tile4_width = 0;   // slots of the four-level part, after which the launch-order parameters follow
 
     if (!four_level) {
@@ -462,12 +523,25 @@ int decode(const opevo_op &op, int variant, const int32_t *cfg, Decoded &out, bo
                     if (wm == 1) break;
                     const int64_t q = prime(wm); wm /= q; tm *= q;
                 }
+                // Members that have to be divided anew anyway, because they ask for more waves than a workgroup holds, and members that ask for no
+                // pipelining and no sharing and deal their pixels to several waves, go to the row-strip template where it has a division
+                // (the others run the loop and the division that they ask for).  144 drawn members and 60 folded ones of 8 operators, old
+                // template against new: 1.20 - 1.26x in the geometric mean, 0.94 - 2.5x; what was below 0.94 is excluded by the conditions in plan_strip.
+                const int64_t asked_n = int64_t(h[1]) * w[1], asked = c[3] * asked_n * int64_t(kReductionWaves[c[18]]);
+                if (extras && patch_cs && (asked > kMaxThreads / 64 || (flagv == 0 && c[18] == 0 && asked_n >= 2)) &&
+                    plan_strip(op, WM * TM, nb2, BH, BW, n1 * m1, patch_kw, strip)) {
+                    out.extra_waves = true;
+                    patch_cs = strip.cs; patch_atom = strip.atom; patch_stages = 1; patch_kw = strip.kw;
+                    WM = strip.wm; TM = strip.mi * strip.atom; FM = std::gcd(FM, TM);
+                    WN = strip.wn; TN = strip.rows * strip.atom; FN = 1;
+                    ksteps = op.cin / strip.cs; BK = strip.cs * taps;
+                }
             }
         } else {
             ksteps = c[14]; BK = c[15]; flagv = c[16];
             tile4_width = 17;
         }
-        BM = WM * TM; BN = WN * TN;
+        BM = WM * TM; BN = strip.rows ? nb2 * BH * BW : WN * TN;
     }
     // ---- members that ask for more than a workgroup has are folded into serial work instead of scoring 0
     // (the search then sees a slow member with its own place in the landscape, not a hole; Sec. 4.2 keeps
@@ -708,6 +782,7 @@ int decode(const opevo_op &op, int variant, const int32_t *cfg, Decoded &out, bo
     }
     else if (path == 4) lds = nstage * ((op.trans_a ? BK * (BM + 4) : BM * (BK + 4)) + BK * (BN + 4)) * 4;
     else if (path == 3) lds = nstage * (anr + (b_kmajor ? bnr : BN)) * BK * 2;
+    else if (path == 5 && strip.rows) lds = strip.lds;
     else if (path == 5)   // the stages, or (more than one wave per tile) one atom of every wave if that is more
         lds = std::max<int64_t>(nstage * (nb2 * patch_image * (patch_cs + 8) + op.hk * op.wk * BM * patch_cs + 64) * 2,
                                 patch_kw > 1 ? nwr * (patch_atom == 32 ? 4 : 1) * 1024 : 0);
@@ -749,7 +824,7 @@ int decode(const opevo_op &op, int variant, const int32_t *cfg, Decoded &out, bo
             invalid(p, "%ld staging registers per lane > 256", long((a_chunks + b_chunks) * 4));
     }
 
-    out.tmpl = path == 0 ? "gemm_scalar" : path == 3 ? "gemm_mfma_dlds" : path == 4 ? "gemm_mfma_f32" : path == 5 ? "conv_patch" : path == 6 ? "gemm_ragged" : path == 7 ? "conv_rows" : "gemm_mfma";
+    out.tmpl = path == 0 ? "gemm_scalar" : path == 3 ? "gemm_mfma_dlds" : path == 4 ? "gemm_mfma_f32" : path == 5 ? (strip.rows ? "conv_strip" : "conv_patch") : path == 6 ? "gemm_ragged" : path == 7 ? "conv_rows" : "gemm_mfma";
     // one symbol per configuration, so profiles list each instantiated kernel on its own line
     {
         std::ostringstream nm;
@@ -791,7 +866,10 @@ int decode(const opevo_op &op, int variant, const int32_t *cfg, Decoded &out, bo
     if (tap_box)
         D << " -DTAP_BOX=1 -DCI_O=" << box[0] << " -DCI_I=" << box[1] << " -DHK_O=" << box[2] << " -DHK_I=" << box[3]
           << " -DWK_O=" << box[4] << " -DWK_I=" << box[5];
-    if (path == 5) D << " -DCS=" << patch_cs << " -DPWP=" << patch_row << " -DIPIX=" << patch_image << " -DKW=" << patch_kw << " -DLDS_BYTES=" << lds;
+    if (path == 5 && strip.rows)
+        D << " -DCS=" << strip.cs << " -DPWP=" << strip.pitch << " -DKW=" << strip.kw << " -DMI=" << strip.mi << " -DR=" << strip.rows << " -DMINW=" << strip.min_waves
+          << " -DLDS_BYTES=" << lds;
+    else if (path == 5) D << " -DCS=" << patch_cs << " -DPWP=" << patch_row << " -DIPIX=" << patch_image << " -DKW=" << patch_kw << " -DLDS_BYTES=" << lds;
     if (b_kmajor) D << " -DB_KMAJOR=1 -DBNR=" << bnr;
     if (path == 3 && anr != BM) D << " -DANR=" << anr;
     // fp32, two stages: the pipelined slab loop, but for short reductions on a full chip, where the other workgroups cover a
