@@ -166,9 +166,9 @@ static void patch_pitches(const opevo_op &op, int64_t bh, int64_t bw, bool padde
 }
 
 // How the ragged MFMA template runs a tile of bm x bn with slabs of about bk: wave grid, atoms per wave, slab width.
-struct Ragged { int wm = 0, wn = 0, mi = 0, ni = 0, ks = 0, slabs = 0, stages = 1; int64_t lds = 0; };
+struct Ragged { int wm = 0, wn = 0, mi = 0, ni = 0, ks = 0, slabs = 0, stages = 1, depth = 1, keep = 0, min_waves = 1; int64_t lds = 0; };
 
-static bool plan_ragged(const opevo_op &op, int64_t bm, int64_t bn, int64_t bk, int64_t kpart, bool pipelined, Ragged &out)
+static bool plan_ragged(const opevo_op &op, int64_t bm, int64_t bn, int64_t bk, int64_t kpart, int64_t wgs, bool pipelined, Ragged &out)
 {
     // every operand is loaded in pieces of 8 consecutive elements of a row, with 32-bit element offsets inside a batch
     if (kpart < 8 || op.N < 8 || (op.trans_a && op.M < 8) || op.M * op.K >= (int64_t(1) << 31) || op.K * op.N >= (int64_t(1) << 31)) return false;
@@ -214,7 +214,18 @@ static bool plan_ragged(const opevo_op &op, int64_t bm, int64_t bn, int64_t bk, 
         const int64_t score = slabs * (ks + 8) + (lds > kMaxLds / 2 ? slabs * 16 : 0);   // two workgroups per compute unit where it can be
         if (score <= best) { best = score; out.ks = int(ks); out.slabs = int(slabs); out.stages = stages; out.lds = lds; }
     }
-    return best != INT64_MAX;
+    if (best == INT64_MAX) return false;
+    // Two slabs on their way instead of one where a workgroup is alone on its compute unit for a long reduction (567 x 330 x 4450 in 27 x 30, 231
+    // workgroups x 70 slabs, 18.1 -> 16.2 us; 110 x 72 x 864, 15 x 27, 5.9 -> 5.1; 840 x 2150 x 1368, 602 x 22, 22.1 -> 24.3); the places of a thread's pieces are kept
+    // in registers where there is room for them, else worked out again for every slab.
+    const int64_t nw = out.wm * out.wn, held = staging(out.ks, 64 * nw);
+    const int64_t fit = std::max<int64_t>(1, std::min(kMaxLds / out.lds, (wgs + 255) / 256));       // workgroups on a compute unit
+    const int64_t waves = std::max((nw + 3) / 4, std::min<int64_t>(2, (nw * fit + 3) / 4));
+    const int64_t rest = held / 4 * 3 + 4 * out.mi * out.ni + 8 * (out.mi + out.ni) + 48;
+    out.depth = out.stages == 2 && wgs <= 256 && out.slabs >= 16 && 2 * held + rest <= 512 / waves ? 2 : 1;
+    out.keep = out.slabs > 1 && out.depth * held + rest <= 512 / waves;
+    out.min_waves = int(out.keep ? waves : (nw + 3) / 4);
+    return true;
 }
 
 // How the few-channels convolution template runs a box: atom, wave grid, atoms per wave, padded kernel row, LDS bytes.
@@ -717,7 +728,7 @@ int decode(const opevo_op &op, int variant, const int32_t *cfg, Decoded &out, bo
     Ragged rg;
     if (four_level && path == 0 && op.dtype != OPEVO_F32 && op.kind != OPEVO_CONV2D && subm * subn == 1 &&
         (op.M % 16 != 0 || op.N % 16 != 0 || op.K % 16 != 0) &&
-        plan_ragged(op, BM, BN, BK, op.K / ksplit, flagv != 0 || op.kind == OPEVO_BMM, rg)) {
+        plan_ragged(op, BM, BN, BK, op.K / ksplit, n1 * m1 * b1, flagv != 0 || op.kind == OPEVO_BMM, rg)) {
         path = 6;
         WM = rg.wm; WN = rg.wn; TM = rg.mi * 16; TN = rg.ni * 16;
         TMacc = TM; TNacc = TN; BK = rg.ks; ksteps = rg.slabs;
@@ -846,7 +857,7 @@ int decode(const opevo_op &op, int variant, const int32_t *cfg, Decoded &out, bo
         if (nwr != WM * WN && path != 5) D << " -DNWR=" << nwr;
     }
     if (path == 7) D << " -DWKP=" << rows.wkp << " -DMI=" << rows.mi << " -DNI=" << rows.ni << " -DLDS_BYTES=" << lds << " -DPERSIST=" << rows.persist << " -DNBOX=" << n1;
-    if (path == 6) D << " -DKS=" << rg.ks << " -DNSL=" << rg.slabs << " -DMI=" << rg.mi << " -DNI=" << rg.ni << " -DLDS_BYTES=" << lds;
+    if (path == 6) D << " -DKS=" << rg.ks << " -DNSL=" << rg.slabs << " -DMI=" << rg.mi << " -DNI=" << rg.ni << " -DLDS_BYTES=" << lds << " -DDEPTH=" << rg.depth << " -DKEEP=" << rg.keep << " -DMINW=" << rg.min_waves;
     if (subm * subn > 1) {
         D << " -DSUBM=" << subm << " -DSUBN=" << subn;
     }
@@ -881,6 +892,10 @@ int decode(const opevo_op &op, int variant, const int32_t *cfg, Decoded &out, bo
     // reductions on a full chip have the plain loop with the second operand read step by step (8 x 64 x 28 x 28 * 64 x 64 x 3 x 3 as 112 x 1 waves 77.5 us so and
     // 82.0 pipelined, as 112 x 7 waves 54.8 and 61.1, on slabs of 2 as 32 x 1 waves 1020 and 1139; 2048 x 2048 x 128, 1024 x 2 waves, 15.7 and 17.5; four other
     // convolutions between 0.7 % slower and 2 % faster).
+    // ragged: where the places of pieces are not kept, they are worked out anew for every slab if the kernel spills otherwise (one in 100 members;
+    // transposed first operands on eight waves of 3 x 7 to 3 x 9 atoms always do)
+    if (path == 6 && op.trans_a && !rg.keep && rg.wm * rg.wn >= 8 && rg.mi >= 3 && rg.mi * rg.ni >= 20) out.tries = {" -DFRESH=1"};
+    else if (path == 6) out.tries = {"", " -DFRESH=1"};
     if (path == 4 && nstage == 2) {
         const bool full_chip = n_blocks * nwr >= 2048;
         if (BKP == 8 && (op.kind == OPEVO_CONV2D || (full_chip && ksteps * BKP <= 128))) out.tries = {" -DSTEP_READS=1", " -DPIPELINED=1", ""};

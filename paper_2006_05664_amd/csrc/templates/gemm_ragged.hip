@@ -7,11 +7,12 @@
 // be rounded up by themselves).  What the atoms compute past the tile is not stored.  The reduction is walked in NSL slabs
 // of KS (the member's slab rounded up to whole MFMA steps), the last one filled up with zeros in both operands.
 //
-// Measured (bf16): 1000^3 in tiles of 20 x 100 168 us on the scalar template (20 waves, the best there), 15.6 us here (128 TFLOP/s); 105 x 972 x 160 in
-// tiles of 15 x 54 60 -> 3.6 us; a batch of 11 x (35 x 36 x 35) 6.2 -> 3.5 us.
-// What bounds it: at these tiles the operand stream (1000^3 in tiles of 20 x 100: 0.12 GB through L2) and, with two workgroups per
-// compute unit, the chain of 11 slabs (counters: matrix pipes 13 %, LDS 40 % of the busy time, a third of that bank conflicts), so the point
-// is to move it in wide pieces whatever the alignment: every operand travels in 16-byte pieces of 8 consecutive elements,
+// Measured (bf16): 1000^3 in tiles of 20 x 100 168 us on the scalar template (20 waves, the best there), 15.6 us with every piece's place worked out
+// for every slab, 12.8 us here (156 TFLOP/s); 120 x 280 x 3650 in 60 x 56 39.7 -> 19.5; 220 x 280 x 950 in 44 x 56 12.3 -> 6.4.  119 drawn and random
+// members against the template before that and before the order of the workgroups followed the XCDs: 1.29x in the geometric mean.
+// What bounds it: at these tiles the LDS (1000^3: per slab and compute unit some 1500 of its cycles, fragments that every wave reads for itself and bank
+// conflicts) and the phases of a slab that follow one another, loads, stores and multiplication in equal parts; deeper prefetch gains nothing there.
+// Every operand travels in 16-byte pieces of 8 consecutive elements,
 // loaded at the 2-byte alignment an odd row length leaves.  A piece that would reach past its row is loaded from as far left as
 // it must be to end with the row, and shifted down when it is stored: no load leaves its operand's rows.
 //   * A [M][K]: pieces along k.  LDS As[row][KS + 8]: a fragment is one 16-byte read; the odd number of pieces per row spreads 16 rows
@@ -19,7 +20,7 @@
 //   * B [K][N] (and a first operand stored [K][M]): pieces along n.  LDS Bs[k][LDX] as memory has it, fragments read with the
 //     transposing LDS load (two per fragment).  LDX is an odd multiple of 32 bytes and every 8 rows lie 128 bytes
 //     further, so the 4 rows x 32 bytes that two groups of 16 lanes read together (8 rows apart) fall into 8 different groups of banks.
-// NSTG = 2: the pieces of slab s+1 are in registers while slab s is multiplied and are stored to the other stage afterwards
+// NSTG = 2: the pieces of the next DEPTH slabs are in registers while slab s is multiplied; the next one's are stored to the other stage afterwards
 // (one barrier per slab).  NSTG = 1: load, barrier, store, barrier, multiply.
 
 #if IN_DTYPE == 1
@@ -28,6 +29,12 @@ typedef __attribute__((ext_vector_type(8))) __bf16 frag_t;
 #else
 typedef __attribute__((ext_vector_type(8))) _Float16 frag_t;
 #define MFMA(a, b, c) __builtin_amdgcn_mfma_f32_16x16x32_f16(a, b, c, 0, 0, 0)
+#endif
+#ifdef FRESH
+#undef KEEP
+#define KEEP 0
+#undef DEPTH
+#define DEPTH 1
 #endif
 typedef u32x4 __attribute__((aligned(2))) u32x4_a2;
 typedef __attribute__((ext_vector_type(4))) short v4s;
@@ -63,75 +70,115 @@ __device__ __forceinline__ u32x4 shift_down(u32x4 v, int sh)
     return r;
 }
 
-// k-contiguous operand: piece q of a slab that starts at reduction position k0
-__device__ __forceinline__ u32x4 load_kc(const u16 *__restrict__ base, int q, int k0)
-{
-    const int row = q / CK, k = k0 + q % CK * 8;
-    return *(const u32x4_a2 *)(base + (u32)(row * K + (K_TAIL ? min(k, KPART - 8) : k)));
-}
-__device__ __forceinline__ void store_kc(u16 *S, u32x4 v, int q, int k0, bool last)
-{
-    const int c = q % CK;
-    if (K_TAIL && last) v = shift_down(v, max(k0 + c * 8 - (KPART - 8), 0));
-    *(u32x4 *)(S + q / CK * LDK + c * 8) = v;
-}
-// operand of k rows: LEN elements of a row in memory, of which the tile's begin at x0; C pieces per row
-template <int LEN, int C>
-__device__ __forceinline__ u32x4 load_kr(const u16 *__restrict__ base, int q, int k0, int x0)
-{
-    const int k = k0 + q / C;
-    return *(const u32x4_a2 *)(base + (u32)((K_TAIL ? min(k, KPART - 1) : k) * LEN + min(x0 + q % C * 8, LEN - 8)));
-}
-template <int LEN, int C, int LD, int TILE>
-__device__ __forceinline__ void store_kr(u16 *S, u32x4 v, int q, int k0, int x0, bool last)
-{
-    const int kr = q / C, x = q % C * 8;
-    // A last piece can reach past the row's end in the last tile, and with tiles of 2 and 3 also in the ones before it (8 past the
-    // start of a tile is then more than two tiles on); whole multiples of 8 never do.
-    constexpr bool EARLIER_TOO = (TILE + 7) / 8 * 8 > 2 * TILE;
-    if (TILE % 8 != 0 && (EARLIER_TOO || x0 + TILE == LEN)) v = shift_down(v, max(x0 + x - (LEN - 8), 0));
-    if (K_TAIL && last && k0 + kr >= KPART) { const u32x4 z = {0u, 0u, 0u, 0u}; v = z; }
-    *(u32x4 *)(S + kr_off(LD, kr) + x) = v;
-}
+// Where a thread's pieces come from and go to, worked out once: recomputed for every slab, the places cost more vector instructions
+// than the slab has of all other kinds (1000^3 in tiles of 20 x 100: 210 of 230 in its loop).
+//   g: byte offset from the operand at the slab's first reduction position.
+//   t: the same for the last slab where it is not full (from 8 positions further left for a k-contiguous operand, if there is a slab before it): no load
+//      reaches past the operand's rows.
+//   s: LDS element.
+constexpr int LAST0 = (NSL - 1) * KS, TAIL0 = NSL > 1 ? LAST0 - 8 : 0;
+template <int N_>
+struct Pieces { u32 g[N_], t[K_TAIL ? N_ : 1], s[N_]; };
 
-__device__ __forceinline__ void load_slab(Slab &s, const u16 *__restrict__ Ab, const u16 *__restrict__ Bb, int m0, int n0, int k0, int tid)
+__device__ __forceinline__ void plan_kc(Pieces<NA> &p, int tid)
 {
 #pragma unroll
     for (int i = 0; i < NA; ++i) {
-        const int q = tid + i * NT;
-        if (A_PIECES % NT == 0 || q < A_PIECES) {
-#if A_TRANS
-            s.a[i] = load_kr<M, CM>(Ab, q, k0, m0);
-#else
-            s.a[i] = load_kc(Ab, q, k0);
-#endif
-        }
+        const int q = tid + i * NT < A_PIECES ? tid + i * NT : 0, row = q / CK, c = q % CK * 8;
+        p.g[i] = 2u * (u32)(row * K + c);
+        if (K_TAIL) p.t[i] = 2u * (u32)(row * K + min(LAST0 + c, KPART - 8) - TAIL0);
+        p.s[i] = (u32)(row * LDK + c);
     }
+}
+template <int N_, int PIECES, int LEN, int C, int LD>
+__device__ __forceinline__ void plan_kr(Pieces<N_> &p, int x0, int tid)
+{
 #pragma unroll
-    for (int i = 0; i < NB; ++i) {
-        const int q = tid + i * NT;
-        if (B_PIECES % NT == 0 || q < B_PIECES) s.b[i] = load_kr<N, CN>(Bb, q, k0, n0);
+    for (int i = 0; i < N_; ++i) {
+        const int q = tid + i * NT < PIECES ? tid + i * NT : 0, kr = q / C, x = q % C * 8, at = min(x0 + x, LEN - 8);
+        p.g[i] = 2u * (u32)(kr * LEN + at);
+        if (K_TAIL) p.t[i] = 2u * (u32)((min(LAST0 + kr, KPART - 1) - LAST0) * LEN + at);
+        p.s[i] = (u32)(kr_off(LD, kr) + x);
     }
 }
 
-__device__ __forceinline__ void store_slab(const Slab &s, u16 *As, u16 *Bs, int m0, int n0, int k0, bool last, int tid)
+struct Plan {
+    Pieces<NA> a;
+    Pieces<NB> b;
+};
+// KEEP = 0: few registers for the places; where they are worked out, and what of them is kept, is left to the compiler, or (FRESH, a kernel that
+// spills otherwise) they are worked out for every slab: the thread number is opaque then
+__device__ __forceinline__ void plan_slab(Plan &p, int m0, int n0, int tid)
 {
+#ifdef FRESH
+    asm volatile("" : "+v"(tid));
+    tid &= 1023;
+#endif
+#if A_TRANS
+    plan_kr<NA, A_PIECES, M, CM, LDM>(p.a, m0, tid);
+#else
+    plan_kc(p.a, tid);
+#endif
+    plan_kr<NB, B_PIECES, N, CN, LDN>(p.b, n0, tid);
+}
+
+// slab j of the operands; last: it is the last one.  (A thread without an i-th piece loads its operand's first.)
+__device__ __forceinline__ void load_slab(Slab &s, const Plan &kept, const u16 *__restrict__ Ab, const u16 *__restrict__ Bb, int j, bool last, int m0, int n0, int tid)
+{
+    Plan fresh;
+    if (!KEEP) plan_slab(fresh, m0, n0, tid);
+    const Plan &p = KEEP ? kept : fresh;
+    const bool tail = last && K_TAIL;
+#if A_TRANS
+    const char *a = (const char *)(Ab + (long)(tail ? LAST0 : j * KS) * M);
+#else
+    const char *a = (const char *)(Ab + (tail ? TAIL0 : j * KS));
+#endif
+    const char *b = (const char *)(Bb + (long)(tail ? LAST0 : j * KS) * N);
 #pragma unroll
     for (int i = 0; i < NA; ++i) {
-        const int q = tid + i * NT;
-        if (A_PIECES % NT == 0 || q < A_PIECES) {
-#if A_TRANS
-            store_kr<M, CM, LDM, BM>(As, s.a[i], q, k0, m0, last);
-#else
-            store_kc(As, s.a[i], q, k0, last);
-#endif
-        }
+        const u32 g = p.a.g[i], t = K_TAIL ? p.a.t[K_TAIL ? i : 0] : g;
+        s.a[i] = *(const u32x4_a2 *)(a + (tail ? t : g));
     }
 #pragma unroll
     for (int i = 0; i < NB; ++i) {
-        const int q = tid + i * NT;
-        if (B_PIECES % NT == 0 || q < B_PIECES) store_kr<N, CN, LDN, BN>(Bs, s.b[i], q, k0, n0, last);
+        const u32 g = p.b.g[i], t = K_TAIL ? p.b.t[K_TAIL ? i : 0] : g;
+        s.b[i] = *(const u32x4_a2 *)(b + (tail ? t : g));
     }
+}
+
+// Pieces of k rows are shifted where they were loaded from further left to end with their row, in tiles that reach the row's end (and, with tiles of 2 and
+// 3, also in the ones before it: 8 past the start of a tile is then more than two tiles on; whole multiples of 8 never are).
+constexpr bool edge_tile(int tile, int x0, int len) { return tile % 8 != 0 && ((tile + 7) / 8 * 8 > 2 * tile || x0 + tile == len); }
+template <int N_, int PIECES, int LEN, int C>
+__device__ __forceinline__ void store_kr(u16 *S, const u32x4 (&r)[N_], const Pieces<N_> &p, bool last, bool edge, int x0, int tid)
+{
+#pragma unroll
+    for (int i = 0; i < N_; ++i) {
+        const int q = tid + i * NT;
+        u32x4 v = r[i];
+        if (edge) v = shift_down(v, max(x0 + q % C * 8 - (LEN - 8), 0));
+        if (last && K_TAIL && LAST0 + q / C >= KPART) { const u32x4 z = {0u, 0u, 0u, 0u}; v = z; }
+        if ((i + 1) * NT <= PIECES || q < PIECES) *(u32x4 *)(S + p.s[i]) = v;
+    }
+}
+__device__ __forceinline__ void store_slab(const Slab &s, const Plan &kept, u16 *As, u16 *Bs, bool last, bool edge_a, bool edge_b, int m0, int n0, int tid)
+{
+    Plan fresh;
+    if (!KEEP) plan_slab(fresh, m0, n0, tid);
+    const Plan &p = KEEP ? kept : fresh;
+#if A_TRANS
+    store_kr<NA, A_PIECES, M, CM>(As, s.a, p.a, last, edge_a, m0, tid);
+#else
+#pragma unroll
+    for (int i = 0; i < NA; ++i) {
+        const int q = tid + i * NT;
+        u32x4 v = s.a[i];
+        if (last && K_TAIL) v = shift_down(v, max(LAST0 + q % CK * 8 - (KPART - 8), 0));
+        if ((i + 1) * NT <= A_PIECES || q < A_PIECES) *(u32x4 *)(As + p.a.s[i]) = v;
+    }
+#endif
+    store_kr<NB, B_PIECES, N, CN>(Bs, s.b, p.b, last, edge_b, n0, tid);
 }
 
 // Fragment of an atom whose first row / column is x0, K step kk.  Lane l supplies row or column l % 16, the 8 reduction
@@ -173,7 +220,84 @@ __device__ __forceinline__ void compute_slab(f32x4 (&acc)[MI][NI], const u16 *As
     }
 }
 
-extern "C" __global__ __launch_bounds__(NT)
+// The whole reduction of one tile.  edge_a, edge_b: its pieces may have to be shifted (constants with KEEP).
+__device__ __forceinline__ void walk(f32x4 (&acc)[MI][NI], const Plan &plan, const u16 *__restrict__ Ab, const u16 *__restrict__ Bb, u16 *As, u16 *Bs,
+                                     bool edge_a, bool edge_b, int m0, int n0, int wm, int wn, int lane, int tid, int bi)
+{
+    // slab j of the walk, if there is one, into or from a set of registers
+    Slab slab[DEPTH];
+    auto load = [&](int j, int d) {
+        if (j < NSL) load_slab(slab[d], plan, Ab, Bb, j, j == NSL - 1, m0, n0, tid);
+    };
+    auto store = [&](int j, int d, int stage) {
+        if (j < NSL) store_slab(slab[d], plan, As + stage * A_STAGE, Bs + stage * B_STAGE, j == NSL - 1, edge_a, edge_b, m0, n0, tid);
+    };
+    auto compute = [&](int stage) { compute_slab(acc, As + stage * A_STAGE, Bs + stage * B_STAGE, wm, wn, lane); };
+#if NSTG == 2
+    if (bi > 0) __syncthreads();                       // the previous batch's last slab has been multiplied
+#if KEEP
+    // Slab s in stage s & 1, slabs s+1 .. s+DEPTH in registers or on their way there: slab j in set j % DEPTH.  The steps whose slabs
+    // may be the last one, or past it, are laid out one by one.
+#pragma unroll
+    for (int d = 0; d < DEPTH; ++d) load(d, d);
+    store(0, 0, 0);
+    load(DEPTH, 0);
+    __syncthreads();
+    constexpr int MAIN = NSL > DEPTH + 2 ? (NSL - DEPTH - 2) / DEPTH * DEPTH : 0;
+#pragma unroll 1
+    for (int s0 = 0; s0 < MAIN; s0 += DEPTH) {
+#pragma unroll
+        for (int d = 0; d < DEPTH; ++d) {
+            const int s = s0 + d, set = (d + 1) % DEPTH;
+            __builtin_amdgcn_sched_barrier(0);
+            compute(s & 1);
+            __builtin_amdgcn_sched_barrier(0);
+            store_slab(slab[set], plan, As + (~s & 1) * A_STAGE, Bs + (~s & 1) * B_STAGE, false, edge_a, edge_b, m0, n0, tid);
+            load_slab(slab[set], plan, Ab, Bb, s + 1 + DEPTH, false, m0, n0, tid);
+            __syncthreads();
+        }
+    }
+#pragma unroll
+    for (int s = MAIN; s < NSL; ++s) {
+        __builtin_amdgcn_sched_barrier(0);
+        compute(s & 1);
+        __builtin_amdgcn_sched_barrier(0);
+        store(s + 1, (s + 1) % DEPTH, ~s & 1);
+        load(s + 1 + DEPTH, (s + 1) % DEPTH);
+        if (s + 1 < NSL) __syncthreads();
+    }
+#else
+    // (large tiles: one loop whose last pass loads and stores the last slab once more, into the stage nobody reads any longer)
+    load(0, 0);
+    store(0, 0, 0);
+    __syncthreads();
+#pragma unroll 1
+    for (int s = 0; s < NSL; ++s) {
+        const int sn = s + 1 < NSL ? s + 1 : NSL - 1;
+        load(sn, 0);
+        __builtin_amdgcn_sched_barrier(0);
+        compute(s & 1);
+        __builtin_amdgcn_sched_barrier(0);
+        store(sn, 0, ~s & 1);
+        __syncthreads();
+    }
+#endif
+#else
+    auto step = [&](int s, bool last) {
+        load_slab(slab[0], plan, Ab, Bb, s, last, m0, n0, tid);
+        __syncthreads();
+        store_slab(slab[0], plan, As, Bs, last, edge_a, edge_b, m0, n0, tid);
+        __syncthreads();
+        compute(0);
+    };
+#pragma unroll 1
+    for (int s = 0; s < NSL - KEEP; ++s) step(s, !KEEP && s == NSL - 1);
+    if (KEEP) step(NSL - 1, true);
+    __syncthreads();
+#endif
+}
+
+extern "C" __global__ __launch_bounds__(NT, MINW)
 void KERNEL_NAME(const u16 *__restrict__ A, const u16 *__restrict__ B, float *__restrict__ C,
                  unsigned long long *ctl /* unused: members of this template are never folded */)
 {
@@ -182,6 +306,8 @@ void KERNEL_NAME(const u16 *__restrict__ A, const u16 *__restrict__ B, float *__
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, wm = wave / WN, wn = wave % WN;
     const BlockId bid = block_id();
     const int m0 = bid.m * BM, n0 = bid.n * BN;
+    Plan plan;
+    if (KEEP) plan_slab(plan, m0, n0, tid);
 
     for (int bi = 0; bi < BATCH_INNER; ++bi) {
 #if KSPLIT > 1   // MatMul, reduction split over grid z: this workgroup owns K range [bid.b * KPART, + KPART)
@@ -205,35 +331,12 @@ void KERNEL_NAME(const u16 *__restrict__ A, const u16 *__restrict__ B, float *__
 #pragma unroll
                 for (int r = 0; r < 4; ++r) acc[i][j][r] = 0.f;
 
-        Slab slab;
-#if NSTG == 2
-        if (bi > 0) __syncthreads();                   // the previous batch's last slab has been multiplied
-        load_slab(slab, Ab, Bb, m0, n0, 0, tid);
-        store_slab(slab, As, Bs, m0, n0, 0, NSL == 1, tid);
-        __syncthreads();
-#pragma unroll 1
-        for (int s = 0; s < NSL; ++s) {
-            const int cur = s & 1, nxt = cur ^ 1;
-            // past the last slab: the last once more, into the stage nobody reads any longer
-            const int sn = s + 1 < NSL ? s + 1 : NSL - 1;
-            load_slab(slab, Ab, Bb, m0, n0, sn * KS, tid);
-            __builtin_amdgcn_sched_barrier(0);
-            compute_slab(acc, As + cur * A_STAGE, Bs + cur * B_STAGE, wm, wn, lane);
-            __builtin_amdgcn_sched_barrier(0);
-            store_slab(slab, As + nxt * A_STAGE, Bs + nxt * B_STAGE, m0, n0, sn * KS, sn == NSL - 1, tid);
-            __syncthreads();
-        }
-#else
-#pragma unroll 1
-        for (int s = 0; s < NSL; ++s) {
-            load_slab(slab, Ab, Bb, m0, n0, s * KS, tid);
-            __syncthreads();
-            store_slab(slab, As, Bs, m0, n0, s * KS, s == NSL - 1, tid);
-            __syncthreads();
-            compute_slab(acc, As, Bs, wm, wn, lane);
-        }
-        __syncthreads();
-#endif
+        const bool edge_a = A_TRANS && edge_tile(BM, m0, M), edge_b = edge_tile(BN, n0, N);
+        auto run = [&](bool ea, bool eb) { walk(acc, plan, Ab, Bb, As, Bs, ea, eb, m0, n0, wm, wn, lane, tid, bi); };
+        if (!KEEP) run(edge_a, edge_b);
+        else if (edge_a) { if (edge_b) run(true, true); else run(true, false); }
+        else if (edge_b) run(false, true);
+        else run(false, false);
         // register r of an atom is row 4 * (l / 16) + r of column l % 16
 #pragma unroll
         for (int i = 0; i < MI; ++i)
