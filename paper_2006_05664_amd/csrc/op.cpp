@@ -328,6 +328,40 @@ static bool plan_strip(const opevo_op &op, int64_t bm, int64_t nb2, int64_t bh, 
     return best < 1e300;
 }
 
+// How the workgroups of a MatMul / BatchMatMul grid are dealt to tiles.  Consecutive workgroups go to the eight XCDs in turn, each with
+// an L2 of its own, so that in the launch's natural order (0) an XCD walks every eighth tile: columns that share cache lines, and the tiles of
+// one batch, are spread over all eight.  1 / 2: an XCD walks a contiguous eighth of the tiles, columns / rows first.
+// The choice compares the bytes per reduction row that the tiles an XCD has under way at a time take from beyond its L2; a
+// column panel that is not surrounded by its neighbours also pays for the rest of its cache lines.
+// Measured, natural / columns first / rows first (us): 245 x 7650 x 1590 in 7 x 30 257 / 150 / 108; 2496 x 7072 x 6848 in 64 x 32 1040 / 697 / 749; 6680 x 1650 x 400 in
+// 40 x 30 74 / 68 / 83; 506 x (128 x 160 x 160) in 128 x 32 28 / 17 / 18; 8192^3 in 256 x 256 890 / 942 / 995; 512 x 4096 x 1024 fp32 in 64 x 64 47 / 51 / 48.
+// Operands that an L2 holds gain nothing and pay for the division (1000^3 in 20 x 100 13.6 / 14.2 / 14.1, 6048 x 108 x 75 3.4 / 3.6 / 3.7), nor do
+// small batches (52 x (224 x 192 x 64), 12 MB 5.1 / 5.5 / 5.5): from 4 MiB of operands on, or 16 MB of traffic with batches.
+static int xcd_walk(const opevo_op &op, int64_t n1, int64_t m1, int64_t b1, int64_t bm, int64_t bn, int64_t binner, int64_t resident)
+{
+    const int64_t e = op.elem_size(), tiles = n1 * m1, W = 32 * std::max<int64_t>(1, std::min<int64_t>(8, resident));
+    auto up = [](int64_t a, int64_t b) { return (a + b - 1) / b; };
+    auto alone = [&](int64_t w) { return w * e + (w * e % 128 == 0 ? 0 : w * e % 64 == 0 ? 64 : 126); };
+    const int64_t row = op.trans_a && m1 > 1 ? alone(bm) : bm * e, col = n1 > 1 ? alone(bn) : bn * e;
+    // natural order over a window of `tiles_in` tiles: an XCD's distinct columns and rows
+    auto natural = [&](int64_t tiles_in) {
+        const int64_t r = std::min(m1, up(tiles_in, n1));
+        const int64_t c = std::min(n1, up(n1, 8) * std::min<int64_t>(8 / std::gcd<int64_t>(n1, 8), r));
+        return double(c * col + r * row);
+    };
+    if (tiles * b1 < 64) return 0;
+    if (b1 > 1) {
+        const double mine = std::max(1.0, tiles / 8.0);                  // tiles of a batch that one XCD has
+        const double nat = std::min(natural(tiles) / mine, double(col + row)), walk = double(n1 * bn * e + m1 * bm * e) / tiles;
+        return nat * double(op.K) * double(tiles) * double(b1 * binner) >= 16e6 && walk < 0.75 * nat ? 1 : 0;
+    }
+    if ((op.a_elems() + op.b_elems()) * e <= (int64_t(4) << 20)) return 0;
+    const double nat = natural(std::min(tiles, 8 * W));
+    const double by_col = double(std::min(n1, W) * bn * e + 128 + up(W, n1) * row), by_row = double(up(W, m1) * bn * e + 128 + std::min(m1, W) * bm * e);
+    if (std::min(by_col, by_row) >= 0.75 * nat) return 0;
+    return by_col <= by_row ? 1 : 2;
+}
+
 // Members that cannot run without the few-channels template (a slab with too many staging registers, say) stay invalid:
 // which members of a space are valid does not depend on it.
 static bool valid_without_rows(const opevo_op &op, int variant, const int32_t *cfg)
@@ -906,6 +940,9 @@ int decode(const opevo_op &op, int variant, const int32_t *cfg, Decoded &out, bo
     if (ksplit > 1) D << " -DKSPLIT=" << ksplit;
     out.zero_bytes = ksplit > 1 ? op.c_elems() * 4 : 0;
     out.prepass = nhwc ? 1 : (b_kmajor && op.kind == OPEVO_MATMUL) ? 2 : 0;
+    if (extras && !linear && four_level && op.kind != OPEVO_CONV2D && ksplit == 1 && n_blocks < (int64_t(1) << 30))
+        if (const int walk = xcd_walk(op, n1, m1, b1, BM * subm, BN * subn, binner, lds > 0 ? kMaxLds / lds : 8))
+            D << " -DXCD_WALK=" << walk << " -DGRID_N1=" << n1 << " -DGRID_M1=" << m1 << " -DGRID_B1=" << b1;
     if (linear)
         D << " -DGRID_LINEAR=1 -DGRID_N1=" << n1 << " -DGRID_M1=" << m1 << " -DGRID_B1=" << b1 << " -DORDER0=" << order[0]
           << " -DORDER1=" << order[1] << " -DORDER2=" << order[2] << " -DGROUP=" << group;

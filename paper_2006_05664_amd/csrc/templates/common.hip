@@ -57,6 +57,8 @@ __device__ __forceinline__ float to_f32(in_t x) { return (float)__builtin_bit_ca
 // ORDER0 (fastest), ORDER1, ORDER2; GROUP consecutive tiles of axis ORDER1 are walked together:
 // a group goes through the whole of axis ORDER0 (second-axis index fastest inside the group)
 // before the next group starts; a ragged last group is narrower.
+// With XCD_WALK the grid is three-dimensional, but the workgroups of one XCD (every eighth) walk a contiguous eighth of the tiles, batch by
+// batch, columns (1) or rows (2) first: neighbours share operand panels, and cache lines, in that XCD's L2.
 struct BlockId { int n, m, b; };
 __device__ __forceinline__ BlockId block_id()
 {
@@ -74,6 +76,16 @@ __device__ __forceinline__ BlockId block_id()
     idx[ORDER1] = first + in_group % gsz;
     idx[ORDER2] = rest;
     id.n = idx[0]; id.m = idx[1]; id.b = idx[2];
+#elif defined(XCD_WALK)
+    constexpr int total = GRID_N1 * GRID_M1 * GRID_B1;
+    const int L = (blockIdx.z * GRID_M1 + blockIdx.y) * GRID_N1 + blockIdx.x, xcd = L % 8;
+    const int j = xcd * (total / 8) + min(xcd, total % 8) + L / 8, in = j % (GRID_N1 * GRID_M1);
+    id.b = j / (GRID_N1 * GRID_M1);
+#if XCD_WALK == 1
+    id.n = in % GRID_N1; id.m = in / GRID_N1;
+#else
+    id.m = in % GRID_M1; id.n = in / GRID_M1;
+#endif
 #else
     id.n = blockIdx.x; id.m = blockIdx.y; id.b = blockIdx.z;
 #endif
