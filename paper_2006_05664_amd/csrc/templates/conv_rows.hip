@@ -19,9 +19,10 @@
 //   * Taps past the kernel's width (and kernel rows past its height, where a step takes several) are zeros in the kernel tensor's
 //     fragments AND are cleared in the image's: what the patch holds there are other pixels, which may be infinite.
 // Measured: 512 x 3 x 227 x 227 * 64 x 3 x 11 x 11, stride 4, bf16 (boxes of 4 images x 55 pixels): 980 us on the register-staged template (73
-// TFLOP/s: some ten instructions per gathered value), 205 us here (350 TFLOP/s, 2.7 TB/s).  Its matrix work alone is about
-// 60 us and its bytes 115; the boxes' loads, multiplications and stores follow one another and overlap only through the
-// second workgroup of a compute unit.
+// TFLOP/s: some ten instructions per gathered value), 198 - 215 us here with the output stored column by column, 184 us row by row (390 TFLOP/s, 3.0
+// TB/s).  What bounds it: 396 MB of output in rows of 220 bytes that begin anywhere in a cache line (alone, without fill and
+// multiplication, 136 us column by column and 109 row by row; non-temporal stores take 386, a contiguous run of boxes per
+// workgroup 249), and that a box's load, multiplication and store follow one another, with two workgroups per compute unit.
 // PERSIST > 0: that many workgroups along the boxes, each taking several; the kernel tensor is then fetched once per workgroup.
 // Boxes are dealt so that the workgroups of one XCD (every eighth) walk one contiguous eighth of them: boxes one above the other share
 // HK - STRIDE of their image rows, through that XCD's L2.
@@ -82,6 +83,11 @@ __device__ __forceinline__ int div_rows(int row)
     if constexpr ((ROWS + RPP) * PH < (1 << 20) && ROWS + RPP <= 4095 && PH > 1) return (int)(((u32)row & 4095u) * ((1u << 20) / PH + 1) >> 20);
     return row / PH;
 }
+
+// a place in the output of a box's images
+template <bool SMALL> struct OutOff { typedef u32 type; };
+template <> struct OutOff<false> { typedef unsigned long type; };
+typedef OutOff<(unsigned long)NB2 * M * HOUT * WOUT * 4 < (1ul << 32)>::type out_off;
 
 // v shifted by sh elements towards element 0 (sh > 0) or away from it (sh < 0), zeros shifted in; 8 and more: all zeros
 __device__ __forceinline__ u32x4 shift_elements(u32x4 v, int sh)
@@ -252,19 +258,25 @@ void KERNEL_NAME(const u16 *__restrict__ A, const u16 *__restrict__ B, float *__
         }
         // an atom's result sits with column (l % ATOM) in lane l; 32x32: register r is row 8*(r/4) + 4*(l/32) + r%4;
         // 16x16: register r is row 4*(l/16) + r
+        // Row by row, all of a row's columns one after the other: the atoms of a row share cache lines (rows of 55 pixels begin anywhere in
+        // one), and a line that is completed at once is written to memory once (512 x 3 x 227 x 227 above, 396 MB of output: 214 us column by column, 184 so).
+        float *const out = C + (((long)cb.nb0 * M + m0 + wm * MI * ATOM) * HOUT + cb.y0) * WOUT + cb.x0;
+        out_off at[NI];                                    // byte offsets of the lane's columns, in its first row of an atom
+        bool on[NI];
 #pragma unroll
         for (int j = 0; j < NI; ++j) {
             const int cn = (wn * NI + j) * ATOM + lrow;
-            if (cn < BN) {
-                float *c = C + conv_c_index(cb, m0 + wm * MI * ATOM, cn);
-#pragma unroll
-                for (int i = 0; i < MI; ++i)
-#pragma unroll
-                    for (int r = 0; r < NACC; ++r) {
-                        const int row = i * ATOM + (ATOM == 32 ? 8 * (r / 4) + 4 * (lane / 32) + r % 4 : 4 * (lane / 16) + r);
-                        c[(long)row * (HOUT * WOUT)] = acc[i][j][r];
-                    }
-            }
+            on[j] = cn < BN;
+            at[j] = 4 * ((out_off)((cn / (BH * BW) * M + lane / ATOM * 4) * HOUT + cn / BW % BH) * WOUT + cn % BW);
         }
+#pragma unroll
+        for (int i = 0; i < MI; ++i)
+#pragma unroll
+            for (int r = 0; r < NACC; ++r) {
+                char *const row = (char *)(out + (long)(i * ATOM + 8 * (r / 4) + r % 4) * (HOUT * WOUT));
+#pragma unroll
+                for (int j = 0; j < NI; ++j)
+                    if (on[j]) *(float *)(row + at[j]) = acc[i][j][r];
+            }
     }
 }
