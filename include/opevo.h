@@ -210,7 +210,8 @@ typedef enum { OPEVO_F32 = 0, OPEVO_BF16 = 1, OPEVO_F16 = 2 } opevo_dtype;
  *         `order` (first = fastest varying); a DISCRETE parameter `group` in {1, 2, 4, 8, 16}
  *         is the number of consecutive tiles of the second axis that are walked together (each
  *         group goes through the whole first axis before the next group starts), which decides
- *         what the workgroups resident at one time share in L2.  Flat encoding: the TILE4 slots,
+ *         what the workgroups resident at one time share in L2.  (In the spaces without these two, the
+ *         workgroups of one L2 walk neighbouring tiles where that spares traffic.)  Flat encoding: the TILE4 slots,
  *         then the permutation (2 or 3 slots), then the index of the group width.
  *  TILE4P: Conv2d only, the space as App. B.3 lays it out: the reduction axes are split
  *         separately,
@@ -285,7 +286,10 @@ typedef enum { OPEVO_F32 = 0, OPEVO_BF16 = 1, OPEVO_F16 = 2 } opevo_dtype;
  *         through LDS after the last slab, in the order of the waves (deterministic).  The workgroup then has
  *         (waves along Cout) x (waves along the pixels) x kwaves waves; where it cannot hold them (16 waves, registers,
  *         LDS for the final sum) the member runs with kwaves = 1.  With kwaves = 1, workgroups of one or two waves that
- *         do not fill the chip run with two or four waves per tile. */
+ *         do not fill the chip run with two or four waves per tile.
+ *         Members of unit stride that ask for more than 16 waves, or for unroll = 0, kwaves = 1 and at least two waves
+ *         along the pixels, keep their workgroup tile but run it in wave tiles of whole rows of pixels where the rows fill
+ *         four of five lanes: slab length, waves and kwaves are then the library's choice (opevo_plan reports slab and threads). */
 typedef enum { OPEVO_TILE2 = 0, OPEVO_TILE4 = 1, OPEVO_TILE4X = 2, OPEVO_TILE4P = 3, OPEVO_TILE4K = 4, OPEVO_TILE4C = 5, OPEVO_TILE4T = 6,
                OPEVO_TILE4A = 7, OPEVO_TILE4L = 8 } opevo_variant;
 
@@ -370,8 +374,8 @@ int opevo_compile_pool_deadline(double seconds);
  * timing return OPEVO_E_INVALID: it would be slow, it would break the load counting of path 3,
  * and one spilling member of the register-staged template once gave wrong rows.  opevo_tune
  * scores both as invalid trials.  What a template does of its own accord (path 4's pipelined
- * loop, path 7, path 5's extra waves per tile, path 3's second group of waves) never makes a member spill: this call compiles
- * it a second time without, if the first code object does. */
+ * loop, path 7, path 5's extra waves per tile or rows of pixels, path 6's places kept from slab to slab, path 3's second
+ * group of waves) never makes a member spill: this call compiles it again without, if the first code object does. */
 int opevo_kernel_build(const opevo_op *op, int variant, const int32_t *cfg,
                        opevo_kernel **out, double *compile_ms);
 /* Compiling is by far the longest part of a trial (Sec. 6 gives it 8 CPU threads), and runs of

@@ -29,11 +29,11 @@ namespace opevo {
 
 struct Decoded {
     opevo_plan plan;
-    std::string tmpl;      // template name: "gemm_scalar" or "gemm_mfma"
+    std::string tmpl;      // template name (templates/<name>.hip)
     std::string defines;   // space separated -D options
     // Options to compile with beside `defines`, the best first: a build whose kernel spills with one goes on to the next.
     std::vector<std::string> tries = {""};
-    bool extra_waves = false;   // more waves share a wave tile, or the reduction, than the configuration asks for
+    bool extra_waves = false;   // divided among the waves otherwise than the configuration asks for, with an option that extras = false leaves out
     std::string kernel_name;   // symbol of the instantiated kernel
     int64_t zero_bytes = 0;    // bytes of the output the host clears before every launch (split reduction), else 0
     // pre-pass before every launch: 0 none; 1 Conv2d: the kernel reads channels-last copies of both operands;
@@ -42,8 +42,8 @@ struct Decoded {
 };
 
 // OPEVO_OK (plan.status says valid/invalid) or OPEVO_E_ILLEGAL / OPEVO_E_ARG.
-// extras = false: without the few-channels convolution template and without waves that a patch or direct-to-LDS member did not ask for (a
-// member that turned out to spill with them).
+// extras = false: without the few-channels and the row-strip convolution templates, without waves that a patch or direct-to-LDS member did not
+// ask for, and with the grid's natural order (a member that turned out to spill with them).
 int decode(const opevo_op &op, int variant, const int32_t *cfg, Decoded &out, bool extras = true);
 int op_param_descs(const opevo_op &op, int variant, std::vector<opevo_param_desc> &descs);
 
