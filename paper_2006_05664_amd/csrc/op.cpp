@@ -935,6 +935,12 @@ int decode(const opevo_op &op, int variant, const int32_t *cfg, Decoded &out, bo
         if (BKP == 8 && (op.kind == OPEVO_CONV2D || (full_chip && ksteps * BKP <= 128))) out.tries = {" -DSTEP_READS=1", " -DPIPELINED=1", ""};
         else if (!(full_chip && ksteps < 8)) out.tries = {" -DPIPELINED=1", ""};
     }
+    // fp32, short reductions: outputs that the eight L2s (32 MiB) would hold and write back when the kernel ends are stored past them.  44 further
+    // MatMul / BMM members of K <= 224 with outputs of 2 - 32 MiB, drawn after the rule was made, 1.00 - 1.28x, 1.04x in the geometric mean (727 x (128 x 64 x 64)
+    // 16.1 -> 13.1 us, 448 x 2112 x 192 6.87 -> 6.64); smaller outputs 0.96 - 1.06x, larger ones 0.95 - 1.07x, K of 256 to 6208 0.91 - 1.02x (mostly 1.00).  Rows of 64 or of any number of bytes (16-bit
+    // inputs on 16 x 16 atoms, ragged tiles) 0.59 - 1.20x without a line between them: those stay with ordinary stores.
+    const int64_t out_bytes = op.c_elems() * 4;
+    if (path == 4 && op.kind != OPEVO_CONV2D && ksplit == 1 && op.K <= 224 && out_bytes >= (int64_t(2) << 20) && out_bytes <= (int64_t(32) << 20)) D << " -DNT_OUT=1";
     if (kgrp > 1) D << " -DKGRP=" << kgrp;
     if (kunroll) D << " -DKUNROLL=" << kunroll;
     if (ksplit > 1) D << " -DKSPLIT=" << ksplit;

@@ -31,6 +31,9 @@ typedef f32x16 acc_t;
 #ifndef STEP_READS
 #define STEP_READS 0
 #endif
+#ifndef NT_OUT
+#define NT_OUT 0   // 1: a half wave's 32 columns are one whole cache line, stored past the L2 (which would write it back when the kernel ends)
+#endif
 #ifndef BKP
 #define BKP BK
 #endif
@@ -356,6 +359,8 @@ void KERNEL_NAME(const float *__restrict__ A, const float *__restrict__ B, float
                     // the overhang of a rounded-up wave tile is not stored
                     if ((TM % 32 == 0 || row < TM) && (TN % 32 == 0 || col < TN))
                         c_out(&C[conv_c_index(cb, m0 + wm * TM + row, wn * TN + col)], acc[i][j][r]);
+#elif NT_OUT
+                    __builtin_nontemporal_store(acc[i][j][r], &Cb[(long)(m0 + wm * TM + row) * N + n0 + wn * TN + col]);
 #else
                     c_out(&Cb[(long)(m0 + wm * TM + row) * N + n0 + wn * TN + col], acc[i][j][r]);
 #endif
