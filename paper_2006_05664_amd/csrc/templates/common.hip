@@ -155,4 +155,12 @@ __device__ __forceinline__ long conv_c_index(const ColBlock &cb, int m, int c)
     const int x = cb.x0 + c % BW;
     return (((long)nb * M + m) * HOUT + y) * WOUT + x;
 }
+// Byte offset of row m, column c of a box from its row 0, column 0: 32 bits where a box's images have less than 4 GiB of output
+template <bool SMALL> struct OutOff { typedef u32 type; };
+template <> struct OutOff<false> { typedef unsigned long type; };
+typedef OutOff<(unsigned long)NB2 * M * HOUT * WOUT * 4 < (1ul << 32)>::type out_off;
+__device__ __forceinline__ out_off conv_c_offset(int m, int c)
+{
+    return 4 * ((((out_off)(c / (BH * BW)) * M + m) * HOUT + c / BW % BH) * WOUT + c % BW);
+}
 #endif

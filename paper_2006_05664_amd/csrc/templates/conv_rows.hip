@@ -84,11 +84,6 @@ __device__ __forceinline__ int div_rows(int row)
     return row / PH;
 }
 
-// a place in the output of a box's images
-template <bool SMALL> struct OutOff { typedef u32 type; };
-template <> struct OutOff<false> { typedef unsigned long type; };
-typedef OutOff<(unsigned long)NB2 * M * HOUT * WOUT * 4 < (1ul << 32)>::type out_off;
-
 // v shifted by sh elements towards element 0 (sh > 0) or away from it (sh < 0), zeros shifted in; 8 and more: all zeros
 __device__ __forceinline__ u32x4 shift_elements(u32x4 v, int sh)
 {
@@ -267,7 +262,7 @@ void KERNEL_NAME(const u16 *__restrict__ A, const u16 *__restrict__ B, float *__
         for (int j = 0; j < NI; ++j) {
             const int cn = (wn * NI + j) * ATOM + lrow;
             on[j] = cn < BN;
-            at[j] = 4 * ((out_off)((cn / (BH * BW) * M + lane / ATOM * 4) * HOUT + cn / BW % BH) * WOUT + cn % BW);
+            at[j] = conv_c_offset(lane / ATOM * 4, cn);
         }
 #pragma unroll
         for (int i = 0; i < MI; ++i)

@@ -2,12 +2,14 @@
 groups of 8): every global load lies inside its tensor, every LDS store and fragment read inside the patch and aligned for its
 width, boxes are covered once, taps past the kernel are cleared whatever the patch holds there, and the sums the
 fragments form are the convolution (direct convolution of integer data, exact) -- for every workgroup, wave, lane, column and step."""
+import ctypes
 import re
 
 import numpy as np
 import pytest
 
 import paper_2006_05664_amd as P
+from host_code import compile_common
 
 V4, V4C, V4L, V4P, V4X = P.OPEVO_TILE4, P.OPEVO_TILE4C, P.OPEVO_TILE4L, P.OPEVO_TILE4P, P.OPEVO_TILE4X
 CASES = [   # label, dims (B Cin H W Cout Hk Wk stride pad), space, configuration
@@ -158,6 +160,31 @@ def test_boxes_dealt_to_persistent_workgroups_are_covered_once():
             for box in range(w % 8 * per + w // 8, last, persist // 8):
                 seen[box] += 1
         assert np.all(seen == 1), (nbox, persist)
+
+
+PLACES = [CASES[0], CASES[1],
+          ("eight images of 17 GB of output in a box", (8, 1, 32772, 8, 32768, 5, 5, 1, 0), V4C,
+           [1, 8, 512, 2, 1, 32, 32768, 1, 1, 1, 1, 1, 4, 1, 1, 1, 25, 0, 0]),
+          ("just below 4 GiB of outputs a box", (7, 1, 3102, 16, 4096, 3, 3, 1, 0), V4, [1, 7, 64, 2, 1, 32, 775, 1, 4, 1, 1, 1, 14, 1, 1, 9, 0])]
+
+
+@pytest.mark.parametrize("label,dims,variant,cfg", PLACES, ids=[c[0] for c in PLACES])
+def test_a_column_s_place_in_the_output(label, dims, variant, cfg):
+    """The offset the template stores at, as it is compiled, against the 64-bit index of every (row, column) of a box that begins or ends a range."""
+    op = P.opevo_op_create(P.OPEVO_CONV2D, dims, P.OPEVO_BF16)
+    plan = P.opevo_kernel_plan(op, variant, cfg)
+    assert plan.status == P.OPEVO_OK and plan.path == 7, (plan.path, plan.reason)
+    _, D = _defs(op, variant, cfg)
+    lib = compile_common(P.opevo_kernel_defines(op, variant, cfg), """
+extern "C" unsigned long offset(int m, int c) { return conv_c_offset(m, c); }
+extern "C" long wanted(int m, int c) { const ColBlock cb = {0, 0, 0}; return 4 * (conv_c_index(cb, m, c) - conv_c_index(cb, 0, 0)); }
+""")
+    lib.offset.restype, lib.wanted.restype = ctypes.c_ulong, ctypes.c_long
+    box = D["BH"] * D["BW"]
+    columns = {b * box + y * D["BW"] + x for b in range(D["NB2"]) for y in {0, D["BH"] - 1} for x in {0, D["BW"] - 1}}
+    for c in columns:
+        for m in (0, 1, 4, 28):
+            assert lib.offset(m, c) == lib.wanted(m, c), (m, c)
 
 
 def test_which_members_take_the_few_channels_template():
