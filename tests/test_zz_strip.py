@@ -23,6 +23,12 @@ CASES = [   # label, dims (B, Cin, H, W, Cout, Hk, Wk, stride, pad), dtype, conf
     ("1x1, two rows a wave", (4, 64, 14, 14, 64, 1, 1, 1, 0), "bf16", [4, 1, 1, 2, 1, 32, 1, 7, 2, 1, 1, 1, 14, 1, 4, 16, 0, 2, 0], dict(CS=64)),
     ("3x3 without padding, wider image than output", (2, 32, 16, 16, 64, 3, 3, 1, 0), "bf16", [2, 1, 1, 2, 1, 32, 1, 7, 2, 1, 1, 1, 14, 1, 2, 16, 0, 2, 0], dict(ATOM=16)),
     ("1x9, 48 output channels", (2, 32, 8, 36, 48, 1, 9, 1, 0), "bf16", [2, 1, 1, 3, 1, 16, 1, 8, 1, 1, 1, 1, 28, 1, 1, 32, 0, 2, 0], dict(WM=3)),
+    ("3x3, two waves share a tile of seven atoms: the final sum in passes of six and one", (2, 256, 14, 14, 64, 3, 3, 1, 1), "bf16",
+     [1, 2, 2, 2, 1, 16, 1, 7, 2, 1, 1, 1, 1, 14, 8, 32, 1, 2, 1], dict(KW=2, MI=1, R=7, LDS_BYTES=103424)),
+    ("3x3, odd width, three waves, nine atoms in three passes of three", (2, 64, 27, 27, 32, 3, 3, 1, 1), "f16",
+     [2, 1, 1, 4, 1, 8, 3, 1, 3, 3, 1, 9, 1, 3, 32, 2, 0, 2, 1], dict(KW=3, R=9, LDS_BYTES=41984)),
+    ("3x3, six waves, fourteen atoms in passes of five", (2, 128, 14, 14, 32, 3, 3, 1, 1), "bf16",
+     [2, 1, 1, 1, 32, 1, 1, 7, 1, 2, 1, 14, 1, 1, 32, 4, 1, 2, 3], dict(KW=6, LDS_BYTES=70656)),
     ("5x3, 12 columns of 14 pixels", (2, 32, 12, 14, 48, 5, 3, 1, 1), "bf16", [2, 1, 1, 3, 1, 16, 1, 2, 5, 1, 1, 1, 14, 1, 1, 32, 0, 2, 0], dict(WM=3, R=2)),
 ]
 # members of the same space that keep the patch template
@@ -37,6 +43,36 @@ STAY = [
 def _defs(op, cfg):
     tmpl, rest = P.opevo_kernel_defines(op, V, cfg).split(":", 1)
     return tmpl, {m.group(1): int(m.group(2)) for m in (re.match(r"-D(\w+)=(-?\d+)$", t) for t in rest.split()) if m}
+
+
+def _final_sum(D):
+    """The partial sums of KW waves by way of LDS: every place lies inside it, a pass reads what it wrote, every atom is stored once.  Returns the
+    atoms a pass takes and those a wave has."""
+    Q, atoms, tiles, KW = (4 if D["ATOM"] == 32 else 1), D["MI"] * D["R"], D["WM"] * D["WN"], D["KW"]
+    waves = tiles * KW
+    per_pass = min(D["LDS_BYTES"] // (waves * Q * 1024), atoms)
+    assert per_pass >= 1
+    lane = np.arange(64)
+    stored = np.zeros((tiles, atoms), dtype=int)
+    for a0 in range(0, atoms, per_pass):
+        held = np.full(D["LDS_BYTES"] // 16, -1, dtype=np.int64)        # who wrote a place in this pass: ((wave, atom), quarter, lane)
+        name = lambda wave, a, q: ((wave * atoms + a) * Q + q) * 64 + lane
+        here = range(a0, min(a0 + per_pass, atoms))
+        for wave in range(waves):
+            for a in here:
+                for q in range(Q):
+                    at = (((a - a0) * waves + wave) * Q + q) * 64 + lane
+                    assert (at < held.size).all() and (held[at] == -1).all()
+                    held[at] = name(wave, a, q)
+        for wave in range(waves):
+            wk, tile = wave // tiles, wave % tiles
+            for a in range(a0 + wk, here.stop, KW):
+                stored[tile, a] += 1
+                for q in range(Q):
+                    for k in range(KW):
+                        assert (held[(((a - a0) * waves + k * tiles + tile) * Q + q) * 64 + lane] == name(k * tiles + tile, a, q)).all()
+    assert (stored == 1).all()
+    return per_pass, atoms
 
 
 def _emulate(dims, cfg, img=None, ker=None, blocks=None):
@@ -57,6 +93,8 @@ def _emulate(dims, cfg, img=None, ker=None, blocks=None):
     assert (STAGE + 512) * 2 <= D["LDS_BYTES"] == plan.lds_bytes <= 160 * 1024 and MI * R * NACC == plan.acc_per_lane <= 256
     assert plan.grid[0] * NB2 * BH * BW == nimg * HOUT * WOUT and plan.grid[1] * BM == cout and plan.grid[2] == 1
     aligned = win % 2 == 0
+    if KW > 1:
+        _final_sum(D)
 
     def swz(p):
         if NCH == 16:
@@ -199,6 +237,16 @@ def test_the_template_computes_the_convolution(label, dims, dtype, cfg, want):
     else:
         _, written = _emulate(dims, cfg)
         assert (written == 1).all()
+
+
+def test_final_sums_of_one_and_of_several_passes():
+    passes = set()
+    for label, dims, dtype, cfg, _ in CASES:
+        _, D = _defs(P.opevo_op_create(P.OPEVO_CONV2D, dims, synth.DTYPE_CODE[dtype]), cfg)
+        if D["KW"] > 1:
+            per_pass, atoms = _final_sum(D)
+            passes.add("one" if per_pass == atoms else "even" if atoms % per_pass == 0 else "uneven")
+    assert passes == {"one", "even", "uneven"}
 
 
 @pytest.mark.parametrize("label,dims,cfg", STAY, ids=[c[0] for c in STAY])
