@@ -35,6 +35,8 @@ typedef __attribute__((ext_vector_type(8))) _Float16 frag_t;
 #define KEEP 0
 #undef DEPTH
 #define DEPTH 1
+#undef MINW   // nothing of a plan for a second workgroup's registers holds
+#define MINW ((NT / 64 + 3) / 4)
 #endif
 typedef u32x4 __attribute__((aligned(2))) u32x4_a2;
 typedef __attribute__((ext_vector_type(4))) short v4s;
