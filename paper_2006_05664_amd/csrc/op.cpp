@@ -223,8 +223,11 @@ static bool plan_ragged(const opevo_op &op, int64_t bm, int64_t bn, int64_t bk, 
     const int64_t waves = std::max((nw + 3) / 4, std::min<int64_t>(2, (nw * fit + 3) / 4));
     const int64_t rest = held / 4 * 3 + 4 * out.mi * out.ni + 8 * (out.mi + out.ni) + 48;
     out.depth = out.stages == 2 && wgs <= 256 && out.slabs >= 16 && 2 * held + rest <= 512 / waves ? 2 : 1;
-    out.keep = out.slabs > 1 && out.depth * held + rest <= 512 / waves;
-    out.min_waves = int(out.keep ? waves : (nw + 3) / 4);
+    // (2: up to 15 % over, where the compiler fits most of them all the same, is for it to say.  19 such members, two stages, 1.12 to 1.38 times as fast with kept
+    // places as without, all 19 within the registers: 1620 x 252 x 1419, 4 x 3 atoms, 68.5 -> 51.4 us; 760 x 594 x 513, 6 x 5 atoms, 30.2 -> 27.0.)
+    const int64_t need = out.depth * held + rest, have = 512 / waves;
+    out.keep = out.slabs < 2 || 20 * need > 23 * have ? 0 : need > have ? 2 : 1;
+    out.min_waves = int(out.keep == 1 ? waves : (nw + 3) / 4);
     return true;
 }
 
@@ -891,7 +894,7 @@ int decode(const opevo_op &op, int variant, const int32_t *cfg, Decoded &out, bo
         if (nwr != WM * WN && path != 5) D << " -DNWR=" << nwr;
     }
     if (path == 7) D << " -DWKP=" << rows.wkp << " -DMI=" << rows.mi << " -DNI=" << rows.ni << " -DLDS_BYTES=" << lds << " -DPERSIST=" << rows.persist << " -DNBOX=" << n1;
-    if (path == 6) D << " -DKS=" << rg.ks << " -DNSL=" << rg.slabs << " -DMI=" << rg.mi << " -DNI=" << rg.ni << " -DLDS_BYTES=" << lds << " -DDEPTH=" << rg.depth << " -DKEEP=" << rg.keep << " -DMINW=" << rg.min_waves;
+    if (path == 6) D << " -DKS=" << rg.ks << " -DNSL=" << rg.slabs << " -DMI=" << rg.mi << " -DNI=" << rg.ni << " -DLDS_BYTES=" << lds << " -DDEPTH=" << rg.depth << " -DMINW=" << rg.min_waves;
     if (subm * subn > 1) {
         D << " -DSUBM=" << subm << " -DSUBN=" << subn;
     }
@@ -917,6 +920,15 @@ int decode(const opevo_op &op, int variant, const int32_t *cfg, Decoded &out, bo
     else if (path == 5) D << " -DCS=" << patch_cs << " -DPWP=" << patch_row << " -DIPIX=" << patch_image << " -DKW=" << patch_kw << " -DLDS_BYTES=" << lds;
     if (b_kmajor) D << " -DB_KMAJOR=1 -DBNR=" << bnr;
     if (path == 3 && anr != BM) D << " -DANR=" << anr;
+    // ragged: the places of pieces kept where they fit, or may fit; else worked out where they are needed, for every slab anew if the kernel spills
+    // otherwise (one in 100 members; transposed first operands on eight waves of 3 x 7 to 3 x 9 atoms always do)
+    if (path == 6) {
+        const bool spills = op.trans_a && rg.keep != 1 && rg.wm * rg.wn >= 8 && rg.mi >= 3 && rg.mi * rg.ni >= 20;
+        out.tries.clear();
+        if (rg.keep == 1 || (rg.keep == 2 && !spills)) out.tries.push_back(" -DKEEP=1");
+        if (rg.keep != 1 && !spills) out.tries.push_back(" -DKEEP=0");
+        out.tries.push_back(" -DKEEP=0 -DFRESH=1");
+    }
     // fp32, two stages: the pipelined slab loop, but for short reductions on a full chip, where the other workgroups cover a
     // slab's latency and the registers are better spent on them (a batch of 960 of 128 x 64 x 128 with the first operand transposed:
     // 960 x 4 waves, 4 slabs, 27.0 us without and 29.9 with; 132 x 64 x 224 x 128, 924 x 2 waves, 2 slabs, 16.2 and 13.9).  Against the
@@ -926,10 +938,6 @@ int decode(const opevo_op &op, int variant, const int32_t *cfg, Decoded &out, bo
     // reductions on a full chip have the plain loop with the second operand read step by step (8 x 64 x 28 x 28 * 64 x 64 x 3 x 3 as 112 x 1 waves 77.5 us so and
     // 82.0 pipelined, as 112 x 7 waves 54.8 and 61.1, on slabs of 2 as 32 x 1 waves 1020 and 1139; 2048 x 2048 x 128, 1024 x 2 waves, 15.7 and 17.5; four other
     // convolutions between 0.7 % slower and 2 % faster).
-    // ragged: where the places of pieces are not kept, they are worked out anew for every slab if the kernel spills otherwise (one in 100 members;
-    // transposed first operands on eight waves of 3 x 7 to 3 x 9 atoms always do)
-    if (path == 6 && op.trans_a && !rg.keep && rg.wm * rg.wn >= 8 && rg.mi >= 3 && rg.mi * rg.ni >= 20) out.tries = {" -DFRESH=1"};
-    else if (path == 6) out.tries = {"", " -DFRESH=1"};
     if (path == 4 && nstage == 2) {
         const bool full_chip = n_blocks * nwr >= 2048;
         if (BKP == 8 && (op.kind == OPEVO_CONV2D || (full_chip && ksteps * BKP <= 128))) out.tries = {" -DSTEP_READS=1", " -DPIPELINED=1", ""};

@@ -30,13 +30,19 @@ typedef __attribute__((ext_vector_type(8))) __bf16 frag_t;
 typedef __attribute__((ext_vector_type(8))) _Float16 frag_t;
 #define MFMA(a, b, c) __builtin_amdgcn_mfma_f32_16x16x32_f16(a, b, c, 0, 0, 0)
 #endif
-#ifdef FRESH
-#undef KEEP
-#define KEEP 0
+#if !KEEP   // nothing of a plan for two slabs under way, or for a second workgroup's registers, holds
 #undef DEPTH
 #define DEPTH 1
-#undef MINW   // nothing of a plan for a second workgroup's registers holds
+#undef MINW
 #define MINW ((NT / 64 + 3) / 4)
+#endif
+// Two stages without kept places (and not FRESH), mostly pieces of k rows: each is placed where it is loaded and where it is stored.  With the choice between
+// two places per piece and the shift decided before, which serve kept ones, the compiler made several branches of every such piece (420 x 2295 x 2400 in 70 x 459,
+// eight waves of 5 x 6 atoms, 134 us against 127; 312 x 950 x 1875 in 26 x 950, 1 x 15 atoms, 94 against 85; with 7 x 2 and 13 x 2 atoms 65 against 79, 46 against 50).
+#if !KEEP && NSTG == 2 && !defined(FRESH) && NI > MI && !A_TRANS
+#define RECALC 1
+#else
+#define RECALC 0
 #endif
 typedef u32x4 __attribute__((aligned(2))) u32x4_a2;
 typedef __attribute__((ext_vector_type(4))) short v4s;
@@ -124,6 +130,66 @@ __device__ __forceinline__ void plan_slab(Plan &p, int m0, int n0, int tid)
     plan_kr<NB, B_PIECES, N, CN, LDN>(p.b, n0, tid);
 }
 
+// Pieces of k rows are shifted where they were loaded from further left to end with their row, in tiles that reach the row's end (and, with tiles of 2 and
+// 3, also in the ones before it: 8 past the start of a tile is then more than two tiles on; whole multiples of 8 never are).
+constexpr bool edge_tile(int tile, int x0, int len) { return tile % 8 != 0 && ((tile + 7) / 8 * 8 > 2 * tile || x0 + tile == len); }
+
+#if RECALC
+// k-contiguous operand: piece q of a slab that starts at reduction position k0
+__device__ __forceinline__ u32x4 load_kc(const u16 *__restrict__ base, int q, int k0)
+{
+    const int row = q / CK, k = k0 + q % CK * 8;
+    return *(const u32x4_a2 *)(base + (u32)(row * K + (K_TAIL ? min(k, KPART - 8) : k)));
+}
+__device__ __forceinline__ void store_kc(u16 *S, u32x4 v, int q, int k0, bool last)
+{
+    const int c = q % CK;
+    if (K_TAIL && last) v = shift_down(v, max(k0 + c * 8 - (KPART - 8), 0));
+    *(u32x4 *)(S + q / CK * LDK + c * 8) = v;
+}
+// operand of k rows: LEN elements of a row in memory, of which the tile's begin at x0; C pieces per row
+template <int LEN, int C>
+__device__ __forceinline__ u32x4 load_kr(const u16 *__restrict__ base, int q, int k0, int x0)
+{
+    const int k = k0 + q / C;
+    return *(const u32x4_a2 *)(base + (u32)((K_TAIL ? min(k, KPART - 1) : k) * LEN + min(x0 + q % C * 8, LEN - 8)));
+}
+template <int LEN, int C, int LD, int TILE>
+__device__ __forceinline__ void store_kr(u16 *S, u32x4 v, int q, int k0, int x0, bool last)
+{
+    const int kr = q / C, x = q % C * 8;
+    if (edge_tile(TILE, x0, LEN)) v = shift_down(v, max(x0 + x - (LEN - 8), 0));
+    if (K_TAIL && last && k0 + kr >= KPART) { const u32x4 z = {0u, 0u, 0u, 0u}; v = z; }
+    *(u32x4 *)(S + kr_off(LD, kr) + x) = v;
+}
+__device__ __forceinline__ void load_slab(Slab &s, const Plan &, const u16 *__restrict__ Ab, const u16 *__restrict__ Bb, int j, bool, int m0, int n0, int tid)
+{
+#pragma unroll
+    for (int i = 0; i < NA; ++i) {
+        const int q = tid + i * NT;
+        if (A_PIECES % NT == 0 || q < A_PIECES) s.a[i] = load_kc(Ab, q, j * KS);
+    }
+#pragma unroll
+    for (int i = 0; i < NB; ++i) {
+        const int q = tid + i * NT;
+        if (B_PIECES % NT == 0 || q < B_PIECES) s.b[i] = load_kr<N, CN>(Bb, q, j * KS, n0);
+    }
+}
+__device__ __forceinline__ void store_slab(const Slab &s, int j, u16 *As, u16 *Bs, int m0, int n0, int tid)
+{
+    const bool last = j == NSL - 1;
+#pragma unroll
+    for (int i = 0; i < NA; ++i) {
+        const int q = tid + i * NT;
+        if (A_PIECES % NT == 0 || q < A_PIECES) store_kc(As, s.a[i], q, j * KS, last);
+    }
+#pragma unroll
+    for (int i = 0; i < NB; ++i) {
+        const int q = tid + i * NT;
+        if (B_PIECES % NT == 0 || q < B_PIECES) store_kr<N, CN, LDN, BN>(Bs, s.b[i], q, j * KS, n0, last);
+    }
+}
+#else
 // slab j of the operands; last: it is the last one.  (A thread without an i-th piece loads its operand's first.)
 __device__ __forceinline__ void load_slab(Slab &s, const Plan &kept, const u16 *__restrict__ Ab, const u16 *__restrict__ Bb, int j, bool last, int m0, int n0, int tid)
 {
@@ -149,9 +215,6 @@ __device__ __forceinline__ void load_slab(Slab &s, const Plan &kept, const u16 *
     }
 }
 
-// Pieces of k rows are shifted where they were loaded from further left to end with their row, in tiles that reach the row's end (and, with tiles of 2 and
-// 3, also in the ones before it: 8 past the start of a tile is then more than two tiles on; whole multiples of 8 never are).
-constexpr bool edge_tile(int tile, int x0, int len) { return tile % 8 != 0 && ((tile + 7) / 8 * 8 > 2 * tile || x0 + tile == len); }
 template <int N_, int PIECES, int LEN, int C>
 __device__ __forceinline__ void store_kr(u16 *S, const u32x4 (&r)[N_], const Pieces<N_> &p, bool last, bool edge, int x0, int tid)
 {
@@ -182,6 +245,7 @@ __device__ __forceinline__ void store_slab(const Slab &s, const Plan &kept, u16 
 #endif
     store_kr<NB, B_PIECES, N, CN>(Bs, s.b, p.b, last, edge_b, n0, tid);
 }
+#endif
 
 // Fragment of an atom whose first row / column is x0, K step kk.  Lane l supplies row or column l % 16, the 8 reduction
 // values from 8 * (l / 16).
@@ -232,7 +296,11 @@ __device__ __forceinline__ void walk(f32x4 (&acc)[MI][NI], const Plan &plan, con
         if (j < NSL) load_slab(slab[d], plan, Ab, Bb, j, j == NSL - 1, m0, n0, tid);
     };
     auto store = [&](int j, int d, int stage) {
+#if RECALC
+        if (j < NSL) store_slab(slab[d], j, As + stage * A_STAGE, Bs + stage * B_STAGE, m0, n0, tid);
+#else
         if (j < NSL) store_slab(slab[d], plan, As + stage * A_STAGE, Bs + stage * B_STAGE, j == NSL - 1, edge_a, edge_b, m0, n0, tid);
+#endif
     };
     auto compute = [&](int stage) { compute_slab(acc, As + stage * A_STAGE, Bs + stage * B_STAGE, wm, wn, lane); };
 #if NSTG == 2
