@@ -82,18 +82,21 @@ int build_kernel(const opevo_op &op, int variant, const int32_t *cfg, opevo_kern
         if (!cached) code_cache_put(key, r.code);
         return true;
     };
-    const std::string plain = d.defines;
-    for (size_t i = 0; i < d.tries.size(); ++i) {
-        if (i > 0 && !spills()) break;
-        compile(plain + d.tries[i]);
-    }
+    auto compile_tries = [&]() {
+        const std::string plain = d.defines;
+        for (size_t i = 0; i < d.tries.size(); ++i) {
+            if (i > 0 && !spills()) break;
+            compile(plain + d.tries[i]);
+        }
+    };
+    compile_tries();
     if ((d.plan.path == 7 || d.extra_waves) && spills()) {
         // the few-channels template keeps the kernel tensor in registers, and waves that share a tile need some for the
         // final sum, as two groups of them do that share a reduction: a member whose estimate was too low runs as it would without them
         d = Decoded();
         if (int rc = decode(op, variant, cfg, d, false)) return rc;
         if (d.plan.status != OPEVO_OK) return fail(OPEVO_E_INVALID, "invalid configuration: %s", d.plan.reason);
-        compile(std::string(d.defines));
+        compile_tries();
     }
     if (r.status == OPEVO_E_INVALID)
         return fail(r.status, "invalid configuration: %s [%s]", r.log.c_str(), d.kernel_name.c_str());

@@ -954,9 +954,18 @@ int decode(const opevo_op &op, int variant, const int32_t *cfg, Decoded &out, bo
     if (ksplit > 1) D << " -DKSPLIT=" << ksplit;
     out.zero_bytes = ksplit > 1 ? op.c_elems() * 4 : 0;
     out.prepass = nhwc ? 1 : (b_kmajor && op.kind == OPEVO_MATMUL) ? 2 : 0;
-    if (extras && !linear && four_level && op.kind != OPEVO_CONV2D && ksplit == 1 && n_blocks < (int64_t(1) << 30))
-        if (const int walk = xcd_walk(op, n1, m1, b1, BM * subm, BN * subn, binner, lds > 0 ? kMaxLds / lds : 8))
-            D << " -DXCD_WALK=" << walk << " -DGRID_N1=" << n1 << " -DGRID_M1=" << m1 << " -DGRID_B1=" << b1;
+    std::string walked;
+    if (!linear && four_level && op.kind != OPEVO_CONV2D && ksplit == 1 && n_blocks < (int64_t(1) << 30))
+        if (const int walk = xcd_walk(op, n1, m1, b1, BM * subm, BN * subn, binner, lds > 0 ? kMaxLds / lds : 8)) {
+            std::ostringstream W;
+            W << " -DXCD_WALK=" << walk << " -DGRID_N1=" << n1 << " -DGRID_M1=" << m1 << " -DGRID_B1=" << b1;
+            walked = W.str();
+        }
+    if (!walked.empty()) {   // a member that spills with the walk, whatever else is tried, is built in the natural order
+        const std::vector<std::string> natural = out.tries;
+        for (std::string &t : out.tries) t += walked;
+        out.tries.insert(out.tries.end(), natural.begin(), natural.end());
+    }
     if (linear)
         D << " -DGRID_LINEAR=1 -DGRID_N1=" << n1 << " -DGRID_M1=" << m1 << " -DGRID_B1=" << b1 << " -DORDER0=" << order[0]
           << " -DORDER1=" << order[1] << " -DORDER2=" << order[2] << " -DGROUP=" << group;
