@@ -959,6 +959,11 @@ int decode(const opevo_op &op, int variant, const int32_t *cfg, Decoded &out, bo
         if (const int walk = xcd_walk(op, n1, m1, b1, BM * subm, BN * subn, binner, lds > 0 ? kMaxLds / lds : 8)) {
             std::ostringstream W;
             W << " -DXCD_WALK=" << walk << " -DGRID_N1=" << n1 << " -DGRID_M1=" << m1 << " -DGRID_B1=" << b1;
+            // A single row of tiles is number 0, which the natural order's code does not know.  Members that read their fragments straight from global memory,
+            // several batches a workgroup, in 9 to 15 steps stand where it decides whether the compiler unrolls all steps; unrolled over two batches every
+            // load was waited for by itself (64, 100, 190, 512 x (128 x 128 x 192) in 128 x 32 8.3, 12.2, 17.4, 31.7 us in the natural order, 14.0, 14.5,
+            // 18.1, 36.3 walked, 8.5, 8.8, 12.3, 23.2 walked without that knowledge; with one batch a workgroup, or on 16-row atoms, it is a gain).
+            if (path == 1 && !stage_lds && binner > 1 && m1 == 1 && op.K / 16 > 8 && op.K / 16 < 16) W << " -DROW_UNKNOWN=1";
             walked = W.str();
         }
     if (!walked.empty()) {   // a member that spills with the walk, whatever else is tried, is built in the natural order

@@ -86,6 +86,9 @@ __device__ __forceinline__ BlockId block_id()
 #else
     id.m = in % GRID_M1; id.n = in / GRID_M1;
 #endif
+#ifdef ROW_UNKNOWN
+    id.m = blockIdx.y;   // zero, which the compiler is not to know (the host says where)
+#endif
 #else
     id.n = blockIdx.x; id.m = blockIdx.y; id.b = blockIdx.z;
 #endif

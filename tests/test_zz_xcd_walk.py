@@ -41,6 +41,12 @@ extern "C" void tiles(int *out)
         assert (np.diff(j[x::8]) == 1).all()
 
 
+def test_a_row_that_the_compiler_is_not_to_know_is_row_zero():
+    lib = compile_common("-DOP=1 -DIN_DTYPE=1 -DXCD_WALK=1 -DROW_UNKNOWN=1 -DGRID_N1=4 -DGRID_M1=1 -DGRID_B1=32",
+                         'extern "C" int row(int x, int z) { blockIdx.x = x; blockIdx.y = 0; blockIdx.z = z; return block_id().m; }')
+    assert {lib.row(x, z) for x in range(4) for z in range(32)} == {0}
+
+
 CASES = [   # label, kind, dims, dtype, configuration, walk
     ("batches of 5 tiles, 18 MB of operands", P.OPEVO_BMM_TA, (506, 128, 160, 160), "bf16", [506, 1, 1, 2, 1, 64, 5, 1, 1, 32, 5, 32, 1], 1),
     ("fp32 batches of 4 tiles", P.OPEVO_BMM, (330, 64, 256, 64), "f32", [330, 1, 1, 2, 1, 32, 4, 2, 1, 32, 1, 64, 1], 1),
@@ -67,11 +73,12 @@ def test_split_reductions_and_chosen_launch_orders_keep_their_own():
     assert _walk(P.OPEVO_MATMUL, (2496, 7072, 6848), "bf16", [39, 1, 2, 32, 221, 1, 1, 32, 214, 32, 1, 0, 1, 0], P.OPEVO_TILE4X)[2] == 0
 
 
-def test_which_paths_walk():
+def test_which_paths_walk_and_where_the_row_is_kept_from_the_compiler():
     walking = [(_walk(kind, dims, dtype, cfg)[0:2], label, cfg) for label, kind, dims, dtype, cfg, walk in CASES if walk]
     assert {plan.path for (_, plan), _, _ in walking} >= {0, 1, 2, 3, 4, 6}
     for (op, plan), label, cfg in walking:
         d = P.opevo_kernel_defines(op, P.OPEVO_TILE4, cfg)
+        assert ("ROW_UNKNOWN" in d) == (label == "the same, one row of tiles, two batches a workgroup"), label
         assert ("SUBM" in d) == ("sub-tiles" in label)
 
 
