@@ -338,6 +338,8 @@ static bool plan_strip(const opevo_op &op, int64_t bm, int64_t nb2, int64_t bh, 
 // column panel that is not surrounded by its neighbours also pays for the rest of its cache lines.
 // Measured, natural / columns first / rows first (us): 245 x 7650 x 1590 in 7 x 30 257 / 150 / 108; 2496 x 7072 x 6848 in 64 x 32 1040 / 697 / 749; 6680 x 1650 x 400 in
 // 40 x 30 74 / 68 / 83; 506 x (128 x 160 x 160) in 128 x 32 28 / 17 / 18; 8192^3 in 256 x 256 890 / 942 / 995; 512 x 4096 x 1024 fp32 in 64 x 64 47 / 51 / 48.
+// The order alone (the rest compiled alike): 43 scalar members 1.13x in the geometric mean (0.92 - 1.76), 25 folded scalar ones 1.07x (0.83 - 1.40), 118 register-staged ones
+// 1.19x (0.91 - 2.21), 50 on the fp32 and ragged templates 1.16x (0.97 - 1.78); no line was found around the slower ones.
 // Operands that an L2 holds gain nothing and pay for the division (1000^3 in 20 x 100 13.6 / 14.2 / 14.1, 6048 x 108 x 75 3.4 / 3.6 / 3.7), nor do
 // small batches (52 x (224 x 192 x 64), 12 MB 5.1 / 5.5 / 5.5): from 4 MiB of operands on, or 16 MB of traffic with batches.
 static int xcd_walk(const opevo_op &op, int64_t n1, int64_t m1, int64_t b1, int64_t bm, int64_t bn, int64_t binner, int64_t resident)
@@ -945,7 +947,8 @@ int decode(const opevo_op &op, int variant, const int32_t *cfg, Decoded &out, bo
     }
     // fp32, short reductions: outputs that the eight L2s (32 MiB) would hold and write back when the kernel ends are stored past them.  44 further
     // MatMul / BMM members of K <= 224 with outputs of 2 - 32 MiB, drawn after the rule was made, 1.00 - 1.28x, 1.04x in the geometric mean (727 x (128 x 64 x 64)
-    // 16.1 -> 13.1 us, 448 x 2112 x 192 6.87 -> 6.64); smaller outputs 0.96 - 1.06x, larger ones 0.95 - 1.07x, K of 256 to 6208 0.91 - 1.02x (mostly 1.00).  Rows of 64 or of any number of bytes (16-bit
+    // 16.1 -> 13.1 us, 448 x 2112 x 192 6.87 -> 6.64); smaller outputs 0.96 - 1.06x, larger ones 0.95 - 1.07x; 42 further ones with an elementwise pass over the
+    // output after them 1.01x for the two together (0.94 - 1.13), 1.03x alone; K of 256 to 6208 0.91 - 1.02x (mostly 1.00).  Rows of 64 or of any number of bytes (16-bit
     // inputs on 16 x 16 atoms, ragged tiles) 0.59 - 1.20x without a line between them: those stay with ordinary stores.
     const int64_t out_bytes = op.c_elems() * 4;
     if (path == 4 && op.kind != OPEVO_CONV2D && ksplit == 1 && op.K <= 224 && out_bytes >= (int64_t(2) << 20) && out_bytes <= (int64_t(32) << 20)) D << " -DNT_OUT=1";

@@ -8,7 +8,7 @@
 // of KS (the member's slab rounded up to whole MFMA steps), the last one filled up with zeros in both operands.
 //
 // Measured (bf16): 1000^3 in tiles of 20 x 100 168 us on the scalar template (20 waves, the best there), 15.6 us with every piece's place worked out
-// for every slab, 12.8 us here (156 TFLOP/s); 120 x 280 x 3650 in 60 x 56 39.7 -> 19.5; 220 x 280 x 950 in 44 x 56 12.3 -> 6.4.  119 drawn and random
+// for every slab, 12.5 us here (160 TFLOP/s); 120 x 280 x 3650 in 60 x 56 39.7 -> 19.5; 220 x 280 x 950 in 44 x 56 12.3 -> 6.4.  119 drawn and random
 // members against the template before that and before the order of the workgroups followed the XCDs: 1.29x in the geometric mean.
 // What bounds it: at these tiles the LDS (1000^3: per slab and compute unit some 1500 of its cycles, fragments that every wave reads for itself and bank
 // conflicts) and the phases of a slab that follow one another, loads, stores and multiplication in equal parts; deeper prefetch gains nothing there.
