@@ -375,7 +375,7 @@ int opevo_compile_pool_deadline(double seconds);
  * and one spilling member of the register-staged template once gave wrong rows.  opevo_tune
  * scores both as invalid trials.  What a template does of its own accord (path 4's pipelined
  * loop, path 7, path 5's extra waves per tile or rows of pixels, path 6's places kept from slab to slab, path 3's second
- * group of waves) never makes a member spill: this call compiles it again without, if the first code object does. */
+ * group of waves, the order of the workgroups) never makes a member spill: this call compiles it again without, if the first code object does. */
 int opevo_kernel_build(const opevo_op *op, int variant, const int32_t *cfg,
                        opevo_kernel **out, double *compile_ms);
 /* Compiling is by far the longest part of a trial (Sec. 6 gives it 8 CPU threads), and runs of
