@@ -367,9 +367,9 @@ static int xcd_walk(const opevo_op &op, int64_t n1, int64_t m1, int64_t b1, int6
     return by_col <= by_row ? 1 : 2;
 }
 
-// Members that cannot run without the few-channels template (a slab with too many staging registers, say) stay invalid:
-// which members of a space are valid does not depend on it.
-static bool valid_without_rows(const opevo_op &op, int variant, const int32_t *cfg)
+// Members that cannot run without the few-channels template, or the one that takes fp32 values apart (a slab with too many staging registers, or
+// too long for the LDS, say), stay invalid: which members of a space are valid does not depend on them.
+static bool valid_without_extras(const opevo_op &op, int variant, const int32_t *cfg)
 {
     Decoded d;
     return decode(op, variant, cfg, d, false) == OPEVO_OK && d.plan.status == OPEVO_OK;
@@ -776,7 +776,7 @@ int decode(const opevo_op &op, int variant, const int32_t *cfg, Decoded &out, bo
     // kernel row as the reduction's groups of 8
     Rows rows;
     if (extras && four_level && op.dtype != OPEVO_F32 && op.kind == OPEVO_CONV2D && (path == 0 || path == 1 || path == 2) && !nhwc_ok && subm * subn == 1 &&
-        ksplit == 1 && plan_rows(op, BM, nb2, BH, BW, n1, m1, linear, rows) && valid_without_rows(op, variant, cfg)) {
+        ksplit == 1 && plan_rows(op, BM, nb2, BH, BW, n1, m1, linear, rows) && valid_without_extras(op, variant, cfg)) {
         path = 7;
         WM = rows.wm; WN = rows.wn; TM = rows.mi * rows.atom; TN = rows.ni * rows.atom;
         TMacc = TM; TNacc = TN; BK = op.K; BKP = op.K; ksteps = 1; ragged = false; tap_box = false;
@@ -801,6 +801,21 @@ int decode(const opevo_op &op, int variant, const int32_t *cfg, Decoded &out, bo
         for (int st = std::min(4, nstage_dlds); pays && st >= 2 && kgrp == 1; --st)
             if (2 * st * stage <= kMaxLds && nw * TM * TN * 4 <= 2 * st * stage && (2 * st - 2) * per <= 63 &&
                 !(dlds_atom16 && BK % 64 != 0 && st % 2 != 0)) { kgrp = 2; nstage_dlds = 2 * st; out.extra_waves = true; }
+    }
+    // fp32 MatMul / BMM members with two stages, workgroup tiles of 32 or 64 rows and columns and long reductions: the template that takes values apart for the bf16
+    // matrix pipes, its waves sharing the reduction.  From K = 320 on, 448 for tiles of 64 x 64, which pay for a longer final sum: 64 x 64 tiles at K = 320
+    // 8.3 -> 9.1 us (34 workgroups) and 9.4 -> 10.3 (182), at 480 87.6 -> 81.6, at 512 12.8 -> 11.7; 32 x 64 at K = 320 23 -> 18.4, at 384 9.8 -> 6.7, at 256 12.9 -> 12.7; K of 64 to
+    // 256 0.73 - 1.1 times as fast.  30 drawn operators of K = 448 - 7808: 1.07 - 2.5x.
+    // Eight waves instead of four where a compute unit has one workgroup at most and each wave still gets 88 steps: 672 x 192 x 2560 (63 workgroups) 23.9 -> 21.4, 64 x 1152
+    // x 4096 (18) 52.7 -> 45.9, 1024 x 480 x 736 (240) 12.5 -> 11.4, but 512 x 4096 x 1024 (512) 39.8 -> 43.9 and 64 x 64 x 448 steps and less alike.
+    int f32_kw = 0;
+    if (extras && path == 4 && op.kind != OPEVO_CONV2D && flagv && ksteps > 1 && ksplit == 1 && subm * subn == 1 && WM * WN <= kMaxThreads / 64 &&
+        (BM == 32 || BM == 64) && (BN == 32 || BN == 64) && op.K % 32 == 0 && op.K >= (BM * BN == 64 * 64 ? 448 : 320) &&
+        op.M < (1 << 22) && op.N < (1 << 22) && op.K < (1 << 22) &&         // (a lane's byte offsets within 32 bits)
+        valid_without_extras(op, variant, cfg)) {
+        f32_kw = n1 * m1 * b1 <= 256 && op.K >= 704 ? 8 : 4;
+        out.extra_waves = true;
+        WM = 1; WN = f32_kw; TM = BM; TN = BN; TMacc = TM; TNacc = TN; FM = std::gcd(FM, TM); FN = std::gcd(FN, TN);
     }
     const bool b_kmajor = path == 3 && (b_packed || op.kind == OPEVO_CONV2D);
     const bool nhwc = nhwc_ok && (path == 1 || path == 2 || path == 3);
@@ -830,6 +845,7 @@ int decode(const opevo_op &op, int variant, const int32_t *cfg, Decoded &out, bo
         const int64_t a_rows = (WM - 1) * TM + TMacc, b_cols = ((WN - 1) * TN + TNacc + 3) / 4 * 4;   // with the overhang
         lds = nstage * (a_rows * (BKP + 4) + BKP * (b_cols + 4)) * 4;
     }
+    else if (path == 4 && f32_kw) lds = f32_kw * BM * std::max<int64_t>(op.trans_a ? 0 : 32, BN) * 4;
     else if (path == 4) lds = nstage * ((op.trans_a ? BK * (BM + 4) : BM * (BK + 4)) + BK * (BN + 4)) * 4;
     else if (path == 3) lds = nstage * (anr + (b_kmajor ? bnr : BN)) * BK * 2;
     else if (path == 5 && strip.rows) lds = strip.lds;
@@ -860,12 +876,12 @@ int decode(const opevo_op &op, int variant, const int32_t *cfg, Decoded &out, bo
         invalid(p, "%ld bytes of LDS > %ld", long(lds), long(kMaxLds));
     else if (!linear && (m1 > 65535 || b1 > 65535)) invalid(p, "grid y/z %ld x %ld > 65535", long(m1), long(b1));
     else if (linear && n_blocks > INT32_MAX) invalid(p, "%ld workgroups in a one-dimensional grid", long(n_blocks));
-    else if (path == 4) {
+    else if (path == 4 && !f32_kw) {
         const int64_t chunks = op.kind == OPEVO_CONV2D ? (BM * (BKP / 4) + NT - 1) / NT + (BKP * ((BN + 3) / 4) + NT - 1) / NT
                                                        : (BM * (BK / 4) + NT - 1) / NT + (BK * (BN / 4) + NT - 1) / NT;
         if (chunks * 4 > 256) invalid(p, "%ld staging registers per lane > 256", long(chunks * 4));
     }
-    else if (path != 0 && path != 3 && path != 5 && path != 6 && path != 7 && stage_lds) {
+    else if (path != 0 && path != 3 && path != 4 && path != 5 && path != 6 && path != 7 && stage_lds) {
         // register budget of the slab in flight: 16-byte pieces per thread
         const int64_t a_chunks = op.trans_a ? 8 * (((BK / 8) * (BM / 8) + NT - 1) / NT) : (BM * (BKP / 8) + NT - 1) / NT;
         const int64_t b_chunks = (op.kind == OPEVO_CONV2D) ? (BN * (BKP / 8) + NT - 1) / NT
@@ -874,7 +890,7 @@ int decode(const opevo_op &op, int variant, const int32_t *cfg, Decoded &out, bo
             invalid(p, "%ld staging registers per lane > 256", long((a_chunks + b_chunks) * 4));
     }
 
-    out.tmpl = path == 0 ? "gemm_scalar" : path == 3 ? "gemm_mfma_dlds" : path == 4 ? "gemm_mfma_f32" : path == 5 ? (strip.rows ? "conv_strip" : "conv_patch") : path == 6 ? "gemm_ragged" : path == 7 ? "conv_rows" : "gemm_mfma";
+    out.tmpl = path == 0 ? "gemm_scalar" : path == 3 ? "gemm_mfma_dlds" : path == 4 ? (f32_kw ? "gemm_f32_split" : "gemm_mfma_f32") : path == 5 ? (strip.rows ? "conv_strip" : "conv_patch") : path == 6 ? "gemm_ragged" : path == 7 ? "conv_rows" : "gemm_mfma";
     // one symbol per configuration, so profiles list each instantiated kernel on its own line
     {
         std::ostringstream nm;
@@ -940,7 +956,8 @@ int decode(const opevo_op &op, int variant, const int32_t *cfg, Decoded &out, bo
     // reductions on a full chip have the plain loop with the second operand read step by step (8 x 64 x 28 x 28 * 64 x 64 x 3 x 3 as 112 x 1 waves 77.5 us so and
     // 82.0 pipelined, as 112 x 7 waves 54.8 and 61.1, on slabs of 2 as 32 x 1 waves 1020 and 1139; 2048 x 2048 x 128, 1024 x 2 waves, 15.7 and 17.5; four other
     // convolutions between 0.7 % slower and 2 % faster).
-    if (path == 4 && nstage == 2) {
+    if (f32_kw) out.tries = {" -DPIPELINED=1"};        // the loop of the template that takes values apart
+    else if (path == 4 && nstage == 2) {
         const bool full_chip = n_blocks * nwr >= 2048;
         if (BKP == 8 && (op.kind == OPEVO_CONV2D || (full_chip && ksteps * BKP <= 128))) out.tries = {" -DSTEP_READS=1", " -DPIPELINED=1", ""};
         else if (!(full_chip && ksteps < 8)) out.tries = {" -DPIPELINED=1", ""};
@@ -952,6 +969,7 @@ int decode(const opevo_op &op, int variant, const int32_t *cfg, Decoded &out, bo
     // inputs on 16 x 16 atoms, ragged tiles) 0.59 - 1.20x without a line between them: those stay with ordinary stores.
     const int64_t out_bytes = op.c_elems() * 4;
     if (path == 4 && op.kind != OPEVO_CONV2D && ksplit == 1 && op.K <= 224 && out_bytes >= (int64_t(2) << 20) && out_bytes <= (int64_t(32) << 20)) D << " -DNT_OUT=1";
+    if (f32_kw) D << " -DKW=" << f32_kw << " -DLDS_BYTES=" << lds << " -DMINW=2";
     if (kgrp > 1) D << " -DKGRP=" << kgrp;
     if (kunroll) D << " -DKUNROLL=" << kunroll;
     if (ksplit > 1) D << " -DKSPLIT=" << ksplit;

@@ -1,0 +1,130 @@
+"""The template that multiplies fp32 values as three bf16 parts each: which members it takes, and its results where its parts meet: every tile, parts of the
+reduction of unequal length, four and eight waves, a transposed first operand, batches, values that cannot be taken apart, sums beyond the range."""
+import numpy as np
+import pytest
+
+import paper_2006_05664_amd as P
+from paper_2006_05664_amd import synth
+
+MM, BMM, TA = P.OPEVO_MATMUL, P.OPEVO_BMM, P.OPEVO_BMM_TA
+V, X, K3 = P.OPEVO_TILE4, P.OPEVO_TILE4X, P.OPEVO_TILE4K
+CASES = [   # label, kind, dims, variant, configuration, waves that share the reduction (0: not on this template)
+    ("64 x 64, 15 chunks on four waves", MM, (128, 192, 480), V, [2, 2, 1, 32, 3, 2, 1, 32, 15, 32, 1], 4),
+    ("32 x 64, 11 chunks on four waves", MM, (64, 128, 352), V, [2, 1, 1, 32, 2, 1, 2, 32, 11, 32, 1], 4),
+    ("64 x 32, the shortest reduction", MM, (64, 96, 320), V, [1, 1, 2, 32, 3, 1, 1, 32, 10, 32, 1], 4),
+    ("32 x 32, 23 chunks on eight waves", MM, (96, 64, 736), V, [3, 1, 1, 32, 2, 1, 1, 32, 23, 32, 1], 8),
+    ("64 x 64, eight waves", MM, (64, 64, 1024), V, [1, 2, 1, 32, 1, 2, 1, 32, 16, 64, 1], 8),
+    ("slabs of 8, a launch order of its own", MM, (128, 64, 704), X, [2, 1, 2, 32, 1, 2, 1, 32, 88, 8, 1, 1, 0, 2], 8),
+    ("batches, two per workgroup", BMM, (6, 64, 32, 416), V, [3, 2, 2, 1, 1, 32, 1, 1, 1, 32, 13, 32, 1], 4),
+    ("transposed first operand, 64 x 64", TA, (4, 64, 128, 448), V, [2, 2, 1, 2, 1, 32, 2, 2, 1, 32, 14, 32, 1], 4),
+    ("transposed first operand, 32 x 32", TA, (2, 96, 32, 768), V, [2, 1, 3, 1, 1, 32, 1, 1, 1, 32, 24, 32, 1], 8),
+    ("workgroups enough for the chip", MM, (1024, 1088, 704), V, [16, 2, 1, 32, 17, 2, 1, 32, 11, 64, 1], 4),
+    ("64 x 64, shorter", MM, (128, 192, 416), V, [2, 2, 1, 32, 3, 2, 1, 32, 13, 32, 1], 0),
+    ("32 x 64, shorter", MM, (64, 128, 288), V, [2, 1, 1, 32, 2, 1, 2, 32, 9, 32, 1], 0),
+    ("no whole chunks", MM, (64, 128, 336), V, [2, 1, 1, 32, 2, 1, 2, 32, 21, 16, 1], 0),
+    ("96 columns", MM, (64, 96, 512), V, [2, 1, 1, 32, 1, 1, 3, 32, 16, 32, 1], 0),
+    ("no pipelining asked for", MM, (64, 128, 512), V, [2, 1, 1, 32, 2, 1, 2, 32, 16, 32, 0], 0),
+    ("split reduction", MM, (64, 128, 1024), K3, [2, 1, 1, 32, 2, 1, 2, 32, 2, 16, 32, 1], 0),
+]
+
+
+def _waves(kind, dims, variant, cfg):
+    op = P.opevo_op_create(kind, dims, P.OPEVO_F32)
+    plan = P.opevo_kernel_plan(op, variant, cfg)
+    assert plan.status == P.OPEVO_OK and plan.path == 4, (plan.path, plan.reason)
+    words = P.opevo_kernel_defines(op, variant, cfg).split()
+    return plan.block // 64 if words[0] == "gemm_f32_split:" else 0
+
+
+@pytest.mark.parametrize("label,kind,dims,variant,cfg,waves", CASES, ids=[c[0] for c in CASES])
+def test_which_members_it_takes(label, kind, dims, variant, cfg, waves):
+    assert _waves(kind, dims, variant, cfg) == waves
+
+
+def test_members_that_could_not_run_without_it_stay_invalid():
+    """One wave on slabs of 144 would stage 288 registers a lane on the fp32 atoms' template."""
+    op = P.opevo_op_create(MM, (64, 64, 576), P.OPEVO_F32)
+    assert P.opevo_kernel_plan(op, V, [1, 1, 2, 32, 1, 1, 2, 32, 4, 144, 1]).status == P.OPEVO_E_INVALID
+    assert _waves(MM, (64, 64, 576), V, [1, 2, 1, 32, 1, 1, 2, 32, 4, 144, 1]) == 4
+
+
+def _run(kind, dims, variant, cfg, a, b, n):
+    import torch
+    op = P.opevo_op_create(kind, dims, P.OPEVO_F32)
+    da, db = torch.from_numpy(np.ascontiguousarray(a)).to("cuda:0"), torch.from_numpy(np.ascontiguousarray(b)).to("cuda:0")
+    dc = torch.full((n,), float("nan"), device="cuda:0")
+    kernel, _ = P.opevo_kernel_build(op, variant, cfg)
+    for _ in range(2):                                     # the second launch overwrites what the first one left
+        P.opevo_kernel_launch(kernel, da.data_ptr(), db.data_ptr(), dc.data_ptr(), torch.cuda.current_stream().cuda_stream)
+    torch.cuda.synchronize()
+    P.opevo_kernel_destroy(kernel)
+    return dc.cpu().numpy()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("label,kind,dims,variant,cfg,waves", [c for c in CASES if c[-1]], ids=[c[0] for c in CASES if c[-1]])
+def test_results_match_the_oracle(label, kind, dims, variant, cfg, waves):
+    """A wave adds at most 256 products, 16 at a time in six roundings: 96 roundings of growing sums, some 10 of the result's norm by their
+    random signs; the final sum has at most 8.  1.2e-6 is 20."""
+    from oracle import tensor as T
+    a, b = {MM: synth.matmul_inputs, BMM: synth.bmm_inputs, TA: synth.bmm_ta_inputs}[kind](*dims, "f32", 5)
+    want = (T.matmul(a, b) if kind == MM else T.bmm(a if kind == BMM else np.ascontiguousarray(a.transpose(0, 2, 1)), b)).ravel()
+    got = _run(kind, dims, variant, cfg, a, b, want.size).astype(np.float64)
+    assert np.all(np.isfinite(got)) and np.linalg.norm(got - want) <= 1.2e-6 * np.linalg.norm(want), label
+
+
+def _operands():
+    g = np.random.default_rng(7)
+    return g.standard_normal((64, 480)).astype(np.float32), g.standard_normal((480, 64)).astype(np.float32)
+
+
+MEMBER = (MM, (64, 64, 480), V, [1, 2, 1, 32, 1, 2, 1, 32, 15, 32, 1])
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("scale_a,scale_b", [(2.0 ** -60, 2.0 ** -60), (2.0 ** -99, 2.0 ** 99), (2.0 ** -120, 2.0 ** 100), (2.0 ** -135, 2.0 ** 40), (2.0 ** 118, 1.0)])
+def test_operands_of_any_magnitude(scale_a, scale_b):
+    """Scaling by powers of two changes no relative error as long as the values keep their 24 bits (rounded to fp32 here, as the operands are)."""
+    a, b = _operands()
+    a, b = (a * np.float32(scale_a)).astype(np.float32), (b * np.float32(scale_b)).astype(np.float32)
+    want = a.astype(np.float64) @ b.astype(np.float64)
+    got = _run(*MEMBER, a, b, want.size).astype(np.float64).reshape(want.shape)
+    assert np.linalg.norm(got - want) <= 1.2e-6 * np.linalg.norm(want)
+
+
+@pytest.mark.gpu
+def test_a_single_value_that_cannot_be_taken_apart():
+    """Rows and columns whose only values lie below 2^-100, one for each place of a lane's 8 and each wave, beside ordinary ones and zeros."""
+    a, b = _operands()
+    a[np.abs(a) < 0.5] = 0.0
+    for i in range(32):
+        a[i] = 0.0
+        a[i, (i * 37) % 480] = np.float32(1.2345678e-34)
+        b[:, i] = 0.0
+        b[(i * 41) % 480, i] = np.float32(-7.654321e-33)
+    b[:, 32:] *= np.float32(1e20)
+    a[32:] *= np.float32(1e15)
+    want = a.astype(np.float64) @ b.astype(np.float64)
+    got = _run(*MEMBER, a, b, want.size).astype(np.float64).reshape(want.shape)
+    for part in (np.s_[:32, 32:], np.s_[32:, :32]):            # one product each: rounded once (2^-24), or a chain of zeros and one product
+        assert np.all(np.abs(got[part] - want[part]) <= 2.0 ** -23 * np.abs(want[part]))
+    assert np.linalg.norm(got[32:, 32:] - want[32:, 32:]) <= 1.2e-6 * np.linalg.norm(want[32:, 32:])
+
+
+@pytest.mark.gpu
+def test_infinities_nan_and_sums_beyond_the_range():
+    a, b = _operands()
+    a[3, 100], a[4, 101], b[470, 9] = np.inf, np.nan, -np.inf
+    a[5], a[6] = 0.0, np.abs(a[6]) * np.float32(2.0 ** 125)    # row 6: every sum of like signs is far beyond the range
+    with np.errstate(invalid="ignore"):
+        want = a.astype(np.float64) @ np.abs(b).astype(np.float64)
+    got = _run(*MEMBER, a, np.abs(b), want.size).reshape(want.shape)
+    with np.errstate(over="ignore"):
+        assert np.array_equal(np.isnan(got), np.isnan(want)) and np.array_equal(np.isinf(got), np.isinf(want.astype(np.float32)))
+    # the early products alone leave the range upwards, the late ones downwards, all together upwards: infinite in order, a NaN as the sum of partial sums
+    a, b = _operands()
+    a, b = np.abs(a) * np.float32(2.0 ** 124), np.abs(b)
+    b[240:] *= np.float32(-0.25)
+    want = a.astype(np.float64) @ b.astype(np.float64)
+    got = _run(*MEMBER, a, b, want.size).reshape(want.shape)
+    assert np.all(np.isfinite(a)) and np.all(want > 3.5e38) and np.all(np.isposinf(got))
