@@ -342,10 +342,11 @@ static bool plan_strip(const opevo_op &op, int64_t bm, int64_t nb2, int64_t bh, 
 // 1.19x (0.91 - 2.21), 50 on the fp32 and ragged templates 1.16x (0.97 - 1.78); no line was found around the slower ones.
 // Operands that an L2 holds gain nothing and pay for the division (1000^3 in 20 x 100 13.6 / 14.2 / 14.1, 6048 x 108 x 75 3.4 / 3.6 / 3.7), nor do
 // small batches (52 x (224 x 192 x 64), 12 MB 5.1 / 5.5 / 5.5): from 4 MiB of operands on, or 16 MB of traffic with batches.
-static int xcd_walk(const opevo_op &op, int64_t n1, int64_t m1, int64_t b1, int64_t bm, int64_t bn, int64_t binner, int64_t resident)
+static int xcd_walk(const opevo_op &op, int64_t n1, int64_t m1, int64_t b1, int64_t bm, int64_t bn, int64_t binner, int64_t resident, bool matrix)
 {
-    const int64_t e = op.elem_size(), tiles = n1 * m1, W = 32 * std::max<int64_t>(1, std::min<int64_t>(8, resident));
     auto up = [](int64_t a, int64_t b) { return (a + b - 1) / b; };
+    const int64_t e = op.elem_size(), tiles = n1 * m1;
+    int64_t W = 32 * std::max<int64_t>(1, std::min<int64_t>(8, resident));      // tiles an XCD has under way
     auto alone = [&](int64_t w) { return w * e + (w * e % 128 == 0 ? 0 : w * e % 64 == 0 ? 64 : 126); };
     const int64_t row = op.trans_a && m1 > 1 ? alone(bm) : bm * e, col = n1 > 1 ? alone(bn) : bn * e;
     // natural order over a window of `tiles_in` tiles: an XCD's distinct columns and rows
@@ -361,6 +362,10 @@ static int xcd_walk(const opevo_op &op, int64_t n1, int64_t m1, int64_t b1, int6
         return nat * double(op.K) * double(tiles) * double(b1 * binner) >= 16e6 && walk < 0.75 * nat ? 1 : 0;
     }
     if ((op.a_elems() + op.b_elems()) * e <= (int64_t(4) << 20)) return 0;
+    // Grids that do not fill the chip: an XCD has an eighth of the tiles.  On the matrix templates and with reductions of 2100 bytes and more 41 drawn members 1.10x in
+    // the geometric mean (0.98 - 1.57: 2112 x 128 x 4064 in 64 x 64 18.0 -> 13.2 us, 180 x 1056 x 3267 in 60 x 32 17.1 -> 11.2); shorter ones pay for the
+    // division (96 x 4224 x 896 4.51 -> 4.68).  40 random ragged members 1.14x (0.96 - 1.86).  39 random scalar members gain less and lose more (1.06x, 0.94 - 1.40).
+    if (matrix && op.K * e >= 2100) W = std::min(W, up(tiles, 8));
     const double nat = natural(std::min(tiles, 8 * W));
     const double by_col = double(std::min(n1, W) * bn * e + 128 + up(W, n1) * row), by_row = double(up(W, m1) * bn * e + 128 + std::min(m1, W) * bm * e);
     if (std::min(by_col, by_row) >= 0.75 * nat) return 0;
@@ -977,7 +982,7 @@ int decode(const opevo_op &op, int variant, const int32_t *cfg, Decoded &out, bo
     out.prepass = nhwc ? 1 : (b_kmajor && op.kind == OPEVO_MATMUL) ? 2 : 0;
     std::string walked;
     if (!linear && four_level && op.kind != OPEVO_CONV2D && ksplit == 1 && n_blocks < (int64_t(1) << 30))
-        if (const int walk = xcd_walk(op, n1, m1, b1, BM * subm, BN * subn, binner, lds > 0 ? kMaxLds / lds : 8)) {
+        if (const int walk = xcd_walk(op, n1, m1, b1, BM * subm, BN * subn, binner, lds > 0 ? kMaxLds / lds : 8, path != 0)) {
             std::ostringstream W;
             W << " -DXCD_WALK=" << walk << " -DGRID_N1=" << n1 << " -DGRID_M1=" << m1 << " -DGRID_B1=" << b1;
             // A single row of tiles is number 0, which the natural order's code does not know.  Members that read their fragments straight from global memory,
