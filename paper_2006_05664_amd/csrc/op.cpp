@@ -770,12 +770,31 @@ int decode(const opevo_op &op, int variant, const int32_t *cfg, Decoded &out, bo
     // (that tile's best scalar member, 20 waves, 168), 10 x 20 (2.6) 39 against 519, 8 x 8 (4) 79 against 310, 4 x 8 and 8 x 4 (8 times)
     // 144 and 171 against 356 and 381: by about 16 times nothing is left, so the line lies at 8.
     Ragged rg;
+    int rg_kw = 0;
     if (four_level && path == 0 && op.dtype != OPEVO_F32 && op.kind != OPEVO_CONV2D && subm * subn == 1 &&
         (op.M % 16 != 0 || op.N % 16 != 0 || op.K % 16 != 0) &&
         plan_ragged(op, BM, BN, BK, op.K / ksplit, n1 * m1 * b1, flagv != 0 || op.kind == OPEVO_BMM, rg)) {
         path = 6;
         WM = rg.wm; WN = rg.wn; TM = rg.mi * 16; TN = rg.ni * 16;
         TMacc = TM; TNacc = TN; BK = rg.ks; ksteps = rg.slabs;
+        // Waves that share the reduction, each with the whole tile as its wave tile and a part of the LDS of its own, where no more than one workgroup falls on a compute unit:
+        // eight, as far as the LDS goes.  60 drawn and random members of K >= 448 and up to 20 atoms against the slab walk: 0.93 - 2.9x, 1.6x in the geometric mean (480 x 360 x 4893,
+        // 90 workgroups, 29.5 -> 12.9 us; 40 x 100 x 2517, 8, 19.8 -> 7.5); below, 56 x 56 at K = 324 4.3 -> 4.6, 32 x 44 at 360 3.2 -> 3.4; with 500 workgroups of 20 x 100
+        // at K = 1000 13.2 -> 13.4, with 860 of 50 x 32 32.0 -> 39.6.
+        // Two waves on fuller grids where an operand's pieces begin at odd elements, which this loop shifts into place: 12 members of up to 1024 workgroups and 12 atoms 1.02 -
+        // 2.0x, 1.4x in the mean (100 x 5439 x 1056 in 50 x 21 20.4 -> 11.1; 1078 workgroups 39.9 -> 41.6, 1125 23.9 -> 18.9, 1575 25.8 -> 26.0).
+        const int64_t ma = (BM + 15) / 16, na = (BN + 15) / 16, wgs = n1 * m1 * b1;
+        const bool odd = op.N % 2 != 0 || (BN % 2 != 0 && n1 > 1) || (op.trans_a && (op.M % 2 != 0 || (BM % 2 != 0 && m1 > 1)));
+        auto odd16 = [](int64_t n) { return ((n + 15) / 16 | 1) * 16; };
+        const int64_t a_part = op.trans_a ? 32 * odd16(ma * 16) + 192 : ma * 16 * 40, b_part = 32 * odd16(na * 16) + 192;
+        const int64_t per = std::max(2 * (a_part + b_part), ma * 16 * (na * 16 + 4) * 4);           // bytes of LDS a wave's operands, or its sums, take
+        int64_t kw = 0;
+        if (extras && ksplit == 1 && op.K >= 448) kw = wgs <= 256 && ma * na <= 20 ? std::min<int64_t>(8, kMaxLds / per) : odd && op.K >= 500 && wgs <= 1024 && ma * na <= 12 ? 2 : 0;
+        if (kw == 2 || kw >= 4) {
+            rg_kw = int(kw); rg.lds = kw * per; rg.min_waves = 2;
+            out.extra_waves = true;
+            WM = 1; WN = kw; TM = ma * 16; TN = na * 16; TMacc = TM; TNacc = TN;
+        }
     }
     // Conv2d with fewer than 16 input channels (no slab of whole channels for the patch template): image rows in LDS, taps of a
     // kernel row as the reduction's groups of 8
@@ -918,6 +937,7 @@ int decode(const opevo_op &op, int variant, const int32_t *cfg, Decoded &out, bo
     }
     if (path == 7) D << " -DWKP=" << rows.wkp << " -DMI=" << rows.mi << " -DNI=" << rows.ni << " -DLDS_BYTES=" << lds << " -DPERSIST=" << rows.persist << " -DNBOX=" << n1;
     if (path == 6) D << " -DKS=" << rg.ks << " -DNSL=" << rg.slabs << " -DMI=" << rg.mi << " -DNI=" << rg.ni << " -DLDS_BYTES=" << lds << " -DDEPTH=" << rg.depth << " -DMINW=" << rg.min_waves;
+    if (rg_kw) D << " -DKWAVES=" << rg_kw;
     if (subm * subn > 1) {
         D << " -DSUBM=" << subm << " -DSUBN=" << subn;
     }

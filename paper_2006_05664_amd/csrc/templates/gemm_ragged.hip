@@ -22,6 +22,13 @@
 //     further, so the 4 rows x 32 bytes that two groups of 16 lanes read together (8 rows apart) fall into 8 different groups of banks.
 // NSTG = 2: the pieces of the next DEPTH slabs are in registers while slab s is multiplied; the next one's are stored to the other stage afterwards
 // (one barrier per slab).  NSTG = 1: load, barrier, store, barrier, multiply.
+//
+// KWAVES: another way, for long reductions on grids that leave a compute unit to one workgroup.  Every wave has the whole tile as its wave tile and a
+// contiguous part of the reduction, in steps of 32 positions through a part of the LDS of its own, so that nothing waits at a barrier until the sums
+// meet at the end and each operand is read from the LDS once.  The last step begins early enough to be full and leaves out what has been
+// added; a tile at the end of a row begins far enough left for whole pieces, its surplus columns are not stored: no load reaches past an operand and the loop
+// has one form.  What bounds it: the load unit (16 bytes a lane: 19 cycles a wave from L1 at 4-byte alignment, 68 at 2-byte), then the LDS stores.
+// The sums are written to LDS as rows, so that consecutive threads store consecutive columns.
 
 #if IN_DTYPE == 1
 typedef __attribute__((ext_vector_type(8))) __bf16 frag_t;
@@ -48,8 +55,10 @@ typedef u32x4 __attribute__((aligned(2))) u32x4_a2;
 typedef __attribute__((ext_vector_type(4))) short v4s;
 
 constexpr int KPART = K / KSPLIT;                 // reduction length of this workgroup
+#ifndef KWAVES
 static_assert(NSL * KS >= KPART && (NSL - 1) * KS < KPART && KS % 32 == 0 && KPART >= 8, "decoder and template disagree");
 static_assert(WM * MI * 16 >= BM && WN * NI * 16 >= BN && NT == 64 * WM * WN, "decoder and template disagree");
+#endif
 constexpr bool K_TAIL = KPART % KS != 0;          // the last slab is not full
 
 constexpr int odd16(int n) { return ((n + 15) / 16 | 1) * 16; }
@@ -58,7 +67,9 @@ constexpr int LDM = odd16(WM * MI * 16), LDN = odd16(WN * NI * 16);
 __device__ __forceinline__ constexpr int kr_off(int ld, int k) { return k * ld + (k >> 3) * 64; }   // LDS element of k row k
 constexpr int A_STAGE = A_TRANS ? KS * LDM + (KS / 8) * 64 : WM * MI * 16 * LDK;
 constexpr int B_STAGE = KS * LDN + (KS / 8) * 64;
+#ifndef KWAVES
 static_assert(NSTG * (A_STAGE + B_STAGE) * 2 <= LDS_BYTES, "stages exceed the LDS the host asks for");
+#endif
 constexpr int CK = KS / 8;                        // pieces of a k-contiguous row
 constexpr int CM = (BM + 7) / 8, CN = (BN + 7) / 8;   // pieces of a k row
 constexpr int A_PIECES = A_TRANS ? KS * CM : BM * CK, B_PIECES = KS * CN;
@@ -78,6 +89,217 @@ __device__ __forceinline__ u32x4 shift_down(u32x4 v, int sh)
     return r;
 }
 
+// Fragment of k rows, an atom whose first row / column is x0, from the LDS rows of one MFMA step: in each group of 16 lanes, lane s addresses 4
+// consecutive elements of k row s / 4, and lane i receives the 4 values of element i
+template <int LD>
+__device__ __forceinline__ frag_t kr_frag(const u16 *S, int x0, int lane)
+{
+    const int s = lane & 15;
+    const u16 *p = S + kr_off(LD, 8 * (lane >> 4)) + (s >> 2) * LD + x0 + 4 * (s & 3);
+    const v4s lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) v4s *)p);
+    const v4s hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) v4s *)(p + 4 * LD));
+    return __builtin_bit_cast(frag_t, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+}
+
+// ---------------------------------------------------------------- waves that share the reduction (KWAVES)
+#ifdef KWAVES
+constexpr int KC = 32;                               // reduction positions of a step
+constexpr int MA = (BM + 15) / 16, NATOM = (BN + 15) / 16;
+constexpr int NSTEP = (K + KC - 1) / KC, DUP = NSTEP * KC - K;   // the last step begins DUP positions early and leaves them out
+constexpr int LA = A_TRANS ? odd16(MA * 16) : KC + 8, LB = odd16(NATOM * 16);
+constexpr int KR_GAPS = (KC / 8 - 1) * 64;
+constexpr int A_PART = A_TRANS ? KC * LA + KR_GAPS : MA * 16 * LA, B_PART = KC * LB + KR_GAPS, PART = A_PART + B_PART;
+constexpr int PA = A_TRANS ? KC * CM : BM * (KC / 8), PB = KC * CN;
+constexpr int QA = (PA + 63) / 64, QB = (PB + 63) / 64;
+// partial sums: P[wave][row][LC]; four rows further on is a quarter of the banks further on
+constexpr int LC = NATOM * 16 + 4;
+constexpr int RED_ROWS = MA * 16;
+static_assert(K >= KC && NT == 64 * KWAVES && KWAVES <= NSTEP && KSPLIT == 1, "decoder and template disagree");
+static_assert(KWAVES * (PART * 2 > RED_ROWS * LC * 4 ? PART * 2 : RED_ROWS * LC * 4) == LDS_BYTES, "decoder and template disagree");
+
+#define GLOBAL __attribute__((address_space(1)))
+typedef GLOBAL u32x4_a2 g_u32x4;
+typedef GLOBAL u16 g_u16;
+// base (in scalar registers, and left there) + a lane's byte offset
+template <typename T>
+__device__ __forceinline__ auto load_at(const u16 *base, u32 off)
+{
+    const GLOBAL char *p = (const GLOBAL char *)base;
+    asm("" : "+s"(p));
+    return *(const T *)(p + off);
+}
+// Operands of k rows with pieces that begin at odd elements.  A 16-byte load that is not 4-byte aligned takes the load unit 68 cycles a wave instead of 19
+// (8-byte aligned: 19 - 22, measured from L1 and L2), so such a piece is loaded from one element to the left, its last element by a load of its own (9
+// cycles), and shifted by half a word when it is stored: 100 x 5439 x 1056 in 50 x 21 15.5 -> 11.1 us.  Not the k-contiguous rows of four pieces, where the
+// single elements cost as much as they spare (162 x 2100 x 2079 in 54 x 60 10.2 us without and 12.8 with, 200 x 6880 x 2275 in 50 x 32 32.5 and 39.7).
+constexpr bool ODD_A = A_TRANS && (M % 2 != 0 || (BM % 2 != 0 && M > BM)), ODD_B = N % 2 != 0 || (BN % 2 != 0 && N > BN);
+template <int Q, bool ODD> struct Pieces16 { u32x4 v[Q]; u32 e[ODD ? Q : 1]; };
+struct Step { Pieces16<QA, ODD_A> a; Pieces16<QB, ODD_B> b; };
+// a lane's pieces: element offset from the step's first position (ODD: plus the parity of that position), LDS element
+struct Places { u32 ga[QA], gb[QB], sa[QA], sb[QB]; };
+
+__device__ __forceinline__ void place_kr(u32 &g, u32 &s, int q, int pieces, int c, int len, int ld)
+{
+    if (q >= pieces) q = 0;
+    g = (u32)(q / c * len + q % c * 8);
+    s = (u32)(kr_off(ld, q / c) + q % c * 8);
+}
+// Operand's pieces from element `from` of it on.  back: in the step that ends with the operand, the last piece of an operand as wide as the tile, no multiple of
+// 8, would reach that far past its end: it is loaded from further left and shifted.
+template <int Q, bool ODD>
+__device__ __forceinline__ void load_pieces(Pieces16<Q, ODD> &r, const u32 (&g)[Q], const u16 *operand, long from, int last_lane, int back)
+{
+    const u32 odd = ODD ? (u32)from & 1u : 0u;
+    const u16 *base = operand + (from - odd);
+#pragma unroll
+    for (int i = 0; i < Q; ++i) {
+        u32 at = g[i] + odd;
+        if (back > 0 && i == Q - 1 && last_lane >= 0) at -= (int)(threadIdx.x & 63) == last_lane ? back : 0;
+        r.v[i] = load_at<g_u32x4>(base, 2u * (ODD ? at & ~1u : at));
+        if (ODD) r.e[i] = load_at<g_u16>(base, 2u * at + 14u);
+    }
+}
+template <int Q, bool ODD>
+__device__ __forceinline__ void store_pieces(const Pieces16<Q, ODD> &r, const u32 (&g)[Q], const u32 (&s)[Q], u16 *S, int pieces, long from, int lane, int last_lane, int back)
+{
+#pragma unroll
+    for (int i = 0; i < Q; ++i) {
+        u32x4 v = r.v[i];
+        int shift_by = 0;
+        if (back > 0 && i == Q - 1 && last_lane >= 0) shift_by = lane == last_lane ? back : 0;
+        if (ODD) {
+            const u32 sh = ((g[i] + (u32)from - shift_by) & 1u) << 4;
+            v.x = __builtin_amdgcn_alignbit(v.y, v.x, sh); v.y = __builtin_amdgcn_alignbit(v.z, v.y, sh);
+            v.z = __builtin_amdgcn_alignbit(v.w, v.z, sh); v.w = __builtin_amdgcn_alignbit(r.e[i], v.w, sh);
+        }
+        if (back > 0 && i == Q - 1 && last_lane >= 0) v = shift_down(v, shift_by);
+        if ((i + 1) * 64 <= pieces || lane + i * 64 < pieces) *(u32x4 *)(S + s[i]) = v;
+    }
+}
+// the first reduction position of step s, and how far the last piece of its operands reaches past their ends
+constexpr int BACK_A = A_TRANS && M < 8 * CM ? 8 * CM - M : 0, BACK_B = N < 8 * CN ? 8 * CN - N : 0;
+struct From { long a, b; int end_a, end_b; };
+__device__ __forceinline__ From from_of(long a0, long b0, int s)
+{
+    const bool last = s == NSTEP - 1;
+    const long k0 = last ? K - KC : s * KC;
+    const From f = {a0 + (A_TRANS ? k0 * M : k0), b0 + k0 * N, last ? (PA - 1) % 64 : -1, last ? (PB - 1) % 64 : -1};
+    return f;
+}
+__device__ __forceinline__ void load_step(Step &r, const Places &p, const u16 *A, const u16 *B, const From &f)
+{
+    load_pieces<QA, ODD_A>(r.a, p.ga, A, f.a, f.end_a, BACK_A);
+    load_pieces<QB, ODD_B>(r.b, p.gb, B, f.b, f.end_b, BACK_B);
+}
+__device__ __forceinline__ void store_step(const Step &r, const Places &p, u16 *As, u16 *Bs, const From &f, int lane)
+{
+    store_pieces<QA, ODD_A>(r.a, p.ga, p.sa, As, PA, f.a, lane, f.end_a, BACK_A);
+    store_pieces<QB, ODD_B>(r.b, p.gb, p.sb, Bs, PB, f.b, lane, f.end_b, BACK_B);
+}
+template <bool MASK>
+__device__ __forceinline__ void multiply_step(f32x4 (&acc)[MA][NATOM], const u16 *As, const u16 *Bs, int lane)
+{
+    u32x4 keep;                                      // (the last step) which of the lane's 8 positions have not been added yet
+#pragma unroll
+    for (int d = 0; d < 4; ++d) keep[d] = (lane / 16 * 8 + 2 * d >= DUP ? 0xffffu : 0u) | (lane / 16 * 8 + 2 * d + 1 >= DUP ? 0xffff0000u : 0u);
+    auto masked = [&](frag_t f) { return MASK ? __builtin_bit_cast(frag_t, __builtin_bit_cast(u32x4, f) & keep) : f; };
+    frag_t af[MA];
+#pragma unroll
+    for (int i = 0; i < MA; ++i)
+#if A_TRANS
+        af[i] = masked(kr_frag<LA>(As, i * 16, lane));
+#else
+        af[i] = masked(__builtin_bit_cast(frag_t, *(const u32x4 *)(As + (i * 16 + lane % 16) * LA + lane / 16 * 8)));
+#endif
+#pragma unroll
+    for (int j = 0; j < NATOM; ++j) {
+        const frag_t bf = masked(kr_frag<LB>(Bs, j * 16, lane));
+#pragma unroll
+        for (int i = 0; i < MA; ++i) acc[i][j] = MFMA(af[i], bf, acc[i][j]);
+    }
+}
+
+extern "C" __global__ __launch_bounds__(NT, MINW)
+void KERNEL_NAME(const u16 *__restrict__ A, const u16 *__restrict__ B, float *__restrict__ C,
+                 unsigned long long *ctl /* unused: members of this template are never folded */)
+{
+    extern __shared__ __attribute__((aligned(16))) u16 smem[];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    u16 *const As = smem + wave * PART, *const Bs = As + A_PART;
+    const BlockId bid = block_id();
+    // a tile whose pieces would reach past the row's end begins further left; its first columns are computed and not stored
+    const int m0 = bid.m * BM, n0 = bid.n * BN;
+    const int ms = A_TRANS && M >= 8 * CM ? min(m0, M - 8 * CM) : m0, ns = N >= 8 * CN ? min(n0, N - 8 * CN) : n0;
+    const int s0 = NSTEP * wave / KWAVES, s1 = NSTEP * (wave + 1) / KWAVES;
+    Places p;
+#pragma unroll
+    for (int i = 0; i < QA; ++i) {
+#if A_TRANS
+        place_kr(p.ga[i], p.sa[i], lane + i * 64, PA, CM, M, LA);
+#else
+        const int q = lane + i * 64 < PA ? lane + i * 64 : 0;
+        p.ga[i] = (u32)(q / (KC / 8) * K + q % (KC / 8) * 8);
+        p.sa[i] = (u32)(q / (KC / 8) * LA + q % (KC / 8) * 8);
+#endif
+    }
+#pragma unroll
+    for (int i = 0; i < QB; ++i) place_kr(p.gb[i], p.sb[i], lane + i * 64, PB, CN, N, LB);
+
+    for (int bi = 0; bi < BATCH_INNER; ++bi) {
+        const long batch = (long)bid.b * BATCH_INNER + bi;
+        const long a0 = batch * M * K + (A_TRANS ? (long)ms : (long)m0 * K), b0 = batch * K * N + ns;
+        float *Cb = C + batch * M * N + (long)m0 * N + n0;
+        f32x4 acc[MA][NATOM];
+#pragma unroll
+        for (int i = 0; i < MA; ++i)
+#pragma unroll
+            for (int j = 0; j < NATOM; ++j)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) acc[i][j][r] = 0.f;
+        Step step;
+        load_step(step, p, A, B, from_of(a0, b0, s0));
+        // (a loop-carried value that is a load on every way in becomes a load at its use)
+#pragma unroll
+        for (int i = 0; i < QA; ++i) { asm volatile("" : "+v"(step.a.v[i])); if (ODD_A) asm volatile("" : "+v"(step.a.e[ODD_A ? i : 0])); }
+#pragma unroll
+        for (int i = 0; i < QB; ++i) { asm volatile("" : "+v"(step.b.v[i])); if (ODD_B) asm volatile("" : "+v"(step.b.e[ODD_B ? i : 0])); }
+        if (bi > 0) __syncthreads();                  // the previous batch's sums have been read
+#pragma unroll 1
+        for (int s = s0; s < s1 - 1; ++s) {
+            store_step(step, p, As, Bs, from_of(a0, b0, s), lane);
+            load_step(step, p, A, B, from_of(a0, b0, s + 1));
+            __builtin_amdgcn_sched_barrier(0);
+            multiply_step<false>(acc, As, Bs, lane);
+        }
+        store_step(step, p, As, Bs, from_of(a0, b0, s1 - 1), lane);
+        if (DUP > 0 && wave == KWAVES - 1) multiply_step<true>(acc, As, Bs, lane);
+        else multiply_step<false>(acc, As, Bs, lane);
+
+        // The waves' sums meet in LDS, every wave's as rows of the tile; then the threads walk the tile's rows.
+        __syncthreads();
+        float *const red = (float *)smem;
+        {
+            float *const mine = red + wave * (RED_ROWS * LC) + lane / 16 * 4 * LC + lane % 16;
+#pragma unroll
+            for (int i = 0; i < MA; ++i)
+#pragma unroll
+                for (int j = 0; j < NATOM; ++j)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) mine[(i * 16 + r) * LC + j * 16] = acc[i][j][r];
+        }
+        __syncthreads();
+        const float *const from = red + (m0 - ms) * LC + (n0 - ns);
+#pragma unroll 2
+        for (int e = tid; e < BM * BN; e += NT) {
+            const int row = e / BN, col = e % BN;
+            float sum = from[row * LC + col];
+#pragma unroll
+            for (int w = 1; w < KWAVES; ++w) sum += from[w * (RED_ROWS * LC) + row * LC + col];
+            Cb[(long)row * N + col] = sum;
+        }
+    }
+}
+#else
 // Where a thread's pieces come from and go to, worked out once: recomputed for every slab, the places cost more vector instructions
 // than the slab has of all other kinds (1000^3 in tiles of 20 x 100: 210 of 230 in its loop).
 //   g: byte offset from the operand at the slab's first reduction position.
@@ -419,3 +641,5 @@ void KERNEL_NAME(const u16 *__restrict__ A, const u16 *__restrict__ B, float *__
             }
     }
 }
+
+#endif
