@@ -437,8 +437,9 @@ int opevo_mfma_ceiling_atom(int in_dtype, int random_data, int atom, void *strea
 
 /* Parity gate: c and ref are DEVICE fp32 arrays of n elements.
  * max_scaled = max |c-ref| / (|ref|+1), rel_fro = ||c-ref||_F / ||ref||_F (0 if both 0).
- * Uses a library-owned workspace (device memory and two words of pinned host memory, allocated on first
- * use, one for every call under way at the same time, at most 8 kept per device). Synchronises `stream`. */
+ * Uses a library-owned workspace (device memory and three words of pinned host memory, allocated on first
+ * use, one for every call under way at the same time, at most 8 kept per device). Returns when the comparison, and with it
+ * everything enqueued on `stream` before it, has finished. */
 int opevo_compare_f32(const float *c, const float *ref, int64_t n, void *stream,
                       double *max_scaled, double *rel_fro);
 
@@ -450,7 +451,7 @@ int opevo_compare_rows_f32(const float *c, const float *ref_rows, const int32_t 
                            double *max_scaled, double *rel_fro);
 
 /* opevo_compare_f32 for callers that cannot allocate (code under HIP graph capture, tight serving
- * loops, harnesses that forbid hipMalloc): the same comparison with the same two kernels, but the
+ * loops, harnesses that forbid hipMalloc): the same comparison with the same kernels, but the
  * per-workgroup partial results live in a fixed array of 24 KiB of device memory that is part of the
  * library's code object (one copy per GPU, held until the process ends), and nothing is copied back:
  * result is a DEVICE pointer to two doubles that receive {max_scaled, rel_fro}, valid once the

@@ -5,8 +5,10 @@
 // Any NaN in c makes max_scaled infinite, so a broken kernel can never pass.
 #include <hip/hip_runtime.h>
 
+#include <chrono>
 #include <cmath>
 #include <cstdint>
+#include <cstring>
 #include <mutex>
 #include <vector>
 
@@ -25,6 +27,10 @@ typedef float f32x4_t __attribute__((ext_vector_type(4)));
 constexpr int kBlocks = 1024;
 static_assert(sizeof(scratch) == sizeof(double) * 3 * kBlocks, "scratch holds one triple per workgroup");
 constexpr int kThreads = 256;
+// Comparisons of at most this many elements, one pass of a workgroup, run as a single workgroup without a second kernel (1000 elements 13.5 us with two and 11.5 with one, 5000
+// 13.5 and 12.5; 16384, four passes: 13.5 and 14.0, 32768 17.3).
+constexpr int kSmallThreads = 1024;
+constexpr int64_t kSmall = 4 * kSmallThreads;
 
 // What one lane has seen of a comparison.  `seen` is the largest scaled error of the whole wave as of its last batch
 // (a hair below it, so that rounding in the test cannot hide a larger one).
@@ -57,6 +63,33 @@ __device__ __forceinline__ void compare_batch(const float (&c)[NV], const float 
     }
 }
 
+// Where a comparison leaves its result: [0] = max_scaled, [1] = rel_fro.  done (or NULL): host memory, set to `ticket` once both can be read there.
+struct CompareOut { double *result; unsigned long long *done, ticket; };
+
+// The triples of a workgroup's threads, folded into thread 0's in a fixed order.
+template <int THREADS>
+__device__ __forceinline__ void fold(double &mx, double &se, double &sr)
+{
+    __shared__ double smx[THREADS], sse[THREADS], ssr[THREADS];
+    smx[threadIdx.x] = mx; sse[threadIdx.x] = se; ssr[threadIdx.x] = sr;
+    __syncthreads();
+    for (int s = THREADS / 2; s > 0; s >>= 1) {
+        if (threadIdx.x < s) {
+            smx[threadIdx.x] = fmax(smx[threadIdx.x], smx[threadIdx.x + s]);
+            sse[threadIdx.x] += sse[threadIdx.x + s];
+            ssr[threadIdx.x] += ssr[threadIdx.x + s];
+        }
+        __syncthreads();
+    }
+    mx = smx[0]; se = sse[0]; sr = ssr[0];
+}
+__device__ __forceinline__ void finish(const CompareOut &out, double mx, double se, double sr)
+{
+    out.result[0] = mx;
+    out.result[1] = sr > 0.0 ? sqrt(se / sr) : (se > 0.0 ? INFINITY : 0.0);
+    if (out.done) __hip_atomic_store(out.done, out.ticket, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
 __device__ __forceinline__ void load_vec(float (&v)[4], const float *p) { const f32x4_t t = *(const f32x4_t *)p; v[0] = t.x; v[1] = t.y; v[2] = t.z; v[3] = t.w; }
 __device__ __forceinline__ void load_vec(float (&v)[1], const float *p) { v[0] = *p; }
 
@@ -68,19 +101,20 @@ __device__ __forceinline__ void load_vec(float (&v)[1], const float *p) { v[0] =
 // 111 us, launch and wait for the result included (5.1 TB/s; a large copy moves 4.8); with one 4-byte pair per lane, a 64-bit division
 // per element, a copy back and a fold on the host it was 201 us, and 24 KB took 25 us instead of 19.  Where the rows are sampled, a lane's place moves by the
 // same number of rows and columns every step: no division by row_len per element.
-template <int V, bool ROWS>
-__global__ __launch_bounds__(kThreads)
+// THREADS = kSmallThreads: a single workgroup, which finishes the comparison itself; otherwise one of several, which leaves its triple in part.
+template <int V, bool ROWS, int THREADS>
+__global__ __launch_bounds__(THREADS)
 void compare_partial(const float *__restrict__ c, const float *__restrict__ ref, long n, const int *__restrict__ rows,
-                     long row_len, long drow, long dcol /* rows and columns a lane moves by per step */, double *__restrict__ part)
+                     long row_len, long drow, long dcol /* rows and columns a lane moves by per step */, double *__restrict__ part, CompareOut out)
 {
     constexpr int U = 4;
     CompareAcc a = {0.0, 0.0, 0.0, 0.0};
-    const long step = (long)gridDim.x * kThreads, first = (long)blockIdx.x * kThreads + threadIdx.x, pieces = n / V;
+    const long step = (long)gridDim.x * THREADS, first = (long)blockIdx.x * THREADS + threadIdx.x, pieces = n / V;
     long row = 0, col = 0;
     if (ROWS) { row = first * V / row_len; col = first * V % row_len; }
     // The loop runs for whole workgroups (compare_batch looks across the lanes of a wave): a lane past the end takes
     // zeros for both values, which count for nothing.
-    for (long base = (long)blockIdx.x * kThreads; base < pieces; base += U * step) {
+    for (long base = (long)blockIdx.x * THREADS; base < pieces; base += U * step) {
         float cv[U][V], rv[U][V];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
@@ -105,28 +139,20 @@ void compare_partial(const float *__restrict__ c, const float *__restrict__ ref,
         compare_batch<1>(cv, rv, a);
     }
     double mx = a.mx, se = a.se, sr = a.sr;
-    __shared__ double smx[kThreads], sse[kThreads], ssr[kThreads];
-    smx[threadIdx.x] = mx; sse[threadIdx.x] = se; ssr[threadIdx.x] = sr;
-    __syncthreads();
-    for (int s = kThreads / 2; s > 0; s >>= 1) {
-        if (threadIdx.x < s) {
-            smx[threadIdx.x] = fmax(smx[threadIdx.x], smx[threadIdx.x + s]);
-            sse[threadIdx.x] += sse[threadIdx.x + s];
-            ssr[threadIdx.x] += ssr[threadIdx.x + s];
-        }
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) {
-        part[blockIdx.x * 3 + 0] = smx[0];
-        part[blockIdx.x * 3 + 1] = sse[0];
-        part[blockIdx.x * 3 + 2] = ssr[0];
+    fold<THREADS>(mx, se, sr);
+    if (threadIdx.x != 0) return;
+    if (THREADS == kSmallThreads) {
+        finish(out, mx, se, sr);
+    } else {
+        part[blockIdx.x * 3 + 0] = mx;
+        part[blockIdx.x * 3 + 1] = se;
+        part[blockIdx.x * 3 + 2] = sr;
     }
 }
 
-// Finishes a comparison on the device: one workgroup folds the per-workgroup partials (always in the same order) and
-// writes result[0] = max_scaled, result[1] = rel_fro.
+// Finishes a comparison on the device: one workgroup folds the per-workgroup partials (always in the same order).
 __global__ __launch_bounds__(kThreads)
-void compare_finish(const double *__restrict__ part, int blocks, double *__restrict__ result)
+void compare_finish(const double *__restrict__ part, int blocks, CompareOut out)
 {
     double mx = 0.0, se = 0.0, sr = 0.0;
     for (int b = threadIdx.x; b < blocks; b += kThreads) {
@@ -134,21 +160,8 @@ void compare_finish(const double *__restrict__ part, int blocks, double *__restr
         se += part[b * 3 + 1];
         sr += part[b * 3 + 2];
     }
-    __shared__ double smx[kThreads], sse[kThreads], ssr[kThreads];
-    smx[threadIdx.x] = mx; sse[threadIdx.x] = se; ssr[threadIdx.x] = sr;
-    __syncthreads();
-    for (int s = kThreads / 2; s > 0; s >>= 1) {
-        if (threadIdx.x < s) {
-            smx[threadIdx.x] = fmax(smx[threadIdx.x], smx[threadIdx.x + s]);
-            sse[threadIdx.x] += sse[threadIdx.x + s];
-            ssr[threadIdx.x] += ssr[threadIdx.x + s];
-        }
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) {
-        result[0] = smx[0];
-        result[1] = ssr[0] > 0.0 ? sqrt(sse[0] / ssr[0]) : (sse[0] > 0.0 ? INFINITY : 0.0);
-    }
+    fold<kThreads>(mx, se, sr);
+    if (threadIdx.x == 0) finish(out, mx, se, sr);
 }
 
 // Deadline control block of the scalar template: {start tick, allowed ticks, expired flag}.
@@ -290,30 +303,35 @@ double g_ticks_per_ms[64] = {0.0};
 
 namespace opevo {
 
-// Both kernels of a comparison on `stream`: part holds 3 doubles for each of kBlocks workgroups, result 2 doubles (device
-// memory, or host memory the device can write).
+// The kernels of a comparison on `stream`: part holds 3 doubles for each of kBlocks workgroups; out.result is 2 doubles of device
+// memory, or of host memory the device can write.
 static int enqueue_compare(const float *c, const float *ref, int64_t n, const int *rows, int64_t row_len,
-                           hipStream_t stream, double *part, double *result)
+                           hipStream_t stream, double *part, const CompareOut &out)
 {
     const bool vec = reinterpret_cast<uintptr_t>(c) % 16 == 0 && reinterpret_cast<uintptr_t>(ref) % 16 == 0 &&
                      (!rows || row_len % 4 == 0);
-    const int64_t per_block = int64_t(kThreads) * (vec ? 4 : 1);
-    const int blocks = int(std::max<int64_t>(1, std::min<int64_t>(kBlocks, (n + per_block - 1) / per_block)));
-    auto *k = vec ? (rows ? compare_partial<4, true> : compare_partial<4, false>)
-                  : (rows ? compare_partial<1, true> : compare_partial<1, false>);
+    const bool small = n <= kSmall;
+    const int threads = small ? kSmallThreads : kThreads;
+    const int64_t per_block = int64_t(threads) * (vec ? 4 : 1);
+    const int blocks = small ? 1 : int(std::max<int64_t>(1, std::min<int64_t>(kBlocks, (n + per_block - 1) / per_block)));
+    auto *k = small ? (vec ? (rows ? compare_partial<4, true, kSmallThreads> : compare_partial<4, false, kSmallThreads>)
+                           : (rows ? compare_partial<1, true, kSmallThreads> : compare_partial<1, false, kSmallThreads>))
+                    : (vec ? (rows ? compare_partial<4, true, kThreads> : compare_partial<4, false, kThreads>)
+                           : (rows ? compare_partial<1, true, kThreads> : compare_partial<1, false, kThreads>));
     const int64_t step = int64_t(blocks) * per_block;
-    hipLaunchKernelGGL(k, dim3(blocks), dim3(kThreads), 0, stream, c, ref, (long)n, rows, (long)row_len,
-                       (long)(step / row_len), (long)(step % row_len), part);
+    hipLaunchKernelGGL(k, dim3(blocks), dim3(threads), 0, stream, c, ref, (long)n, rows, (long)row_len,
+                       (long)(step / row_len), (long)(step % row_len), part, out);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return hip_fail(e, "compare_partial launch");
-    hipLaunchKernelGGL(compare_finish, dim3(1), dim3(kThreads), 0, stream, (const double *)part, blocks, result);
+    if (small) return OPEVO_OK;
+    hipLaunchKernelGGL(compare_finish, dim3(1), dim3(kThreads), 0, stream, (const double *)part, blocks, out);
     e = hipGetLastError();
     return e == hipSuccess ? OPEVO_OK : hip_fail(e, "compare_finish launch");
 }
 
-// What a comparison that returns to the host needs: partials on the device and two doubles of pinned host memory that
-// the device writes (no copy back).  One per comparison under way on a device; kept for the next one, at most kSpare of them.
-struct CompareWorkspace { double *part = nullptr, *result = nullptr; };
+// What a comparison that returns to the host needs: partials on the device, and pinned host memory that the device writes (no copy back): two
+// doubles and the ticket of the comparison that wrote them.  One per comparison under way on a device; kept for the next one, at most kSpare of them.
+struct CompareWorkspace { double *part = nullptr, *result = nullptr; unsigned long long ticket = 0; };
 static constexpr size_t kSpare = 8;
 static std::vector<CompareWorkspace> g_spare[64];
 
@@ -322,6 +340,21 @@ static void release(CompareWorkspace &w)
     if (w.part) (void)hipFree(w.part);
     if (w.result) (void)hipHostFree(w.result);
     w = CompareWorkspace();
+}
+
+// Looks at a word of pinned host memory until the device has written `ticket` there, for at most 0.2 ms: a short comparison is known to be
+// finished that much sooner than through the runtime, which waits for the end of the stream's last kernel to be signalled (65536 elements 18.4 us a
+// comparison through the runtime and 13.6 so, 2 M 24.5 and 19.5, 71.7 M 116 and 111).  False: ask the runtime (earlier work on the stream takes long, or has failed).
+static bool wait_for(const unsigned long long *word, unsigned long long ticket)
+{
+    const auto until = std::chrono::steady_clock::now() + std::chrono::microseconds(200);
+    for (;;) {
+        for (int i = 0; i < 64; ++i) {
+            if (__atomic_load_n(word, __ATOMIC_ACQUIRE) == ticket) return true;
+            __builtin_ia32_pause();
+        }
+        if (std::chrono::steady_clock::now() >= until) return false;
+    }
 }
 
 int compare_f32(const float *c, const float *ref, int64_t n, const int *rows, int64_t row_len,
@@ -342,11 +375,14 @@ int compare_f32(const float *c, const float *ref, int64_t n, const int *rows, in
     }
     if (!w.part) {
         e = hipMalloc(&w.part, sizeof(double) * 3 * kBlocks);
-        if (e == hipSuccess) e = hipHostMalloc(&w.result, sizeof(double) * 2, hipHostMallocDefault);
+        if (e == hipSuccess) e = hipHostMalloc(&w.result, sizeof(double) * 3, hipHostMallocDefault);
         if (e != hipSuccess) { release(w); return hip_fail(e, "compare workspace"); }
+        std::memset(w.result, 0, sizeof(double) * 3);
     }
-    int rc = enqueue_compare(c, ref, n, rows, row_len, stream, w.part, w.result);
-    if (rc == OPEVO_OK) {
+    unsigned long long *const done = reinterpret_cast<unsigned long long *>(w.result + 2);
+    const CompareOut out = {w.result, done, ++w.ticket};
+    int rc = enqueue_compare(c, ref, n, rows, row_len, stream, w.part, out);
+    if (rc == OPEVO_OK && !wait_for(done, out.ticket)) {
         e = hipStreamSynchronize(stream);
         if (e != hipSuccess) rc = hip_fail(e, "hipStreamSynchronize");
     }
@@ -385,7 +421,8 @@ int compare_f32_static(const float *c, const float *ref, int64_t n, hipStream_t 
     if (int rc = static_scratch(&ws)) return rc;
     // every workgroup overwrites its own three partials and the fold reads only those of the workgroups launched,
     // so nothing left in the array by an earlier call is ever read: no clearing needed
-    return enqueue_compare(c, ref, n, nullptr, 1, stream, ws, result_dev);
+    const CompareOut out = {result_dev, nullptr, 0};
+    return enqueue_compare(c, ref, n, nullptr, 1, stream, ws, out);
 }
 
 int deadline_ctl(unsigned long long **ctl)
