@@ -14,8 +14,10 @@
 //     piece shifted, 512 x 3 x 227 x 227 below took 233 us; now 205.
 //     A fragment is 16 bytes at x*STRIDE elements.  With an odd stride every second pixel starts at an odd element; those read a second copy
 //     of the patch that lies one element further left (NCOPY = 2), so that every fragment is at least 4-byte aligned.
-//   * The kernel tensor never enters the LDS: every wave keeps the fragments of its own output channels for the whole reduction in
-//     registers (STEPS x MI of them).
+//   * Every wave keeps the kernel tensor's fragments of its own output channels for the whole reduction in registers (STEPS x MI of them).  They come
+//     through the LDS where that has room (STAGE_A): the workgroup's rows are one run of memory, loaded by consecutive lanes and picked apart
+//     there.  Straight from memory every lane of a fragment's load is in a cache line of its own, 68 cycles of the load unit each, for
+//     33 of them 60 % of what one box of 11 x 11 taps took (5 x 3 x 64 x 64 * 64 x 3 x 11 x 11, stride 2: 12.9 -> 7.0 us; 99 x 3 x 56 x 56 * 64 x 3 x 5 x 5 35.0 -> 26.5).
 //   * Taps past the kernel's width (and kernel rows past its height, where a step takes several) are zeros in the kernel tensor's
 //     fragments AND are cleared in the image's: what the patch holds there are other pixels, which may be infinite.
 // Measured: 512 x 3 x 227 x 227 * 64 x 3 x 11 x 11, stride 4, bf16 (boxes of 4 images x 55 pixels): 980 us on the register-staged template (73
@@ -142,6 +144,46 @@ void KERNEL_NAME(const u16 *__restrict__ A, const u16 *__restrict__ B, float *__
     }
     // the kernel tensor's fragments: lane = output channel, 8 taps from (ci, r, s0)
     frag_t af[MI][STEPS];
+#if STAGE_A
+    {
+#if STAGE_A == 1   // where the patch will be
+        u16 *const rows = smem;
+#else
+        __shared__ __attribute__((aligned(16))) u16 rows[BM * K + 128];
+#endif
+        constexpr int PIECES = BM * K / 8, NP = (PIECES + NT - 1) / NT, AT_ONCE = NP < 16 ? NP : 16;
+        const u32x4_a2 *const from = (const u32x4_a2 *)(A + (long)m0 * K);
+        for (int p0 = 0; p0 < NP; p0 += AT_ONCE) {
+            u32x4 v[AT_ONCE];
+#pragma unroll
+            for (int i = 0; i < AT_ONCE; ++i) v[i] = from[min(tid + (p0 + i) * NT, PIECES - 1)];
+#pragma unroll
+            for (int i = 0; i < AT_ONCE; ++i)
+                if (tid + (p0 + i) * NT < PIECES) ((u32x4 *)rows)[tid + (p0 + i) * NT] = v[i];
+        }
+        __syncthreads();
+        const int r0 = kg / Q, s0 = kg % Q * 8;
+#pragma unroll
+        for (int i = 0; i < MI; ++i) {
+            // Words from the one that holds the first tap; where that is the word's upper half, the fragment is half a word further on.  at + step is
+            // that word for an even number of taps before a step's, one further for an odd one where the lane's own first tap is odd.
+            const int first = ((wm * MI + i) * ATOM + lrow) * K + r0 * WK + s0, odd = first & 1;
+            const u32 *const at = (const u32 *)rows + (first >> 1);
+#pragma unroll
+            for (int t = 0; t < STEPS; ++t) {
+                const int step = (t / SPC * HK + t % SPC * RPS) * WK;
+                const u32 *const w = (step & 1 ? at + odd : at) + (step >> 1);
+                u32x4 v = {w[0], w[1], w[2], w[3]};
+                if (K % 2 != 0 || WK % 2 != 0) {
+                    const u32 sh = (u32)(odd ^ (step & 1)) << 4;
+                    v.x = __builtin_amdgcn_alignbit(v.y, v.x, sh); v.y = __builtin_amdgcn_alignbit(v.z, v.y, sh);
+                    v.z = __builtin_amdgcn_alignbit(v.w, v.z, sh); v.w = __builtin_amdgcn_alignbit(w[4], v.w, sh);
+                }
+                af[i][t] = __builtin_bit_cast(frag_t, keep_taps(v, mask, ROW_TAIL && t % SPC == SPC - 1));
+            }
+        }
+    }
+#else
     {
         const int r0 = kg / Q, s0 = kg % Q * 8;
 #pragma unroll
@@ -160,6 +202,7 @@ void KERNEL_NAME(const u16 *__restrict__ A, const u16 *__restrict__ B, float *__
             }
         }
     }
+#endif
     // this lane's places in the patch: per column of atoms its output pixel under tap (0, 0), plus its group of taps
     // (columns past the box read its last pixel and are not stored)
     int b_lane[NI];
