@@ -976,6 +976,13 @@ int decode(const opevo_op &op, int variant, const int32_t *cfg, Decoded &out, bo
         if (rg.keep != 1 && !spills) out.tries.push_back(" -DKEEP=0");
         out.tries.push_back(" -DKEEP=0 -DFRESH=1");
     }
+    // A patch: two slabs of global loads in flight instead of one where a slab's MFMAs are too few to cover its loads: kernel tensors of
+    // one tap, and up to nine taps on waves that share their tiles' steps in grids of one workgroup per compute unit.  One tap: 36 drawn
+    // members 0.97 - 1.26x, 1.09x in the geometric mean (88 x 256 x 27 x 27 * 128 x 256 33.6 -> 30.4 us, 6 x 256 x 27 x 27 * 192 x 256 8.2 -> 6.5,
+    // and the slowest 216 x 96 x 13 x 13 * 192 x 96 13.3 -> 13.7); shared tiles 30 members 1.02 - 1.17x, 1.09x (40 x 256 x 7 x 7 * 96 x 256 x 3 x 3
+    // 12.2 -> 10.7).  The same with 25 taps 0.93 - 1.13x, five larger grids 0.77 - 1.06x, 22 members that share nothing 0.85 - 1.03x, 0.94x.
+    if (path == 5 && !strip.rows && nstage == 2 && ksteps >= 3 && (op.hk * op.wk == 1 || (patch_kw > 1 && op.hk * op.wk <= 9 && n_blocks <= 256)))
+        out.tries = {" -DSLABS_AHEAD=2", ""};
     // fp32, two stages: the pipelined slab loop, but for short reductions on a full chip, where the other workgroups cover a
     // slab's latency and the registers are better spent on them (a batch of 960 of 128 x 64 x 128 with the first operand transposed:
     // 960 x 4 waves, 4 slabs, 27.0 us without and 29.9 with; 132 x 64 x 224 x 128, 924 x 2 waves, 2 slabs, 16.2 and 13.9).  Against the

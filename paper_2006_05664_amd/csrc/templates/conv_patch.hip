@@ -75,6 +75,9 @@ constexpr int DUMP = 64;                                      // elements at the
 constexpr int P_STAGE = NPIX * PITCH, A_STAGE = T * BM * CS, STAGE = P_STAGE + A_STAGE + DUMP;   // elements
 constexpr int MI = TM / ATOM, NI = (TN + ATOM - 1) / ATOM;    // atoms per wave tile (the last column of atoms may hang over)
 constexpr int KK = CS / KA;                                   // MFMA steps per tap
+#ifndef SLABS_AHEAD
+#define SLABS_AHEAD 1                                         // slabs whose global loads are in flight while one is multiplied (FLAG = 1)
+#endif
 #ifndef KW
 #define KW 1                                                  // waves that share a wave tile and split the reduction steps of every slab
 #endif
@@ -172,6 +175,18 @@ __device__ __forceinline__ void load_slab(Regs &r, const Fill &f, const u16 *__r
     for (int i = 0; i < NAT; ++i)
 #pragma unroll
         for (int t = 0; t < T; ++t) r.a[i][t] = *(const u32 *)(As + f.ag[i] + 4 * t);
+}
+
+// The registers stay what a loop carries from one pass to the next (the compiler would otherwise carry the addresses and
+// load where the values are used).
+__device__ __forceinline__ void pin(Regs &r)
+{
+#pragma unroll
+    for (int i = 0; i < NPT; ++i) asm volatile("" : "+v"(r.p[i][0]), "+v"(r.p[i][1]));
+#pragma unroll
+    for (int i = 0; i < NAT; ++i)
+#pragma unroll
+        for (int t = 0; t < T; ++t) asm volatile("" : "+v"(r.a[i][t]));
 }
 
 // S = the stage as 4-byte words (the patch part is first, the kernel-tensor part follows)
@@ -334,8 +349,33 @@ void KERNEL_NAME(const u16 *__restrict__ A, const u16 *__restrict__ B, float *__
 #if FLAG
     // Two stages: while slab s is multiplied the loads of slab s+1 are in flight; they are written to the other stage
     // afterwards (one barrier per slab).  Branch-free body (the loads must not sink below the MFMAs): past the last slab
-    // the last one is loaded and stored once more, into the stage nobody reads any longer.  (Loading two slabs ahead
-    // into a second register set was measured: no faster, and the registers cost members their place on this template.)
+    // the last one is loaded and stored once more, into the stage nobody reads any longer.
+#if SLABS_AHEAD == 2
+    // The loads of slab s+2 as well, into a second set of registers: for slabs with few MFMAs for every wave, whose loads
+    // take longer than they do (128 channels in slabs of 16, one tap, 27 x 27 pixels, 72 workgroups: 5.2 -> 4.4 us).
+    Regs regs1;
+    load_slab(regs1, fill, A, B, KSTEPS > 1 ? 1 : 0);
+    pin(regs);
+    pin(regs1);
+    __syncthreads();                                   // the zeros are in place
+    store_slab(regs, fill, (u32 *)smem);
+    __syncthreads();
+    const auto step = [&](int s, Regs &far, const Regs &near) {
+        u16 *cur = smem + (s & 1) * STAGE, *nxt = smem + (NSTG == 2 ? (s + 1) & 1 : 0) * STAGE;
+        load_slab(far, fill, A, B, s + 2 < KSTEPS ? s + 2 : KSTEPS - 1);
+        __builtin_amdgcn_sched_barrier(0);
+        compute_slab(acc, cur + P_STAGE, cur, al, b_lane, wk);
+        __builtin_amdgcn_sched_barrier(0);
+        if (NSTG == 2) store_slab(near, fill, (u32 *)nxt);
+        __syncthreads();
+    };
+#pragma unroll 1
+    for (int s = 0; s < KSTEPS / 2 * 2; s += 2) {
+        step(s, regs, regs1);
+        step(s + 1, regs1, regs);
+    }
+    if (KSTEPS % 2) step(KSTEPS - 1, regs, regs1);
+#else
     __syncthreads();                                   // the zeros are in place
     store_slab(regs, fill, (u32 *)smem);
     __syncthreads();
@@ -349,6 +389,7 @@ void KERNEL_NAME(const u16 *__restrict__ A, const u16 *__restrict__ B, float *__
         if (NSTG == 2) store_slab(regs, fill, (u32 *)nxt);
         __syncthreads();
     }
+#endif
 #else
 #pragma unroll 1
     for (int s = 0; s < KSTEPS; ++s) {
