@@ -830,6 +830,24 @@ int decode(const opevo_op &op, int variant, const int32_t *cfg, Decoded &out, bo
             if (2 * st * stage <= kMaxLds && nw * TM * TN * 4 <= 2 * st * stage && (2 * st - 2) * per <= 63 &&
                 !(dlds_atom16 && BK % 64 != 0 && st % 2 != 0)) { kgrp = 2; nstage_dlds = 2 * st; out.extra_waves = true; }
     }
+    // Grids of direct-to-LDS MatMul / BMM members that do not fit the chip at once, with eight waves or fewer on a compute unit: a ring of fewer stages leaves
+    // room for more workgroups, which hide a slab's latency as well as the slabs ahead do.  The most stages with which the grid does fit: 88 drawn members 0.91 - 1.46x,
+    // 1.12x in the geometric mean, three of them below 0.99 (1040 workgroups of two waves, 128 x 64, five slabs of 32: 11.7 -> 12.7 us).
+    // With two waves or fewer on a compute unit, if it does not fit with any, the most stages that give it more: 20 drawn members 1.07 -
+    // 1.40x, 1.22x (4544 x 3328 x 2112 in 64 x 128, two waves: 143 -> 104 us).  Three and more waves in grids that do
+    // not fit in any case: 0.84 - 1.17x, 1.04x; those keep the ring.
+    if (path == 3 && kgrp == 1 && op.kind != OPEVO_CONV2D && !dlds_atom16) {
+        const int64_t nw = WM * WN, stage = (BM + BN) * BK * 2, wgs = n1 * m1 * b1;
+        auto resident = [&](int st) { return std::min<int64_t>(kMaxLds / (st * stage), 32 / nw); };
+        const int64_t had = resident(nstage_dlds);
+        if (wgs > 256 * had && had * nw <= 8) {
+            int st = nstage_dlds;
+            while (st > 2 && wgs > 256 * resident(st)) --st;
+            if (wgs > 256 * resident(st) && had * nw <= 2)
+                for (st = nstage_dlds; st > 2 && (resident(st) == had || resident(st) * nw < 4); --st) {}
+            if (wgs <= 256 * resident(st) || (had * nw <= 2 && resident(st) > had)) nstage_dlds = st;
+        }
+    }
     // fp32 MatMul / BMM members with two stages, workgroup tiles of 32 or 64 rows and columns and long reductions: the template that takes values apart for the bf16
     // matrix pipes, its waves sharing the reduction.  From K = 320 on, 448 for tiles of 64 x 64, which pay for a longer final sum: 64 x 64 tiles at K = 320
     // 8.3 -> 9.1 us (34 workgroups) and 9.4 -> 10.3 (182), at 480 87.6 -> 81.6, at 512 12.8 -> 11.7; 32 x 64 at K = 320 23 -> 18.4, at 384 9.8 -> 6.7, at 256 12.9 -> 12.7; K of 64 to
