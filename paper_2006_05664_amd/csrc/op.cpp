@@ -783,7 +783,7 @@ int decode(const opevo_op &op, int variant, const int32_t *cfg, Decoded &out, bo
         TMacc = TM; TNacc = TN; BK = rg.ks; ksteps = rg.slabs;
         // Waves that share the reduction, each with the whole tile as its wave tile and a part of the LDS of its own, where no more than one workgroup falls on a compute unit:
         // eight, as far as the LDS goes.  60 drawn and random members of K >= 448 and up to 20 atoms against the slab walk: 0.93 - 2.9x, 1.6x in the geometric mean (480 x 360 x 4893,
-        // 90 workgroups, 29.5 -> 12.9 us; 40 x 100 x 2517, 8, 19.8 -> 7.5); below, 56 x 56 at K = 324 4.3 -> 4.6, 32 x 44 at 360 3.2 -> 3.4; with 500 workgroups of 20 x 100
+        // 90 workgroups, 29.8 -> 21.1 us; 40 x 100 x 2517, 8, 19.8 -> 7.5); below, 56 x 56 at K = 324 4.3 -> 4.6, 32 x 44 at 360 3.2 -> 3.4; with 500 workgroups of 20 x 100
         // at K = 1000 13.2 -> 13.4, with 860 of 50 x 32 32.0 -> 39.6.
         // Two waves on fuller grids where an operand's pieces begin at odd elements, which this loop shifts into place: 12 members of up to 1024 workgroups and 12 atoms 1.02 -
         // 2.0x, 1.4x in the mean (100 x 5439 x 1056 in 50 x 21 20.4 -> 11.1; 1078 workgroups 39.9 -> 41.6, 1125 23.9 -> 18.9, 1575 25.8 -> 26.0).

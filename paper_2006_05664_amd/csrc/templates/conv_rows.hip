@@ -21,8 +21,8 @@
 //   * Taps past the kernel's width (and kernel rows past its height, where a step takes several) are zeros in the kernel tensor's
 //     fragments AND are cleared in the image's: what the patch holds there are other pixels, which may be infinite.
 // Measured: 512 x 3 x 227 x 227 * 64 x 3 x 11 x 11, stride 4, bf16 (boxes of 4 images x 55 pixels): 980 us on the register-staged template (73
-// TFLOP/s: some ten instructions per gathered value), 198 - 215 us here with the output stored column by column, 184 us row by row (390 TFLOP/s, 3.0
-// TB/s).  What bounds it: 396 MB of output in rows of 220 bytes that begin anywhere in a cache line (alone, without fill and
+// TFLOP/s: some ten instructions per gathered value), here 198 - 215 us with the output stored column by column, 173 - 184 us row by row, and
+// 161 us with the kernel tensor through the LDS (450 TFLOP/s, 3.4 TB/s).  What bounds it: 396 MB of output in rows of 220 bytes that begin anywhere in a cache line (alone, without fill and
 // multiplication, 136 us column by column and 109 row by row; non-temporal stores take 386, a contiguous run of boxes per
 // workgroup 249), and that a box's load, multiplication and store follow one another, with two workgroups per compute unit.
 // PERSIST > 0: that many workgroups along the boxes, each taking several; the kernel tensor is then fetched once per workgroup.
