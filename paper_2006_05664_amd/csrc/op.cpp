@@ -586,8 +586,12 @@ int decode(const opevo_op &op, int variant, const int32_t *cfg, Decoded &out, bo
                 // pipelining and no sharing and deal their pixels to several waves, go to the row-strip template where it has a division
                 // (the others run the loop and the division that they ask for).  144 drawn members and 60 folded ones of 8 operators, old
                 // template against new: 1.20 - 1.26x in the geometric mean, 0.94 - 2.5x; what was below 0.94 is excluded by the conditions in plan_strip.
+                // Members that ask for pipelining go there too on more workgroups than compute units: the second stage costs them the other workgroups that would
+                // hide a slab's latency.  94 drawn and random members with three pixel waves and more 0.94 - 2.7x, 1.28x in the geometric mean (53 x 256 x 27 x 27 *
+                // 64 x 256 x 3 x 3 31.2 -> 26.5 us, 163 x 256 x 14 x 14 * 256 x 256 x 3 x 3 74.4 -> 53.3; the slowest 11 x 32 x 56 x 56 * 128 x 32 x 3 x 3 10.9 -> 11.5).  On fewer
+                // workgroups, and with two pixel waves, they keep the two-stage loop that they ask for.
                 const int64_t asked_n = int64_t(h[1]) * w[1], asked = c[3] * asked_n * int64_t(kReductionWaves[c[18]]);
-                if (extras && patch_cs && (asked > kMaxThreads / 64 || (flagv == 0 && c[18] == 0 && asked_n >= 2)) &&
+                if (extras && patch_cs && (asked > kMaxThreads / 64 || (c[18] == 0 && (flagv == 0 ? asked_n >= 2 : asked_n >= 3 && n1 * m1 > 256))) &&
                     plan_strip(op, WM * TM, nb2, BH, BW, n1 * m1, patch_kw, strip)) {
                     out.extra_waves = true;
                     patch_cs = strip.cs; patch_atom = strip.atom; patch_stages = 1; patch_kw = strip.kw;
