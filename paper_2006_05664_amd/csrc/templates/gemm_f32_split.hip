@@ -13,13 +13,12 @@
 //   * A [M][K]: 16-byte pieces, whole cache lines, through a part of the LDS that is the wave's own (32 reduction steps, no barrier), pieces
 //     permuted within their row so that the 16 lanes of a turn of a fragment read fall on 16 groups of banks.
 //   * While a step's MFMAs run, the next step's values are taken apart between them, and the step after that is on its way.
-// What bounds it: instruction issue (14 vector instructions per two values; 9 beside every MFMA of a 64 x 64 tile, 95 cycles for what 64 cycles of the
+// What bounds it: instruction issue (15 vector instructions per two values; 10 beside every MFMA of a 64 x 64 tile, 95 cycles for what 64 cycles of the
 // pipes need) and, on the whole chip, the pipes' power.  Times on this card, fp32 atoms -> here: 512 x 4096 x 1024 in 64 x 64 tiles 46.0 -> 40.6 us; 2336 x 3200 x 1088
 // in 32 x 64 240 -> 179; few workgroups: 64 x 1152 x 4096 (18) 80 -> 46, 672 x 192 x 2560 (63) 53 -> 22, 224 x 512 x 896 (56) 20 -> 11.4.
 typedef __attribute__((ext_vector_type(8))) __bf16 frag_t;
 typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
 typedef __attribute__((ext_vector_type(2))) float f32x2;
-typedef __attribute__((ext_vector_type(2))) unsigned short u16x2;
 typedef f32x16 acc_t;
 #ifndef NT_OUT
 #define NT_OUT 0
@@ -32,7 +31,7 @@ static_assert(BM % 32 == 0 && BN % 32 == 0 && K % KC == 0 && MI <= 2 && NI <= 2 
 constexpr int A_WAVE = A_TRANS ? 0 : BM * KC;       // floats of LDS that are a wave's own
 constexpr int RED = KW * BM * BN;                   // floats of the partial sums, in the same place
 static_assert(4 * (KW * A_WAVE > RED ? KW * A_WAVE : RED) == LDS_BYTES, "decoder and template disagree");
-constexpr u32 SMALL = 2 * 27u * 128u;               // twice the upper 16 bits of 2^-100
+constexpr u32 SMALL = 2u * (27u << 23) - 1;         // 2^-100 (see magnitude)
 
 // base (in scalar registers, and left there) + a lane's byte offset
 #define GLOBAL __attribute__((address_space(1)))
@@ -70,19 +69,19 @@ __device__ __forceinline__ u32 pack(float a, float b)
 }
 __device__ __forceinline__ float lower(u32 v) { return __builtin_bit_cast(float, v << 16); }
 __device__ __forceinline__ float upper(u32 v) { return __builtin_bit_cast(float, v & 0xffff0000u); }
-// Word i of the planes: values 2i and 2i + 1.  low: the smallest of 2 * |upper part| - 1 as bits, where a zero counts as the largest.
+// Word i of the planes: values 2i and 2i + 1.  low: the smallest of twice the values' bits - 1, without the sign, where a zero counts as the largest
+// (the values' own bits: what is at most 2^-134 has upper parts of zero all the same).
 // (The statement that does nothing keeps the values from being taken apart before their turn.)
-__device__ __forceinline__ void split(Planes &p, int i, float a, float b, u16x2 &low)
+__device__ __forceinline__ u32 magnitude(float v) { return (__builtin_bit_cast(u32, v) << 1) - 1; }
+__device__ __forceinline__ void split(Planes &p, int i, float a, float b, u32 &low)
 {
     asm volatile("" : "+v"(a), "+v"(b));
+    low = min(min(magnitude(a), magnitude(b)), low);
     const u32 h = pack(a, b);
     a -= lower(h); b -= upper(h);
     const u32 m = pack(a, b);
     a -= lower(m); b -= upper(m);
     p.h[i] = h; p.m[i] = m; p.l[i] = pack(a, b);
-    u32 e;
-    asm("v_pk_mad_u16 %0, %1, 2, -1 op_sel_hi:[1,0,0]" : "=v"(e) : "v"(h));
-    low = __builtin_elementwise_min(low, __builtin_bit_cast(u16x2, e));
 }
 
 struct Lane {
@@ -126,7 +125,7 @@ __device__ __forceinline__ void fetch_a(const ARegs &, const Lane &l, int t, int
 
 // A wave's part of the reduction, chunks c0 .. c1 - 1.  EXACT: on the fp32 matrix pipes.  Returns what the values' smallest magnitude is judged by.
 template <bool EXACT>
-__device__ __forceinline__ u16x2 reduce(acc_t (&acc)[MI][NI], const Lane &l, int c0, int c1)
+__device__ __forceinline__ u32 reduce(acc_t (&acc)[MI][NI], const Lane &l, int c0, int c1)
 {
 #pragma unroll
     for (int i = 0; i < MI; ++i)
@@ -134,7 +133,7 @@ __device__ __forceinline__ u16x2 reduce(acc_t (&acc)[MI][NI], const Lane &l, int
         for (int j = 0; j < NI; ++j)
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
-    u16x2 low = {0xffff, 0xffff};
+    u32 low = ~0u;
     ARegs a;
     KRows<NI> b[2];
     auto load_b = [&](int c, int t) { load_krows<NI, N>(b[t], l.b + ((long)c * KC + t * 16) * N, l.b_off); };
@@ -278,7 +277,7 @@ void KERNEL_NAME(const float *__restrict__ A, const float *__restrict__ B, float
         l.b_off = 4u * (u32)(8 * half * N + l32 * NI);
         if (bi > 0) __syncthreads();
         acc_t acc[MI][NI];
-        const u16x2 low = reduce<false>(acc, l, c0, c1);
+        const u32 low = reduce<false>(acc, l, c0, c1);
         float nan = 0.f;
 #pragma unroll
         for (int i = 0; i < MI; ++i)
@@ -288,7 +287,7 @@ void KERNEL_NAME(const float *__restrict__ A, const float *__restrict__ B, float
                 for (int r = 0; r < 16; ++r) nan = __builtin_fmaf(acc[i][j][r], 0.f, nan);
         // A part with values too small to be taken apart is added up again on the fp32 atoms.  Where a sum is not finite, the first wave adds up the
         // whole reduction there, in one chain: partial sums of either sign beyond the range would make a NaN of what is infinite in order.
-        const bool small = __any(low.x < SMALL || low.y < SMALL), mine = __any(nan != 0.f);
+        const bool small = __any(low < SMALL), mine = __any(nan != 0.f);
         if (lane == 0) beyond[wave] = mine;
         __syncthreads();                            // (also: the waves' parts of the LDS have been read)
         bool chain = false;

@@ -111,6 +111,57 @@ def test_a_single_value_that_cannot_be_taken_apart():
     assert np.linalg.norm(got[32:, 32:] - want[32:, 32:]) <= 1.2e-6 * np.linalg.norm(want[32:, 32:])
 
 
+def _parts(v):
+    """A value's three bf16 parts, as the kernel takes it apart: each the rest rounded to nearest, ties to even."""
+    out = []
+    for _ in range(3):
+        u = v.view(np.uint32)
+        h = ((u + 0x7fff + (u >> 16 & 1)) & np.uint32(0xffff0000)).view(np.float32)
+        out.append(h)
+        v = v - h
+    return out
+
+
+def test_which_values_are_no_sum_of_three_parts():
+    """Whatever is not the sum of its parts is taken for too small by the kernel's test on its bits; nothing from 2^-100 on is, nor is zero."""
+    g = np.random.default_rng(3)
+    exps = np.arange(-149, 120)
+    v = np.concatenate([(g.uniform(1, 2, (64, 1)) * 2.0 ** exps).astype(np.float32).ravel(), (2.0 ** exps).astype(np.float32), np.zeros(2, np.float32)])
+    v = np.concatenate([v, -v])
+    small = ((v.view(np.uint32).astype(np.uint64) << 1) - 1 & 0xffffffff) < 2 * (27 << 23) - 1
+    assert not small[(np.abs(v) >= 2.0 ** -100) | (v == 0)].any()
+    assert small[(np.abs(v) < 2.0 ** -100) & (v != 0)].all()
+    assert np.all((sum(p.astype(np.float64) for p in _parts(v)) == v)[~small])
+    gone = (_parts(v)[0] == 0) & (v != 0)                      # up to 2^-134 no part has anything of them
+    assert gone.any() and small[gone].all() and np.all(np.abs(v[gone]) <= 2.0 ** -134)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("scale_a,scale_b", [(2.0 ** -140, 2.0 ** 40), (2.0 ** -140, 2.0 ** 100), (2.0 ** 100, 2.0 ** -138)])
+def test_an_operand_wholly_below_what_bf16_holds(scale_a, scale_b):
+    """Every value at most 2^-134, few bits each: no product has more than 24 + 15, and the sums are the fp32 atoms' (1.2e-6: 480 products, as above)."""
+    a, b = _operands()
+    a, b = (np.clip(a, -2, 2) * np.float32(scale_a)).astype(np.float32), (np.clip(b, -2, 2) * np.float32(scale_b)).astype(np.float32)
+    tiny = a if scale_a < 1 else b
+    assert np.all(np.abs(tiny) <= 2.0 ** -134) and np.mean(tiny != 0) > 0.9
+    want = a.astype(np.float64) @ b.astype(np.float64)
+    got = _run(*MEMBER, a, b, want.size).astype(np.float64).reshape(want.shape)
+    assert np.linalg.norm(got - want) <= 1.2e-6 * np.linalg.norm(want)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("value", [2.0 ** -149, 2.0 ** -134, 1.5 * 2.0 ** -135])
+def test_the_only_value_of_a_wave_s_part(value):
+    """One product for each row, in the first wave's part, the last one's and one between: exact (the other factor is a power of two)."""
+    a, b = np.zeros((64, 480), np.float32), np.zeros((480, 64), np.float32)
+    for i, k in enumerate((0, 127, 200, 479)):
+        a[16 * i + 3, k] = np.float32(value)
+        b[k] = np.float32(2.0 ** (100 + i))
+    want = a.astype(np.float64) @ b.astype(np.float64)
+    got = _run(*MEMBER, a, b, want.size).reshape(want.shape)
+    assert np.count_nonzero(want) == 4 * 64 and np.array_equal(got.astype(np.float64), want)
+
+
 @pytest.mark.gpu
 def test_infinities_nan_and_sums_beyond_the_range():
     a, b = _operands()
