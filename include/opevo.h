@@ -314,13 +314,18 @@ int opevo_op_space(const opevo_op *op, int variant, opevo_space **out);
 typedef struct {
     int32_t status;        /* OPEVO_OK or OPEVO_E_INVALID                                      */
     int32_t path;          /* 0 scalar FMA, 1 MFMA 32x32x16, 2 MFMA 16x16x32, 3 MFMA 32x32x16 with
-                              operands streamed global -> LDS directly, 4 fp32 MFMA 32x32x2,
+                              operands streamed global -> LDS directly, 4 fp32 inputs: MFMA 32x32x2, or for
+                              MatMul / BMM with long reductions every value as three bf16 parts on
+                              MFMA 32x32x16, eight of the nine products of parts: a product rounds as in
+                              fp32, a long sum less often; values and sums for which that does not hold
+                              (below 2^-100 and 2^-110, not finite) are computed by MFMA 32x32x2,
                               5 Conv2d with an LDS-resident image patch (either atom), 6 MatMul / BMM
                               whose extents are no multiples of 16, tiles of any extent on MFMA 16x16x32,
                               7 Conv2d with fewer than 16 input channels, image rows in LDS (either atom) */
     int32_t grid[3];
     int32_t block;         /* threads per workgroup (path 3: with the second group of waves, where two
-                              share the reduction; path 5: with the waves that share a tile)  */
+                              share the reduction; path 5: with the waves that share a tile; paths 4
+                              and 6: with those that share the reduction, where they do)      */
     int32_t lds_bytes;
     int32_t acc_per_lane;  /* fp32 accumulators each lane holds                                */
     int32_t tile[3];       /* workgroup tile BM, BN, BK                                        */
@@ -375,7 +380,7 @@ int opevo_compile_pool_deadline(double seconds);
  * and one spilling member of the register-staged template once gave wrong rows.  opevo_tune
  * scores both as invalid trials.  What a template does of its own accord (path 4's pipelined
  * loop, path 7, path 5's extra waves per tile or rows of pixels, path 6's places kept from slab to slab, path 3's second
- * group of waves, the order of the workgroups) never makes a member spill: this call compiles it again without, if the first code object does. */
+ * group of waves, waves that share the reduction on paths 4 and 6, the order of the workgroups) never makes a member spill: this call compiles it again without, if the first code object does. */
 int opevo_kernel_build(const opevo_op *op, int variant, const int32_t *cfg,
                        opevo_kernel **out, double *compile_ms);
 /* Compiling is by far the longest part of a trial (Sec. 6 gives it 8 CPU threads), and runs of

@@ -853,15 +853,17 @@ int decode(const opevo_op &op, int variant, const int32_t *cfg, Decoded &out, bo
         }
     }
     // fp32 MatMul / BMM members with two stages, workgroup tiles of 32 or 64 rows and columns and long reductions: the template that takes values apart for the bf16
-    // matrix pipes, its waves sharing the reduction.  From K = 320 on, 448 for tiles of 64 x 64, which pay for a longer final sum: 64 x 64 tiles at K = 320
-    // 8.3 -> 9.1 us (34 workgroups) and 9.4 -> 10.3 (182), at 480 87.6 -> 81.6, at 512 12.8 -> 11.7; 32 x 64 at K = 320 23 -> 18.4, at 384 9.8 -> 6.7, at 256 12.9 -> 12.7; K of 64 to
-    // 256 0.73 - 1.1 times as fast.  30 drawn operators of K = 448 - 7808: 1.07 - 2.5x.
-    // Eight waves instead of four where a compute unit has one workgroup at most and each wave still gets 88 steps: 672 x 192 x 2560 (63 workgroups) 23.9 -> 21.4, 64 x 1152
-    // x 4096 (18) 52.7 -> 45.9, 1024 x 480 x 736 (240) 12.5 -> 11.4, but 512 x 4096 x 1024 (512) 39.8 -> 43.9 and 64 x 64 x 448 steps and less alike.
+    // matrix pipes, its waves sharing the reduction.  From K = 320 on, 448 for tiles of 64 x 64, which pay for a longer final sum.  Against the fp32 atoms
+    // 64 members drawn for these rules 1.00 - 3.3x, 1.5x in the geometric mean, the least 64 x 64 tiles on a full chip at K = 480 - 576 (2368 x 2432 x 480 56.3 -> 56.1 us).  64 x 64
+    // tiles with the first operand transposed need more registers than there are.  Batches on more than 400 workgroups, whose operands few tiles share, are bound by
+    // bytes as much as by the pipes: 342 x (32 x 64 x 896), transposed, 23.9 -> 27.4, 250 x (128 x 64 x 704) 31.2 -> 34.4, 12 such members 0.87 - 1.17x, 0.99x; up to 360
+    // 82 x (64 x 64 x 480) 11.2 -> 8.8 and no member below 1.00.
+    // Eight waves instead of four where a compute unit has one workgroup at most and each wave still gets 88 steps: 672 x 192 x 2560 in 32 x 64 (63 workgroups) 23.9 -> 21.4, 1024 x 480 x 736 in
+    // 64 x 32 (240) 12.5 -> 11.4, while 64 x 64 x 448 steps and less are alike (six products in one accumulator; the waves' shares are the same with eight in two).
     int f32_kw = 0;
     if (extras && path == 4 && op.kind != OPEVO_CONV2D && flagv && ksteps > 1 && ksplit == 1 && subm * subn == 1 && WM * WN <= kMaxThreads / 64 &&
-        (BM == 32 || BM == 64) && (BN == 32 || BN == 64) && op.K % 32 == 0 && op.K >= (BM * BN == 64 * 64 ? 448 : 320) &&
-        op.M < (1 << 22) && op.N < (1 << 22) && op.K < (1 << 22) &&         // (a lane's byte offsets within 32 bits)
+        (BM == 32 || BM == 64) && (BN == 32 || BN == 64) && !(op.trans_a && BM * BN == 64 * 64) && op.K % 32 == 0 && op.K >= (BM * BN == 64 * 64 ? 448 : 320) &&
+        (op.kind == OPEVO_MATMUL || n1 * m1 * b1 <= 400) && op.M < (1 << 22) && op.N < (1 << 22) && op.K < (1 << 22) &&         // (a lane's byte offsets within 32 bits)
         valid_without_extras(op, variant, cfg)) {
         f32_kw = n1 * m1 * b1 <= 256 && op.K >= 704 ? 8 : 4;
         out.extra_waves = true;
@@ -887,7 +889,7 @@ int decode(const opevo_op &op, int variant, const int32_t *cfg, Decoded &out, bo
         NT = ((BM * BN + 63) / 64) * 64;
         if (NT > 256) NT = 256;
     }
-    int64_t acc = (path == 0) ? (BM * BN + NT - 1) / NT : (TMacc * TNacc) / 64;
+    int64_t acc = (path == 0) ? (BM * BN + NT - 1) / NT : (TMacc * TNacc) / 64 * (f32_kw ? 2 : 1);
     const int nstage = path == 7 ? 1 : path == 6 ? rg.stages : path == 5 ? patch_stages : path == 3 ? nstage_dlds : (path != 0 && flagv && ksteps > 1) ? 2 : 1;
     int64_t lds = 0;
     if (path == 0) lds = (BM * BK + BK * BN) * 4;
@@ -895,7 +897,7 @@ int decode(const opevo_op &op, int variant, const int32_t *cfg, Decoded &out, bo
         const int64_t a_rows = (WM - 1) * TM + TMacc, b_cols = ((WN - 1) * TN + TNacc + 3) / 4 * 4;   // with the overhang
         lds = nstage * (a_rows * (BKP + 4) + BKP * (b_cols + 4)) * 4;
     }
-    else if (path == 4 && f32_kw) lds = f32_kw * BM * std::max<int64_t>(op.trans_a ? 0 : 32, BN) * 4;
+    else if (path == 4 && f32_kw) lds = f32_kw * BM * std::max<int64_t>(op.trans_a ? 0 : 64, BN) * 4;
     else if (path == 4) lds = nstage * ((op.trans_a ? BK * (BM + 4) : BM * (BK + 4)) + BK * (BN + 4)) * 4;
     else if (path == 3) lds = nstage * (anr + (b_kmajor ? bnr : BN)) * BK * 2;
     else if (path == 5 && strip.rows) lds = strip.lds;

@@ -16,9 +16,11 @@ CASES = [   # label, kind, dims, variant, configuration, waves that share the re
     ("64 x 64, eight waves", MM, (64, 64, 1024), V, [1, 2, 1, 32, 1, 2, 1, 32, 16, 64, 1], 8),
     ("slabs of 8, a launch order of its own", MM, (128, 64, 704), X, [2, 1, 2, 32, 1, 2, 1, 32, 88, 8, 1, 1, 0, 2], 8),
     ("batches, two per workgroup", BMM, (6, 64, 32, 416), V, [3, 2, 2, 1, 1, 32, 1, 1, 1, 32, 13, 32, 1], 4),
-    ("transposed first operand, 64 x 64", TA, (4, 64, 128, 448), V, [2, 2, 1, 2, 1, 32, 2, 2, 1, 32, 14, 32, 1], 4),
+    ("transposed first operand, 64 x 32", TA, (4, 64, 96, 448), V, [2, 2, 1, 2, 1, 32, 3, 1, 1, 32, 14, 32, 1], 4),
+    ("transposed first operand, 32 x 64", TA, (4, 96, 128, 704), V, [2, 2, 3, 1, 1, 32, 2, 2, 1, 32, 22, 32, 1], 8),
     ("transposed first operand, 32 x 32", TA, (2, 96, 32, 768), V, [2, 1, 3, 1, 1, 32, 1, 1, 1, 32, 24, 32, 1], 8),
     ("workgroups enough for the chip", MM, (1024, 1088, 704), V, [16, 2, 1, 32, 17, 2, 1, 32, 11, 64, 1], 4),
+    ("transposed first operand, 64 x 64", TA, (4, 64, 128, 448), V, [2, 2, 1, 2, 1, 32, 2, 2, 1, 32, 14, 32, 1], 0),
     ("64 x 64, shorter", MM, (128, 192, 416), V, [2, 2, 1, 32, 3, 2, 1, 32, 13, 32, 1], 0),
     ("32 x 64, shorter", MM, (64, 128, 288), V, [2, 1, 1, 32, 2, 1, 2, 32, 9, 32, 1], 0),
     ("no whole chunks", MM, (64, 128, 336), V, [2, 1, 1, 32, 2, 1, 2, 32, 21, 16, 1], 0),
@@ -39,6 +41,29 @@ def _waves(kind, dims, variant, cfg):
 @pytest.mark.parametrize("label,kind,dims,variant,cfg,waves", CASES, ids=[c[0] for c in CASES])
 def test_which_members_it_takes(label, kind, dims, variant, cfg, waves):
     assert _waves(kind, dims, variant, cfg) == waves
+
+
+@pytest.mark.parametrize("bm", [32, 64])
+def test_where_the_first_operand_s_pieces_go(bm):
+    """A chunk of 32 reduction steps, 16 bytes a lane and load: every value once, inside the half it is meant for, where the fragments are read, and the
+    16 lanes of a turn of a fragment read on 16 groups of 4 banks."""
+    K, lane = 96, np.arange(64)
+    lds = np.full(bm * 32, -1)
+    a_off = lane // 8 * K + (lane % 8 ^ lane >> 4) * 4                # elements
+    for i in range(bm // 8):
+        at = a_off ^ 16 if i & 1 else a_off
+        for e in range(4):
+            assert (lds[i * 256 + lane * 4 + e] == -1).all()
+            lds[i * 256 + lane * 4 + e] = i * 8 * K + at + e
+    for i in range(bm // 32):
+        for t in range(2):
+            row, p = i * 32 + lane % 32, 4 * t + 2 * (lane // 32)
+            key = row >> 1 & 7
+            for half in range(2):
+                piece = row * 8 + (p + half ^ key)
+                for e in range(4):
+                    assert (lds[piece * 4 + e] == row * K + t * 16 + 8 * (lane // 32) + 4 * half + e).all()
+                assert all(len(set(piece[g:g + 16] % 16)) == 16 for g in range(0, 64, 16))
 
 
 def test_members_that_could_not_run_without_it_stay_invalid():
@@ -64,8 +89,8 @@ def _run(kind, dims, variant, cfg, a, b, n):
 @pytest.mark.gpu
 @pytest.mark.parametrize("label,kind,dims,variant,cfg,waves", [c for c in CASES if c[-1]], ids=[c[0] for c in CASES if c[-1]])
 def test_results_match_the_oracle(label, kind, dims, variant, cfg, waves):
-    """A wave adds at most 256 products, 16 at a time in six roundings: 96 roundings of growing sums, some 10 of the result's norm by their
-    random signs; the final sum has at most 8.  1.2e-6 is 20."""
+    """A wave adds at most 256 products, 16 at a time: 16 roundings of a growing sum, some 4 of the result's norm by their random signs; the final
+    sum has at most 8.  1.2e-6 is 20."""
     from oracle import tensor as T
     a, b = {MM: synth.matmul_inputs, BMM: synth.bmm_inputs, TA: synth.bmm_ta_inputs}[kind](*dims, "f32", 5)
     want = (T.matmul(a, b) if kind == MM else T.bmm(a if kind == BMM else np.ascontiguousarray(a.transpose(0, 2, 1)), b)).ravel()
@@ -90,6 +115,47 @@ def test_operands_of_any_magnitude(scale_a, scale_b):
     want = a.astype(np.float64) @ b.astype(np.float64)
     got = _run(*MEMBER, a, b, want.size).astype(np.float64).reshape(want.shape)
     assert np.linalg.norm(got - want) <= 1.2e-6 * np.linalg.norm(want)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("label,kind,dims,variant,cfg,waves", [c for c in CASES if c[-1] and c[1] == MM and c[3] == V], ids=[c[0] for c in CASES if c[-1] and c[1] == MM and c[3] == V])
+def test_no_further_from_64_bits_than_the_fp32_atoms(label, kind, dims, variant, cfg, waves):
+    """The same operands through the same tile without pipelining, which runs on the fp32 atoms: its sums are rounded eight times for 16 products."""
+    a, b = synth.matmul_inputs(*dims, "f32", 5)
+    want = a.astype(np.float64) @ b.astype(np.float64)
+    off = [np.linalg.norm(_run(kind, dims, variant, cfg[:-1] + [flag], a, b, want.size).reshape(want.shape) - want) for flag in (1, 0)]
+    assert _waves(kind, dims, variant, cfg[:-1] + [0]) == 0 and off[0] <= off[1], off
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("seed", [1, 2])
+def test_sums_of_a_single_product(seed):
+    """Selections and sparse rows: the product of the upper parts is exact, the seven others are at most 2^-7 of it and lose no more than 2^-24 of that
+    each time they are added to, so the one rounding of their sum is all but fp32's (2^-24): 2^-24 + 2^-28, and 2 % in the norm."""
+    g = np.random.default_rng(seed)
+    a, b = np.zeros((64, 480), np.float32), g.standard_normal((480, 64)).astype(np.float32)
+    k = g.permutation(480)[:64]
+    a[np.arange(64), k] = g.standard_normal(64).astype(np.float32)
+    a[0, k[0]] = 1.0
+    want = a.astype(np.float64) @ b.astype(np.float64)
+    got = _run(*MEMBER, a, b, want.size).astype(np.float64).reshape(want.shape)
+    rounded = want.astype(np.float32)
+    assert np.array_equal(got[0], b[k[0]].astype(np.float64)), "a value times one is that value"
+    assert np.all(np.abs(got - want) <= (2.0 ** -24 + 2.0 ** -28) * np.abs(want))
+    assert np.linalg.norm(got - want) <= 1.02 * np.linalg.norm(rounded - want)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("scale", [2.0 ** -60, 2.0 ** -64, 2.0 ** -70])
+def test_products_that_are_subnormal_or_nearly(scale):
+    """One product for each output, of values that can be taken apart, whose smaller parts have no 24 bits left: rounded once, as on the fp32 atoms."""
+    g = np.random.default_rng(4)
+    a, b = np.zeros((64, 480), np.float32), (g.standard_normal((480, 64)) * scale).astype(np.float32)
+    a[np.arange(64), g.permutation(480)[:64]] = (g.standard_normal(64) * scale).astype(np.float32)
+    assert np.all(np.abs(b) > 2.0 ** -100) and np.all((np.abs(a) > 2.0 ** -100) | (a == 0))
+    want = a.astype(np.float64) @ b.astype(np.float64)
+    got = _run(*MEMBER, a, b, want.size).reshape(want.shape)
+    assert np.array_equal(got, want.astype(np.float32))
 
 
 @pytest.mark.gpu
