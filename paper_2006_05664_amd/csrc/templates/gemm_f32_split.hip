@@ -134,9 +134,10 @@ __device__ __forceinline__ void fetch_a(const ARegs &, const Lane &l, int c, int
 }
 #endif
 
-// A wave's part of the reduction, chunks c0 .. c1 - 1.  EXACT: on the fp32 matrix pipes.  Returns what the values' smallest magnitude is judged by.
+// A wave's part of the reduction, chunks c0 .. c1 - 1.  EXACT: on the fp32 matrix pipes; with only >= 0 that atom of the tile alone, i * NI + j.  Returns
+// what the values' smallest magnitude is judged by.
 template <bool EXACT>
-__device__ __forceinline__ u32 reduce(acc_t (&acc)[MI][NI], const Lane &l, int c0, int c1)
+__device__ __forceinline__ u32 reduce(acc_t (&acc)[MI][NI], const Lane &l, int c0, int c1, int only = -1)
 {
 #pragma unroll
     for (int i = 0; i < MI; ++i)
@@ -186,11 +187,13 @@ __device__ __forceinline__ u32 reduce(acc_t (&acc)[MI][NI], const Lane &l, int c
 #pragma unroll
                 for (int i = 0; i < MI; ++i) fetch_a(a, l, c, t, i, x[i]);
 #pragma unroll
-                for (int k = 0; k < 8; ++k)
+                for (int i = 0; i < MI; ++i)
 #pragma unroll
-                    for (int i = 0; i < MI; ++i)
+                    for (int j = 0; j < NI; ++j) {
+                        if (only >= 0 && only != i * NI + j) continue;
 #pragma unroll
-                        for (int j = 0; j < NI; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(x[i][k], b[t].k[k].v[j], acc[i][j], 0, 0, 0);
+                        for (int k = 0; k < 8; ++k) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(x[i][k], b[t].k[k].v[j], acc[i][j], 0, 0, 0);
+                    }
                 load_b(cn, t);
 #if A_TRANS
                 load_a(a, l, cn, t);
@@ -335,8 +338,11 @@ void KERNEL_NAME(const float *__restrict__ A, const float *__restrict__ B, float
                 small_sum = small_sum || magnitude(v) < SMALL_SUM;
             });
         }
-        // A part with values too small to be taken apart, or sums too small for their products' parts, is added up again on the fp32 atoms.  Where a sum is not finite, the first wave adds up the
-        // whole reduction there, in one chain: partial sums of either sign beyond the range would make a NaN of what is infinite in order.
+        // A part with values too small to be taken apart, or sums too small for their products' parts, is added up again on the fp32 atoms.  Where a sum is not
+        // finite, the tile's whole reduction is, in one chain for each atom of it, an atom a wave: partial sums of either sign beyond the range would make a NaN of
+        // what is infinite in order.  What that costs, 512 x 4096 x 1024 in 64 x 64 tiles / 672 x 192 x 2560 in 32 x 32 (ordinary values 37 / 16 us, also with zeros; on the
+        // fp32 atoms alone 39 / 53 whatever the values): one value of 1e-40 50 / 23, one of 1e-32 in every row 68 / 23, every value or sum too small 72 / 28; one
+        // infinity 59 / 70, one in every row, or a NaN, 84 / 71 (one wave for the whole tile: 93 - 127 / 71).
         const bool small = __any(low < SMALL || small_sum), mine = __any(!finite);
         if (lane == 0) beyond[wave] = mine;
         __syncthreads();                            // (also: the waves' parts of the LDS have been read)
@@ -344,7 +350,7 @@ void KERNEL_NAME(const float *__restrict__ A, const float *__restrict__ B, float
 #pragma unroll
         for (int k = 0; k < KW; ++k) chain |= beyond[k] != 0;
         chain = __builtin_amdgcn_readfirstlane(chain);
-        if (chain ? wave == 0 : small) reduce<true>(acc, l, chain ? 0 : c0, chain ? NCHUNK : c1);
+        if (chain ? wave < MI * NI : small) reduce<true>(acc, l, chain ? 0 : c0, chain ? NCHUNK : c1, chain ? wave : -1);
 
         auto row_of = [&](int i, int r) {
             const int row = 8 * (r / 4) + 4 * half + r % 4;
@@ -352,14 +358,14 @@ void KERNEL_NAME(const float *__restrict__ A, const float *__restrict__ B, float
         };
         float *const out = Cb + (long)m0 * N + n0 + l32 * NI;
         if (chain) {
-            if (wave == 0) {
 #pragma unroll
-                for (int i = 0; i < MI; ++i)
+            for (int i = 0; i < MI; ++i)
 #pragma unroll
-                    for (int r = 0; r < 16; ++r)
+                for (int j = 0; j < NI; ++j) {
+                    if (wave != i * NI + j) continue;
 #pragma unroll
-                        for (int j = 0; j < NI; ++j) out[(long)row_of(i, r) * N + j] = acc[i][j][r];
-            }
+                    for (int r = 0; r < 16; ++r) out[(long)row_of(i, r) * N + j] = acc[i][j][r];
+                }
             continue;
         }
         __syncthreads();                            // nobody reads operands from the LDS any longer
