@@ -799,6 +799,7 @@ int decode(const opevo_op &op, int variant, const int32_t *cfg, Decoded &out, bo
         int64_t kw = 0;
         if (extras && ksplit == 1 && op.K >= 448) kw = wgs <= 256 && ma * na <= 20 ? std::min<int64_t>(8, kMaxLds / per) : odd && op.K >= 500 && wgs <= 1024 && ma * na <= 12 ? 2 : 0;
         if (kw == 2 || kw >= 4) {
+            // (256 registers a lane whatever the number of waves: 13 members of two waves 1.00 - 1.04 times as fast as with 512)
             rg_kw = int(kw); rg.lds = kw * per; rg.min_waves = 2;
             out.extra_waves = true;
             WM = 1; WN = kw; TM = ma * 16; TN = na * 16; TMacc = TM; TNacc = TN;
@@ -964,8 +965,8 @@ int decode(const opevo_op &op, int variant, const int32_t *cfg, Decoded &out, bo
         if (nwr != WM * WN && path != 5) D << " -DNWR=" << nwr;
     }
     if (path == 7) D << " -DWKP=" << rows.wkp << " -DMI=" << rows.mi << " -DNI=" << rows.ni << " -DLDS_BYTES=" << lds << " -DPERSIST=" << rows.persist << " -DNBOX=" << n1 << " -DSTAGE_A=" << rows.stage;
-    if (path == 6) D << " -DKS=" << rg.ks << " -DNSL=" << rg.slabs << " -DMI=" << rg.mi << " -DNI=" << rg.ni << " -DLDS_BYTES=" << lds << " -DDEPTH=" << rg.depth << " -DMINW=" << rg.min_waves;
-    if (rg_kw) D << " -DKWAVES=" << rg_kw;
+    if (rg_kw) D << " -DKWAVES=" << rg_kw << " -DLDS_BYTES=" << lds << " -DMINW=" << rg.min_waves;
+    else if (path == 6) D << " -DKS=" << rg.ks << " -DNSL=" << rg.slabs << " -DMI=" << rg.mi << " -DNI=" << rg.ni << " -DLDS_BYTES=" << lds << " -DDEPTH=" << rg.depth << " -DMINW=" << rg.min_waves;
     if (subm * subn > 1) {
         D << " -DSUBM=" << subm << " -DSUBN=" << subn;
     }
@@ -993,7 +994,7 @@ int decode(const opevo_op &op, int variant, const int32_t *cfg, Decoded &out, bo
     if (path == 3 && anr != BM) D << " -DANR=" << anr;
     // ragged: the places of pieces kept where they fit, or may fit; else worked out where they are needed, for every slab anew if the kernel spills
     // otherwise (one in 100 members; transposed first operands on eight waves of 3 x 7 to 3 x 9 atoms always do)
-    if (path == 6) {
+    if (path == 6 && !rg_kw) {
         const bool spills = op.trans_a && rg.keep != 1 && rg.wm * rg.wn >= 8 && rg.mi >= 3 && rg.mi * rg.ni >= 20;
         out.tries.clear();
         if (rg.keep == 1 || (rg.keep == 2 && !spills)) out.tries.push_back(" -DKEEP=1");

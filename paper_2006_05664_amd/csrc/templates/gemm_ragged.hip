@@ -37,7 +37,7 @@ typedef __attribute__((ext_vector_type(8))) __bf16 frag_t;
 typedef __attribute__((ext_vector_type(8))) _Float16 frag_t;
 #define MFMA(a, b, c) __builtin_amdgcn_mfma_f32_16x16x32_f16(a, b, c, 0, 0, 0)
 #endif
-#if !KEEP   // nothing of a plan for two slabs under way, or for a second workgroup's registers, holds
+#if !defined(KWAVES) && !KEEP   // nothing of a plan for two slabs under way, or for a second workgroup's registers, holds
 #undef DEPTH
 #define DEPTH 1
 #undef MINW
@@ -54,28 +54,25 @@ typedef __attribute__((ext_vector_type(8))) _Float16 frag_t;
 typedef u32x4 __attribute__((aligned(2))) u32x4_a2;
 typedef __attribute__((ext_vector_type(4))) short v4s;
 
-constexpr int KPART = K / KSPLIT;                 // reduction length of this workgroup
+constexpr int odd16(int n) { return ((n + 15) / 16 | 1) * 16; }
+__device__ __forceinline__ constexpr int kr_off(int ld, int k) { return k * ld + (k >> 3) * 64; }   // LDS element of k row k
+constexpr int CM = (BM + 7) / 8, CN = (BN + 7) / 8;   // pieces of a k row
 #ifndef KWAVES
+constexpr int KPART = K / KSPLIT;                 // reduction length of this workgroup
 static_assert(NSL * KS >= KPART && (NSL - 1) * KS < KPART && KS % 32 == 0 && KPART >= 8, "decoder and template disagree");
 static_assert(WM * MI * 16 >= BM && WN * NI * 16 >= BN && NT == 64 * WM * WN, "decoder and template disagree");
-#endif
 constexpr bool K_TAIL = KPART % KS != 0;          // the last slab is not full
-
-constexpr int odd16(int n) { return ((n + 15) / 16 | 1) * 16; }
 constexpr int LDK = KS + 8;                       // elements per LDS row of a k-contiguous operand
 constexpr int LDM = odd16(WM * MI * 16), LDN = odd16(WN * NI * 16);
-__device__ __forceinline__ constexpr int kr_off(int ld, int k) { return k * ld + (k >> 3) * 64; }   // LDS element of k row k
 constexpr int A_STAGE = A_TRANS ? KS * LDM + (KS / 8) * 64 : WM * MI * 16 * LDK;
 constexpr int B_STAGE = KS * LDN + (KS / 8) * 64;
-#ifndef KWAVES
 static_assert(NSTG * (A_STAGE + B_STAGE) * 2 <= LDS_BYTES, "stages exceed the LDS the host asks for");
-#endif
 constexpr int CK = KS / 8;                        // pieces of a k-contiguous row
-constexpr int CM = (BM + 7) / 8, CN = (BN + 7) / 8;   // pieces of a k row
 constexpr int A_PIECES = A_TRANS ? KS * CM : BM * CK, B_PIECES = KS * CN;
 constexpr int NA = (A_PIECES + NT - 1) / NT, NB = (B_PIECES + NT - 1) / NT;
 
 struct Slab { u32x4 a[NA], b[NB]; };
+#endif
 
 // v shifted down by sh elements (0 .. 7), zeros from above; sh >= 8: zeros
 __device__ __forceinline__ u32x4 shift_down(u32x4 v, int sh)

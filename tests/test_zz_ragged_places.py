@@ -9,9 +9,9 @@ import paper_2006_05664_amd as P
 from paper_2006_05664_amd import synth
 
 CASES = [   # label, kind, dims, configuration, what the decoder must choose
-    ("two slabs on their way, 40 slabs and a tail", P.OPEVO_MATMUL, (54, 60, 1310), [2, 1, 1, 27, 2, 1, 1, 30, 131, 10, 1], dict(DEPTH=2, KEEP=1)),
-    ("two on their way, no tail, edges in the last column", P.OPEVO_MATMUL, (30, 45, 2048), [1, 1, 1, 30, 3, 1, 1, 15, 32, 64, 1], dict(DEPTH=2, KEEP=1)),
-    ("one on its way, 14 slabs and a tail of two", P.OPEVO_MATMUL, (60, 44, 450), [1, 1, 1, 60, 1, 1, 1, 44, 15, 30, 1], dict(DEPTH=1, KEEP=1)),
+    ("two slabs on their way, 40 slabs and a tail", P.OPEVO_MATMUL, (120, 90, 1310), [2, 1, 1, 60, 1, 1, 1, 90, 131, 10, 1], dict(DEPTH=2, KEEP=1, NSL=41)),
+    ("two on their way, no tail, edges in the last column", P.OPEVO_MATMUL, (100, 95, 2048), [1, 1, 1, 100, 1, 1, 1, 95, 64, 32, 1], dict(DEPTH=2, KEEP=1, NSL=64)),
+    ("one on its way, 14 slabs and a tail of two", P.OPEVO_MATMUL, (90, 60, 450), [1, 1, 1, 90, 1, 1, 1, 60, 15, 30, 1], dict(DEPTH=1, KEEP=1, NSL=15)),
     ("one stage, several slabs", P.OPEVO_MATMUL, (45, 50, 300), [1, 1, 1, 45, 1, 2, 1, 25, 5, 60, 0], dict(NSTG=1, KEEP=1)),
     ("transposed first operand, both edges", P.OPEVO_BMM_TA, (3, 27, 35, 330), [3, 1, 3, 1, 1, 9, 5, 1, 1, 7, 6, 55, 1], dict(KEEP=1)),
     ("several batches a workgroup", P.OPEVO_BMM, (6, 25, 40, 250), [2, 3, 1, 1, 1, 25, 1, 1, 1, 40, 5, 50, 1], dict(KEEP=1, BATCH_INNER=3)),
@@ -29,7 +29,7 @@ def _defs(op, cfg):
 def test_offsets_from_a_slab_s_base(label, kind, dims, cfg, want):
     op = P.opevo_op_create(kind, dims, P.OPEVO_BF16)
     plan, D = P.opevo_kernel_plan(op, P.OPEVO_TILE4, cfg), _defs(op, cfg)
-    assert plan.status == P.OPEVO_OK and plan.path == 6 and {k: D[k] for k in want} == want, D
+    assert plan.status == P.OPEVO_OK and plan.path == 6 and "KWAVES" not in D and {k: D.get(k) for k in want} == want, D
     KS, NSL, NT, K, N, M, BM, BN = (D[k] for k in "KS NSL NT K N M BM BN".split())
     last0, tail = (NSL - 1) * KS, K % KS != 0
     tail0 = last0 - 8 if NSL > 1 else 0
