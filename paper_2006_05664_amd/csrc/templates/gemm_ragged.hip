@@ -193,6 +193,14 @@ __device__ __forceinline__ void store_step(const Step &r, const Places &p, u16 *
     store_pieces<QA, ODD_A>(r.a, p.ga, p.sa, As, PA, f.a, lane, f.end_a, BACK_A);
     store_pieces<QB, ODD_B>(r.b, p.gb, p.sb, Bs, PB, f.b, lane, f.end_b, BACK_B);
 }
+// The lanes of a wave exchange operands through LDS that is the wave's own.  Its accesses to the LDS take effect in the order of the code; this keeps the
+// compiler from moving one lane's reads before another's writes, or its next writes before those reads.  No instruction comes of it.
+__device__ __forceinline__ void exchange()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
 template <bool MASK>
 __device__ __forceinline__ void multiply_step(f32x4 (&acc)[MA][NATOM], const u16 *As, const u16 *Bs, int lane)
 {
@@ -264,11 +272,14 @@ void KERNEL_NAME(const u16 *__restrict__ A, const u16 *__restrict__ B, float *__
 #pragma unroll 1
         for (int s = s0; s < s1 - 1; ++s) {
             store_step(step, p, As, Bs, from_of(a0, b0, s), lane);
+            exchange();
             load_step(step, p, A, B, from_of(a0, b0, s + 1));
             __builtin_amdgcn_sched_barrier(0);
             multiply_step<false>(acc, As, Bs, lane);
+            exchange();
         }
         store_step(step, p, As, Bs, from_of(a0, b0, s1 - 1), lane);
+        exchange();
         if (DUP > 0 && wave == KWAVES - 1) multiply_step<true>(acc, As, Bs, lane);
         else multiply_step<false>(acc, As, Bs, lane);
 
