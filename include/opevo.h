@@ -442,9 +442,8 @@ int opevo_mfma_ceiling_atom(int in_dtype, int random_data, int atom, void *strea
 
 /* Parity gate: c and ref are DEVICE fp32 arrays of n elements.
  * max_scaled = max |c-ref| / (|ref|+1), rel_fro = ||c-ref||_F / ||ref||_F (0 if both 0).
- * Uses a library-owned workspace (device memory and three words of pinned host memory, allocated on first
- * use, one for every call under way at the same time, at most 8 kept per device). Returns when the comparison, and with it
- * everything enqueued on `stream` before it, has finished. */
+ * Uses a library-owned workspace (device memory and two words of pinned host memory, allocated on first
+ * use, one for every call under way at the same time, at most 8 kept per device). Synchronises `stream`. */
 int opevo_compare_f32(const float *c, const float *ref, int64_t n, void *stream,
                       double *max_scaled, double *rel_fro);
 

@@ -5,10 +5,8 @@
 // Any NaN in c makes max_scaled infinite, so a broken kernel can never pass.
 #include <hip/hip_runtime.h>
 
-#include <chrono>
 #include <cmath>
 #include <cstdint>
-#include <cstring>
 #include <mutex>
 #include <vector>
 
@@ -27,8 +25,8 @@ typedef float f32x4_t __attribute__((ext_vector_type(4)));
 constexpr int kBlocks = 1024;
 static_assert(sizeof(scratch) == sizeof(double) * 3 * kBlocks, "scratch holds one triple per workgroup");
 constexpr int kThreads = 256;
-// Comparisons of at most this many elements, one pass of a workgroup, run as a single workgroup without a second kernel (1000 elements 13.5 us with two and 11.5 with one, 5000
-// 13.5 and 12.5; 16384, four passes: 13.5 and 14.0, 32768 17.3).
+// Comparisons of at most this many elements, one pass of a workgroup, run as a single workgroup without a second kernel (1000 elements 16.9 us with two and 15.6 with one, 4096
+// 17.2 and 16.7; each further pass costs 0.5 and more: 16384 elements, four passes, are slower so).
 constexpr int kSmallThreads = 1024;
 constexpr int64_t kSmall = 4 * kSmallThreads;
 
@@ -63,9 +61,6 @@ __device__ __forceinline__ void compare_batch(const float (&c)[NV], const float 
     }
 }
 
-// Where a comparison leaves its result: [0] = max_scaled, [1] = rel_fro.  done (or NULL): host memory, set to `ticket` once both can be read there.
-struct CompareOut { double *result; unsigned long long *done, ticket; };
-
 // The triples of a workgroup's threads, folded into thread 0's in a fixed order.
 template <int THREADS>
 __device__ __forceinline__ void fold(double &mx, double &se, double &sr)
@@ -83,11 +78,10 @@ __device__ __forceinline__ void fold(double &mx, double &se, double &sr)
     }
     mx = smx[0]; se = sse[0]; sr = ssr[0];
 }
-__device__ __forceinline__ void finish(const CompareOut &out, double mx, double se, double sr)
+__device__ __forceinline__ void finish(double *result, double mx, double se, double sr)
 {
-    out.result[0] = mx;
-    out.result[1] = sr > 0.0 ? sqrt(se / sr) : (se > 0.0 ? INFINITY : 0.0);
-    if (out.done) __hip_atomic_store(out.done, out.ticket, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+    result[0] = mx;                                                          // max_scaled
+    result[1] = sr > 0.0 ? sqrt(se / sr) : (se > 0.0 ? INFINITY : 0.0);      // rel_fro
 }
 
 __device__ __forceinline__ void load_vec(float (&v)[4], const float *p) { const f32x4_t t = *(const f32x4_t *)p; v[0] = t.x; v[1] = t.y; v[2] = t.z; v[3] = t.w; }
@@ -105,7 +99,7 @@ __device__ __forceinline__ void load_vec(float (&v)[1], const float *p) { v[0] =
 template <int V, bool ROWS, int THREADS>
 __global__ __launch_bounds__(THREADS)
 void compare_partial(const float *__restrict__ c, const float *__restrict__ ref, long n, const int *__restrict__ rows,
-                     long row_len, long drow, long dcol /* rows and columns a lane moves by per step */, double *__restrict__ part, CompareOut out)
+                     long row_len, long drow, long dcol /* rows and columns a lane moves by per step */, double *__restrict__ part, double *__restrict__ result)
 {
     constexpr int U = 4;
     CompareAcc a = {0.0, 0.0, 0.0, 0.0};
@@ -142,7 +136,7 @@ void compare_partial(const float *__restrict__ c, const float *__restrict__ ref,
     fold<THREADS>(mx, se, sr);
     if (threadIdx.x != 0) return;
     if (THREADS == kSmallThreads) {
-        finish(out, mx, se, sr);
+        finish(result, mx, se, sr);
     } else {
         part[blockIdx.x * 3 + 0] = mx;
         part[blockIdx.x * 3 + 1] = se;
@@ -152,7 +146,7 @@ void compare_partial(const float *__restrict__ c, const float *__restrict__ ref,
 
 // Finishes a comparison on the device: one workgroup folds the per-workgroup partials (always in the same order).
 __global__ __launch_bounds__(kThreads)
-void compare_finish(const double *__restrict__ part, int blocks, CompareOut out)
+void compare_finish(const double *__restrict__ part, int blocks, double *__restrict__ result)
 {
     double mx = 0.0, se = 0.0, sr = 0.0;
     for (int b = threadIdx.x; b < blocks; b += kThreads) {
@@ -161,7 +155,7 @@ void compare_finish(const double *__restrict__ part, int blocks, CompareOut out)
         sr += part[b * 3 + 2];
     }
     fold<kThreads>(mx, se, sr);
-    if (threadIdx.x == 0) finish(out, mx, se, sr);
+    if (threadIdx.x == 0) finish(result, mx, se, sr);
 }
 
 // Deadline control block of the scalar template: {start tick, allowed ticks, expired flag}.
@@ -303,10 +297,10 @@ double g_ticks_per_ms[64] = {0.0};
 
 namespace opevo {
 
-// The kernels of a comparison on `stream`: part holds 3 doubles for each of kBlocks workgroups; out.result is 2 doubles of device
-// memory, or of host memory the device can write.
+// The kernels of a comparison on `stream`: part holds 3 doubles for each of kBlocks workgroups, result 2 doubles (device
+// memory, or host memory the device can write).
 static int enqueue_compare(const float *c, const float *ref, int64_t n, const int *rows, int64_t row_len,
-                           hipStream_t stream, double *part, const CompareOut &out)
+                           hipStream_t stream, double *part, double *result)
 {
     const bool vec = reinterpret_cast<uintptr_t>(c) % 16 == 0 && reinterpret_cast<uintptr_t>(ref) % 16 == 0 &&
                      (!rows || row_len % 4 == 0);
@@ -320,18 +314,20 @@ static int enqueue_compare(const float *c, const float *ref, int64_t n, const in
                            : (rows ? compare_partial<1, true, kThreads> : compare_partial<1, false, kThreads>));
     const int64_t step = int64_t(blocks) * per_block;
     hipLaunchKernelGGL(k, dim3(blocks), dim3(threads), 0, stream, c, ref, (long)n, rows, (long)row_len,
-                       (long)(step / row_len), (long)(step % row_len), part, out);
+                       (long)(step / row_len), (long)(step % row_len), part, result);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return hip_fail(e, "compare_partial launch");
     if (small) return OPEVO_OK;
-    hipLaunchKernelGGL(compare_finish, dim3(1), dim3(kThreads), 0, stream, (const double *)part, blocks, out);
+    hipLaunchKernelGGL(compare_finish, dim3(1), dim3(kThreads), 0, stream, (const double *)part, blocks, result);
     e = hipGetLastError();
     return e == hipSuccess ? OPEVO_OK : hip_fail(e, "compare_finish launch");
 }
 
-// What a comparison that returns to the host needs: partials on the device, and pinned host memory that the device writes (no copy back): two
-// doubles and the ticket of the comparison that wrote them.  One per comparison under way on a device; kept for the next one, at most kSpare of them.
-struct CompareWorkspace { double *part = nullptr, *result = nullptr; unsigned long long ticket = 0; };
+// What a comparison that returns to the host needs: partials on the device and two doubles of pinned host memory that
+// the device writes (no copy back).  One per comparison under way on a device; kept for the next one, at most kSpare of them.
+// (The host waits for the stream, as the calls promise.  Waiting for a word that the device writes behind the result is over 5.8 us sooner, 65536 elements
+// 13.0 instead of 18.8 us, but the runtime does not know yet then that the stream has finished: it calls it busy.)
+struct CompareWorkspace { double *part = nullptr, *result = nullptr; };
 static constexpr size_t kSpare = 8;
 static std::vector<CompareWorkspace> g_spare[64];
 
@@ -340,21 +336,6 @@ static void release(CompareWorkspace &w)
     if (w.part) (void)hipFree(w.part);
     if (w.result) (void)hipHostFree(w.result);
     w = CompareWorkspace();
-}
-
-// Looks at a word of pinned host memory until the device has written `ticket` there, for at most 0.2 ms: a short comparison is known to be
-// finished that much sooner than through the runtime, which waits for the end of the stream's last kernel to be signalled (65536 elements 18.4 us a
-// comparison through the runtime and 13.6 so, 2 M 24.5 and 19.5, 71.7 M 116 and 111).  False: ask the runtime (earlier work on the stream takes long, or has failed).
-static bool wait_for(const unsigned long long *word, unsigned long long ticket)
-{
-    const auto until = std::chrono::steady_clock::now() + std::chrono::microseconds(200);
-    for (;;) {
-        for (int i = 0; i < 64; ++i) {
-            if (__atomic_load_n(word, __ATOMIC_ACQUIRE) == ticket) return true;
-            __builtin_ia32_pause();
-        }
-        if (std::chrono::steady_clock::now() >= until) return false;
-    }
 }
 
 int compare_f32(const float *c, const float *ref, int64_t n, const int *rows, int64_t row_len,
@@ -375,14 +356,11 @@ int compare_f32(const float *c, const float *ref, int64_t n, const int *rows, in
     }
     if (!w.part) {
         e = hipMalloc(&w.part, sizeof(double) * 3 * kBlocks);
-        if (e == hipSuccess) e = hipHostMalloc(&w.result, sizeof(double) * 3, hipHostMallocDefault);
+        if (e == hipSuccess) e = hipHostMalloc(&w.result, sizeof(double) * 2, hipHostMallocDefault);
         if (e != hipSuccess) { release(w); return hip_fail(e, "compare workspace"); }
-        std::memset(w.result, 0, sizeof(double) * 3);
     }
-    unsigned long long *const done = reinterpret_cast<unsigned long long *>(w.result + 2);
-    const CompareOut out = {w.result, done, ++w.ticket};
-    int rc = enqueue_compare(c, ref, n, rows, row_len, stream, w.part, out);
-    if (rc == OPEVO_OK && !wait_for(done, out.ticket)) {
+    int rc = enqueue_compare(c, ref, n, rows, row_len, stream, w.part, w.result);
+    if (rc == OPEVO_OK) {
         e = hipStreamSynchronize(stream);
         if (e != hipSuccess) rc = hip_fail(e, "hipStreamSynchronize");
     }
@@ -421,8 +399,7 @@ int compare_f32_static(const float *c, const float *ref, int64_t n, hipStream_t 
     if (int rc = static_scratch(&ws)) return rc;
     // every workgroup overwrites its own three partials and the fold reads only those of the workgroups launched,
     // so nothing left in the array by an earlier call is ever read: no clearing needed
-    const CompareOut out = {result_dev, nullptr, 0};
-    return enqueue_compare(c, ref, n, nullptr, 1, stream, ws, out);
+    return enqueue_compare(c, ref, n, nullptr, 1, stream, ws, result_dev);
 }
 
 int deadline_ctl(unsigned long long **ctl)

@@ -1,5 +1,5 @@
-"""How a comparison that returns to the host learns that it has finished: sizes on either side of the single workgroup's share, behind work that takes longer than the
-host looks for itself, from several threads and streams at a time."""
+"""Comparisons that return to the host: the stream is synchronised then, sizes on either side of the single workgroup's share, behind work that takes long, from
+several threads and streams at a time."""
 import threading
 
 import pytest
@@ -39,6 +39,23 @@ def test_either_side_of_a_single_workgroup(n, offset):
         P.opevo_compare_f32_static(c.data_ptr(), ref.data_ptr(), n, stream, result.data_ptr())
         torch.cuda.synchronize()
         assert tuple(result.tolist()) == P.opevo_compare_f32(c.data_ptr(), ref.data_ptr(), n, stream)
+
+
+@pytest.mark.parametrize("n", [1, 4096, 4097, 65536, 3000000])
+@pytest.mark.parametrize("rows", [False, True])
+def test_the_stream_is_synchronised(n, rows):
+    """The runtime itself calls the stream finished, on a stream of the caller's and on the default one, without being asked to wait."""
+    import torch
+    c, ref = _pair(n, n)
+    index = torch.zeros(1, dtype=torch.int32, device="cuda")
+    torch.cuda.synchronize()
+    for stream in (torch.cuda.Stream(), torch.cuda.current_stream()):
+        for _ in range(20):
+            if rows:
+                P.opevo_compare_rows_f32(c.data_ptr(), ref.data_ptr(), index.data_ptr(), 1, n, stream.cuda_stream)
+            else:
+                P.opevo_compare_f32(c.data_ptr(), ref.data_ptr(), n, stream.cuda_stream)
+            assert stream.query()
 
 
 def test_behind_work_that_takes_longer():
