@@ -120,6 +120,7 @@ int build_kernel(const opevo_op &op, int variant, const int32_t *cfg, opevo_kern
     k->name = d.kernel_name;
     k->zero_bytes = size_t(d.zero_bytes);
     k->prepass = d.prepass;
+    k->static_lds = d.static_lds;
     if (d.prepass == 1) {          // image [B][Cin][H*W] -> [B][H*W][Cin]; kernel tensor [Cout][Cin][Hk*Wk] -> [Cout][Hk*Wk][Cin]
         k->pp_batches0 = op.nimg; k->pp_rows0 = op.cin; k->pp_cols0 = op.hin * op.win;
         k->pp_batches1 = op.M; k->pp_rows1 = op.cin; k->pp_cols1 = op.hk * op.wk;
@@ -146,10 +147,11 @@ int load_kernel(opevo_kernel *k, bool refuse_spills)
         e = hipFuncGetAttribute(&scratch_bytes, HIP_FUNC_ATTRIBUTE_LOCAL_SIZE_BYTES, k->fn);
         k->scratch_bytes = e == hipSuccess ? scratch_bytes : 0;
         (void)hipGetLastError();
-        if (k->plan.path != 3 && k->plan.lds_bytes > 32768) {
+        const int dyn_lds = k->plan.lds_bytes - k->static_lds;
+        if (dyn_lds > 32768) {
             e = hipFuncSetAttribute(reinterpret_cast<const void *>(k->fn),
-                                    hipFuncAttributeMaxDynamicSharedMemorySize, k->plan.lds_bytes);
-            if (e != hipSuccess && k->plan.lds_bytes > 65536) return hip_fail(e, "hipFuncSetAttribute(max dynamic LDS)");
+                                    hipFuncAttributeMaxDynamicSharedMemorySize, dyn_lds);
+            if (e != hipSuccess && dyn_lds > 65536) return hip_fail(e, "hipFuncSetAttribute(max dynamic LDS)");
             (void)hipGetLastError();
         }
     }
@@ -192,8 +194,8 @@ int launch_kernel(opevo_kernel *k, const void *a, const void *b, void *c, hipStr
         else b = second;
     }
     void *args[] = {(void *)&a, (void *)&b, (void *)&c, (void *)&ctl};
-    // the direct-to-LDS template declares its stages statically; the others take dynamic LDS
-    const unsigned dyn_lds = k->plan.path == 3 ? 0u : unsigned(k->plan.lds_bytes);
+    // the direct-to-LDS template declares its stages itself, the few-channels one the kernel tensor's rows; the rest is dynamic
+    const unsigned dyn_lds = unsigned(k->plan.lds_bytes - k->static_lds);
     HIP_TRY(hipModuleLaunchKernel(k->fn, k->plan.grid[0], k->plan.grid[1], k->plan.grid[2],
                                   k->plan.block, 1, 1, dyn_lds, stream, args, nullptr));
     return OPEVO_OK;

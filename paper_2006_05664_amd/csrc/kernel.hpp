@@ -18,6 +18,7 @@ struct opevo_kernel {
     hipModule_t module = nullptr;  // loaded on first launch
     hipFunction_t fn = nullptr;
     int scratch_bytes = 0;         // private scratch per lane the compiler used (known once loaded)
+    int32_t static_lds = 0;        // bytes of plan.lds_bytes that the kernel declares itself
     // Members whose kernel reads re-laid-out operands.  Every launch first runs one pre-pass kernel on
     // the same stream that writes them into `workspace` (allocated when the module is loaded).
     //   prepass 1 (Conv2d, channels last): [kernel tensor as [Cout][Hk*Wk][Cin]] [256 bytes of zeros]

@@ -232,7 +232,7 @@ static bool plan_ragged(const opevo_op &op, int64_t bm, int64_t bn, int64_t bk, 
 }
 
 // How the few-channels convolution template runs a box: atom, wave grid, atoms per wave, padded kernel row, LDS bytes.
-struct Rows { int atom = 0, wm = 0, wn = 0, mi = 0, ni = 0, wkp = 0, persist = 0, stage = 0; int64_t lds = 0; };
+struct Rows { int atom = 0, wm = 0, wn = 0, mi = 0, ni = 0, wkp = 0, persist = 0, stage = 0; int64_t lds = 0, beside = 0; };   // beside: what of lds is the kernel's own array
 
 static bool plan_rows(const opevo_op &op, int64_t bm, int64_t nb2, int64_t bh, int64_t bw, int64_t boxes, int64_t m1, bool linear, Rows &out)
 {
@@ -268,6 +268,7 @@ static bool plan_rows(const opevo_op &op, int64_t bm, int64_t nb2, int64_t bh, i
     // as many workgroups with it.  Drawn members 1.03 - 1.85 times as fast as with fragments straight from memory (0), 44 random ones 0.97 - 1.98, 1.16x in the geometric mean.
     const int64_t rows_bytes = (bm * op.K + 128) * 2;
     out.stage = rows_bytes <= lds ? 1 : rows_bytes <= 65536 && (lds + rows_bytes) * std::max<int64_t>(1, 8 / (out.wm * out.wn)) <= kMaxLds ? 2 : 0;
+    if (out.stage == 2) { out.beside = rows_bytes; out.lds += rows_bytes; }
     // with four and more boxes for every workgroup the chip holds, that many workgroups take them in turn and fetch the kernel
     // tensor once
     const int64_t resident = 256 * std::max<int64_t>(1, std::min<int64_t>(8 / (out.wm * out.wn), kMaxLds / lds));
@@ -916,6 +917,7 @@ int decode(const opevo_op &op, int variant, const int32_t *cfg, Decoded &out, bo
     if (rows.persist > 0) p.grid[0] = rows.persist;   // workgroups that take several boxes each
     p.block = int32_t(NT > INT32_MAX ? INT32_MAX : NT * kgrp);
     p.lds_bytes = int32_t(lds > INT32_MAX ? INT32_MAX : lds);
+    out.static_lds = path == 3 ? p.lds_bytes : int32_t(rows.beside);
     p.acc_per_lane = int32_t(acc > INT32_MAX ? INT32_MAX : acc);
     p.tile[0] = int32_t(BM); p.tile[1] = int32_t(BN); p.tile[2] = int32_t(BK);
     p.wave_tile[0] = int32_t(four_level ? TM : BM); p.wave_tile[1] = int32_t(four_level ? TN : BN);

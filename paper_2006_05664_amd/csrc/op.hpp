@@ -39,6 +39,7 @@ struct Decoded {
     // pre-pass before every launch: 0 none; 1 Conv2d: the kernel reads channels-last copies of both operands;
     // 2 MatMul: the kernel reads a copy of the second operand transposed to [N][K]
     int prepass = 0;
+    int32_t static_lds = 0;    // bytes of plan.lds_bytes that the kernel declares itself; a launch asks for the others
 };
 
 // OPEVO_OK (plan.status says valid/invalid) or OPEVO_E_ILLEGAL / OPEVO_E_ARG.

@@ -38,8 +38,8 @@ def test_a_fragment_s_words_and_shift(label, dims, variant, cfg, stage):
     _, CIN, _, _, M, HK, WK, _, _ = dims
     BM, K, atom, NT = D["BM"], CIN * HK * WK, D["ATOM"], D["NT"]
     room = BM * K + 128
-    assert BM * K % 8 == 0 and (stage == 2 or room * 2 <= plan.lds_bytes) and room * 2 <= 65536 + 64 * 1024 * (stage == 1)
-    assert plan.lds_bytes + (room * 2 if stage == 2 else 0) <= 160 * 1024 // max(1, 8 // (D["WM"] * D["WN"]))
+    assert BM * K % 8 == 0 and room * 2 <= plan.lds_bytes and room * 2 <= 65536 + 64 * 1024 * (stage == 1)
+    assert plan.lds_bytes == D["LDS_BYTES"] <= 160 * 1024 // max(1, 8 // (D["WM"] * D["WN"]))
     Q = D["WKP"] // 8
     RPS = (2 if atom == 32 else 4) // Q
     SPC = -(-HK // RPS)
@@ -61,6 +61,20 @@ def test_a_fragment_s_words_and_shift(label, dims, variant, cfg, stage):
                     tap, r = kg % Q * 8 + e, t % SPC * RPS + kg // Q
                     if tap < WK and r < HK:                                   # the others are cleared
                         assert words[e] == row * K + (t // SPC * HK + r) * WK + tap
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("label,dims,variant,cfg,stage", CASES, ids=[c[0] for c in CASES])
+def test_the_plan_counts_all_the_lds(label, dims, variant, cfg, stage):
+    """The kernel tensor's rows beside the patch are an array of the kernel's own, which the plan's figure includes."""
+    op = P.opevo_op_create(P.OPEVO_CONV2D, dims, P.OPEVO_BF16)
+    kernel, _ = P.opevo_kernel_build(op, variant, cfg)
+    static = P.opevo_kernel_resources(kernel)["static_lds"]
+    P.opevo_kernel_destroy(kernel)
+    plan = P.opevo_kernel_plan(op, variant, cfg)
+    tmpl, D = _defs(op, variant, cfg)
+    assert static == ((D["BM"] * D["K"] + 128) * 2 if tmpl == "conv_rows" and stage == 2 else 0)
+    assert static == 0 or static < plan.lds_bytes == D["LDS_BYTES"]
 
 
 @pytest.mark.gpu
