@@ -1019,8 +1019,7 @@ int decode(const opevo_op &op, int variant, const int32_t *cfg, Decoded &out, bo
     // reductions on a full chip have the plain loop with the second operand read step by step (8 x 64 x 28 x 28 * 64 x 64 x 3 x 3 as 112 x 1 waves 77.5 us so and
     // 82.0 pipelined, as 112 x 7 waves 54.8 and 61.1, on slabs of 2 as 32 x 1 waves 1020 and 1139; 2048 x 2048 x 128, 1024 x 2 waves, 15.7 and 17.5; four other
     // convolutions between 0.7 % slower and 2 % faster).
-    if (f32_kw) out.tries = {" -DPIPELINED=1"};        // the loop of the template that takes values apart
-    else if (path == 4 && nstage == 2) {
+    if (path == 4 && nstage == 2 && !f32_kw) {
         const bool full_chip = n_blocks * nwr >= 2048;
         if (BKP == 8 && (op.kind == OPEVO_CONV2D || (full_chip && ksteps * BKP <= 128))) out.tries = {" -DSTEP_READS=1", " -DPIPELINED=1", ""};
         else if (!(full_chip && ksteps < 8)) out.tries = {" -DPIPELINED=1", ""};

@@ -16,11 +16,15 @@ def _loop(kind, dims, cfg):
     plan = P.opevo_kernel_plan(op, P.OPEVO_TILE4, cfg)
     assert plan.status == P.OPEVO_OK and plan.path == 4, (plan.path, plan.reason)
     words = P.opevo_kernel_defines(op, P.OPEVO_TILE4, cfg).split()
+    if words[0] != "gemm_mfma_f32:":
+        return words[0]
     return "pipelined" if "-DPIPELINED=1" in words else "step" if "-DSTEP_READS=1" in words else "plain"
 
 
 @pytest.mark.parametrize("kind,dims,cfg,want", [
-    (MM, (512, 4096, 1024), [8, 2, 16, 2, 64, 2, 32, 1, 16, 64, 1], "pipelined"),
+    (MM, (512, 4096, 1024), [8, 2, 16, 2, 64, 2, 32, 1, 16, 64, 1], "gemm_f32_split:"),     # another template, with a loop of its own
+    (MM, (512, 4032, 1024), [8, 2, 16, 2, 42, 1, 96, 1, 16, 64, 1], "pipelined"),           # 96 columns
+    (TA, (4, 64, 128, 448), [2, 2, 1, 2, 1, 32, 2, 2, 1, 32, 14, 32, 1], "pipelined"),
     (MM, (512, 4096, 1024), [8, 2, 16, 2, 64, 2, 32, 1, 16, 64, 0], "plain"),           # one stage
     (TA, (960, 128, 64, 128), [960, 1, 1, 2, 2, 32, 1, 2, 1, 32, 4, 32, 1], "plain"),   # 960 x 4 waves, 4 slabs
     (MM, (2048, 2048, 128), [32, 1, 1, 64, 32, 2, 1, 32, 16, 8, 1], "step"),            # 1024 x 2 waves, 16 slabs of 8: 15.7 us; pipelined 17.5
