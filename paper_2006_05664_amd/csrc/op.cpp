@@ -946,21 +946,31 @@ int decode(const opevo_op &op, int variant, const int32_t *cfg, Decoded &out, bo
     }
 
     out.tmpl = path == 0 ? "gemm_scalar" : path == 3 ? "gemm_mfma_dlds" : path == 4 ? (f32_kw ? "gemm_f32_split" : "gemm_mfma_f32") : path == 5 ? (strip.rows ? "conv_strip" : "conv_patch") : path == 6 ? "gemm_ragged" : path == 7 ? "conv_rows" : "gemm_mfma";
-    // one symbol per configuration, so profiles list each instantiated kernel on its own line
+    // One symbol per configuration, so profiles list each instantiated kernel on its own line.  Templates that take the workgroup tile alone and divide it by
+    // themselves make one program of all configurations with that tile (box): they are named by it, and given no constant that they do not read, so
+    // that the program is compiled once.
+    const bool whole = f32_kw || rg_kw;             // every wave has the whole tile
     {
         std::ostringstream nm;
-        nm << "opevo_" << (op.kind == OPEVO_MATMUL ? "mm" : op.kind == OPEVO_BMM ? (op.trans_a ? "bmmt" : "bmm") : "conv")
+        nm << "opevo_" << (op.kind == OPEVO_MATMUL ? "mm" : op.kind == OPEVO_BMM ? (op.trans_a ? "bmmt" : "bmm") : "conv");
+        if (whole) {
+            nm << (f32_kw ? "_split_" : "_shared_") << BM << "_" << BN << "_" << (f32_kw ? f32_kw : rg_kw) << "_" << binner;
+            if (linear) nm << "_" << order[0] << order[1] << order[2] << "_" << group;
+        } else if (strip.rows) {
+            nm << "_strip_" << BM << "_" << nb2 << "_" << BH << "_" << BW << "_" << strip.cs << "_" << strip.wm << "_" << strip.rows << "_" << strip.kw;
+            flagv = 0; FM = FN = 1;
+        } else nm
            << (variant == OPEVO_TILE4P ? "p" : variant == OPEVO_TILE4K ? "k" : variant == OPEVO_TILE4C ? "c" : variant == OPEVO_TILE4T ? "t" : variant == OPEVO_TILE4A ? "a" : variant == OPEVO_TILE4L ? "l" : four_level ? "4" : "2");
         int width = 0;
         for (const auto &d : descs) width += d.type == OPEVO_FACTOR ? d.nu : d.type == OPEVO_PERMUTATION ? d.n_values : 1;
-        for (int i = 0; i < width; ++i) nm << "_" << cfg[i];
+        for (int i = 0; i < width && !whole && !strip.rows; ++i) nm << "_" << cfg[i];
         out.kernel_name = nm.str();
     }
     D << "-DKERNEL_NAME=" << out.kernel_name << " ";
     D << "-DOP=" << op.kind << " -DIN_DTYPE=" << op.dtype << " -DM=" << op.M << " -DN=" << op.N
-      << " -DK=" << op.K << " -DBM=" << BM << " -DBN=" << BN << " -DBK=" << BK << " -DKSTEPS=" << ksteps
-      << " -DNT=" << NT << " -DBATCH_INNER=" << binner << " -DFLAG=" << flagv << " -DA_TRANS=" << (op.trans_a ? 1 : 0);
-    if (path != 0) {
+      << " -DK=" << op.K << " -DBM=" << BM << " -DBN=" << BN << " -DNT=" << NT << " -DBATCH_INNER=" << binner << " -DA_TRANS=" << (op.trans_a ? 1 : 0);
+    if (!whole) D << " -DBK=" << BK << " -DKSTEPS=" << ksteps << " -DFLAG=" << flagv;
+    if (path != 0 && !whole) {
         D << " -DATOM=" << (path == 7 ? rows.atom : path == 5 ? patch_atom : (path == 2 || path == 6 || dlds_atom16) ? 16 : 32) << " -DWM=" << WM << " -DWN=" << WN << " -DTM=" << TM
           << " -DTN=" << TN << " -DFM=" << FM << " -DFN=" << FN << " -DPAD=" << kPad
           << " -DNSTAGE=" << nstage << " -DNSTG=" << nstage << " -DSTAGE_LDS=" << (stage_lds ? 1 : 0);
@@ -1030,7 +1040,7 @@ int decode(const opevo_op &op, int variant, const int32_t *cfg, Decoded &out, bo
     // output after them 1.01x for the two together (0.94 - 1.13), 1.03x alone; K of 256 to 6208 0.91 - 1.02x (mostly 1.00).  Rows of 64 or of any number of bytes (16-bit
     // inputs on 16 x 16 atoms, ragged tiles) 0.59 - 1.20x without a line between them: those stay with ordinary stores.
     const int64_t out_bytes = op.c_elems() * 4;
-    if (path == 4 && op.kind != OPEVO_CONV2D && ksplit == 1 && op.K <= 224 && out_bytes >= (int64_t(2) << 20) && out_bytes <= (int64_t(32) << 20)) D << " -DNT_OUT=1";
+    if (path == 4 && !f32_kw && op.kind != OPEVO_CONV2D && ksplit == 1 && op.K <= 224 && out_bytes >= (int64_t(2) << 20) && out_bytes <= (int64_t(32) << 20)) D << " -DNT_OUT=1";
     if (f32_kw) D << " -DKW=" << f32_kw << " -DLDS_BYTES=" << lds << " -DMINW=2";
     if (kgrp > 1) D << " -DKGRP=" << kgrp;
     if (kunroll) D << " -DKUNROLL=" << kunroll;

@@ -25,9 +25,6 @@ typedef __attribute__((ext_vector_type(8))) __bf16 frag_t;
 typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
 typedef __attribute__((ext_vector_type(2))) float f32x2;
 typedef f32x16 acc_t;
-#ifndef NT_OUT
-#define NT_OUT 0
-#endif
 
 constexpr int MI = BM / 32, NI = BN / 32;
 constexpr int KC = 32;                              // reduction steps of a chunk: two MFMA steps
