@@ -215,8 +215,9 @@ static bool plan_ragged(const opevo_op &op, int64_t bm, int64_t bn, int64_t bk, 
         if (score <= best) { best = score; out.ks = int(ks); out.slabs = int(slabs); out.stages = stages; out.lds = lds; }
     }
     if (best == INT64_MAX) return false;
-    // Two slabs on their way instead of one where a workgroup is alone on its compute unit for a long reduction (567 x 330 x 4450 in 27 x 30, 231
-    // workgroups x 70 slabs, 18.1 -> 16.2 us; 110 x 72 x 864, 15 x 27, 5.9 -> 5.1; 840 x 2150 x 1368, 602 x 22, 22.1 -> 24.3); the places of a thread's pieces are kept
+    // Two slabs on their way instead of one where a workgroup is alone on its compute unit for a long reduction (600 x 990 x 2250 in 60 x 110, 90
+    // workgroups x 71 slabs, 29.2 -> 25.3 us; 900 x 1080 x 3150 in 90 x 90, 120 x 50, 34.3 -> 31.8; but 1200 x 900 x 1310 in 60 x 90, 200 x 41, 16.2 -> 17.3, and with a second
+    // workgroup, 840 x 2150 x 1368, 602 x 22, 22.1 -> 24.3; tiles of up to 20 atoms and K >= 448 share the reduction instead); the places of a thread's pieces are kept
     // in registers where there is room for them, else worked out again for every slab.
     const int64_t nw = out.wm * out.wn, held = staging(out.ks, 64 * nw);
     const int64_t fit = std::max<int64_t>(1, std::min(kMaxLds / out.lds, (wgs + 255) / 256));       // workgroups on a compute unit
@@ -368,8 +369,8 @@ static int xcd_walk(const opevo_op &op, int64_t n1, int64_t m1, int64_t b1, int6
     }
     if ((op.a_elems() + op.b_elems()) * e <= (int64_t(4) << 20)) return 0;
     // Grids that do not fill the chip: an XCD has an eighth of the tiles.  On the matrix templates and with reductions of 2100 bytes and more 41 drawn members 1.10x in
-    // the geometric mean (0.98 - 1.57: 2112 x 128 x 4064 in 64 x 64 18.0 -> 13.2 us, 180 x 1056 x 3267 in 60 x 32 17.1 -> 11.2); shorter ones pay for the
-    // division (96 x 4224 x 896 4.51 -> 4.68).  40 random ragged members 1.14x (0.96 - 1.86).  39 random scalar members gain less and lose more (1.06x, 0.94 - 1.40).
+    // the geometric mean (0.98 - 1.57: 2112 x 128 x 4064 in 64 x 64 18.0 -> 13.2 us, 180 x 1056 x 3267 in 60 x 32 17.1 -> 11.2), 26 further ones 0.99 - 1.64x.  The line is on the safe
+    // side: short ones can pay for the division (96 x 4224 x 896 4.51 -> 4.68, 4352 x 96 x 480 6.15 -> 6.34), most gain (18 members of 832 - 2000 bytes 0.97 - 1.62x, 1.19x).  40 random ragged members 1.14x (0.96 - 1.86).  39 random scalar members gain less and lose more (1.06x, 0.94 - 1.40).
     if (matrix && op.K * e >= 2100) W = std::min(W, up(tiles, 8));
     const double nat = natural(std::min(tiles, 8 * W));
     const double by_col = double(std::min(n1, W) * bn * e + 128 + up(W, n1) * row), by_row = double(up(W, m1) * bn * e + 128 + std::min(m1, W) * bm * e);
@@ -589,8 +590,8 @@ int decode(const opevo_op &op, int variant, const int32_t *cfg, Decoded &out, bo
                 // template against new: 1.20 - 1.26x in the geometric mean, 0.94 - 2.5x; what was below 0.94 is excluded by the conditions in plan_strip.
                 // Members that ask for pipelining go there too on more workgroups than compute units: the second stage costs them the other workgroups that would
                 // hide a slab's latency.  94 drawn and random members with three pixel waves and more 0.94 - 2.7x, 1.28x in the geometric mean (53 x 256 x 27 x 27 *
-                // 64 x 256 x 3 x 3 31.2 -> 26.5 us, 163 x 256 x 14 x 14 * 256 x 256 x 3 x 3 74.4 -> 53.3; the slowest 11 x 32 x 56 x 56 * 128 x 32 x 3 x 3 10.9 -> 11.5).  On fewer
-                // workgroups, and with two pixel waves, they keep the two-stage loop that they ask for.
+                // 64 x 256 x 3 x 3 31.2 -> 26.5 us, 163 x 256 x 14 x 14 * 256 x 256 x 3 x 3 74.4 -> 53.3; the slowest 11 x 32 x 56 x 56 * 128 x 32 x 3 x 3 10.9 -> 11.5).  Two pixel waves
+                // (11 members 1.4 - 2.4x as fast there) and grids of up to 256 workgroups (17 members 1.04 - 1.30x) were too few to draw a line by: they stay.
                 const int64_t asked_n = int64_t(h[1]) * w[1], asked = c[3] * asked_n * int64_t(kReductionWaves[c[18]]);
                 if (extras && patch_cs && (asked > kMaxThreads / 64 || (c[18] == 0 && (flagv == 0 ? asked_n >= 2 : asked_n >= 3 && n1 * m1 > 256))) &&
                     plan_strip(op, WM * TM, nb2, BH, BW, n1 * m1, patch_kw, strip)) {
@@ -841,7 +842,8 @@ int decode(const opevo_op &op, int variant, const int32_t *cfg, Decoded &out, bo
     // 1.12x in the geometric mean, three of them below 0.99 (1040 workgroups of two waves, 128 x 64, five slabs of 32: 11.7 -> 12.7 us).
     // With two waves or fewer on a compute unit, if it does not fit with any, the most stages that give it more: 20 drawn members 1.07 -
     // 1.40x, 1.22x (4544 x 3328 x 2112 in 64 x 128, two waves: 143 -> 104 us).  Three and more waves in grids that do
-    // not fit in any case: 0.84 - 1.17x, 1.04x; those keep the ring.
+    // not fit in any case: 0.84 - 1.17x, 1.04x; those keep the ring.  So do members on 16x16x32 atoms: 30 drawn ones 0.59 - 1.76x, 1.14x, the slow ones (5120 x 1920 x 4096 in
+    // 128 x 128, two waves, 115 -> 196 us; 5504 x 1536 x 1024 in 128 x 256, eight waves, 33 -> 40) with no line around them yet.
     if (path == 3 && kgrp == 1 && op.kind != OPEVO_CONV2D && !dlds_atom16) {
         const int64_t nw = WM * WN, stage = (BM + BN) * BK * 2, wgs = n1 * m1 * b1;
         auto resident = [&](int st) { return std::min<int64_t>(kMaxLds / (st * stage), 32 / nw); };

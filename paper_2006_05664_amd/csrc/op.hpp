@@ -43,8 +43,8 @@ struct Decoded {
 };
 
 // OPEVO_OK (plan.status says valid/invalid) or OPEVO_E_ILLEGAL / OPEVO_E_ARG.
-// extras = false: without the few-channels and the row-strip convolution templates, and without waves that a patch or direct-to-LDS member did not
-// ask for (a member that turned out to spill with them).  The order of the workgroups is one of the `tries`.
+// extras = false: without the few-channels and the row-strip convolution templates and the one that takes fp32 values apart, and without waves that a
+// patch, direct-to-LDS or ragged member did not ask for (a member that turned out to spill with them).  The order of the workgroups is one of the `tries`.
 int decode(const opevo_op &op, int variant, const int32_t *cfg, Decoded &out, bool extras = true);
 int op_param_descs(const opevo_op &op, int variant, std::vector<opevo_param_desc> &descs);
 

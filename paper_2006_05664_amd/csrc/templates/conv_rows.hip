@@ -24,7 +24,8 @@
 // TFLOP/s: some ten instructions per gathered value), here 198 - 215 us with the output stored column by column, 173 - 184 us row by row, and
 // 161 us with the kernel tensor through the LDS (450 TFLOP/s, 3.4 TB/s).  What bounds it: 396 MB of output in rows of 220 bytes that begin anywhere in a cache line (alone, without fill and
 // multiplication, 136 us column by column and 109 row by row; non-temporal stores take 386, a contiguous run of boxes per
-// workgroup 249), and that a box's load, multiplication and store follow one another, with two workgroups per compute unit.
+// workgroup 249), and that a box's load, multiplication and store follow one another, with two workgroups per compute unit (of 163 us, without
+// the stores 116, without the fill 134, without the multiplication 168: that is covered by the other workgroup).
 // PERSIST > 0: that many workgroups along the boxes, each taking several; the kernel tensor is then fetched once per workgroup.
 // Boxes are dealt so that the workgroups of one XCD (every eighth) walk one contiguous eighth of them: boxes one above the other share
 // HK - STRIDE of their image rows, through that XCD's L2.
