@@ -1,10 +1,14 @@
 """The template that multiplies fp32 values as three bf16 parts each: which members it takes, and its results where its parts meet: every tile, parts of the
 reduction of unequal length, four and eight waves, a transposed first operand, batches, values that cannot be taken apart, sums beyond the range."""
+import re
+import subprocess
+
 import numpy as np
 import pytest
 
 import paper_2006_05664_amd as P
 from paper_2006_05664_amd import synth
+from test_zz_load_base_wait import OBJDUMP, short_of_wait_states
 
 MM, BMM, TA = P.OPEVO_MATMUL, P.OPEVO_BMM, P.OPEVO_BMM_TA
 V, X, K3 = P.OPEVO_TILE4, P.OPEVO_TILE4X, P.OPEVO_TILE4K
@@ -64,6 +68,63 @@ def test_where_the_first_operand_s_pieces_go(bm):
                 for e in range(4):
                     assert (lds[piece * 4 + e] == row * K + t * 16 + 8 * (lane // 32) + 4 * half + e).all()
                 assert all(len(set(piece[g:g + 16] % 16)) == 16 for g in range(0, 64, 16))
+
+
+@pytest.mark.parametrize("dims,cfg,atoms", [
+    ((128, 192, 480), [2, 2, 1, 32, 3, 2, 1, 32, 15, 32, 1], (2, 2)),
+    ((64, 128, 352), [2, 1, 1, 32, 2, 1, 2, 32, 11, 32, 1], (1, 2)),
+    ((64, 96, 320), [1, 1, 2, 32, 3, 1, 1, 32, 10, 32, 1], (2, 1)),
+    ((96, 64, 736), [3, 1, 1, 32, 2, 1, 1, 32, 23, 32, 1], (1, 1)),
+])
+def test_every_fragment_is_read_after_its_loads(dims, cfg, atoms, tmp_path):
+    """The loop of the compiled kernel, three times round.  The first operand's loads go to the LDS unseen by the compiler, so the kernel waits for them itself:
+    when the fragments of a chunk's second step are read, the chunk's loads were issued two rounds before, when the next chunk's first step is, one round
+    before.  Waits leave the youngest loads under way; loads are served in order."""
+    op = P.opevo_op_create(MM, dims, P.OPEVO_F32)
+    P.opevo_code_cache_configure(str(tmp_path), 0)
+    try:
+        kernel, _ = P.opevo_kernel_build(op, V, cfg)
+        P.opevo_kernel_destroy(kernel)
+    finally:
+        P.opevo_code_cache_configure(None, 256 << 20)
+    files = list(tmp_path.iterdir())
+    assert len(files) == 1, "one compilation: it does not spill"
+    data = files[0].read_bytes()
+    code = tmp_path / "kernel.co"
+    code.write_bytes(data[data.index(b"\x7fELF"):])
+    asm = subprocess.run([OBJDUMP, "-d", "--mcpu=gfx950", str(code)], capture_output=True, text=True, check=True).stdout
+    assert short_of_wait_states(asm) == []
+    ins = []                                                  # (address, text)
+    for line in asm.splitlines():
+        m = re.match(r"\t(.*?)\s*// ([0-9A-F]{12}):", line)
+        if m:
+            ins.append((int(m[2], 16), m[1].strip()))
+    at = {a: i for i, (a, _) in enumerate(ins)}
+    loops = []
+    for i, (a, t) in enumerate(ins):
+        m = re.match(r"s_cbranch_\w+ (\d+)", t)
+        if m and int(m[1]) > 32767 and a + 4 + 4 * (int(m[1]) - 65536) in at:
+            loops.append([t for _, t in ins[at[a + 4 + 4 * (int(m[1]) - 65536)]:i]])
+    body = [b for b in loops if sum("mfma_f32_32x32x16_bf16" in t for t in b) == 16 * atoms[0] * atoms[1]]
+    assert len(body) == 1
+    body, pieces = body[0], 4 * atoms[0]
+    assert sum(t.startswith("global_load_lds") for t in body) == pieces and sum(t.startswith("ds_read_b128") for t in body) == 4 * atoms[0]
+    pending = []                                              # rounds of the loads to the LDS under way, None for loads to registers; the oldest first
+    for r in range(4):
+        reads = 0
+        for t in body:
+            if t.startswith("global_load_lds"):
+                pending.append(r)
+            elif t.startswith("global_load"):
+                pending.append(None)
+            elif t.startswith("s_waitcnt") and "vmcnt" in t:
+                left = int(re.search(r"vmcnt\((\d+)\)", t)[1])
+                pending = pending[len(pending) - left:] if left < len(pending) else pending
+            elif t.startswith("ds_read_b128"):
+                done_by = r - 2 if reads < 2 * atoms[0] else r - 1
+                assert all(p is None or p > done_by for p in pending), (r, reads, pending)
+                reads += 1
+            assert not t.startswith(("ds_write", "s_barrier"))
 
 
 def test_members_that_could_not_run_without_it_stay_invalid():
