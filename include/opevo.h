@@ -317,8 +317,9 @@ typedef struct {
                               operands streamed global -> LDS directly, 4 fp32 inputs: MFMA 32x32x2, or for
                               MatMul / BMM with long reductions every value as three bf16 parts on
                               MFMA 32x32x16, eight of the nine products of parts: a product rounds as in
-                              fp32, a long sum less often; values and sums for which that does not hold
-                              (below 2^-100 and 2^-110, not finite) are computed by MFMA 32x32x2,
+                              fp32, a sum less often (of few products whose magnitudes lie many powers of
+                              two apart: up to 1.2 times the error); values and sums for which that does
+                              not hold (below 2^-100 and 2^-110, not finite) are computed by MFMA 32x32x2,
                               5 Conv2d with an LDS-resident image patch (either atom), 6 MatMul / BMM
                               whose extents are no multiples of 16, tiles of any extent on MFMA 16x16x32,
                               7 Conv2d with fewer than 16 input channels, image rows in LDS (either atom) */

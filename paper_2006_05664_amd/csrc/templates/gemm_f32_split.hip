@@ -3,11 +3,12 @@
 // Every fp32 value is taken apart into three bf16 values, each the rest rounded to nearest, that add up to it exactly (3 x 8 bits; magnitudes from 2^-100
 // on; G. Henry, P. T. P. Tang, A. Heinecke, "Leveraging the bfloat16 Artificial Intelligence Datatype For Higher-Precision Computations", ARITH 2019).
 // Of the nine products of two such triples all but the smallest, at most 2^-36 of the whole, are multiplied on 32x32x16 bf16 atoms.  The product of the
-// upper parts, exact in fp32, has an accumulator of its own, the seven others (2^-7 of it and less) share one, and the two are added at the end.  A
+// upper parts, exact in fp32, has an accumulator of its own, the seven others (2^-7 of it and less) share one, and the two are added when the waves' sums have met.  A
 // bf16 atom whose product is larger than its accumulator cuts the accumulator off at the product's last bit, so that in one
 // accumulator a sum of a single product was wrong in the last place in one case of five (norm of the errors 3.4e-8); so it is rounded once,
 // as by fp32 arithmetic (normal operands: largest error 5.97e-8, norm 2.54e-8; fp32 atoms 5.95e-8, 2.53e-8), and long sums are rounded once instead of eight
-// times for 16 products: against 64 bits, K = 1024 5.7e-7 -> 1.0e-7, 4096 1.1e-6 -> 1.4e-7 (four or eight partial sums; smaller for each of 38 drawn operators).
+// times for 16 products: against 64 bits, K = 1024 5.7e-7 -> 1.0e-7, 4096 1.1e-6 -> 1.4e-7 (four or eight partial sums; smaller for each of 38 drawn operators).  Sums of 2 - 64
+// normal products 0.34 - 0.87 times the fp32 atoms' error; of 2 - 16 products whose magnitudes lie up to 2^48 apart, where that cut falls on the upper parts' sum, 0.4 - 1.2 times.
 // Values below 2^-100, sums below 2^-110 (whose smaller parts would be subnormal), infinities, NaN and sums beyond the range take the fp32 atoms (EXACT).
 //
 // KW waves share a tile: each takes a contiguous part of the reduction with the whole tile as its wave tile, and the sums meet in LDS at the end.  So
@@ -19,8 +20,8 @@
 //     registers a 64 x 64 tile needs 300 of them: one wave on a SIMD, 512 x 4096 x 1024 44 us; so, and with a fragment read when its turn comes, 251.
 //   * While a step's MFMAs run, the next step's values are taken apart between them, and the step after that is on its way.
 // What bounds it: instruction issue (15 vector instructions per two values, 7.5 beside every MFMA of a 64 x 64 tile) about as much as the pipes, and on
-// the whole chip the pipes' power.  Times on this card, fp32 atoms -> here: 512 x 4096 x 1024 in 64 x 64 tiles 40.1 -> 37.3 us; 2336 x 3200 x 1088
-// in 32 x 32 230 -> 178; few workgroups: 64 x 1152 x 4096 (18) 80 -> 47, 672 x 192 x 2560 (126) 53 -> 15.8, 224 x 512 x 896 (56) 20 -> 12.2.
+// the whole chip the pipes' power.  Times on this card, fp32 atoms -> here: 512 x 4096 x 1024 in 64 x 64 tiles 40.1 -> 37.7 us; 2336 x 3200 x 1088
+// in 32 x 32 230 -> 178; few workgroups: 64 x 1152 x 4096 (18) 80 -> 48, 672 x 192 x 2560 (126) 53 -> 16.2, 224 x 512 x 896 (56) 20 -> 12.7.
 typedef __attribute__((ext_vector_type(8))) __bf16 frag_t;
 typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
 typedef __attribute__((ext_vector_type(2))) float f32x2;
@@ -29,7 +30,7 @@ typedef f32x16 acc_t;
 constexpr int MI = BM / 32, NI = BN / 32;
 constexpr int KC = 32;                              // reduction steps of a chunk: two MFMA steps
 constexpr int NCHUNK = K / KC;
-static_assert(BM % 32 == 0 && BN % 32 == 0 && K % KC == 0 && MI <= 2 && NI <= 2 && NT == 64 * KW && KW > 1 && KW <= NCHUNK, "decoder and template disagree");
+static_assert(BM % 32 == 0 && BN % 32 == 0 && K % KC == 0 && MI <= 2 && NI <= 2 && NT == 64 * KW && KW > 1 && KW <= NCHUNK && 8 % KW == 0, "decoder and template disagree");
 constexpr int A_WAVE = A_TRANS ? 0 : 2 * BM * KC;   // floats of LDS that are a wave's own
 constexpr int RED = KW * BM * BN;                   // floats of the partial sums, in the same place
 static_assert(4 * (KW * A_WAVE > RED ? KW * A_WAVE : RED) == LDS_BYTES, "decoder and template disagree");
@@ -131,10 +132,7 @@ __device__ __forceinline__ void fetch_a(const ARegs &, const Lane &l, int c, int
 }
 #endif
 
-// A wave's part of the reduction, chunks c0 .. c1 - 1.  EXACT: on the fp32 matrix pipes; with only >= 0 that atom of the tile alone, i * NI + j.  Returns
-// what the values' smallest magnitude is judged by.
-template <bool EXACT>
-__device__ __forceinline__ u32 reduce(acc_t (&acc)[MI][NI], const Lane &l, int c0, int c1, int only = -1)
+__device__ __forceinline__ void clear(acc_t (&acc)[MI][NI])
 {
 #pragma unroll
     for (int i = 0; i < MI; ++i)
@@ -142,6 +140,14 @@ __device__ __forceinline__ u32 reduce(acc_t (&acc)[MI][NI], const Lane &l, int c
         for (int j = 0; j < NI; ++j)
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+}
+
+// A wave's part of the reduction, chunks c0 .. c1 - 1: the sums of the products of upper parts, and of the others.  EXACT: on the fp32 matrix pipes, in acc; with
+// only >= 0 that atom of the tile alone, i * NI + j.  Returns what the values' smallest magnitude is judged by.
+template <bool EXACT>
+__device__ __forceinline__ u32 reduce(acc_t (&hi)[MI][NI], acc_t (&acc)[MI][NI], const Lane &l, int c0, int c1, int only = -1)
+{
+    clear(acc);
     u32 low = ~0u;
     ARegs a;
     KRows<NI> b[2];
@@ -203,6 +209,7 @@ __device__ __forceinline__ u32 reduce(acc_t (&acc)[MI][NI], const Lane &l, int c
 #if !A_TRANS
         wait_loads<0>();                                // nothing is on its way to the LDS any longer
 #endif
+        clear(hi);
         return low;
     }
     Planes pa[2][MI], pb[2][NI];
@@ -219,13 +226,7 @@ __device__ __forceinline__ u32 reduce(acc_t (&acc)[MI][NI], const Lane &l, int c
     // MFMAs of a step; after which of them the second operand's values are no longer waited for, and where the first operand's first fragment is read
     constexpr int WORDS = 4 * (MI + NI), MFMAS = 8 * MI * NI, LOAD_AT = 4 * MFMAS / WORDS, EARLY = 4;
     constexpr auto fetch_at = [](int i) { return MFMAS * (NI + i) / (NI + MI) - EARLY; };
-    acc_t hi[MI][NI];                                   // the products of the upper parts (acc: of the others)
-#pragma unroll
-    for (int i = 0; i < MI; ++i)
-#pragma unroll
-        for (int j = 0; j < NI; ++j)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) hi[i][j][r] = 0.f;
+    clear(hi);
     {
         float x[MI][8];
 #pragma unroll
@@ -276,12 +277,6 @@ __device__ __forceinline__ u32 reduce(acc_t (&acc)[MI][NI], const Lane &l, int c
 #if !A_TRANS
     wait_loads<0>();                                    // nothing is on its way to the LDS any longer
 #endif
-#pragma unroll
-    for (int i = 0; i < MI; ++i)
-#pragma unroll
-        for (int j = 0; j < NI; ++j)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) acc[i][j][r] += hi[i][j][r];
     return low;
 }
 
@@ -314,8 +309,8 @@ void KERNEL_NAME(const float *__restrict__ A, const float *__restrict__ B, float
         l.b = Bb + n0;
         l.b_off = 4u * (u32)(8 * half * N + l32 * NI);
         if (bi > 0) __syncthreads();
-        acc_t acc[MI][NI];
-        const u32 low = reduce<false>(acc, l, c0, c1);
+        acc_t hi[MI][NI], acc[MI][NI];
+        const u32 low = reduce<false>(hi, acc, l, c0, c1);
         // Sums that are not finite, or too small for their products' parts.  As bits less 2^-110's ordinary ones come first, then what is not finite, zeros, and
         // what is smaller than 2^-110; only if there is any but the first is it told apart.
         auto each = [&](auto f) {
@@ -324,12 +319,17 @@ void KERNEL_NAME(const float *__restrict__ A, const float *__restrict__ B, float
 #pragma unroll
                 for (int j = 0; j < NI; ++j)
 #pragma unroll
-                    for (int r = 0; r < 16; ++r) f(acc[i][j][r]);
+                    for (int r = 0; r < 16; ++r) f(hi[i][j][r] + acc[i][j][r]);
         };
         u32 last = 0;
         each([&](float v) { last = max(magnitude(v) - SMALL_SUM, last); });
         bool finite = true, small_sum = false;
         if (__any(last >= NOT_FINITE - SMALL_SUM)) {
+            // (the sums are added up once more here: kept, they would be 64 registers too many)
+#pragma unroll
+            for (int i = 0; i < MI; ++i)
+#pragma unroll
+                for (int j = 0; j < NI; ++j) asm volatile("" : "+v"(hi[i][j]));
             each([&](float v) {
                 finite = finite && __builtin_isfinite(v);
                 small_sum = small_sum || magnitude(v) < SMALL_SUM;
@@ -337,9 +337,9 @@ void KERNEL_NAME(const float *__restrict__ A, const float *__restrict__ B, float
         }
         // A part with values too small to be taken apart, or sums too small for their products' parts, is added up again on the fp32 atoms.  Where a sum is not
         // finite, the tile's whole reduction is, in one chain for each atom of it, an atom a wave: partial sums of either sign beyond the range would make a NaN of
-        // what is infinite in order.  What that costs, 512 x 4096 x 1024 in 64 x 64 tiles / 672 x 192 x 2560 in 32 x 32 (ordinary values 37 / 16 us, also with zeros; on the
-        // fp32 atoms alone 39 / 53 whatever the values): one value of 1e-40 50 / 23, one of 1e-32 in every row 68 / 23, every value or sum too small 72 / 28; one
-        // infinity 59 / 70, one in every row, or a NaN, 84 / 71 (one wave for the whole tile: 93 - 127 / 71).
+        // what is infinite in order.  What that costs, 512 x 4096 x 1024 in 64 x 64 tiles / 672 x 192 x 2560 in 32 x 32 (ordinary values 38 / 16 us, also with zeros; on the
+        // fp32 atoms alone 39 / 53 whatever the values): one value of 1e-40 50 / 24, one of 1e-32 in every row 67 / 24, every value or sum too small 71 / 29; one
+        // infinity or NaN 58 / 79, one in every row 82 / 80 (one wave for the whole tile: 93 - 127 / 71).
         const bool small = __any(low < SMALL || small_sum), mine = __any(!finite);
         if (lane == 0) beyond[wave] = mine;
         __syncthreads();                            // (also: the waves' parts of the LDS have been read)
@@ -347,7 +347,7 @@ void KERNEL_NAME(const float *__restrict__ A, const float *__restrict__ B, float
 #pragma unroll
         for (int k = 0; k < KW; ++k) chain |= beyond[k] != 0;
         chain = __builtin_amdgcn_readfirstlane(chain);
-        if (chain ? wave < MI * NI : small) reduce<true>(acc, l, chain ? 0 : c0, chain ? NCHUNK : c1, chain ? wave : -1);
+        if (chain ? wave < MI * NI : small) reduce<true>(hi, acc, l, chain ? 0 : c0, chain ? NCHUNK : c1, chain ? wave : -1);
 
         auto row_of = [&](int i, int r) {
             const int row = 8 * (r / 4) + 4 * half + r % 4;
@@ -365,29 +365,45 @@ void KERNEL_NAME(const float *__restrict__ A, const float *__restrict__ B, float
                 }
             continue;
         }
-        __syncthreads();                            // nobody reads operands from the LDS any longer
-        Vals<NI> *const red = (Vals<NI> *)smem_f32;
+        // The waves' sums meet in the LDS, those of the upper parts' products first, then the others.  With the two added up in every wave, which spares 0.3 - 0.9 us, each
+        // wave rounded its products before the sum did: sums of two to four normal products had 1.01 - 1.16 times the fp32 atoms' error, now 0.65 - 0.87 times.
+        // (A lane's accumulators of consecutive rows go through the LDS together, 16 bytes at a time, so that none is moved to another register first.)
+        constexpr int W = MI * 16 / KW < 4 ? 2 : 4, GROUPS = MI * 16 / W, SHARE = GROUPS / KW;      // rows of a group; groups of the tile, and a wave's share
+        typedef __attribute__((ext_vector_type(W))) float rows_t;
+        rows_t *const red = (rows_t *)smem_f32;
+        rows_t sum[SHARE][NI];
+        auto meet = [&](const acc_t (&part)[MI][NI], auto f) {
+            __syncthreads();                        // nobody reads operands, or the other sums, from the LDS any longer
 #pragma unroll
-        for (int i = 0; i < MI; ++i)
+            for (int t = 0; t < GROUPS; ++t)
 #pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                Vals<NI> v;
+                for (int j = 0; j < NI; ++j) {
+                    rows_t v;
 #pragma unroll
-                for (int j = 0; j < NI; ++j) v.v[j] = acc[i][j][r];
-                red[((wave * MI + i) * 16 + r) * 64 + lane] = v;
+                    for (int w = 0; w < W; ++w) v[w] = part[t * W / 16][j][t * W % 16 + w];
+                    red[((wave * GROUPS + t) * NI + j) * 64 + lane] = v;
+                }
+            __syncthreads();
+#pragma unroll
+            for (int s = 0; s < SHARE; ++s)
+#pragma unroll
+                for (int j = 0; j < NI; ++j) {
+                    const rows_t *const from = red + ((wave + s * KW) * NI + j) * 64 + lane;
+                    rows_t all = from[0];
+#pragma unroll
+                    for (int k = 1; k < KW; ++k) all += from[k * GROUPS * NI * 64];
+                    f(sum[s][j], all);
+                }
+        };
+        meet(hi, [](rows_t &to, const rows_t &all) { to = all; });
+        meet(acc, [](rows_t &to, const rows_t &all) { to += all; });
+#pragma unroll
+        for (int s = 0; s < SHARE; ++s)
+#pragma unroll
+            for (int w = 0; w < W; ++w) {
+                const int r = (wave + s * KW) * W + w;
+#pragma unroll
+                for (int j = 0; j < NI; ++j) out[(long)row_of(r / 16, r % 16) * N + j] = sum[s][j][w];
             }
-        __syncthreads();
-#pragma unroll 2
-        for (int t = wave; t < MI * 16; t += KW) {
-            Vals<NI> sum = red[t * 64 + lane];
-#pragma unroll
-            for (int k = 1; k < KW; ++k) {
-                const Vals<NI> v = red[(k * MI * 16 + t) * 64 + lane];
-#pragma unroll
-                for (int j = 0; j < NI; ++j) sum.v[j] += v.v[j];
-            }
-#pragma unroll
-            for (int j = 0; j < NI; ++j) out[(long)row_of(t / 16, t % 16) * N + j] = sum.v[j];
-        }
     }
 }

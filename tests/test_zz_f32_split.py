@@ -207,6 +207,25 @@ def test_sums_of_a_single_product(seed):
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("K", [480, 1024])
+@pytest.mark.parametrize("terms", [2, 3, 4, 8])
+def test_sums_of_a_few_products(terms, K):
+    """Beside the fp32 atoms of the same tile, which round once for each product: the sums of the upper parts' products (16 bits each) are exact or nearly, those of the
+    others 2^-7 of them, so a sum is rounded about once, wherever in the reduction and in whichever waves' parts its products lie.  64 x 64 x 6 sums: their norms
+    agree to 1 %, 2 % are allowed."""
+    cfg, off = [1, 2, 1, 32, 1, 2, 1, 32, K // 32, 32], {0: 0.0, 1: 0.0}
+    for seed in range(6):
+        g = np.random.default_rng(seed)
+        a, b = np.zeros((64, K), np.float32), g.standard_normal((K, 64)).astype(np.float32)
+        for i in range(64):
+            a[i, g.permutation(K)[:terms]] = g.standard_normal(terms).astype(np.float32)
+        want = a.astype(np.float64) @ b.astype(np.float64)
+        for flag in off:
+            off[flag] += np.linalg.norm(_run(MM, (64, 64, K), V, cfg + [flag], a, b, want.size).reshape(want.shape) - want) ** 2
+    assert _waves(MM, (64, 64, K), V, cfg + [1]) > 0 and off[1] <= 1.02 ** 2 * off[0], off
+
+
+@pytest.mark.gpu
 @pytest.mark.parametrize("scale", [2.0 ** -60, 2.0 ** -64, 2.0 ** -70])
 def test_products_that_are_subnormal_or_nearly(scale):
     """One product for each output, of values that can be taken apart, whose smaller parts have no 24 bits left: rounded once, as on the fp32 atoms."""
