@@ -857,19 +857,23 @@ int decode(const opevo_op &op, int variant, const int32_t *cfg, Decoded &out, bo
         }
     }
     // fp32 MatMul / BMM members with two stages, workgroup tiles of 32 or 64 rows and columns and long reductions: the template that takes values apart for the bf16
-    // matrix pipes, its waves sharing the reduction.  From K = 320 on, 448 for tiles of 64 x 64, which pay for a longer final sum.  Against the fp32 atoms
-    // 64 members drawn for these rules 1.00 - 3.3x, 1.5x in the geometric mean, the least 64 x 64 tiles on a full chip at K = 480 - 576 (2368 x 2432 x 480 56.3 -> 56.1 us).  64 x 64
+    // matrix pipes, its waves sharing the reduction, where the fp32 atoms are slower.  Up to 512 workgroups, which leave the fp32 atoms' members few waves a compute unit, from K = 320
+    // on: 50 drawn operators 0.97 - 2.7x against the fastest of their fp32 members (slabs of 16, 32, 64, every division of the tile), 1.46x in the geometric mean.  On more workgroups the fp32
+    // atoms' other workgroups hide what sharing the reduction does: K of 320 - 1024 0.81 - 1.1x (1792 x 2528 x 320 in 64 x 32 35.4 -> 43.3 us, 1344 x 2400 x 352 29.8 -> 36.2),
+    // above 0.88 - 1.25x against the fastest and 0.89 - 1.54x, 1.2x in the mean, against 20 random ones: from 1056 on.  64 x 64 tiles, whose fp32 members read least: K of 448 - 864 0.86 - 1.0x
+    // (512 x 192 x 544 11.8 -> 13.8), 896 - 1600 0.99 - 1.26x up to 512 workgroups; on more 704 0.98x, 768 - 1504 1.02 - 1.12x.  64 x 64
     // tiles with the first operand transposed need more registers than there are.  Batches on more than 400 workgroups, whose operands few tiles share, are bound by
-    // bytes as much as by the pipes: 342 x (32 x 64 x 896), transposed, 23.9 -> 27.4, 250 x (128 x 64 x 704) 31.2 -> 34.4, 12 such members 0.87 - 1.17x, 0.99x; up to 360
-    // 82 x (64 x 64 x 480) 11.2 -> 8.8 and no member below 1.00.
-    // Eight waves instead of four where a compute unit has one workgroup at most and each wave still gets 88 steps: 672 x 192 x 2560 in 32 x 64 (63 workgroups) 23.9 -> 21.4, 1024 x 480 x 736 in
-    // 64 x 32 (240) 12.5 -> 11.4, while 64 x 64 x 448 steps and less are alike (six products in one accumulator; the waves' shares are the same with eight in two).
+    // bytes as much as by the pipes: 342 x (32 x 64 x 896), transposed, 23.9 -> 27.4, 250 x (128 x 64 x 704) 31.2 -> 34.4, 12 such members 0.87 - 1.17x, 0.99x; up to 400
+    // 30 random ones in smaller tiles 1.06 - 2.9x, 15 of 64 x 64 0.98 - 1.64x.  69 further random members of what these lines leave, against the fp32 atoms 1.04 - 2.9x.
+    // Eight waves instead of four where a compute unit has one workgroup at most and each wave still gets 88 steps: 44 drawn members 0.96 - 1.19x, 1.07x in the geometric
+    // mean (416 x 320 x 704 in 32 x 64 10.8 -> 11.2 us, 64 x 64 x 1248 batches in 32 x 32 12.1 -> 10.2).
     int f32_kw = 0;
+    const int64_t f32_wgs = n1 * m1 * b1, f32_least = BM * BN == 64 * 64 ? (f32_wgs <= 512 ? 896 : 768) : f32_wgs <= 512 ? 320 : 1056;
     if (extras && path == 4 && op.kind != OPEVO_CONV2D && flagv && ksteps > 1 && ksplit == 1 && subm * subn == 1 && WM * WN <= kMaxThreads / 64 &&
-        (BM == 32 || BM == 64) && (BN == 32 || BN == 64) && !(op.trans_a && BM * BN == 64 * 64) && op.K % 32 == 0 && op.K >= (BM * BN == 64 * 64 ? 448 : 320) &&
-        (op.kind == OPEVO_MATMUL || n1 * m1 * b1 <= 400) && op.M < (1 << 22) && op.N < (1 << 22) && op.K < (1 << 22) &&         // (a lane's byte offsets within 32 bits)
+        (BM == 32 || BM == 64) && (BN == 32 || BN == 64) && !(op.trans_a && BM * BN == 64 * 64) && op.K % 32 == 0 && op.K >= f32_least &&
+        (op.kind == OPEVO_MATMUL || f32_wgs <= 400) && op.M < (1 << 22) && op.N < (1 << 22) && op.K < (1 << 22) &&         // (a lane's byte offsets within 32 bits)
         valid_without_extras(op, variant, cfg)) {
-        f32_kw = n1 * m1 * b1 <= 256 && op.K >= 704 ? 8 : 4;
+        f32_kw = f32_wgs <= 256 && op.K >= 704 ? 8 : 4;
         out.extra_waves = true;
         WM = 1; WN = f32_kw; TM = BM; TN = BN; TMacc = TM; TNacc = TN; FM = std::gcd(FM, TM); FN = std::gcd(FN, TN);
     }

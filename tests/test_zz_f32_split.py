@@ -13,19 +13,24 @@ from test_zz_load_base_wait import OBJDUMP, short_of_wait_states
 MM, BMM, TA = P.OPEVO_MATMUL, P.OPEVO_BMM, P.OPEVO_BMM_TA
 V, X, K3 = P.OPEVO_TILE4, P.OPEVO_TILE4X, P.OPEVO_TILE4K
 CASES = [   # label, kind, dims, variant, configuration, waves that share the reduction (0: not on this template)
-    ("64 x 64, 15 chunks on four waves", MM, (128, 192, 480), V, [2, 2, 1, 32, 3, 2, 1, 32, 15, 32, 1], 4),
+    ("64 x 64, 29 chunks on four waves", MM, (1024, 1088, 928), V, [16, 2, 1, 32, 17, 2, 1, 32, 29, 32, 1], 4),
     ("32 x 64, 11 chunks on four waves", MM, (64, 128, 352), V, [2, 1, 1, 32, 2, 1, 2, 32, 11, 32, 1], 4),
     ("64 x 32, the shortest reduction", MM, (64, 96, 320), V, [1, 1, 2, 32, 3, 1, 1, 32, 10, 32, 1], 4),
     ("32 x 32, 23 chunks on eight waves", MM, (96, 64, 736), V, [3, 1, 1, 32, 2, 1, 1, 32, 23, 32, 1], 8),
     ("64 x 64, eight waves", MM, (64, 64, 1024), V, [1, 2, 1, 32, 1, 2, 1, 32, 16, 64, 1], 8),
-    ("slabs of 8, a launch order of its own", MM, (128, 64, 704), X, [2, 1, 2, 32, 1, 2, 1, 32, 88, 8, 1, 1, 0, 2], 8),
+    ("slabs of 8, a launch order of its own", MM, (128, 64, 928), X, [2, 1, 2, 32, 1, 2, 1, 32, 116, 8, 1, 1, 0, 2], 8),
     ("batches, two per workgroup", BMM, (6, 64, 32, 416), V, [3, 2, 2, 1, 1, 32, 1, 1, 1, 32, 13, 32, 1], 4),
     ("transposed first operand, 64 x 32", TA, (4, 64, 96, 448), V, [2, 2, 1, 2, 1, 32, 3, 1, 1, 32, 14, 32, 1], 4),
     ("transposed first operand, 32 x 64", TA, (4, 96, 128, 704), V, [2, 2, 3, 1, 1, 32, 2, 2, 1, 32, 22, 32, 1], 8),
     ("transposed first operand, 32 x 32", TA, (2, 96, 32, 768), V, [2, 1, 3, 1, 1, 32, 1, 1, 1, 32, 24, 32, 1], 8),
-    ("workgroups enough for the chip", MM, (1024, 1088, 704), V, [16, 2, 1, 32, 17, 2, 1, 32, 11, 64, 1], 4),
-    ("transposed first operand, 64 x 64", TA, (4, 64, 128, 448), V, [2, 2, 1, 2, 1, 32, 2, 2, 1, 32, 14, 32, 1], 0),
-    ("64 x 64, shorter", MM, (128, 192, 416), V, [2, 2, 1, 32, 3, 2, 1, 32, 13, 32, 1], 0),
+    ("64 x 64, workgroups enough for the chip", MM, (1472, 1472, 768), V, [23, 2, 1, 32, 23, 2, 1, 32, 12, 64, 1], 4),
+    ("64 x 64, no more of them, shorter", MM, (1024, 2048, 864), V, [16, 2, 1, 32, 32, 2, 1, 32, 27, 32, 1], 0),
+    ("64 x 64, workgroups enough, shorter", MM, (1472, 1472, 736), V, [23, 2, 1, 32, 23, 2, 1, 32, 23, 32, 1], 0),
+    ("32 x 64, workgroups enough for the chip", MM, (736, 1472, 1056), V, [23, 1, 1, 32, 23, 2, 1, 32, 33, 32, 1], 4),
+    ("32 x 64, workgroups enough, shorter", MM, (736, 1472, 1024), V, [23, 1, 1, 32, 23, 2, 1, 32, 16, 64, 1], 0),
+    ("64 x 32, no more of them", MM, (1024, 1024, 320), V, [16, 2, 1, 32, 32, 1, 1, 32, 10, 32, 1], 4),
+    ("batches on more workgroups", BMM, (401, 32, 32, 1056), V, [401, 1, 1, 1, 1, 32, 1, 1, 1, 32, 33, 32, 1], 0),
+    ("transposed first operand, 64 x 64", TA, (4, 64, 128, 1024), V, [2, 2, 1, 2, 1, 32, 2, 2, 1, 32, 32, 32, 1], 0),
     ("32 x 64, shorter", MM, (64, 128, 288), V, [2, 1, 1, 32, 2, 1, 2, 32, 9, 32, 1], 0),
     ("no whole chunks", MM, (64, 128, 336), V, [2, 1, 1, 32, 2, 1, 2, 32, 21, 16, 1], 0),
     ("96 columns", MM, (64, 96, 512), V, [2, 1, 1, 32, 1, 1, 3, 32, 16, 32, 1], 0),
@@ -71,7 +76,7 @@ def test_where_the_first_operand_s_pieces_go(bm):
 
 
 @pytest.mark.parametrize("dims,cfg,atoms", [
-    ((128, 192, 480), [2, 2, 1, 32, 3, 2, 1, 32, 15, 32, 1], (2, 2)),
+    ((1024, 1088, 928), [16, 2, 1, 32, 17, 2, 1, 32, 29, 32, 1], (2, 2)),
     ((64, 128, 352), [2, 1, 1, 32, 2, 1, 2, 32, 11, 32, 1], (1, 2)),
     ((64, 96, 320), [1, 1, 2, 32, 3, 1, 1, 32, 10, 32, 1], (2, 1)),
     ((96, 64, 736), [3, 1, 1, 32, 2, 1, 1, 32, 23, 32, 1], (1, 1)),
@@ -129,9 +134,9 @@ def test_every_fragment_is_read_after_its_loads(dims, cfg, atoms, tmp_path):
 
 def test_members_that_could_not_run_without_it_stay_invalid():
     """One wave on slabs of 144 would stage 288 registers a lane on the fp32 atoms' template."""
-    op = P.opevo_op_create(MM, (64, 64, 576), P.OPEVO_F32)
-    assert P.opevo_kernel_plan(op, V, [1, 1, 2, 32, 1, 1, 2, 32, 4, 144, 1]).status == P.OPEVO_E_INVALID
-    assert _waves(MM, (64, 64, 576), V, [1, 2, 1, 32, 1, 1, 2, 32, 4, 144, 1]) == 4
+    op = P.opevo_op_create(MM, (64, 64, 1152), P.OPEVO_F32)
+    assert P.opevo_kernel_plan(op, V, [1, 1, 2, 32, 1, 1, 2, 32, 8, 144, 1]).status == P.OPEVO_E_INVALID
+    assert _waves(MM, (64, 64, 1152), V, [1, 2, 1, 32, 1, 1, 2, 32, 8, 144, 1]) == 8
 
 
 def _run(kind, dims, variant, cfg, a, b, n):
@@ -159,22 +164,28 @@ def test_results_match_the_oracle(label, kind, dims, variant, cfg, waves):
     assert np.all(np.isfinite(got)) and np.linalg.norm(got - want) <= 1.2e-6 * np.linalg.norm(want), label
 
 
-def _operands():
-    g = np.random.default_rng(7)
-    return g.standard_normal((64, 480)).astype(np.float32), g.standard_normal((480, 64)).astype(np.float32)
+FOUR, EIGHT = (MM, (64, 64, 480), V, [1, 2, 1, 32, 2, 1, 1, 32, 15, 32, 1]), (MM, (64, 64, 960), V, [1, 2, 1, 32, 1, 2, 1, 32, 30, 32, 1])
+MEMBERS = pytest.mark.parametrize("member", [FOUR, EIGHT], ids=["64 x 32, four waves", "64 x 64, eight waves"])
 
 
-MEMBER = (MM, (64, 64, 480), V, [1, 2, 1, 32, 1, 2, 1, 32, 15, 32, 1])
+def test_the_members_of_the_tests_below():
+    assert _waves(*FOUR) == 4 and _waves(*EIGHT) == 8
+
+
+def _operands(member):
+    g, K = np.random.default_rng(7), member[1][2]
+    return g.standard_normal((64, K)).astype(np.float32), g.standard_normal((K, 64)).astype(np.float32)
 
 
 @pytest.mark.gpu
+@MEMBERS
 @pytest.mark.parametrize("scale_a,scale_b", [(2.0 ** -60, 2.0 ** -60), (2.0 ** -99, 2.0 ** 99), (2.0 ** -120, 2.0 ** 100), (2.0 ** -135, 2.0 ** 40), (2.0 ** 118, 1.0)])
-def test_operands_of_any_magnitude(scale_a, scale_b):
+def test_operands_of_any_magnitude(member, scale_a, scale_b):
     """Scaling by powers of two changes no relative error as long as the values keep their 24 bits (rounded to fp32 here, as the operands are)."""
-    a, b = _operands()
+    a, b = _operands(member)
     a, b = (a * np.float32(scale_a)).astype(np.float32), (b * np.float32(scale_b)).astype(np.float32)
     want = a.astype(np.float64) @ b.astype(np.float64)
-    got = _run(*MEMBER, a, b, want.size).astype(np.float64).reshape(want.shape)
+    got = _run(*member, a, b, want.size).astype(np.float64).reshape(want.shape)
     assert np.linalg.norm(got - want) <= 1.2e-6 * np.linalg.norm(want)
 
 
@@ -189,17 +200,19 @@ def test_no_further_from_64_bits_than_the_fp32_atoms(label, kind, dims, variant,
 
 
 @pytest.mark.gpu
+@MEMBERS
 @pytest.mark.parametrize("seed", [1, 2])
-def test_sums_of_a_single_product(seed):
+def test_sums_of_a_single_product(member, seed):
     """Selections and sparse rows: the product of the upper parts is exact, the seven others are at most 2^-7 of it and lose no more than 2^-24 of that
     each time they are added to, so the one rounding of their sum is all but fp32's (2^-24): 2^-24 + 2^-28, and 2 % in the norm."""
     g = np.random.default_rng(seed)
-    a, b = np.zeros((64, 480), np.float32), g.standard_normal((480, 64)).astype(np.float32)
-    k = g.permutation(480)[:64]
+    K = member[1][2]
+    a, b = np.zeros((64, K), np.float32), g.standard_normal((K, 64)).astype(np.float32)
+    k = g.permutation(K)[:64]
     a[np.arange(64), k] = g.standard_normal(64).astype(np.float32)
     a[0, k[0]] = 1.0
     want = a.astype(np.float64) @ b.astype(np.float64)
-    got = _run(*MEMBER, a, b, want.size).astype(np.float64).reshape(want.shape)
+    got = _run(*member, a, b, want.size).astype(np.float64).reshape(want.shape)
     rounded = want.astype(np.float32)
     assert np.array_equal(got[0], b[k[0]].astype(np.float64)), "a value times one is that value"
     assert np.all(np.abs(got - want) <= (2.0 ** -24 + 2.0 ** -28) * np.abs(want))
@@ -207,13 +220,14 @@ def test_sums_of_a_single_product(seed):
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("K", [480, 1024])
+@MEMBERS
 @pytest.mark.parametrize("terms", [2, 3, 4, 8])
-def test_sums_of_a_few_products(terms, K):
+def test_sums_of_a_few_products(member, terms):
     """Beside the fp32 atoms of the same tile, which round once for each product: the sums of the upper parts' products (16 bits each) are exact or nearly, those of the
     others 2^-7 of them, so a sum is rounded about once, wherever in the reduction and in whichever waves' parts its products lie.  64 x 64 x 6 sums: their norms
     agree to 1 %, 2 % are allowed."""
-    cfg, off = [1, 2, 1, 32, 1, 2, 1, 32, K // 32, 32], {0: 0.0, 1: 0.0}
+    kind, dims, variant, cfg = member
+    K, off = dims[2], {0: 0.0, 1: 0.0}
     for seed in range(6):
         g = np.random.default_rng(seed)
         a, b = np.zeros((64, K), np.float32), g.standard_normal((K, 64)).astype(np.float32)
@@ -221,37 +235,41 @@ def test_sums_of_a_few_products(terms, K):
             a[i, g.permutation(K)[:terms]] = g.standard_normal(terms).astype(np.float32)
         want = a.astype(np.float64) @ b.astype(np.float64)
         for flag in off:
-            off[flag] += np.linalg.norm(_run(MM, (64, 64, K), V, cfg + [flag], a, b, want.size).reshape(want.shape) - want) ** 2
-    assert _waves(MM, (64, 64, K), V, cfg + [1]) > 0 and off[1] <= 1.02 ** 2 * off[0], off
+            off[flag] += np.linalg.norm(_run(kind, dims, variant, cfg[:-1] + [flag], a, b, want.size).reshape(want.shape) - want) ** 2
+    assert _waves(kind, dims, variant, cfg[:-1] + [0]) == 0 and off[1] <= 1.02 ** 2 * off[0], off
 
 
 @pytest.mark.gpu
+@MEMBERS
 @pytest.mark.parametrize("scale", [2.0 ** -60, 2.0 ** -64, 2.0 ** -70])
-def test_products_that_are_subnormal_or_nearly(scale):
+def test_products_that_are_subnormal_or_nearly(member, scale):
     """One product for each output, of values that can be taken apart, whose smaller parts have no 24 bits left: rounded once, as on the fp32 atoms."""
     g = np.random.default_rng(4)
-    a, b = np.zeros((64, 480), np.float32), (g.standard_normal((480, 64)) * scale).astype(np.float32)
-    a[np.arange(64), g.permutation(480)[:64]] = (g.standard_normal(64) * scale).astype(np.float32)
+    K = member[1][2]
+    a, b = np.zeros((64, K), np.float32), (g.standard_normal((K, 64)) * scale).astype(np.float32)
+    a[np.arange(64), g.permutation(K)[:64]] = (g.standard_normal(64) * scale).astype(np.float32)
     assert np.all(np.abs(b) > 2.0 ** -100) and np.all((np.abs(a) > 2.0 ** -100) | (a == 0))
     want = a.astype(np.float64) @ b.astype(np.float64)
-    got = _run(*MEMBER, a, b, want.size).reshape(want.shape)
+    got = _run(*member, a, b, want.size).reshape(want.shape)
     assert np.array_equal(got, want.astype(np.float32))
 
 
 @pytest.mark.gpu
-def test_a_single_value_that_cannot_be_taken_apart():
+@MEMBERS
+def test_a_single_value_that_cannot_be_taken_apart(member):
     """Rows and columns whose only values lie below 2^-100, one for each place of a lane's 8 and each wave, beside ordinary ones and zeros."""
-    a, b = _operands()
+    a, b = _operands(member)
+    K = member[1][2]
     a[np.abs(a) < 0.5] = 0.0
     for i in range(32):
         a[i] = 0.0
-        a[i, (i * 37) % 480] = np.float32(1.2345678e-34)
+        a[i, (i * 37) % K] = np.float32(1.2345678e-34)
         b[:, i] = 0.0
-        b[(i * 41) % 480, i] = np.float32(-7.654321e-33)
+        b[(i * 41) % K, i] = np.float32(-7.654321e-33)
     b[:, 32:] *= np.float32(1e20)
     a[32:] *= np.float32(1e15)
     want = a.astype(np.float64) @ b.astype(np.float64)
-    got = _run(*MEMBER, a, b, want.size).astype(np.float64).reshape(want.shape)
+    got = _run(*member, a, b, want.size).astype(np.float64).reshape(want.shape)
     for part in (np.s_[:32, 32:], np.s_[32:, :32]):            # one product each: rounded once (2^-24), or a chain of zeros and one product
         assert np.all(np.abs(got[part] - want[part]) <= 2.0 ** -23 * np.abs(want[part]))
     assert np.linalg.norm(got[32:, 32:] - want[32:, 32:]) <= 1.2e-6 * np.linalg.norm(want[32:, 32:])
@@ -283,45 +301,50 @@ def test_which_values_are_no_sum_of_three_parts():
 
 
 @pytest.mark.gpu
+@MEMBERS
 @pytest.mark.parametrize("scale_a,scale_b", [(2.0 ** -140, 2.0 ** 40), (2.0 ** -140, 2.0 ** 100), (2.0 ** 100, 2.0 ** -138)])
-def test_an_operand_wholly_below_what_bf16_holds(scale_a, scale_b):
-    """Every value at most 2^-134, few bits each: no product has more than 24 + 15, and the sums are the fp32 atoms' (1.2e-6: 480 products, as above)."""
-    a, b = _operands()
+def test_an_operand_wholly_below_what_bf16_holds(member, scale_a, scale_b):
+    """Every value at most 2^-134, few bits each: no product has more than 24 + 15, and the sums are the fp32 atoms' (1.2e-6: at most 960 products, as above)."""
+    a, b = _operands(member)
     a, b = (np.clip(a, -2, 2) * np.float32(scale_a)).astype(np.float32), (np.clip(b, -2, 2) * np.float32(scale_b)).astype(np.float32)
     tiny = a if scale_a < 1 else b
     assert np.all(np.abs(tiny) <= 2.0 ** -134) and np.mean(tiny != 0) > 0.9
     want = a.astype(np.float64) @ b.astype(np.float64)
-    got = _run(*MEMBER, a, b, want.size).astype(np.float64).reshape(want.shape)
+    got = _run(*member, a, b, want.size).astype(np.float64).reshape(want.shape)
     assert np.linalg.norm(got - want) <= 1.2e-6 * np.linalg.norm(want)
 
 
 @pytest.mark.gpu
+@MEMBERS
 @pytest.mark.parametrize("value", [2.0 ** -149, 2.0 ** -134, 1.5 * 2.0 ** -135])
-def test_the_only_value_of_a_wave_s_part(value):
+def test_the_only_value_of_a_wave_s_part(member, value):
     """One product for each row, in the first wave's part, the last one's and one between: exact (the other factor is a power of two)."""
-    a, b = np.zeros((64, 480), np.float32), np.zeros((480, 64), np.float32)
-    for i, k in enumerate((0, 127, 200, 479)):
+    K = member[1][2]
+    a, b = np.zeros((64, K), np.float32), np.zeros((K, 64), np.float32)
+    for i, k in enumerate((0, 127, K // 2 - 40, K - 1)):
         a[16 * i + 3, k] = np.float32(value)
         b[k] = np.float32(2.0 ** (100 + i))
     want = a.astype(np.float64) @ b.astype(np.float64)
-    got = _run(*MEMBER, a, b, want.size).reshape(want.shape)
+    got = _run(*member, a, b, want.size).reshape(want.shape)
     assert np.count_nonzero(want) == 4 * 64 and np.array_equal(got.astype(np.float64), want)
 
 
 @pytest.mark.gpu
-def test_infinities_nan_and_sums_beyond_the_range():
-    a, b = _operands()
-    a[3, 100], a[4, 101], b[470, 9] = np.inf, np.nan, -np.inf
+@MEMBERS
+def test_infinities_nan_and_sums_beyond_the_range(member):
+    K = member[1][2]
+    a, b = _operands(member)
+    a[3, 100], a[4, 101], b[K - 10, 9] = np.inf, np.nan, -np.inf
     a[5], a[6] = 0.0, np.abs(a[6]) * np.float32(2.0 ** 125)    # row 6: every sum of like signs is far beyond the range
     with np.errstate(invalid="ignore"):
         want = a.astype(np.float64) @ np.abs(b).astype(np.float64)
-    got = _run(*MEMBER, a, np.abs(b), want.size).reshape(want.shape)
+    got = _run(*member, a, np.abs(b), want.size).reshape(want.shape)
     with np.errstate(over="ignore"):
         assert np.array_equal(np.isnan(got), np.isnan(want)) and np.array_equal(np.isinf(got), np.isinf(want.astype(np.float32)))
     # the early products alone leave the range upwards, the late ones downwards, all together upwards: infinite in order, a NaN as the sum of partial sums
-    a, b = _operands()
+    a, b = _operands(member)
     a, b = np.abs(a) * np.float32(2.0 ** 124), np.abs(b)
-    b[240:] *= np.float32(-0.25)
+    b[K // 2:] *= np.float32(-0.25)
     want = a.astype(np.float64) @ b.astype(np.float64)
-    got = _run(*MEMBER, a, b, want.size).reshape(want.shape)
+    got = _run(*member, a, b, want.size).reshape(want.shape)
     assert np.all(np.isfinite(a)) and np.all(want > 3.5e38) and np.all(np.isposinf(got))

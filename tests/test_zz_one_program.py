@@ -9,8 +9,8 @@ GROUPS = [   # template, kind, dims, dtype, space, configurations of one program
     ("gemm_f32_split", MM, (512, 4096, 1024), P.OPEVO_F32, V,
      [[8, 2, 16, 2, 64, 2, 32, 1, 16, 64, 1], [8, 1, 1, 64, 64, 2, 1, 32, 32, 32, 1], [8, 2, 4, 8, 64, 1, 2, 32, 128, 8, 1]],
      [[16, 1, 1, 32, 64, 2, 1, 32, 16, 64, 1], [8, 2, 16, 2, 128, 1, 1, 32, 16, 64, 1]]),
-    ("gemm_f32_split", MM, (128, 64, 704), P.OPEVO_F32, X,
-     [[2, 1, 2, 32, 1, 2, 1, 32, 88, 8, 1, 1, 0, 2], [2, 2, 1, 32, 1, 1, 2, 32, 22, 32, 1, 1, 0, 2]], [[2, 1, 2, 32, 1, 2, 1, 32, 88, 8, 1, 1, 0, 0]]),
+    ("gemm_f32_split", MM, (128, 64, 928), P.OPEVO_F32, X,
+     [[2, 1, 2, 32, 1, 2, 1, 32, 116, 8, 1, 1, 0, 2], [2, 2, 1, 32, 1, 1, 2, 32, 29, 32, 1, 1, 0, 2]], [[2, 1, 2, 32, 1, 2, 1, 32, 116, 8, 1, 1, 0, 0]]),
     ("gemm_ragged", MM, (63, 105, 457), P.OPEVO_BF16, V,
      [[3, 1, 1, 21, 3, 1, 1, 35, 457, 1, 1], [3, 3, 7, 1, 3, 5, 1, 7, 1, 457, 1], [3, 1, 7, 3, 3, 1, 5, 7, 457, 1, 0]], [[3, 1, 1, 21, 5, 1, 1, 21, 457, 1, 1]]),
     ("gemm_ragged", BMM, (6, 25, 40, 550), P.OPEVO_BF16, V,
