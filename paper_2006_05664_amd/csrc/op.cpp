@@ -982,7 +982,7 @@ int decode(const opevo_op &op, int variant, const int32_t *cfg, Decoded &out, bo
           << " -DNSTAGE=" << nstage << " -DNSTG=" << nstage << " -DSTAGE_LDS=" << (stage_lds ? 1 : 0);
         if (nwr != WM * WN && path != 5) D << " -DNWR=" << nwr;
     }
-    if (path == 7) D << " -DWKP=" << rows.wkp << " -DMI=" << rows.mi << " -DNI=" << rows.ni << " -DLDS_BYTES=" << lds << " -DPERSIST=" << rows.persist << " -DNBOX=" << n1 << " -DSTAGE_A=" << rows.stage;
+    if (path == 7) D << " -DWKP=" << rows.wkp << " -DMI=" << rows.mi << " -DNI=" << rows.ni << " -DLDS_BYTES=" << lds << " -DPERSIST=" << rows.persist << " -DNBOX=" << n1 << " -DBESIDE=" << rows.beside;
     if (rg_kw) D << " -DKWAVES=" << rg_kw << " -DLDS_BYTES=" << lds << " -DMINW=" << rg.min_waves;
     else if (path == 6) D << " -DKS=" << rg.ks << " -DNSL=" << rg.slabs << " -DMI=" << rg.mi << " -DNI=" << rg.ni << " -DLDS_BYTES=" << lds << " -DDEPTH=" << rg.depth << " -DMINW=" << rg.min_waves;
     if (subm * subn > 1) {
@@ -1018,6 +1018,13 @@ int decode(const opevo_op &op, int variant, const int32_t *cfg, Decoded &out, bo
         if (rg.keep == 1 || (rg.keep == 2 && !spills)) out.tries.push_back(" -DKEEP=1");
         if (rg.keep != 1 && !spills) out.tries.push_back(" -DKEEP=0");
         out.tries.push_back(" -DKEEP=0 -DFRESH=1");
+    }
+    // The kernel tensor's rows through the LDS, and straight from memory if the kernel spills so (one of 695 drawn members: 33 x 3 x 224 x 224 * 128 x 3 x 11 x 11, stride 4, on the
+    // register-staged template instead 295 us, 67 so).  What it would have beside the patch is counted all the same.
+    if (path == 7) {
+        out.tries.clear();
+        if (rows.stage) out.tries.push_back(rows.stage == 1 ? " -DSTAGE_A=1" : " -DSTAGE_A=2");
+        out.tries.push_back(" -DSTAGE_A=0");
     }
     // A patch: two slabs of global loads in flight instead of one where a slab's MFMAs are too few to cover its loads: kernel tensors of
     // one tap, and up to nine taps on waves that share their tiles' steps in grids of one workgroup per compute unit.  One tap: 36 drawn

@@ -69,7 +69,7 @@ constexpr int ROWS = NB2 * CIN * PH;
 constexpr int COPY_MIN = ROWS * PITCH + (SPC * RPS - HK) * PITCH + WKP;
 constexpr int COPY = NCOPY == 2 ? (COPY_MIN + 127) / 128 * 128 + 64 : (COPY_MIN + 7) / 8 * 8;
 constexpr int A_ROWS = BM * K + 128;               // elements of the workgroup's rows of the kernel tensor in the LDS, and what fragments of the last one may read past them
-static_assert((NCOPY * COPY + (STAGE_A == 2 ? A_ROWS : 0)) * 2 == LDS_BYTES && (STAGE_A != 1 || A_ROWS * 2 <= LDS_BYTES) && COPY % 8 == 0, "decoder and template disagree");
+static_assert(NCOPY * COPY * 2 + BESIDE == LDS_BYTES && (STAGE_A != 1 || A_ROWS * 2 <= LDS_BYTES) && (STAGE_A != 2 || A_ROWS * 2 == BESIDE) && COPY % 8 == 0, "decoder and template disagree");
 static_assert(WK <= WKP && (WKP == 8 || WKP == 16) && WIN >= 8 && BM == WM * MI * ATOM && WN * NI * ATOM >= BN && NT == 64 * WM * WN, "decoder and template disagree");
 // The fill's split: TPR threads along a patch row, RPP rows at a time, so that a thread keeps its place in the row (XP places if
 // the row is longer than the workgroup) and a pass costs it one small division instead of one of every extent.

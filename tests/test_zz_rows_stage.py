@@ -98,3 +98,18 @@ def test_results_match_the_oracle(label, dims, variant, cfg, stage, dtype):
     P.opevo_kernel_destroy(kernel)
     got = dc.cpu().numpy().astype(np.float64)
     assert np.all(np.isfinite(got)) and np.linalg.norm(got - want) <= 1e-5 * np.linalg.norm(want), label
+
+
+def test_a_member_that_spills_with_it_keeps_its_template(tmp_path):
+    """Straight from memory it does not spill: two compilations, both of this template."""
+    op = P.opevo_op_create(P.OPEVO_CONV2D, (33, 3, 224, 224, 128, 11, 11, 4, 0), P.OPEVO_F16)
+    cfg = [11, 3, 4, 2, 1, 16, 3, 3, 6, 1, 6, 1, 9, 1, 1, 33, 11, 0, 0]
+    assert _defs(op, V4C, cfg)[1]["STAGE_A"] == 1
+    P.opevo_code_cache_configure(str(tmp_path), 0)
+    try:
+        kernel, _ = P.opevo_kernel_build(op, V4C, cfg)
+        P.opevo_kernel_destroy(kernel)
+    finally:
+        P.opevo_code_cache_configure(None, 256 << 20)
+    keys = [f.read_bytes().split(b"\x7fELF")[0] for f in tmp_path.iterdir()]
+    assert sorted(b"STAGE_A=0" in k for k in keys) == [False, True] and all(b"conv_rows" in k for k in keys)
