@@ -1027,11 +1027,12 @@ int decode(const opevo_op &op, int variant, const int32_t *cfg, Decoded &out, bo
         out.tries.push_back(" -DSTAGE_A=0");
     }
     // A patch: two slabs of global loads in flight instead of one where a slab's MFMAs are too few to cover its loads: kernel tensors of
-    // one tap, and up to nine taps on waves that share their tiles' steps in grids of one workgroup per compute unit.  One tap: 36 drawn
-    // members 0.97 - 1.26x, 1.09x in the geometric mean (88 x 256 x 27 x 27 * 128 x 256 33.6 -> 30.4 us, 6 x 256 x 27 x 27 * 192 x 256 8.2 -> 6.5,
-    // and the slowest 216 x 96 x 13 x 13 * 192 x 96 13.3 -> 13.7); shared tiles 30 members 1.02 - 1.17x, 1.09x (40 x 256 x 7 x 7 * 96 x 256 x 3 x 3
-    // 12.2 -> 10.7).  The same with 25 taps 0.93 - 1.13x, five larger grids 0.77 - 1.06x, 22 members that share nothing 0.85 - 1.03x, 0.94x.
-    if (path == 5 && !strip.rows && nstage == 2 && ksteps >= 3 && (op.hk * op.wk == 1 || (patch_kw > 1 && op.hk * op.wk <= 9 && n_blocks <= 256)))
+    // one tap, and up to nine taps on waves that share their tiles' steps in grids of one workgroup per compute unit, in slabs of up to 32 channels.  One tap: 159 random
+    // members 0.89 - 1.58x, 1.05x in the geometric mean (88 x 256 x 27 x 27 * 128 x 256 33.6 -> 30.4 us, 6 x 256 x 27 x 27 * 192 x 256 8.2 -> 6.5); shared tiles 105
+    // members 0.94 - 1.16x, 1.07x (40 x 256 x 7 x 7 * 96 x 256 x 3 x 3 12.2 -> 10.7).  Slabs of 64 channels have MFMAs enough, and their second set of registers costs resident
+    // workgroups: 33 members 0.75 - 1.07x, 0.96x (5 x 256 x 56 x 56 * 192 x 256 on 1680 workgroups of one wave, 232 -> 422 registers, 18.9 -> 25.4).  25 taps 0.93 - 1.13x, five larger grids 0.77 - 1.06x,
+    // 22 members that share nothing 0.85 - 1.03x, 0.94x.
+    if (path == 5 && !strip.rows && nstage == 2 && ksteps >= 3 && patch_cs <= 32 && (op.hk * op.wk == 1 || (patch_kw > 1 && op.hk * op.wk <= 9 && n_blocks <= 256)))
         out.tries = {" -DSLABS_AHEAD=2", ""};
     // fp32, two stages: the pipelined slab loop, but for short reductions on a full chip, where the other workgroups cover a
     // slab's latency and the registers are better spent on them (a batch of 960 of 128 x 64 x 128 with the first operand transposed:

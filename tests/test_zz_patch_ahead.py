@@ -18,6 +18,7 @@ CASES = [   # label, dims, configuration, slabs, waves that share a tile, two sl
     ("nine taps, two waves, stride 2", (1, 64, 9, 9, 32, 3, 3, 2, 1), [1, 1, 1, 2, 1, 16, 1, 1, 1, 5, 1, 1, 1, 5, 4, 16, 1, 2, 1], 4, 2, True),
     ("nine taps, ten slabs, several images", (3, 160, 5, 5, 64, 3, 3, 1, 1), [1, 3, 2, 1, 16, 2, 1, 1, 5, 1, 1, 1, 1, 5, 20, 8, 1, 2, 3], 10, 8, True),
     ("nine taps, five slabs of 32 channels", (3, 160, 5, 5, 64, 3, 3, 1, 1), [1, 3, 4, 8, 2, 1, 1, 1, 1, 5, 1, 1, 1, 5, 5, 32, 1, 2, 2], 5, 4, True),
+    ("one tap, slabs of 64 channels", (2, 256, 8, 8, 32, 1, 1, 1, 0), [1, 2, 1, 1, 1, 32, 1, 1, 2, 4, 2, 4, 1, 1, 4, 64, 1, 2, 0], 4, 1, False),
     ("two slabs", (1, 32, 8, 8, 32, 1, 1, 1, 0), [1, 1, 1, 1, 4, 8, 1, 1, 4, 2, 1, 4, 1, 2, 16, 2, 1, 2, 3], 2, 1, False),
     ("nine taps, no shared tiles", (3, 160, 5, 5, 64, 3, 3, 1, 1), [1, 3, 1, 1, 8, 8, 1, 5, 1, 1, 1, 5, 1, 1, 5, 32, 1, 2, 0], 5, 1, False),
     ("25 taps", (1, 48, 7, 7, 32, 5, 5, 1, 2), [1, 1, 1, 2, 1, 16, 1, 1, 1, 7, 1, 1, 1, 7, 24, 2, 1, 2, 2], 3, 4, False),
