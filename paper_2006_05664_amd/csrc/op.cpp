@@ -589,7 +589,7 @@ int decode(const opevo_op &op, int variant, const int32_t *cfg, Decoded &out, bo
                 // (the others run the loop and the division that they ask for).  144 drawn members and 60 folded ones of 8 operators, old
                 // template against new: 1.20 - 1.26x in the geometric mean, 0.94 - 2.5x; what was below 0.94 is excluded by the conditions in plan_strip.
                 // Members that ask for pipelining go there too on more workgroups than compute units: the second stage costs them the other workgroups that would
-                // hide a slab's latency.  94 drawn and random members with three pixel waves and more 0.94 - 2.7x, 1.28x in the geometric mean (53 x 256 x 27 x 27 *
+                // hide a slab's latency.  144 drawn and random members with three pixel waves and more 0.94 - 2.7x, 1.3x in the geometric mean (53 x 256 x 27 x 27 *
                 // 64 x 256 x 3 x 3 31.2 -> 26.5 us, 163 x 256 x 14 x 14 * 256 x 256 x 3 x 3 74.4 -> 53.3; the slowest 11 x 32 x 56 x 56 * 128 x 32 x 3 x 3 10.9 -> 11.5).  Two pixel waves
                 // (11 members 1.4 - 2.4x as fast there) and grids of up to 256 workgroups (17 members 1.04 - 1.30x) were too few to draw a line by: they stay.
                 const int64_t asked_n = int64_t(h[1]) * w[1], asked = c[3] * asked_n * int64_t(kReductionWaves[c[18]]);
@@ -788,11 +788,11 @@ int decode(const opevo_op &op, int variant, const int32_t *cfg, Decoded &out, bo
         WM = rg.wm; WN = rg.wn; TM = rg.mi * 16; TN = rg.ni * 16;
         TMacc = TM; TNacc = TN; BK = rg.ks; ksteps = rg.slabs;
         // Waves that share the reduction, each with the whole tile as its wave tile and a part of the LDS of its own, where no more than one workgroup falls on a compute unit:
-        // eight, as far as the LDS goes.  60 drawn and random members of K >= 448 and up to 20 atoms against the slab walk: 0.93 - 2.9x, 1.6x in the geometric mean (480 x 360 x 4893,
+        // eight, as far as the LDS goes.  60 drawn and random members of K >= 448 and up to 20 atoms against the slab walk: 0.93 - 2.9x, 1.6x in the geometric mean, 205 further random ones 0.83 - 4.8x, 1.6x, six below 0.98 (480 x 360 x 4893,
         // 90 workgroups, 29.8 -> 21.1 us; 40 x 100 x 2517, 8, 19.8 -> 7.5); below, 56 x 56 at K = 324 4.3 -> 4.6, 32 x 44 at 360 3.2 -> 3.4; with 500 workgroups of 20 x 100
         // at K = 1000 13.2 -> 13.4, with 860 of 50 x 32 32.0 -> 39.6.
-        // Two waves on fuller grids where an operand's pieces begin at odd elements, which this loop shifts into place: 12 members of up to 1024 workgroups and 12 atoms 1.02 -
-        // 2.0x, 1.4x in the mean (100 x 5439 x 1056 in 50 x 21 20.4 -> 11.1; 1078 workgroups 39.9 -> 41.6, 1125 23.9 -> 18.9, 1575 25.8 -> 26.0).
+        // Two waves on fuller grids where an operand's pieces begin at odd elements, which this loop shifts into place: 190 random members of up to 1024 workgroups and 12 atoms 0.80 -
+        // 3.5x, 1.34x in the geometric mean, 18 below 0.98 with no line around them (80 x 3625 x 888 in 40 x 25 8.1 -> 10.2; 100 x 5439 x 1056 in 50 x 21 20.4 -> 11.1; 1078 workgroups 39.9 -> 41.6, 1125 23.9 -> 18.9, 1575 25.8 -> 26.0).
         const int64_t ma = (BM + 15) / 16, na = (BN + 15) / 16, wgs = n1 * m1 * b1;
         const bool odd = op.N % 2 != 0 || (BN % 2 != 0 && n1 > 1) || (op.trans_a && (op.M % 2 != 0 || (BM % 2 != 0 && m1 > 1)));
         auto odd16 = [](int64_t n) { return ((n + 15) / 16 | 1) * 16; };
@@ -839,7 +839,7 @@ int decode(const opevo_op &op, int variant, const int32_t *cfg, Decoded &out, bo
     }
     // Grids of direct-to-LDS MatMul / BMM members that do not fit the chip at once, with eight waves or fewer on a compute unit: a ring of fewer stages leaves
     // room for more workgroups, which hide a slab's latency as well as the slabs ahead do.  The most stages with which the grid does fit: 88 drawn members 0.91 - 1.46x,
-    // 1.12x in the geometric mean, three of them below 0.99 (1040 workgroups of two waves, 128 x 64, five slabs of 32: 11.7 -> 12.7 us).
+    // 1.12x in the geometric mean, 113 random ones 0.85 - 1.64x, 1.22x, three below 0.98 (1040 workgroups of two waves, 128 x 64, five slabs of 32: 11.7 -> 12.7 us).
     // With two waves or fewer on a compute unit, if it does not fit with any, the most stages that give it more: 20 drawn members 1.07 -
     // 1.40x, 1.22x (4544 x 3328 x 2112 in 64 x 128, two waves: 143 -> 104 us).  Three and more waves in grids that do
     // not fit in any case: 0.84 - 1.17x, 1.04x; those keep the ring.  So do members on 16x16x32 atoms: 30 drawn ones 0.59 - 1.76x, 1.14x, the slow ones (5120 x 1920 x 4096 in
@@ -1027,10 +1027,10 @@ int decode(const opevo_op &op, int variant, const int32_t *cfg, Decoded &out, bo
         out.tries.push_back(" -DSTAGE_A=0");
     }
     // A patch: two slabs of global loads in flight instead of one where a slab's MFMAs are too few to cover its loads: kernel tensors of
-    // one tap, and up to nine taps on waves that share their tiles' steps in grids of one workgroup per compute unit, in slabs of up to 32 channels.  One tap: 159 random
-    // members 0.89 - 1.58x, 1.05x in the geometric mean (88 x 256 x 27 x 27 * 128 x 256 33.6 -> 30.4 us, 6 x 256 x 27 x 27 * 192 x 256 8.2 -> 6.5); shared tiles 105
-    // members 0.94 - 1.16x, 1.07x (40 x 256 x 7 x 7 * 96 x 256 x 3 x 3 12.2 -> 10.7).  Slabs of 64 channels have MFMAs enough, and their second set of registers costs resident
-    // workgroups: 33 members 0.75 - 1.07x, 0.96x (5 x 256 x 56 x 56 * 192 x 256 on 1680 workgroups of one wave, 232 -> 422 registers, 18.9 -> 25.4).  25 taps 0.93 - 1.13x, five larger grids 0.77 - 1.06x,
+    // one tap, and up to nine taps on waves that share their tiles' steps in grids of one workgroup per compute unit, in slabs of up to 32 channels.  One tap: 163 random
+    // members 0.89 - 1.58x, 1.05x in the geometric mean (88 x 256 x 27 x 27 * 128 x 256 33.6 -> 30.4 us, 6 x 256 x 27 x 27 * 192 x 256 8.2 -> 6.5); shared tiles 126
+    // members 0.94 - 1.16x, 1.05x (40 x 256 x 7 x 7 * 96 x 256 x 3 x 3 12.2 -> 10.7).  Slabs of 64 channels have MFMAs enough, and their second set of registers costs resident
+    // workgroups: 25 members 0.75 - 1.07x, 0.95x (5 x 256 x 56 x 56 * 192 x 256 on 1680 workgroups of one wave, 232 -> 422 registers, 18.9 -> 25.4).  25 taps 0.93 - 1.13x, five larger grids 0.77 - 1.06x,
     // 22 members that share nothing 0.85 - 1.03x, 0.94x.
     if (path == 5 && !strip.rows && nstage == 2 && ksteps >= 3 && patch_cs <= 32 && (op.hk * op.wk == 1 || (patch_kw > 1 && op.hk * op.wk <= 9 && n_blocks <= 256)))
         out.tries = {" -DSLABS_AHEAD=2", ""};
